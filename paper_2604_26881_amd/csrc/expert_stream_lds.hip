@@ -121,10 +121,10 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
     auto issue = [&](int s, int slot) {
       const uint32_t l = lds0 + (uint32_t)slot * S::STAGE;
       const size_t kb = (size_t)(s + rot >= nk ? s + rot - nk : s + rot) * 128;
-      copy_to_lds_16_stream(W0 + kb, coffW[0], l);
-      copy_to_lds_16_stream(W0 + kb, coffW[1], l + 1024u);
-      copy_to_lds_16_stream(W1 + kb, coffW[0], l + 2048u);
-      copy_to_lds_16_stream(W1 + kb, coffW[1], l + 3072u);
+      copy_to_lds_16(W0 + kb, coffW[0], l, true);
+      copy_to_lds_16(W0 + kb, coffW[1], l + 1024u, true);
+      copy_to_lds_16(W1 + kb, coffW[0], l + 2048u, true);
+      copy_to_lds_16(W1 + kb, coffW[1], l + 3072u, true);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         copy_to_lds_16(Ab + kb, coffX[mt][0], l + (uint32_t)S::WBYTES + (uint32_t)mt * 2048u);

@@ -29,6 +29,16 @@
 // operand reads (32 rows, same chunk) are bank-conflict free.  MFMA 32x32x16 bf16 with the WEIGHT rows as the
 // first operand and the TOKEN rows as the second: a lane then owns 4 consecutive output columns
 // of one token row per accumulator quad, which makes the bf16 stores 8 bytes wide.
+// Single-tile experts: when all rows of an expert fit one tile nobody else reads its weight panel, and
+// the launch is a stream of weights from HBM.  Such tiles request their weights with the read-once hint
+// and start their walk over K at a step that depends on the expert and the column tile (it wraps around;
+// see the weight-streaming kernels for why a common start crowds the memory channels).  The two belong
+// together: with the hint the token panel, which the column tiles of an expert now visit at different
+// steps, stays in L2.  60 experts of 137 rows, H 2048, I 1408 (692 MB of gate/up weights): 174-195 us
+// without either, 166-177 with the rotation alone, 180 with the hint alone, 153-158 with both (down 88-96
+// -> 80-84); 52 rows: 152-174 -> 138.  Experts of several tiles share weight panels through L2, which the
+// hint throws away (60 experts of 273 rows: 256 -> 293 us): those keep the plain requests.  The start
+// depends on nothing but the expert, the column and the tile shape, so results do not depend on the block cut.
 // Rows past the end of an expert are clamped on load (they recompute the expert's last row) and
 // masked on store, which keeps the K loop free of branches.
 #include <math.h>
@@ -79,7 +89,7 @@ __host__ __device__ constexpr int fragment_read_order(int slot, int tb, int nb) 
   return slot == 0 ? tb : (slot == 1 ? 0 : (slot <= nb ? tb + slot - 1 : slot - nb));
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE>
 __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -177,19 +187,21 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   const int run = xcd_walk ? max(1, min(G >> 3, (Lend + 7) >> 3)) : 1;
   if (xcd_walk && slot >= run) return;
 
-    // copy i (of NL) of K step kt into stage buffer st; all NL of them
-#define MOE_TILE_ISSUE1(kt, st, i)                                                                  \
-    copy_to_lds_16(((i) < S::NLA ? Ag : ((GATEUP && (i) >= S::NLA + (S::NL - S::NLA) / 2) ? Bg1 : Bg0)) + (size_t)(kt) * S::ROWB, \
-                   coff[i], lds0 + (uint32_t)(st) * S::STAGE + (uint32_t)wave * 1024u + (uint32_t)(i) * 4096u);
-#define MOE_TILE_ISSUE(kt, st)                                                                      \
-    { _Pragma("unroll") for (int i = 0; i < S::NL; ++i) MOE_TILE_ISSUE1(kt, st, i); }
+    // copy i (of NL) of K step kt into stage buffer st; all NL of them.  once_: the weight rows carry the
+    // read-once hint (see "single-tile experts" above)
+#define MOE_TILE_ISSUE1(kt, st, i, once_)                                                           \
+    copy_to_lds_16(                                                                                 \
+        ((i) < S::NLA ? Ag : ((GATEUP && (i) >= S::NLA + (S::NL - S::NLA) / 2) ? Bg1 : Bg0)) + (size_t)(kt) * S::ROWB, \
+        coff[i], lds0 + (uint32_t)(st) * S::STAGE + (uint32_t)wave * 1024u + (uint32_t)(i) * 4096u, (once_) && (i) >= S::NLA);
 
   // State of a tile: the current one (being multiplied, then stored) and, while the current one is
   // stored, the next one, whose first NS stages are already requested: the latency of those copies
   // hides behind the epilogue instead of opening every tile.
-  struct TileState { int row0, rowEnd, rowsValid, n0, ks, cshift; bf16_t* cbase; bool valid; };
+  struct TileState { int row0, rowEnd, rowsValid, n0, ks, cshift; bf16_t* cbase; bool once, valid; };
   const unsigned char *Ag = nullptr, *Bg0 = nullptr, *Bg1 = nullptr;
   uint32_t coff[S::NL];   // byte offsets of this lane's 16 bytes for each of the NL copies of a stage (K step 0)
+  int krot = 0;           // K step the tile starts at (its walk over K wraps around)
+  auto kstep = [&](int kt) -> int { const int k = kt + krot; return k >= nk ? k - nk : k; };
   int it = 0;
   auto next_tile = [&]() -> TileState {
     TileState t{};
@@ -231,6 +243,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
     t.rowEnd = sh ? rb + a.shared_rows : (a.offsets ? a.offsets[eg + 1] : a.rows_fixed);
     t.rowsValid = min(BM, t.rowEnd - t.row0);
     t.n0 = nt * S::NOUT;
+    t.once = SINGLE && t.rowEnd - rb <= BM;
     // where this tile's rows go: a shared set may have an output tensor of its own
     const bool own_c = sh && a.Cs != nullptr;
     t.cbase = own_c ? a.Cs : a.C;
@@ -272,8 +285,20 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
       coff[i] = (uint32_t)grow * ld * 2u + (uint32_t)cchunk * 16u;
     }
     // all NS stages of the tile are requested up front
+    auto request = [&](auto once_) {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) MOE_TILE_ISSUE(min(s, nk - 1), s);
+      for (int s = 0; s < NS; ++s) {
+        const int k = decltype(once_)::value ? kstep(min(s, nk - 1)) : min(s, nk - 1);
+#pragma unroll
+        for (int i = 0; i < S::NL; ++i) MOE_TILE_ISSUE1(k, s, i, decltype(once_)::value);
+      }
+    };
+    if (SINGLE && t.once) {
+      krot = (int)((unsigned)(eg * 5 + nt * 3) % (unsigned)nk);
+      request(std::true_type{});
+    } else {
+      request(std::false_type{});
+    }
     return t;
   };
 
@@ -342,7 +367,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
             constexpr int NE_ = S::NB + 1 < NFc ? S::NB + 1 : NFc;   /* reads needed early: before the copies */ \
             constexpr int NC_ = (I1) - (I0);                                                        \
             if (q < NE_) MOE_TILE_READ1(faY, fbY, stage_, kk_, fragment_read_order(q < NE_ ? q : 0, TBc, S::NB)) \
-            else if (q < NE_ + NC_) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, (q >= NE_ && q < NE_ + NC_) ? (I0) + q - NE_ : 0); } \
+            else if (q < NE_ + NC_) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, ((q >= NE_ && q < NE_ + NC_) ? (I0) + q - NE_ : 0), ONCE); } \
             else MOE_TILE_READ1(faY, fbY, stage_, kk_, fragment_read_order(q >= NE_ + NC_ ? q - NC_ : 0, TBc, S::NB)) \
           }                                                                                         \
         __builtin_amdgcn_sched_barrier(0x6);                                                        \
@@ -356,7 +381,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
           if (q * NMc / (S::ISSUE0 + NFc) == j) {                                                   \
             constexpr int NE_ = S::NB + 1 < NFc ? S::NB + 1 : NFc;                                  \
             if (q < NE_) MOE_TILE_READ1(faA, fbA, next_stage_, 0, fragment_read_order(q < NE_ ? q : 0, TBc, S::NB)) \
-            else if (q < NE_ + S::ISSUE0) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, (q >= NE_ && q < NE_ + S::ISSUE0) ? q - NE_ : 0); } \
+            else if (q < NE_ + S::ISSUE0) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, ((q >= NE_ && q < NE_ + S::ISSUE0) ? q - NE_ : 0), ONCE); } \
             else MOE_TILE_READ1(faA, fbA, next_stage_, 0, fragment_read_order(q >= NE_ + S::ISSUE0 ? q - S::ISSUE0 : 0, TBc, S::NB)) \
           }                                                                                         \
         __builtin_amdgcn_sched_barrier(0x6);                                                        \
@@ -369,8 +394,9 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
     // completely, so its buffer can take the copy of stage kt+NS.
     // (Past the end of K the requests repeat the last K step into a buffer nobody reads again:
     // every iteration then issues the same number of copies and the wait counts stay constant.)
-    auto pipeline = [&](auto tbc_) {
+    auto pipeline = [&](auto tbc_, auto once_) {
       constexpr int TBc = decltype(tbc_)::value;
+      constexpr bool ONCE = decltype(once_)::value;
       constexpr int NMc = TBc * S::NB;   // MFMAs per 16-wide K slice
       constexpr int NFc = TBc + S::NB;   // operand fragments per slice
       wait_copies_but<S::DIST * S::NL>();   // stage 0 (requested before the previous tile was stored) has landed
@@ -382,7 +408,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
         const int st1 = st + 1 == NS ? 0 : st + 1;
         // the rest of the copies of K step kt-1+NS, whose first part went out during the last slice
         // of K step kt-1 (at kt = 0 this repeats copies of the prologue: same bytes, same place)
-        const int ktd = min(kt - 1 + NS, nk - 1);
+        const int ktd = ONCE ? kstep(min(kt - 1 + NS, nk - 1)) : min(kt - 1 + NS, nk - 1);
         const int std_ = st == 0 ? NS - 1 : st - 1;
         MOE_TILE_SLICE_ISSUE(faA, fbA, faB, fbB, st, 1, ktd, std_, S::ISSUE0, S::ISSUE0 + S::ISSUE1);
         MOE_TILE_SLICE_ISSUE(faB, fbB, faA, fbA, st, 2, ktd, std_, S::ISSUE0 + S::ISSUE1, S::NL);
@@ -396,7 +422,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
         for (int nb = 0; nb < S::NB; ++nb) asm volatile("" : "+v"(fbB[nb]));
         wait_copies_but<(S::DIST - 1) * S::NL>();
         workgroup_barrier();  // stage kt+1 is complete for everyone; stage kt is free for everyone
-        MOE_TILE_SLICE_LAST(st1, min(kt + NS, nk - 1), st);
+        MOE_TILE_SLICE_LAST(st1, ONCE ? kstep(min(kt + NS, nk - 1)) : min(kt + NS, nk - 1), st);
         st = st1;
       }
       MOE_TILE_SLICE(faA, fbA, faB, fbB, st, 1);
@@ -411,13 +437,16 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
     // operand reads keep their places between MFMAs)
     const int tbv = min(S::TB, max(1, (rowsValid - wm * S::WTM + 31) >> 5));
     const long long clk_k0 = clock64();
-    switch (tbv) {
-      case 1: pipeline(std::integral_constant<int, 1>{}); break;
-      case 2: if constexpr (S::TB >= 2) pipeline(std::integral_constant<int, 2>{}); break;
-      case 3: if constexpr (S::TB >= 3) pipeline(std::integral_constant<int, 3>{}); break;
-      case 4: if constexpr (S::TB >= 4) pipeline(std::integral_constant<int, 4>{}); break;
-      default: if constexpr (S::TB >= 5) pipeline(std::integral_constant<int, 5>{}); break;
-    }
+    auto run_pipeline = [&](auto once_) {
+      switch (tbv) {
+        case 1: pipeline(std::integral_constant<int, 1>{}, once_); break;
+        case 2: if constexpr (S::TB >= 2) pipeline(std::integral_constant<int, 2>{}, once_); break;
+        case 3: if constexpr (S::TB >= 3) pipeline(std::integral_constant<int, 3>{}, once_); break;
+        case 4: if constexpr (S::TB >= 4) pipeline(std::integral_constant<int, 4>{}, once_); break;
+        default: if constexpr (S::TB >= 5) pipeline(std::integral_constant<int, 5>{}, once_); break;
+      }
+    };
+    if (SINGLE && cur.once) run_pipeline(std::true_type{}); else run_pipeline(std::false_type{});
     static_assert(S::TB <= 5, "token blocks per wave");
     clk_kloops += clock64() - clk_k0;
     ++clk_tiles;
@@ -497,7 +526,6 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
     cur = nxt;
   }
 #undef MOE_TILE_ISSUE1
-#undef MOE_TILE_ISSUE
   if (clocked && tid == 0) {
     long long* rec = a.clocks + 4 * (size_t)blockIdx.x;
     rec[0] = clock64() - clk_begin;
@@ -539,10 +567,11 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   reinterpret_cast<uint2*>(C)[i] = o;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT = 1>
-static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE>
+static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
-  auto kern = expert_tile_kernel<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT>;
+  auto kern = expert_tile_kernel<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, SINGLE>;
+  static_assert(KSPLIT == 1 || !SINGLE, "a K part of a tile does not wrap around");
   static_assert(KSPLIT == 1 || !GATEUP, "the SwiGLU product needs complete sums");
   if (a.Kdim % (S::BK * KSPLIT) != 0) return -2;
   if (KSPLIT > 1 && a.Cpart == nullptr) return -3;
@@ -578,6 +607,19 @@ static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
     if (hipGetLastError() != hipSuccess) return -4;
   }
   return 0;
+}
+
+// Batches whose mean expert needs more than four tiles hold (next to) no single-tile expert: they run the
+// instance without that path (with it the 256x256 kernels at 16 384 tokens lose 0.6 %, to registers and code
+// that no tile uses), and so does one weight set (the shared expert; with one token its gate/up kernel takes
+// 2 us more with the path than without).  The rule reads layer-wide sizes only.
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT = 1>
+static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
+  if constexpr (KSPLIT == 1) {
+    if (a.offsets && a.mean_rows <= 4 * BM)
+      return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, true>(a, st);
+  }
+  return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, false>(a, st);
 }
 
 // Tile shape codes: 256 = 256x256, 128/129 = 128 token rows x 256 weight rows, 130 = 128x128,
