@@ -46,11 +46,12 @@ Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
     default: p.valid = false; return p;
   }
   // One weight set on all rows (the shared expert): MFMA tiles whose shape each kernel picks from
-  // its tile count (pick_tile_shape).  Routed experts, measured with cold caches at the Qwen shape:
-  // streaming through LDS rings wins up to a mean of about 26 rows per expert (T = 384), the MFMA
-  // tiles beyond (their height picked from the layer-wide mean).
-  const bool few_experts = n_experts_layer < 16;
-  p.stream = !few_experts && mean_rows <= 26;
+  // its tile count (pick_tile_shape).  Routed experts: weight streaming up to a mean of 32 rows per
+  // expert, the MFMA tiles beyond (their height picked from the layer-wide mean).  Measured with cold
+  // caches, gate/up + down in us, streaming against tiles: 60 experts of H 2048, I 1408 at 26 rows 125 + 66
+  // and 135 + 69, at 34 rows 134 + 72 and 137 + 72; 128 of H 1024, I 768 at 31 rows 79 + 45 and 83 + 48;
+  // 8 of H 4096, I 7168 at 5 rows 157 + 77 and 164 + 112, at 30 rows 179 + 83 and 166 + 117.
+  p.stream = n_experts_layer > 1 && mean_rows <= 32;
   p.tile_rows = 0;
   return p;
 }
@@ -253,8 +254,7 @@ int moe_fused_shared_sets(int T, int H, int E, int K, int I, int Is) {
   if (ns > MOE_SHARED_SETS_MAX || E + ns > 256) return 0;
   const long long P = (long long)T * K;
   if ((P + (long long)ns * T) * (H > I ? H : I) >= (1ll << 31)) return 0;
-  const Plan plan = make_plan((int)((P + E - 1) / E), E, 0);
-  return plan.stream ? 0 : ns;     // batches served by weight streaming keep the separate calls
+  return E < 16 || (P + E - 1) / E > 26 ? ns : 0;     // decode-sized batches keep the separate calls
 }
 
 size_t moe_fused_workspace_bytes(int T, int K, int I, int Is) {
@@ -280,7 +280,7 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
   if (workspace_bytes < (size_t)rows * (size_t)I * 2) return MOE_ERR_WORKSPACE;   // h of the routed rows, then of every shared set
   const int mean_rows = (P + E - 1) / E;
   const Plan plan = make_plan(mean_rows, E, policy);
-  if (!plan.valid || plan.stream || plan.tile_rows == 64) return MOE_ERR_SHAPE;
+  if (!plan.valid || (policy & 0xff) == 9 || plan.tile_rows == 64) return MOE_ERR_SHAPE;
   GemmArgs gu{};
   gu.A = (const bf16_t*)x; gu.B0 = (const bf16_t*)Wg; gu.B1 = (const bf16_t*)Wu; gu.C = (bf16_t*)workspace;
   gu.offsets = expert_offsets; gu.lo = group_lo; gu.hi = group_hi; gu.ids = nullptr; gu.rows_total = rows;
@@ -294,7 +294,22 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
   dn.N = H; dn.Kdim = I;
   dn.Bs0 = (const bf16_t*)Wsd; dn.shared_b_step = I; dn.ldb_shared = Is;   // set s: columns [s*I, (s+1)*I) of Wsd [H,Is]
   dn.Cs = (bf16_t*)S_parts;
-  int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream);
+  int rc = 0;
+  if (plan.stream) {
+    // few rows per routed expert: the routed rows go through the streaming kernels (the bits of the plain block
+    // call), the shared sets through tiles of their own
+    Plan tiles = plan;
+    tiles.stream = false;
+    GemmArgs sgu = gu, sdn = dn;
+    sgu.offsets = sdn.offsets = nullptr; sgu.gather = nullptr; sgu.lo = sgu.hi = sdn.lo = sdn.hi = 0;
+    sgu.rows_total = sdn.rows_total = ns * T;
+    gu.n_shared = dn.n_shared = 0;
+    gu.rows_total = dn.rows_total = P;
+    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream);
+    if (rc == 0) rc = ffn_forward(sgu, sdn, tiles, (hipStream_t)stream);
+  } else {
+    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream);
+  }
   if (rc != 0) return rc;
   if (wgate && plan.do_down) return launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
   return MOE_OK;

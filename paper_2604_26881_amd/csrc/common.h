@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 
 namespace moe {
 
@@ -113,6 +114,19 @@ struct GemmArgs {
   long long* clocks;
   int clock_groups;
 };
+// Raises a kernel's dynamic LDS limit once per device: one bit per device id in `done` (the kernel's own),
+// set after the call has succeeded there (two threads may both make the call; it is idempotent).
+inline int raise_lds_limit(const void* kern, int lds, std::atomic<uint64_t>& done) {
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return -4;
+  const uint64_t bit = 1ull << (dev & 63);
+  if (dev >= 64 || !(done.load(std::memory_order_acquire) & bit)) {
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return -4;
+    if (dev < 64) done.fetch_or(bit, std::memory_order_release);
+  }
+  return 0;
+}
+
 // Where the tile-kernel launches of the calling host thread record their clocks (nullptr: nowhere).
 void set_tile_clock_buffer(long long* clocks, int groups);
 
@@ -131,8 +145,11 @@ int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st);
 int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st);
 int tile_down_ksplit(int Kdim);   // K parts of the down projection when tile_rows == 64
 int pick_tile_shape(int rows, int N, int Kdim, bool gateup, bool allow_kcut, bool leave_room);   // one weight set, known rows
-// Streaming kernels that stage the weights through wave-private LDS rings (whole-line requests).
+// Streaming kernels that stage the weights through wave-private LDS rings (whole-line requests): a few rows per
+// expert, and up to a few dozen.
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st);
 int launch_stream_lds_down(const GemmArgs& a, hipStream_t st);
+int launch_stream_wide_gateup(const GemmArgs& a, hipStream_t st);
+int launch_stream_wide_down(const GemmArgs& a, hipStream_t st);
 
 }  // namespace moe

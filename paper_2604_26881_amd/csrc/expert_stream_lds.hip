@@ -236,16 +236,18 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
-// Token tiles per pass from layer-wide sizes: with expert_offsets the rows per expert scatter
-// around the mean (binomial), one tile of 16 covers nearly all experts up to a mean of 10; an
-// expert with more rows takes further passes over its weights.  Ring depths from 2 to 8 stages
-// measured the same within noise; 4 leaves room for five to six workgroups per CU.
+// One tile of 16 rows covers an expert of a few rows; an expert with more takes further passes over its
+// weights.  Ring depths from 2 to 8 stages measured the same within noise; 4 leaves room for five to six
+// workgroups per CU.  Larger experts go to the wide kernels: from a mean of 6 rows on, where both read the
+// weights at the same rate when the batch is even (8.5 rows: 116 + 62 here, 118 + 60 us there) and a hot
+// expert of 127 rows, eight passes here and two there, makes 137 + 70 of it here and 122 + 65 us there.
+// (One weight set stays here.)
 template <bool GATEUP>
 static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.N % 32 != 0 || a.Kdim % 64 != 0) return -2;
-  const int rows = a.offsets ? a.mean_rows : a.rows_fixed;
-  if (rows <= 10) return launch_stream_lds_t<1, GATEUP, 4>(a, st);
-  return launch_stream_lds_t<2, GATEUP, 4>(a, st);
+  if (a.offsets != nullptr && a.mean_rows > 6 && a.N % 64 == 0)
+    return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
+  return launch_stream_lds_t<1, GATEUP, 4>(a, st);
 }
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st) { return launch_stream_lds_any<true>(a, st); }
 int launch_stream_lds_down(const GemmArgs& a, hipStream_t st) { return launch_stream_lds_any<false>(a, st); }

@@ -576,17 +576,9 @@ static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   if (a.Kdim % (S::BK * KSPLIT) != 0) return -2;
   if (KSPLIT > 1 && a.Cpart == nullptr) return -3;
   static_assert(OCC * (NS * S::STAGE + 3600) <= 160 * 1024, "LDS of the resident workgroups must fit a CU");
-  // The kernel's LDS limit is raised once per device: one bit per device id, set after the call has
-  // succeeded there (two threads may both make the call; it is idempotent).
-  static std::atomic<uint64_t> attr_done{0};
+  static std::atomic<uint64_t> lds_raised{0};
   const int lds = NS * S::STAGE;
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return -4;
-  const uint64_t bit = 1ull << (dev & 63);
-  if (dev >= 64 || !(attr_done.load(std::memory_order_acquire) & bit)) {
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return -4;
-    if (dev < 64) attr_done.fetch_or(bit, std::memory_order_release);
-  }
+  if (raise_lds_limit((const void*)kern, lds, lds_raised) != 0) return -4;
   const int nexp = (a.offsets ? a.hi - a.lo : (a.n_shared > 0 ? 0 : 1)) + a.n_shared;
   if (nexp > TILE_EMAX) return -2;
   const int NT = (a.N + S::NOUT - 1) / S::NOUT;

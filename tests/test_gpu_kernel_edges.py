@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import workloads
 from tests.test_gpu_parity import check_close, f64, moe  # noqa: F401  (moe is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +56,57 @@ def test_single_tile_experts_start_anywhere_in_k(moe, oracle64, policy, H, I):
     # and the same bits whatever the block cut
     Yc = run_blocks(moe, c, policy, [(5, 12), (0, 2), (2, 5)])
     assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16))
+
+
+@pytest.mark.parametrize("H,I", [(64, 64), (128, 192), (320, 448)])     # one K step ... more than the ring; a lone column block
+@pytest.mark.parametrize("counts", [
+    [0, 1, 31, 32, 33, 63, 64, 65, 0, 0, 2, 5],                 # one, two, three token blocks
+    [95, 96, 97, 0, 0, 0, 0, 1, 0, 0, 0, 0],                    # the last row of one pass and the first of two
+    [0] * 20 + [191, 192, 193, 0, 289, 0] + [0] * 20,           # two to four passes, blocks dealt unevenly
+    [7] * 256,                                                  # four experts in every lane of the prefix
+], ids=["blocks", "pass", "passes", "many experts"])
+def test_wide_streaming_at_block_and_pass_borders(moe, oracle64, counts, H, I):
+    c = block_case(oracle64, counts, H, I, sum(counts) + H)
+    print(f"[case] wide streaming, {len(counts)} experts, {c['P']} rows, H={H} I={I}", flush=True)
+    Yp = run_blocks(moe, c, 9)
+    check_close(f64(Yp), c["ref"], "Yp")
+    e = c["E"]
+    Yc = run_blocks(moe, c, 9, [(e // 3, e), (0, 1), (1, e // 3)])
+    assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16)), "depends on the block cut"
+    # a list in reverse order, its rows read through src_of_row: the same bits
+    src = torch.arange(c["P"], dtype=torch.int32, device="cuda")
+    ids = torch.arange(e - 1, -1, -1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(int(moe.load().moe_expert_workspace_bytes(c["P"], I)), dtype=torch.uint8, device="cuda")
+    Yl = torch.full_like(Yp, 768.0)
+    moe.moe_expert_list_forward(ids, c["Xp"], src, 1, c["off"], c["Wg"], c["Wu"], c["Wd"], Yl, ws, 9)
+    torch.cuda.synchronize()
+    assert torch.equal(Yp.view(torch.int16), Yl.view(torch.int16)), "depends on list or gather"
+
+
+@pytest.mark.parametrize("E,rows", [(8, 5), (8, 32), (8, 33), (20, 6), (20, 7), (20, 32), (20, 33), (1, 20)])
+def test_automatic_choice_around_its_lines(moe, oracle64, E, rows):
+    # mean rows per expert 6 | 7: narrow or wide streaming; 32 | 33: streaming or tiles
+    g = torch.Generator().manual_seed(E * 100 + rows)
+    cut = torch.sort(torch.randint(0, E * rows + 1, (E - 1,), generator=g)).values.tolist()
+    counts = np.diff([0] + cut + [E * rows])
+    c = block_case(oracle64, counts, 192, 128, rows)
+    check_close(f64(run_blocks(moe, c, 0)), c["ref"], f"Yp, {E} experts of {rows} rows on average")
+
+
+@pytest.mark.parametrize("T", [12, 56])     # 8 experts, top-2: 3 and 14 rows per expert
+def test_block_call_that_hosts_the_shared_experts_on_few_rows(moe, oracle64, T):
+    wl = workloads.prefill(seed=77, T=T, H=192, E=8, K=2, I=128, Is=256)
+    s, g, d = wl.shape, wl.to("cuda"), wl.f32_numpy()
+    ids, w = moe.moe_route(g.x, g.Wr, g.bias, s.K, s.renorm)
+    off, src, rowp, _ = moe.moe_permute(ids, g.x, s.E, materialize=False)
+    buf = moe.LayerBuffers.allocate(s.T, s.H, s.E, s.K, s.I, s.Is)
+    moe.moe_expert_group_forward_fused(0, s.E, g.x, src, s.K, off, g.Wg, g.Wu, g.Wd, g.Wsg, g.Wsu, g.Wsd, g.wgate, buf.Yp,
+                                       buf.S_parts, buf.sg, buf.workspace_fused)
+    Y = torch.empty_like(buf.Yp)
+    moe.moe_expert_group_forward_gather(0, s.E, g.x, src, s.K, off, g.Wg, g.Wu, g.Wd, Y, buf.workspace)
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(torch.int16), buf.Yp.view(torch.int16))
+    for p in range(s.Is // s.I):
+        sl = slice(p * s.I, (p + 1) * s.I)
+        S, sg = oracle64.shared_forward(d["x"], d["Wsg"][sl], d["Wsu"][sl], np.ascontiguousarray(d["Wsd"][:, sl]), d["wgate"])
+        check_close(f64(buf.S_parts[p]), S, f"shared expert {p}")
