@@ -23,8 +23,17 @@ bool dims_ok(int H) { return H > 0 && H % 64 == 0; }
 // only, 0x200: down projection only), so that each can be timed on its own.  Bit 10 (0x400, shared
 // expert with automatic shapes): its first kernel takes no tile shape that fills a CU completely,
 // so that small kernels of other streams (gating, micro-batch construction) run beside it.
-constexpr int SHARED_SMALL_T = 512;     // up to here the workspace has room for a K-cut down projection
-constexpr int SHARED_KPARTS_MAX = 8;    // parts of its down projection along K
+// Shared expert: parts of its down projection along K that the workspace has room for: 8 up to 512 tokens, beyond
+// that as many (a power of two) as it takes 128x128 tiles to 256 items, one round of the chip.
+constexpr int SHARED_SMALL_T = 512;
+constexpr int SHARED_KPARTS_MAX = 8;
+int shared_parts_room(int T, int H) {
+  if (T <= SHARED_SMALL_T) return SHARED_KPARTS_MAX;
+  const long tiles = ((long)T + 127) / 128 * (((long)H + 127) / 128);
+  int parts = 1;
+  while (parts < SHARED_KPARTS_MAX && 2 * parts * tiles <= 256) parts *= 2;
+  return parts > 1 ? parts : 0;
+}
 
 struct Plan { bool valid; bool stream; int tile_rows; bool do_gateup; bool do_down; };
 Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
@@ -56,15 +65,17 @@ Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
   return p;
 }
 
-int ffn_forward(const GemmArgs& gu, const GemmArgs& dn, const Plan& p, hipStream_t st) {
+// *parts: K parts in which the down projection was left in dn.Cpart (1: its output is complete)
+int ffn_forward(const GemmArgs& gu, const GemmArgs& dn, const Plan& p, hipStream_t st, int* parts) {
   int rc = 0;
+  *parts = 1;
   if (p.stream) {
     if (p.do_gateup && (rc = launch_stream_lds_gateup(gu, st)) != 0) return rc;
     if (p.do_down) rc = launch_stream_lds_down(dn, st);
     return rc;
   }
   if (p.do_gateup && (rc = launch_tile_gateup(gu, p.tile_rows, st)) != 0) return rc;
-  if (p.do_down) rc = launch_tile_down(dn, p.tile_rows, st);
+  if (p.do_down) rc = launch_tile_down(dn, p.tile_rows, st, parts);
   return rc;
 }
 
@@ -90,7 +101,8 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   gu.gather = gather; gu.gather_div = gather_div;   // only the first kernel reads token rows
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wd; dn.B1 = nullptr; dn.C = (bf16_t*)Yp;
   dn.N = H; dn.Kdim = I;
-  return ffn_forward(gu, dn, plan, (hipStream_t)stream);
+  int parts;   // (no Cpart: always 1)
+  return ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
 }
 }  // namespace
 
@@ -156,11 +168,11 @@ size_t moe_expert_workspace_bytes(int P, int I) {
   if (P <= 0 || I <= 0) return 0;
   return align256((size_t)P * (size_t)I * 2);
 }
-// h [T,Is] bf16, then (small batches only) the fp32 partial outputs of a down projection cut along K
+// h [T,Is] bf16, then (batches that leave CUs idle otherwise) the fp32 partial outputs of a down projection cut along K
 size_t moe_shared_workspace_bytes(int T, int H, int Is) {
   if (T <= 0 || H <= 0 || Is <= 0) return 0;
   size_t n = align256((size_t)T * (size_t)Is * 2);
-  if (T <= SHARED_SMALL_T) n += (size_t)SHARED_KPARTS_MAX * (size_t)T * (size_t)H * 4;
+  n += (size_t)shared_parts_room(T, H) * (size_t)T * (size_t)H * 4;
   return n;
 }
 size_t moe_workspace_bytes(int T, int H, int E, int K, int I, int Is) {
@@ -294,7 +306,7 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
   dn.N = H; dn.Kdim = I;
   dn.Bs0 = (const bf16_t*)Wsd; dn.shared_b_step = I; dn.ldb_shared = Is;   // set s: columns [s*I, (s+1)*I) of Wsd [H,Is]
   dn.Cs = (bf16_t*)S_parts;
-  int rc = 0;
+  int rc = 0, parts;
   if (plan.stream) {
     // few rows per routed expert: the routed rows go through the streaming kernels (the bits of the plain block
     // call), the shared sets through tiles of their own
@@ -305,10 +317,10 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
     sgu.rows_total = sdn.rows_total = ns * T;
     gu.n_shared = dn.n_shared = 0;
     gu.rows_total = dn.rows_total = P;
-    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream);
-    if (rc == 0) rc = ffn_forward(sgu, sdn, tiles, (hipStream_t)stream);
+    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
+    if (rc == 0) rc = ffn_forward(sgu, sdn, tiles, (hipStream_t)stream, &parts);
   } else {
-    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream);
+    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   }
   if (rc != 0) return rc;
   if (wgate && plan.do_down) return launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
@@ -334,27 +346,29 @@ int moe_shared_forward_ex(const void* x, const void* Wsg, const void* Wsu, const
   const Plan plan = make_plan(T, 1, policy);
   if (!plan.valid) return MOE_ERR_SHAPE;
   const size_t h_bytes = align256((size_t)T * (size_t)Is * 2);
-  const size_t part_bytes = (size_t)tile_down_ksplit(Is) * (size_t)T * (size_t)H * 4;
-  float* part = nullptr;
-  if (!plan.stream && tile_down_ksplit(Is) > 1) {
-    if (plan.tile_rows == 64) {          // asked for by the caller: the room must be there
-      if (workspace_bytes < h_bytes + part_bytes) return MOE_ERR_WORKSPACE;
-      part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes);
-    } else if (plan.tile_rows == 0 && T <= SHARED_SMALL_T) {   // automatic: sizes the helper reports include it
-      if (workspace_bytes < h_bytes + part_bytes) return MOE_ERR_WORKSPACE;
-      part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes);
-    }
+  // Room for K parts of the down projection: the 128x64 shape asked for by the caller and batches up to 512 tokens
+  // must bring it; larger ones (sizes the helper reports include it) use what there is.
+  const size_t one_part = (size_t)T * (size_t)H * 4;
+  int parts_max = 0;
+  if (!plan.stream && (plan.tile_rows == 64 || plan.tile_rows == 0) && tile_down_ksplit(Is) > 1) {
+    const size_t room = workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0;
+    const size_t want = plan.tile_rows == 64 || T <= SHARED_SMALL_T ? (size_t)tile_down_ksplit(Is) : (size_t)shared_parts_room(T, H);
+    if ((plan.tile_rows == 64 || T <= SHARED_SMALL_T) && room < want) return MOE_ERR_WORKSPACE;
+    parts_max = (int)(room < want ? room : want);
   }
+  float* part = parts_max > 1 ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes) : nullptr;
   GemmArgs gu{};
   gu.A = (const bf16_t*)x; gu.B0 = (const bf16_t*)Wsg; gu.B1 = (const bf16_t*)Wsu; gu.C = (bf16_t*)workspace;
   gu.offsets = nullptr; gu.lo = 0; gu.hi = 1; gu.rows_fixed = T; gu.rows_total = T; gu.mean_rows = T;
   gu.N = Is; gu.Kdim = H;
   GemmArgs dn = gu;
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wsd; dn.B1 = nullptr; dn.C = (bf16_t*)S;
-  dn.N = H; dn.Kdim = Is; dn.Cpart = part;
+  dn.N = H; dn.Kdim = Is; dn.Cpart = part; dn.parts_max = part ? parts_max : 0;
   gu.leave_room = (policy >> 10) & 1;
-  int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream);
+  int parts;
+  const int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   if (rc != 0) return rc;
+  if (parts > 1) return launch_sum_parts(part, parts, T, H, S, x, wgate, sg, (hipStream_t)stream);
   if (wgate && plan.do_down) return launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
   return MOE_OK;
 }

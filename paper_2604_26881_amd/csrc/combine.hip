@@ -84,11 +84,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
 }
 
 // sg[t] = <x[t,:], wgate>: one wave per token, fp32.
-__global__ __launch_bounds__(256) void gate_dot_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgate,
-                                                       int T, int H, float* __restrict__ sg) {
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= T) return;
+__device__ __forceinline__ void gate_dot(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgate, int t, int H, int lane,
+                                         float* __restrict__ sg) {
   float a = 0.0f;
   for (int c = lane; c < H / 8; c += 64) {
     const uint4 v = reinterpret_cast<const uint4*>(x + (size_t)t * H)[c];
@@ -100,6 +97,37 @@ __global__ __launch_bounds__(256) void gate_dot_kernel(const bf16_t* __restrict_
   }
   a = wave_sum(a);
   if (lane == 0) sg[t] = a;
+}
+__global__ __launch_bounds__(256) void gate_dot_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgate,
+                                                       int T, int H, float* __restrict__ sg) {
+  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (t < T) gate_dot(x, wgate, t, H, threadIdx.x & 63, sg);
+}
+
+// Second kernel of a down projection whose K was cut: the fp32 parts are added in ascending order and rounded
+// once to bf16.  The workgroups past the sums form the gate logits (wgate may be nullptr), which depend on
+// neither and would otherwise be one more launch of their own (about 4 us behind each K-cut shared expert).
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict__ part, int parts, long n4, bf16_t* __restrict__ C,
+                                                        int sum_groups, const bf16_t* __restrict__ x,
+                                                        const bf16_t* __restrict__ wgate, int T, int H,
+                                                        float* __restrict__ sg) {
+  if ((int)blockIdx.x >= sum_groups) {
+    const int t = ((int)blockIdx.x - sum_groups) * 4 + (threadIdx.x >> 6);
+    if (t < T) gate_dot(x, wgate, t, H, threadIdx.x & 63, sg);
+    return;
+  }
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n4) return;
+  const float4* p = reinterpret_cast<const float4*>(part);
+  float4 s = p[i];
+  for (int k = 1; k < parts; ++k) {
+    const float4 v = p[i + (long)k * n4];
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  uint2 o;
+  o.x = pack_bf16x2(s.x, s.y);
+  o.y = pack_bf16x2(s.z, s.w);
+  reinterpret_cast<uint2*>(C)[i] = o;
 }
 
 // out[t,:] = bf16( u / sqrt(mean_h(u^2) + eps) ),  u = x[t,:] + y[t,:] in fp32: the step between two
@@ -158,6 +186,15 @@ int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, c
   if (T == 0) return 0;
   hipLaunchKernelGGL(combine_kernel, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w,
                      (const bf16_t*)S, n_parts, (long)T * H, sg, H, K, (bf16_t*)out);
+  return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+int launch_sum_parts(const float* part, int parts, int T, int H, void* C, const void* x, const void* wgate, float* sg,
+                     hipStream_t st) {
+  const long n4 = (long)T * H / 4;
+  const int sums = (int)((n4 + 255) / 256), gates = wgate != nullptr ? (T + 3) / 4 : 0;
+  hipLaunchKernelGGL(sum_parts_kernel, dim3(sums + gates), dim3(256), 0, st, part, parts, n4, (bf16_t*)C, sums, (const bf16_t*)x,
+                     (const bf16_t*)wgate, T, H, sg);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 

@@ -91,7 +91,8 @@ struct GemmArgs {
   int mean_rows;       // expected rows per expert (rows_total / experts of the layer): picks kernel shapes
   int N;               // output columns (per branch for gate/up)
   int Kdim;            // contraction length
-  float* Cpart;        // fp32 partial outputs [parts, rows_total, N] of kernels that cut K, else unused
+  float* Cpart;        // room for the fp32 partial outputs [parts, rows_total, N] of kernels that cut K, else unused
+  int parts_max;       // parts that Cpart has room for (0: none)
   const int32_t* gather;   // nullptr: row r of A is A[r]; else row r of A is A[gather[r] / gather_div]
   int gather_div;          // (the token rows themselves, addressed through src_of_row: no permuted copy)
   int leave_room;          // 1: no tile shape that takes a whole CU (all registers of every SIMD): kernels of
@@ -138,13 +139,15 @@ int launch_permute(const int32_t* ids, const void* x, int T, int H, int E, int K
 int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
                    const float* sg, int T, int H, int K, void* out, hipStream_t st);
 int launch_residual_norm(const void* x, const void* y, int T, int H, float eps, void* out, hipStream_t st);
+// C = the `parts` fp32 tensors [T,H] of a K-cut down projection, added in ascending part; with wgate also sg = <x, wgate>
+int launch_sum_parts(const float* part, int parts, int T, int H, void* C, const void* x, const void* wgate, float* sg,
+                     hipStream_t st);
 int launch_gate_dot(const void* x, const void* wgate, int T, int H, float* sg, hipStream_t st);
 int launch_mfma_probe(const void* operands, int iters, int workgroups, long long* clocks, hipStream_t st);
 // Tiled MFMA kernels (many rows per expert) and streaming kernels (few rows per expert).
 int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st);
-int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st);
-int tile_down_ksplit(int Kdim);   // K parts of the down projection when tile_rows == 64
-int pick_tile_shape(int rows, int N, int Kdim, bool gateup, bool allow_kcut, bool leave_room);   // one weight set, known rows
+int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* parts);
+int tile_down_ksplit(int Kdim);   // most K parts of the down projection
 // Streaming kernels that stage the weights through wave-private LDS rings (whole-line requests): a few rows per
 // expert, and up to a few dozen.
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st);

@@ -42,6 +42,7 @@
 // Rows past the end of an expert are clamped on load (they recompute the expert's last row) and
 // masked on store, which keeps the K loop free of branches.
 #include <math.h>
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 #include "common.h"
@@ -64,7 +65,7 @@ struct TileShape {
   static constexpr int NM = TB * NB;              // MFMAs per wave and 16-wide K slice
   static constexpr int DIST = NS - 1;             // stages in flight while one is being multiplied
   static constexpr int NOUT = GATEUP ? BN / 2 : BN;  // output columns per tile
-  static constexpr int GM = BN >= 256 ? 4 : 1;    // token tiles per locality group of the tile walk
+  static constexpr int GM = 4;                    // token tiles per locality group of the tile walk
   // The NL copies of a stage are requested in three places, so that the address unit of the CU
   // (one copy instruction of 1 KB keeps it busy for about 16 clocks) is not asked for a whole stage
   // within one K slice: ISSUE0 of them while the last slice of the stage that frees the buffer is
@@ -156,7 +157,11 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   const int Kdim = a.Kdim;
   const int nk = Kdim / S::BK / KSPLIT;          // K steps of one work item (a tile, or a K part of it)
   const int groupTiles = S::GM * NT;
-  const int Lend = ngrp * groupTiles * KSPLIT;
+  // With one class the walk ends with its last tile.  (With two, the incomplete last group of each leaves a
+  // gap; tiles of a complete index space that do not exist would otherwise push real ones into one more round:
+  // 777 tokens on one weight set are 5 tiles of 160 rows by 44 column tiles, 220 for 256 workgroups, and took
+  // 73 us as 8 x 44 with gaps.)
+  const int Lend = (grp0 == 0 || grp1 == 0 ? (total0 + total1) * NT : ngrp * groupTiles) * KSPLIT;
   // Divisions of the walk, prepared once per workgroup so that finding a tile costs multiplications only:
   // light groups among the first g groups of the merged walk = (g * light_ratio) >> 32, with light_ratio =
   // ceil(grp0 * 2^32 / ngrp): monotone in g, rises by at most one per group, and is exactly grp0 at g = ngrp,
@@ -205,11 +210,16 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   int it = 0;
   auto next_tile = [&]() -> TileState {
     TileState t{};
-    int L = 0, mrow = 0, nt = 0, cls = 0;
+    int L = 0, mrow = 0, nt = 0, cls = 0, ks = 0;
     for (;; ++it) {
       L = xcd_walk ? ((it * 8 + (int)(blockIdx.x & 7)) * run + slot) : (it * G + (int)blockIdx.x);
       if (L >= Lend) { t.valid = false; return t; }
-      const int Lt = KSPLIT > 1 ? L / KSPLIT : L;
+      int Lt = L;
+      ks = 0;
+      if constexpr (KSPLIT > 1) {   // K parts outermost: the items of an XCD share panels, not only sums
+        const int tiles = Lend / KSPLIT;
+        while (Lt >= tiles) { Lt -= tiles; ++ks; }
+      }
       int grp = Lt, rem = 0;
       if (groupTiles > 1) {
         grp = (int)__umulhi((uint32_t)Lt, gt_magic);   // floor(2^32/d) underestimates the quotient by at most one
@@ -219,13 +229,20 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
       // group grp of the merged walk: light groups are spread evenly between the heavy ones
       const int before = (int)(((unsigned long long)(unsigned)grp * light_ratio) >> 32);          // light groups among the first grp
       cls = (int)(((unsigned long long)(unsigned)(grp + 1) * light_ratio) >> 32) > before ? 0 : 1;
-      mrow = (cls == 0 ? before : grp - before) * S::GM + rem % S::GM;
-      nt = rem / S::GM;
-      if (mrow < (cls == 0 ? total0 : total1)) break;
+      const int first = (cls == 0 ? before : grp - before) * S::GM;      // first token tile of the group
+      const int size = min(S::GM, (cls == 0 ? total0 : total1) - first);    // its token tiles
+      if (size == S::GM) {
+        nt = rem / S::GM;
+        mrow = first + rem % S::GM;
+      } else {
+        nt = rem / size;
+        mrow = first + rem - nt * size;
+      }
+      if (nt < NT) break;
     }
     ++it;
     t.valid = true;
-    t.ks = KSPLIT > 1 ? L % KSPLIT : 0;   // K part of this work item
+    t.ks = ks;   // K part of this work item
 
     // expert of this token tile: last e with s_pref[cls][e] <= mrow (an expert of the other class
     // repeats its successor's prefix, so the last one is of this class)
@@ -550,23 +567,6 @@ static int num_cus() {
   return n;
 }
 
-// Sum of the KSPLIT fp32 partial outputs in ascending K part, rounded once to bf16.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part, int ksplit, long n4, long stride4,
-                                                            bf16_t* __restrict__ C) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n4) return;
-  const float4* p = reinterpret_cast<const float4*>(part);
-  float4 s = p[i];
-  for (int k = 1; k < ksplit; ++k) {
-    const float4 v = p[i + (long)k * stride4];
-    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-  }
-  uint2 o;
-  o.x = pack_bf16x2(s.x, s.y);
-  o.y = pack_bf16x2(s.z, s.w);
-  reinterpret_cast<uint2*>(C)[i] = o;
-}
-
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE>
 static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
@@ -592,13 +592,7 @@ static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   launched.clocks = t_clock_buffer;
   launched.clock_groups = t_clock_groups;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, launched);
-  if (hipGetLastError() != hipSuccess) return -4;
-  if (KSPLIT > 1) {
-    const long n4 = (long)a.rows_total * a.N / 4;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, a.Cpart, KSPLIT, n4, n4, a.C);
-    if (hipGetLastError() != hipSuccess) return -4;
-  }
-  return 0;
+  return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
 // Batches whose mean expert needs more than four tiles hold (next to) no single-tile expert: they run the
@@ -614,37 +608,42 @@ static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
   return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, false>(a, st);
 }
 
-// Tile shape codes: 256 = 256x256, 128/129 = 128 token rows x 256 weight rows, 130 = 128x128,
-// 64 = 128x64 (for the down projection with a K cut into parts summed in order by a second kernel
-// when the caller provides room for the partial sums); 0 = choose from layer-wide sizes only
-// (never from the block bounds).
+// Tile shape codes: 256 = 256x256, 160 = 160 token rows x 256 weight rows, 128/129 = 128 x 256,
+// 130 = 128x128, 64 = 128x64 (the last two also with the K of a down projection cut into parts, whose fp32
+// sums a second kernel adds in order, when the caller provides room for them); 0 = choose from layer-wide
+// sizes only (never from the block bounds).
 //
 // One weight set on a known number of rows (the shared expert): the shape with the least estimated
 // time.  A launch takes ceil(items / CUs) rounds of one tile each, a tile costs rows x columns x K
 // times a per-shape factor (smaller tiles move more bytes per flop through LDS).  The factors come
-// from timing the four shapes at T = 128 ... 8192 on the Qwen shape; the K cut pays a reduction
-// pass over its fp32 partial sums.
-int tile_down_ksplit(int Kdim) { return Kdim % 512 == 0 ? 8 : Kdim % 256 == 0 ? 4 : Kdim % 128 == 0 ? 2 : 1; }
-int pick_tile_shape(int rows, int N, int Kdim, bool gateup, bool allow_kcut, bool leave_room) {
-  struct Cand { int code, bm, nout; double c; };
-  const Cand cands[4] = {{256, 256, gateup ? 128 : 256, 1.0}, {129, 128, gateup ? 128 : 256, 1.1},
-                         {130, 128, gateup ? 64 : 128, 1.42}, {64, 128, gateup ? 32 : 64, 1.77}};
+// from timing the five shapes at T = 128 ... 16384 on the Qwen shape; the K cut pays a reduction
+// pass over its fp32 partial sums (5 us and their bytes, written and read, at 5 TB/s).  What the choice is
+// about is filling the chip in whole rounds: gate/up at T = 777 is 176 tiles of 256 rows or 220 of 160 (58 and
+// 46 us), the down projection there 112 tiles of 128x128 or twice as many of half the K (44 and 29 us), at
+// T = 512 64 tiles or 256 quarters (42 and 25 us).
+static int largest_ksplit(int Kdim) { return Kdim % 512 == 0 ? 8 : Kdim % 256 == 0 ? 4 : Kdim % 128 == 0 ? 2 : 1; }
+int tile_down_ksplit(int Kdim) { return largest_ksplit(Kdim); }
+struct TileChoice { int code, parts; };
+static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int parts_max, bool leave_room) {
+  struct Cand { int code, bm, nout; double c; bool cut; };
+  const Cand cands[5] = {{256, 256, gateup ? 128 : 256, 1.0, false}, {160, 160, gateup ? 128 : 256, 1.07, false},
+                         {129, 128, gateup ? 128 : 256, 1.1, false}, {130, 128, gateup ? 64 : 128, 1.42, true},
+                         {64, 128, gateup ? 32 : 64, 1.77, true}};
   const double cus = (double)num_cus();
-  const double units_per_us = 2.1e6;   // 256x256x5632 tile: about 175 us
-  int best = 129;
+  const double units_per_us = 3.0e6;   // 256x256x2048 tile: 45 us
+  TileChoice best{129, 1};
   double best_cost = 0.0;
   for (const Cand& k : cands) {
-    int parts = 1;
     if (k.code == 256 && leave_room) continue;   // 256x256 holds all 512 registers of every SIMD
-    if (k.code == 64) {
-      if (!gateup && !allow_kcut) continue;   // 32 column tiles would leave most CUs idle
-      if (!gateup) parts = tile_down_ksplit(Kdim);
+    const int most = gateup || !k.cut ? 1 : std::max(1, std::min(parts_max, largest_ksplit(Kdim)));
+    for (int parts = 1; parts <= most; parts *= 2) {
+      if (k.code == 64 && !gateup && parts == 1) continue;   // (128x128 serves such a batch better)
+      const double items = (double)((rows + k.bm - 1) / k.bm) * (double)((N + k.nout - 1) / k.nout) * parts;
+      const double rounds = (double)(long)((items + cus - 1) / cus);
+      double cost = rounds * k.bm * k.nout * ((double)Kdim / parts) * k.c;
+      if (parts > 1) cost += (5.0 + (double)rows * N * parts * 8.0 / 5.0e6) * units_per_us;
+      if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = TileChoice{k.code, parts}; }
     }
-    const double items = (double)((rows + k.bm - 1) / k.bm) * (double)((N + k.nout - 1) / k.nout) * parts;
-    const double rounds = (double)(long)((items + cus - 1) / cus);
-    double cost = rounds * k.bm * k.nout * ((double)Kdim / parts) * k.c;
-    if (parts > 1) cost += (4.0 + (double)rows * N * parts * 4.0 / 4.0e6) * units_per_us;
-    if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = k.code; }
   }
   return best;
 }
@@ -657,10 +656,10 @@ int pick_tile_shape(int rows, int N, int Kdim, bool gateup, bool allow_kcut, boo
 // Measured on uniform routing at T = 768 ... 8192 the pick is the fastest shape or within 3 % of
 // it; Zipf-skewed routing (mean 273, median 130) and the multi-tenant batch (mean 137) also run
 // fastest on its choice (160).
-static int pick_tile_rows(const GemmArgs& a, int tile_rows, int nout, bool down) {
-  (void)nout;
-  if (tile_rows != 0) return tile_rows;
-  if (a.offsets == nullptr) return pick_tile_shape(a.rows_total, a.N, a.Kdim, !down, a.Cpart != nullptr, a.leave_room != 0);
+static TileChoice pick_tile(const GemmArgs& a, int tile_rows, bool gateup) {
+  if (tile_rows == 64 && !gateup && a.parts_max > 0) return TileChoice{64, std::min(a.parts_max, largest_ksplit(a.Kdim))};
+  if (tile_rows != 0) return TileChoice{tile_rows, 1};
+  if (a.offsets == nullptr) return pick_tile_shape(a.rows_total, a.N, a.Kdim, gateup, a.parts_max, a.leave_room != 0);
   const double m = (double)a.mean_rows + 1.5 * sqrt((double)a.mean_rows);
   const int heights[3] = {129, 160, 256};
   const double factor[3] = {1.41, 1.23, 1.0};
@@ -671,27 +670,37 @@ static int pick_tile_rows(const GemmArgs& a, int tile_rows, int nout, bool down)
     const double cost = ceil(m / bm) * bm * factor[i];
     if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = heights[i]; }
   }
-  return best;
+  return TileChoice{best, 1};
 }
 int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st) {
-  const int t = pick_tile_rows(a, tile_rows, 128, false);
+  const int t = pick_tile(a, tile_rows, true).code;
   if (t == 64) return launch_tile_t<128, 64, 4, 1, true, 6, 1>(a, st);
   if (t == 130) return launch_tile_t<128, 128, 2, 2, true, 4, 1>(a, st);
   if (t >= 256) return launch_tile_t<256, 256, 2, 2, true, 2, 1>(a, st);
   if (t == 160) return launch_tile_t<160, 256, 1, 4, true, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, true, 3, 1>(a, st);
 }
-int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st) {
-  const int t = pick_tile_rows(a, tile_rows, 256, true);
+// *parts: in how many K parts the output was left in a.Cpart (1: the output itself is written)
+int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* parts) {
+  const TileChoice c = pick_tile(a, tile_rows, false);
+  const int t = c.code;
+  *parts = c.parts;
   if (t == 64) {
-    switch (a.Cpart ? tile_down_ksplit(a.Kdim) : 1) {   // without a buffer for the parts: whole K per tile
+    switch (c.parts) {   // without a buffer for the parts: whole K per tile
       case 8: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 8>(a, st);
       case 4: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 4>(a, st);
       case 2: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 2>(a, st);
       default: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 1>(a, st);
     }
   }
-  if (t == 130) return launch_tile_t<128, 128, 2, 2, false, 4, 1>(a, st);
+  if (t == 130) {
+    switch (c.parts) {
+      case 8: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 8>(a, st);
+      case 4: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 4>(a, st);
+      case 2: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 2>(a, st);
+      default: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 1>(a, st);
+    }
+  }
   if (t >= 256) return launch_tile_t<256, 256, 2, 2, false, 2, 1>(a, st);
   if (t == 160) return launch_tile_t<160, 256, 1, 4, false, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, false, 3, 1>(a, st);

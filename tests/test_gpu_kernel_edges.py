@@ -110,3 +110,39 @@ def test_block_call_that_hosts_the_shared_experts_on_few_rows(moe, oracle64, T):
         sl = slice(p * s.I, (p + 1) * s.I)
         S, sg = oracle64.shared_forward(d["x"], d["Wsg"][sl], d["Wsu"][sl], np.ascontiguousarray(d["Wsd"][:, sl]), d["wgate"])
         check_close(f64(buf.S_parts[p]), S, f"shared expert {p}")
+
+
+@pytest.mark.parametrize("T,H,Is", [(513, 256, 1024), (640, 1024, 256), (700, 1536, 768), (1000, 128, 640),
+                                          (129, 512, 1024), (300, 2048, 512), (1100, 3072, 128)])
+def test_shared_expert_with_the_down_projection_cut_along_k(moe, oracle64, T, H, Is):
+    # the parts that the workspace has room for (at most; K must also divide into them), and none of them
+    wl = workloads.qwen_layer(T, 900 + T, H=H, E=4, K=1, I=64, Is=Is, renorm=False)
+    g, d = wl.to("cuda"), wl.f32_numpy()
+    full = int(moe.load().moe_shared_workspace_bytes(T, H, Is))
+    h_only = (T * Is * 2 + 255) // 256 * 256
+    if T > 512:
+        assert full in (h_only, h_only + 2 * T * H * 4, h_only + 4 * T * H * 4, h_only + 8 * T * H * 4)
+    S_ref, sg_ref = oracle64.shared_forward(d["x"], d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"])
+    for nbytes in {full, h_only} if T > 512 else {full}:
+        print(f"[case] shared expert T={T} H={H} Is={Is}, workspace {nbytes}", flush=True)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        S = torch.full((T, H), 768.0, dtype=torch.bfloat16, device="cuda")
+        sg = torch.full((T,), 768.0, dtype=torch.float32, device="cuda")
+        moe.moe_shared_forward(g.x, g.Wsg, g.Wsu, g.Wsd, g.wgate, S, sg, ws)
+        torch.cuda.synchronize()
+        check_close(f64(S), S_ref, f"S, workspace {nbytes}")
+        assert np.allclose(sg.cpu().numpy(), sg_ref, rtol=1e-4, atol=1e-5)
+
+
+@pytest.mark.parametrize("T", [33, 160, 161, 640, 641, 700])     # 1, 2, 4, 5 token tiles of 160 rows and one row more
+def test_shared_expert_walk_over_incomplete_tile_groups(moe, oracle64, T):
+    wl = workloads.qwen_layer(T, 950 + T, H=128, E=4, K=1, I=64, Is=448, renorm=False)
+    g, d = wl.to("cuda"), wl.f32_numpy()
+    S_ref, _ = oracle64.shared_forward(d["x"], d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"])
+    ws = torch.empty(int(moe.load().moe_shared_workspace_bytes(T, 128, 448)) + 8 * T * 128 * 4, dtype=torch.uint8, device="cuda")
+    for policy in (3, 4, 8, 10, 11):
+        S = torch.full((T, 128), 768.0, dtype=torch.bfloat16, device="cuda")
+        sg = torch.empty(T, dtype=torch.float32, device="cuda")
+        moe.moe_shared_forward(g.x, g.Wsg, g.Wsu, g.Wsd, g.wgate, S, sg, ws, policy)
+        torch.cuda.synchronize()
+        check_close(f64(S), S_ref, f"S, T={T} policy {policy}")
