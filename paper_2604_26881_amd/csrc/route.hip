@@ -2,8 +2,7 @@
 // network selects the top-k experts for each token; Sec. 3: it runs in the orchestrator).
 //
 // A wave keeps TOK token rows in registers as fp32, streams EB router rows per step and forms
-// TOK*EB dot products at once; the waves of a workgroup either share the tokens and split the
-// experts, or each take their own tokens and all the experts.  The dot products are formed
+// TOK*EB dot products at once; the waves of a workgroup share the tokens and split the experts.  The dot products are formed
 // (independent accumulator chains) in the fixed order of the interface: lane j owns elements 512*c + 8*j .. +7 of every 512-element chunk c (one 16-byte
 // load per chunk) and accumulates them in ascending index by fused multiply-add; the 64 lane sums
 // are folded pairwise over lane strides 1, 2, 4, 8, 16, 32.  The fold runs on the VALU with DPP
@@ -128,7 +127,8 @@ __device__ __forceinline__ void softmax_topk(const float (&l)[4], int lane, int 
   }
 }
 
-// Few tokens: the NW waves of a workgroup share TOK tokens and split the experts.
+// Long rows (beyond 2048 elements) and few tokens: the NW waves of a workgroup share one token and split the experts,
+// and every logit is folded by itself.
 // FULL: H == 512 * C, so no lane is beyond the row and the loads carry no predicate.
 // Bias row of token t.  With segment bounds (seg[0] = 0 < ... , n_seg + 1 ascending entries) token
 // t of segment s (seg[s] <= t < seg[s+1]; tokens at or past seg[n_seg] count to the last one) takes
@@ -143,13 +143,13 @@ __device__ __forceinline__ const float* bias_row(const float* bias, const int32_
   return bias + (size_t)s * E;
 }
 
-template <int C, int TOK, int EB, int NW, bool FULL>
+template <int C, int EB, int NW, bool FULL>
 __global__ __launch_bounds__(NW * 64) void route_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wr,
                                                         const float* __restrict__ bias_rows,
                                                         const int32_t* __restrict__ seg, int n_seg, int T, int H,
                                                         int E, int K, int renorm, int32_t* __restrict__ ids,
                                                         float* __restrict__ w) {
-  static_assert(TOK == 1, "one bias row per workgroup");
+  constexpr int TOK = 1;
   __shared__ float s_logit[TOK][ROUTE_EMAX];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int t0 = blockIdx.x * TOK;
@@ -248,23 +248,49 @@ __global__ __launch_bounds__(NW * 64) void route_kernel(const bf16_t* __restrict
   }
 }
 
-// Many tokens: each of the four waves keeps its own TOK tokens and walks all experts EB at a time
-// (the waves read the same router rows at about the same time, so they reach L2 once per
-// workgroup).  The EB * TOK lane sums of a batch are folded together (fold_rows); the four row sums
-// of every logit go to LDS as one float4, and the lane that later owns the expert finishes the fold:
-// strides 16 and 32 pair rows (0,1), (2,3) and then the two results.  Dynamic LDS:
-// 4 * TOK * EP float4, EP = E rounded up to a multiple of EB (the rows of a ragged last batch are
-// clamped copies of row E-1; their sums land in the padding and are never read).
-template <int C, int TOK, int EB, bool FULL>
-__global__ __launch_bounds__(256) void route_many_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wr,
-                                                         const float* __restrict__ bias_rows,
-                                                         const int32_t* __restrict__ seg, int n_seg, int T, int H,
-                                                         int E, int EP, int K, int renorm,
-                                                         int32_t* __restrict__ ids, float* __restrict__ w) {
-  constexpr int NW = 4, WTOK = NW * TOK, NV = EB * TOK, NJ = NV / 4;
+// A workgroup holds TG groups of TOK tokens; NW / TG waves per group split the experts, EB at a time.  What bounds it
+// is the vector ALU and, with few tokens, latency: a product costs one fused multiply-add, a router element one more instruction to widen it, so a
+// router row in registers serves TOK tokens, and the EB * TOK lane sums of a batch are folded together (fold_rows).
+// The four row sums of every logit go to LDS as one float4, and the lane that later owns the expert finishes the
+// fold: strides 16 and 32 pair rows (0,1), (2,3) and then the two results.  Splitting the experts (and not only the
+// tokens) over the waves reads the router once per workgroup instead of once per wave and gives a batch of a few
+// hundred tokens a workgroup on every CU with a short serial chain.  Dynamic LDS: TG * TOK * EP float4, EP = E
+// rounded up to a multiple of EB (the rows of a ragged last batch are clamped copies of row E-1; their sums land
+// in the padding and are never read).
+// OCC = 2 (with four waves) keeps a wave within 256 registers, so that the workgroup fits beside a 128-row GEMM tile of another stream
+// instead of waiting behind it.
+template <int C, int TOK, int EB, int NW, int TG, int OCC, bool FULL>
+__global__ __launch_bounds__(NW * 64, OCC) void route_many_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ Wr,
+                                                              const float* __restrict__ bias_rows,
+                                                              const int32_t* __restrict__ seg, int n_seg, int T, int H,
+                                                              int E, int EP, int K, int renorm,
+                                                              int32_t* __restrict__ ids, float* __restrict__ w) {
+  constexpr int NV = EB * TOK, NJ = NV / 4, WTOK = TG * TOK;
+  constexpr bool AHEAD = NW <= 8;   // (16 waves hide each other's loads, and have half the registers)
   extern __shared__ float4 s_rows[];   // [WTOK][EP] : row sums 0..3 of a logit
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int t0 = blockIdx.x * WTOK + wave * TOK;
+  const int tbase = blockIdx.x * WTOK, tg = wave % TG;   // the TG waves of an expert group run side by side: one reads L2, the others L1
+  const int t0 = tbase + tg * TOK;
+
+  auto load_batch = [&](u32x4 (&wr)[EB][C], int e0) {
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      const int e = min(e0 + i, E - 1);
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int h = 512 * c + 8 * lane;
+        if (FULL) {
+          wr[i][c] = *reinterpret_cast<const u32x4*>(Wr + (size_t)e * H + h);
+        } else {
+          wr[i][c] = u32x4{0u, 0u, 0u, 0u};
+          if (h < H) wr[i][c] = *reinterpret_cast<const u32x4*>(Wr + (size_t)e * H + h);
+        }
+      }
+    }
+  };
+  u32x4 wrA[EB][C];
+  int e0 = wave / TG * EB;
+  if (e0 < E) load_batch(wrA, e0);
 
   float xf[TOK][C][8];
 #pragma unroll
@@ -284,28 +310,12 @@ __global__ __launch_bounds__(256) void route_many_kernel(const bf16_t* __restric
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int v = 4 * j + (lane & 3);
-    slot[j] = ((wave * TOK + v % TOK) * EP + v / TOK) * 4 + (lane >> 4);
+    slot[j] = ((tg * TOK + v % TOK) * EP + v / TOK) * 4 + (lane >> 4);
   }
   const bool writer = (lane & 12) == 0;
   float* s_flat = reinterpret_cast<float*>(s_rows);
 
-  auto load_batch = [&](u32x4 (&wr)[EB][C], int e0) {
-#pragma unroll
-    for (int i = 0; i < EB; ++i) {
-      const int e = min(e0 + i, E - 1);
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const int h = 512 * c + 8 * lane;
-        if (FULL) {
-          wr[i][c] = *reinterpret_cast<const u32x4*>(Wr + (size_t)e * H + h);
-        } else {
-          wr[i][c] = u32x4{0u, 0u, 0u, 0u};
-          if (h < H) wr[i][c] = *reinterpret_cast<const u32x4*>(Wr + (size_t)e * H + h);
-        }
-      }
-    }
-  };
-  auto dot_batch = [&](const u32x4 (&wr)[EB][C], int e0) {
+  auto dot_batch = [&](const u32x4 (&wr)[EB][C], int e_) {
     float a[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) a[v] = 0.0f;
@@ -325,15 +335,14 @@ __global__ __launch_bounds__(256) void route_many_kernel(const bf16_t* __restric
     fold_rows<NV>(a, cs, lane);
     if (writer) {
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) s_flat[slot[j] + e0 * 4] = cs[j];
+      for (int j = 0; j < NJ; ++j) s_flat[slot[j] + e_ * 4] = cs[j];
     }
   };
-  {
-    u32x4 wrA[EB][C], wrB[EB][C];
-    int e0 = 0;
-    load_batch(wrA, e0);
+  constexpr int STEP = NW / TG * EB;
+  if constexpr (AHEAD) {   // the next batch is requested before the current one is multiplied
+    u32x4 wrB[EB][C];
     while (e0 < E) {
-      const int e1 = e0 + EB, e2 = e0 + 2 * EB;
+      const int e1 = e0 + STEP, e2 = e0 + 2 * STEP;
       if (e1 < E) load_batch(wrB, e1);
       dot_batch(wrA, e0);
       if (e1 < E) {
@@ -342,10 +351,15 @@ __global__ __launch_bounds__(256) void route_many_kernel(const bf16_t* __restric
       }
       e0 = e2;
     }
+  } else {
+    while (e0 < E) {
+      dot_batch(wrA, e0);
+      e0 += STEP;
+      if (e0 < E) load_batch(wrA, e0);
+    }
   }
   __syncthreads();
 
-  const int tbase = blockIdx.x * WTOK;
   for (int tk = wave; tk < WTOK; tk += NW) {
     const int t = tbase + tk;
     if (t >= T) break;
@@ -370,53 +384,67 @@ __global__ __launch_bounds__(256) void route_many_kernel(const bf16_t* __restric
                          int E, int K, int renorm, int32_t* ids, float* w, hipStream_t st
 #define MOE_ROUTE_ARGS x, Wr, bias, seg, n_seg, T, H, E, K, renorm, ids, w, st
 
-template <int C, int TOK, int EB, int NW>
+template <int C, int EB, int NW>
 static int launch_route_t(MOE_ROUTE_PARAMS) {
-  const int blocks = (T + TOK - 1) / TOK;
   if (H == 512 * C)
-    hipLaunchKernelGGL((route_kernel<C, TOK, EB, NW, true>), dim3(blocks), dim3(NW * 64), 0, st, (const bf16_t*)x,
+    hipLaunchKernelGGL((route_kernel<C, EB, NW, true>), dim3(T), dim3(NW * 64), 0, st, (const bf16_t*)x,
                        (const bf16_t*)Wr, bias, seg, n_seg, T, H, E, K, renorm, ids, w);
   else
-    hipLaunchKernelGGL((route_kernel<C, TOK, EB, NW, false>), dim3(blocks), dim3(NW * 64), 0, st, (const bf16_t*)x,
+    hipLaunchKernelGGL((route_kernel<C, EB, NW, false>), dim3(T), dim3(NW * 64), 0, st, (const bf16_t*)x,
                        (const bf16_t*)Wr, bias, seg, n_seg, T, H, E, K, renorm, ids, w);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
-template <int C, int TOK, int EB>
+template <int C, int TOK, int EB, int NW, int TG, int OCC>
 static int launch_route_many(MOE_ROUTE_PARAMS) {
-  constexpr int WTOK = 4 * TOK;
+  constexpr int WTOK = TOK * TG;
   const int blocks = (T + WTOK - 1) / WTOK;
   const int EP = (E + EB - 1) / EB * EB;
   const size_t lds = (size_t)WTOK * EP * sizeof(float4);   // at most 16 tokens * 256 experts * 16 B = 64 KiB
   if (H == 512 * C)
-    hipLaunchKernelGGL((route_many_kernel<C, TOK, EB, true>), dim3(blocks), dim3(256), lds, st, (const bf16_t*)x,
+    hipLaunchKernelGGL((route_many_kernel<C, TOK, EB, NW, TG, OCC, true>), dim3(blocks), dim3(NW * 64), lds, st, (const bf16_t*)x,
                        (const bf16_t*)Wr, bias, seg, n_seg, T, H, E, EP, K, renorm, ids, w);
   else
-    hipLaunchKernelGGL((route_many_kernel<C, TOK, EB, false>), dim3(blocks), dim3(256), lds, st, (const bf16_t*)x,
+    hipLaunchKernelGGL((route_many_kernel<C, TOK, EB, NW, TG, OCC, false>), dim3(blocks), dim3(NW * 64), lds, st, (const bf16_t*)x,
                        (const bf16_t*)Wr, bias, seg, n_seg, T, H, E, EP, K, renorm, ids, w);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
-// Few tokens: one token per workgroup of 8 waves that split the experts, each wave takes its
-// experts in one batch (latency).  From 384 tokens: the same with 4 waves (19 against 22 us at
-// T = 512, and with one wave per SIMD the workgroup fits beside a 128-row GEMM tile of another
-// stream instead of waiting behind it).  From 1024 tokens: the many-token kernel (throughput).
+// Tokens of a workgroup: few, so that every CU gets one, until the chip is full; then more, because a router row in
+// registers serves TOK tokens and the TG waves that walk the same experts share it through L1 (L2 delivered about
+// 10 TB/s to these kernels, which bounds the variants that read the router most often).  Where the lines lie, us per
+// launch at H 2048, 60 experts | H 1024, 128 experts, top 8 (graph of 30 launches):
+//   1 token, 16 waves: T = 256 7.0 | 8.3; 301 12.0 | 11.9      (8 waves that fold every logit by itself: 7.9 | 10.3)
+//   2 tokens, 4 waves: T = 256 8.8 | 10.5; 301 8.8 | 10.6; 512 9.1 | 11.0; 600 11.5 | 14.1
+//   4 tokens, 4 waves: T = 512 11.1 | 13.1; 600 11.2 | 13.3; 2048 15.4 | 18.5; 4096 27.5 | 32.5; 16384 99.7 | 113
+//   8 tokens, 4 waves in pairs: T = 2048 18.8 | 24.1; 3000 25.3 | 32.2; 4096 26.0 | 32.9; 16384 90.6 | 112
+// Before, with one token per workgroup below 1024 and every wave on tokens of its own from there on: T = 301 13.7 | 18.5;
+// 777 18.3 | 25.9; 2048 22.9 | 28.5; 4096 30.2 | 36.9.
+// Rows beyond 2048 elements hold half as many tokens in registers; H 4096, 60 experts: T = 301 18.7 -> 13.5,
+// 777 26.2 -> 20.6, 4096 77 -> 71, 16384 288 -> 277 (up to 256 tokens the widening kernel above is still the fastest).
 int launch_route(MOE_ROUTE_PARAMS) {
   const int chunks = (H + 511) / 512;
-  const bool many = T >= 1024, mid = T >= 384;
-  if (chunks <= 1)
-    return many ? launch_route_many<1, 4, 4>(MOE_ROUTE_ARGS)
-                : (mid ? launch_route_t<1, 1, 8, 4>(MOE_ROUTE_ARGS) : launch_route_t<1, 1, 8, 8>(MOE_ROUTE_ARGS));
-  if (chunks <= 2)
-    return many ? launch_route_many<2, 2, 4>(MOE_ROUTE_ARGS)
-                : (mid ? launch_route_t<2, 1, 8, 4>(MOE_ROUTE_ARGS) : launch_route_t<2, 1, 8, 8>(MOE_ROUTE_ARGS));
-  if (chunks <= 4)
-    return many ? launch_route_many<4, 2, 2>(MOE_ROUTE_ARGS)
-                : (mid ? launch_route_t<4, 1, 4, 4>(MOE_ROUTE_ARGS) : launch_route_t<4, 1, 4, 8>(MOE_ROUTE_ARGS));
-  if (chunks <= 8)
-    return many ? launch_route_many<8, 2, 2>(MOE_ROUTE_ARGS)
-                : (mid ? launch_route_t<8, 1, 2, 4>(MOE_ROUTE_ARGS) : launch_route_t<8, 1, 2, 8>(MOE_ROUTE_ARGS));
-  if (chunks <= 16) return launch_route_t<16, 1, 1, 4>(MOE_ROUTE_ARGS);
+  const int size = T <= 256 ? 0 : T <= 512 ? 1 : T <= 1024 ? 2 : T <= 2048 ? 3 : T < 4096 ? 4 : 5;
+  if (chunks <= 1) {
+    if (size == 0) return launch_route_many<1, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
+    return size == 1 ? launch_route_many<1, 2, 4, 4, 1, 2>(MOE_ROUTE_ARGS) : launch_route_many<1, 4, 4, 4, 1, 2>(MOE_ROUTE_ARGS);
+  }
+  if (chunks <= 2) {
+    if (size == 0) return launch_route_many<2, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
+    return size == 1 ? launch_route_many<2, 2, 4, 4, 1, 2>(MOE_ROUTE_ARGS) : launch_route_many<2, 4, 4, 4, 1, 2>(MOE_ROUTE_ARGS);
+  }
+  if (chunks <= 4) {
+    if (size == 0) return launch_route_many<4, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
+    if (size == 1) return launch_route_many<4, 2, 2, 4, 1, 2>(MOE_ROUTE_ARGS);
+    return size < 5 ? launch_route_many<4, 4, 2, 4, 1, 2>(MOE_ROUTE_ARGS) : launch_route_many<4, 4, 2, 4, 2, 2>(MOE_ROUTE_ARGS);
+  }
+  if (chunks <= 8) {
+    if (size == 0) return launch_route_t<8, 2, 8>(MOE_ROUTE_ARGS);
+    if (size == 1) return launch_route_many<8, 2, 2, 4, 1, 1>(MOE_ROUTE_ARGS);
+    if (size == 2) return launch_route_many<8, 2, 2, 4, 2, 1>(MOE_ROUTE_ARGS);
+    return size == 3 ? launch_route_many<8, 2, 2, 4, 4, 1>(MOE_ROUTE_ARGS) : launch_route_many<8, 4, 1, 4, 4, 1>(MOE_ROUTE_ARGS);
+  }
+  if (chunks <= 16) return launch_route_t<16, 1, 4>(MOE_ROUTE_ARGS);
   return -2;
 }
 #undef MOE_ROUTE_ARGS

@@ -146,3 +146,23 @@ def test_shared_expert_walk_over_incomplete_tile_groups(moe, oracle64, T):
         moe.moe_shared_forward(g.x, g.Wsg, g.Wsu, g.Wsd, g.wgate, S, sg, ws, policy)
         torch.cuda.synchronize()
         check_close(f64(S), S_ref, f"S, T={T} policy {policy}")
+
+
+@pytest.mark.parametrize("H", [64, 960, 1024, 1984, 2048, 3072, 4096])
+@pytest.mark.parametrize("T", [1, 255, 256, 257, 511, 512, 513, 1024, 1025, 2049, 4095, 4097])
+def test_router_sums_keep_their_order_in_every_variant(moe, oracle64, T, H):
+    # The batch repeats one token and bias[e] = -(the oracle's fp32 logit of e): every logit becomes exactly 0 when it
+    # has the oracle's bits, and ids 0..K-1 win the tie at weight 1/E; one ulp anywhere changes the ids.
+    E, K = (61, 4) if H % 512 else (66, 7)      # ragged last batches of experts
+    print(f"[case] router variants T={T} H={H}", flush=True)
+    g = torch.Generator().manual_seed(T * 7 + H)
+    x = ((torch.rand((1, H), generator=g) - 0.5) * torch.pow(2.0, torch.randint(-8, 9, (1, H), generator=g).float())).to(torch.bfloat16)
+    Wr = (torch.randn((E, H), generator=g) * 0.05).to(torch.bfloat16)
+    _, _, L = oracle64.route(x.float().numpy(), Wr.float().numpy(), None, K, False, want_logits=True)
+    expect = np.tile(np.arange(K, dtype=np.int32), (T, 1))
+    for sign in (1.0, -1.0):
+        bias = torch.from_numpy(-sign * L[0]).contiguous().cuda()
+        ids, w = moe.moe_route(x.repeat(T, 1).cuda(), (Wr * sign).to(torch.bfloat16).cuda(), bias, K, False)
+        torch.cuda.synchronize()
+        assert np.array_equal(ids.cpu().numpy(), expect), sign
+        assert np.allclose(w.cpu().numpy(), 1.0 / E, rtol=1e-6)
