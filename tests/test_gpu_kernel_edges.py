@@ -166,3 +166,26 @@ def test_router_sums_keep_their_order_in_every_variant(moe, oracle64, T, H):
         torch.cuda.synchronize()
         assert np.array_equal(ids.cpu().numpy(), expect), sign
         assert np.allclose(w.cpu().numpy(), 1.0 / E, rtol=1e-6)
+
+
+@pytest.mark.parametrize("T,H,E,K", [(1, 64, 8, 2), (64, 64, 3, 1), (65, 128, 61, 1), (1023, 64, 256, 1), (257, 192, 60, 4), (341, 64, 256, 3),
+                                     (683, 320, 7, 6), (4095, 64, 60, 1), (4096, 64, 1, 1), (4097, 64, 60, 1), (256, 64, 256, 16)])
+@pytest.mark.parametrize("hot", [False, True])
+def test_sort_of_pairs_at_the_borders_of_its_kernels(moe, oracle64, T, H, E, K, hot):
+    # one workgroup up to 1024 pairs (index arrays only), one launch up to 4096, the table beyond; whole numbers and copied rows: exact
+    print(f"[case] permute borders T={T} H={H} E={E} K={K} hot={hot}", flush=True)
+    rng = np.random.default_rng(T * 3 + E)
+    keys = rng.random((T, E))
+    if hot:
+        keys[:, E // 2] = 2.0      # every token chooses this expert
+    ids = np.argsort(-keys, axis=1)[:, :K].astype(np.int32)
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
+    off_r, src_r, rowp_r = oracle64.permute(ids, E)
+    for materialize in (True, False):
+        off, src, rowp, Xp = moe.moe_permute(torch.from_numpy(ids).cuda(), x.cuda(), E, materialize=materialize)
+        torch.cuda.synchronize()
+        assert np.array_equal(off.cpu().numpy(), off_r)
+        assert np.array_equal(src.cpu().numpy(), src_r)
+        assert np.array_equal(rowp.cpu().numpy(), rowp_r)
+        if materialize:
+            assert torch.equal(Xp.cpu().view(torch.int16), x[torch.from_numpy(src_r.astype(np.int64)) // K].view(torch.int16))
