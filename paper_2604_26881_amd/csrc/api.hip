@@ -96,7 +96,7 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   GemmArgs gu{};
   gu.A = (const bf16_t*)A; gu.B0 = (const bf16_t*)Wg; gu.B1 = (const bf16_t*)Wu; gu.C = (bf16_t*)workspace;
   gu.offsets = expert_offsets; gu.lo = group_lo; gu.hi = group_hi; gu.ids = ids; gu.rows_fixed = 0; gu.rows_total = P;
-  gu.mean_rows = mean_rows; gu.N = I; gu.Kdim = H;
+  gu.mean_rows = mean_rows; gu.experts_layer = E; gu.N = I; gu.Kdim = H;
   GemmArgs dn = gu;
   gu.gather = gather; gu.gather_div = gather_div;   // only the first kernel reads token rows
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wd; dn.B1 = nullptr; dn.C = (bf16_t*)Yp;
@@ -296,7 +296,7 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
   GemmArgs gu{};
   gu.A = (const bf16_t*)x; gu.B0 = (const bf16_t*)Wg; gu.B1 = (const bf16_t*)Wu; gu.C = (bf16_t*)workspace;
   gu.offsets = expert_offsets; gu.lo = group_lo; gu.hi = group_hi; gu.ids = nullptr; gu.rows_total = rows;
-  gu.mean_rows = mean_rows; gu.N = I; gu.Kdim = H;
+  gu.mean_rows = mean_rows; gu.experts_layer = E; gu.N = I; gu.Kdim = H;
   gu.n_shared = ns; gu.shared_rows = T; gu.rows_routed = P;
   GemmArgs dn = gu;
   gu.gather = src_of_row; gu.gather_div = K;

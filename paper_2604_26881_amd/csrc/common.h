@@ -89,6 +89,7 @@ struct GemmArgs {
   int rows_fixed;
   int rows_total;      // number of rows of A and C (upper bound used to size the grid)
   int mean_rows;       // expected rows per expert (rows_total / experts of the layer): picks kernel shapes
+  int experts_layer;   // routed experts of the layer (0: one weight set): with mean_rows, the tiles of the whole layer
   int N;               // output columns (per branch for gate/up)
   int Kdim;            // contraction length
   float* Cpart;        // room for the fp32 partial outputs [parts, rows_total, N] of kernels that cut K, else unused

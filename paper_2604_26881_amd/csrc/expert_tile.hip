@@ -670,6 +670,29 @@ static TileChoice pick_tile(const GemmArgs& a, int tile_rows, bool gateup) {
     const double cost = ceil(m / bm) * bm * factor[i];
     if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = heights[i]; }
   }
+  // Layers with few experts: fewer than two rounds of the chip with that height (the whole layer's tiles, not the
+  // block's).  Then whole rounds count, and narrower tiles that give every CU one: cost = rounds x rows x columns x
+  // factor (the factors above; 1.82 and 2.26 for 128x128 and 128x64).  Down projection, us, before -> now: 8 experts of
+  // H 4096, I 7168 at 34 rows 117 -> 76 (128x256 was 128 tiles), at 200 rows 186 -> 128, 4 of H 2048, I 2560 at 60 rows
+  // 44 -> 23, 8 of H 2048, I 8192 at 40 rows 101 -> 53; gate/up 4 of H 2048, I 2560 at 34 rows 35 -> 26.
+  // (A call that also hosts the shared experts picks the same, so that its routed rows keep the bits of the plain call.)
+  // With two rounds
+  // and more the heights' rule is the better one (8 experts of H 4096 at 1000 rows, gate/up: 903 us as picked, 938 and
+  // 926 with 128 and 160 rows).
+  const long cus = num_cus();
+  auto items_of = [&](int bm, int nout) -> double {
+    return (double)a.experts_layer * ceil(m / bm) * (double)((a.N + nout - 1) / nout);
+  };
+  const int wide = gateup ? 128 : 256;
+  if (a.experts_layer > 0 && items_of(best == 129 ? 128 : best, wide) < 2.0 * (double)cus) {
+    struct Cand { int code, bm, bn; double c; };
+    const Cand cands[5] = {{256, 256, 256, 1.0}, {160, 160, 256, 1.23}, {129, 128, 256, 1.41}, {130, 128, 128, 1.82}, {64, 128, 64, 2.26}};
+    best_cost = 0.0;
+    for (const Cand& k : cands) {
+      const double cost = ceil(items_of(k.bm, gateup ? k.bn / 2 : k.bn) / (double)cus) * k.bm * k.bn * k.c;
+      if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = k.code; }
+    }
+  }
   return TileChoice{best, 1};
 }
 int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st) {

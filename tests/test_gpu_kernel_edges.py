@@ -189,3 +189,15 @@ def test_sort_of_pairs_at_the_borders_of_its_kernels(moe, oracle64, T, H, E, K, 
         assert np.array_equal(rowp.cpu().numpy(), rowp_r)
         if materialize:
             assert torch.equal(Xp.cpu().view(torch.int16), x[torch.from_numpy(src_r.astype(np.int64)) // K].view(torch.int16))
+
+
+# Layers whose tiles do not fill the chip twice: 128x128, 128x64, 160- and 128-row tiles for gate/up and down
+@pytest.mark.parametrize("counts,H,I", [([40] * 16, 64, 2304), ([60] * 4, 128, 320), ([200] * 8, 64, 1024), ([300, 1, 500, 399], 64, 512),
+                                        ([34] * 2, 2048, 64), ([129, 0, 130, 33, 128], 192, 192)])
+def test_few_expert_layers_pick_tiles_from_the_whole_layer(moe, oracle64, counts, H, I):
+    print(f"[case] few experts counts={counts} H={H} I={I}", flush=True)
+    c = block_case(oracle64, counts, H, I, 300 + len(counts))
+    Yp = run_blocks(moe, c, 0)
+    check_close(f64(Yp), c["ref"], "Yp")
+    Yc = run_blocks(moe, c, 0, [(i, i + 1) for i in range(c["E"])])      # the same bits whatever the block cut
+    assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16))
