@@ -16,7 +16,8 @@
  *    kernels on it; they never synchronise and never read device memory on the host.
  *  - Activations and weights are bf16 (16-bit, upper half of an IEEE fp32), row-major, innermost
  *    dimension contiguous; accumulation is fp32.  Indices are int32.
- *  - Return value: MOE_OK (0), or a negative MOE_ERR_* code, in which case nothing was enqueued.
+ *  - Return value: MOE_OK (0), or a negative MOE_ERR_* code, in which case nothing was enqueued (moe_layer_forward, a
+ *    sequence of these calls, states its own rule).
  *  - No hidden state: the result of a call is a function of its arguments alone (Sec. 3: expert
  *    blocks are stateless; the orchestrator keeps no cross-request state), so a call may be
  *    repeated, and calls on disjoint outputs may be issued in any order, on several streams and
@@ -177,6 +178,26 @@ int moe_shared_forward(const void* x, const void* Wsg, const void* Wsu, const vo
  */
 int moe_combine(const void* Yp, const int32_t* row_of_pair, const float* topk_w, const void* S,
                 const float* sg, int T, int H, int K, void* out, void* stream);
+
+/*
+ * The calls above in the order of one layer on one stream (gating, micro-batch construction, one expert block, shared
+ * expert, aggregation), for callers to whom a call per step costs more than the steps: Wsg/Wsu/Wsd and S/sg are NULL and
+ * Is is 0 without a shared expert; seg_offsets selects moe_route_segments (bias is then its bias_rows); Xp NULL: no
+ * permuted copy, the block reads x through src_of_row.  The outputs of every step are written as the steps write them.
+ * Small batches (moe_layer_shared_sets > 0, policy == shared_policy == 0) run the shared expert inside the block's
+ * launches when shared_workspace has room for its parts (moe_shared_workspace_bytes includes it): S then differs from
+ * moe_shared_forward's in the order of its fp32 sum only.  A step that refuses its arguments ends the call with that
+ * step's status; the steps before it have been enqueued.
+ */
+int moe_layer_shared_sets(int T, int H, int E, int K, int I, int Is);   /* 0: the shared expert has launches of its own */
+int moe_layer_forward(const void* x, const void* Wr, const float* bias, const int32_t* seg_offsets, int n_seg,
+                      const void* Wg, const void* Wu, const void* Wd, const void* Wsg, const void* Wsu,
+                      const void* Wsd, const void* wgate, int T, int H, int E, int K, int I, int Is, int renorm,
+                      int group_lo, int group_hi, int policy, int shared_policy, int32_t* topk_ids, float* topk_w,
+                      int32_t* expert_offsets, int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* Yp,
+                      void* S, float* sg, void* out, void* permute_workspace, size_t permute_workspace_bytes,
+                      void* workspace, size_t workspace_bytes, void* shared_workspace,
+                      size_t shared_workspace_bytes, void* stream);
 
 /*
  * Step between two MoE layers when layers are chained without the attention blocks that sit

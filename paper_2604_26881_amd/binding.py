@@ -21,7 +21,7 @@ SYMBOLS = ["moe_status_string", "moe_build_id", "moe_route", "moe_route_segments
            "moe_shared_forward", "moe_shared_forward_ex", "moe_combine", "moe_combine_parts",
            "moe_fused_shared_sets", "moe_fused_workspace_bytes", "moe_expert_group_forward_fused",
            "moe_permute_workspace_bytes", "moe_expert_workspace_bytes", "moe_shared_workspace_bytes",
-           "moe_workspace_bytes", "moe_residual_norm", "moe_probe_mfma", "moe_tile_clock_buffer"]
+           "moe_workspace_bytes", "moe_layer_forward", "moe_layer_shared_sets", "moe_residual_norm", "moe_probe_mfma", "moe_tile_clock_buffer"]
 
 
 class MoeError(RuntimeError):
@@ -95,6 +95,11 @@ def load() -> ctypes.CDLL:
     lib.moe_permute_workspace_bytes.argtypes = [c_int, c_int, c_int]
     lib.moe_expert_workspace_bytes.argtypes = [c_int, c_int]
     lib.moe_shared_workspace_bytes.argtypes = [c_int, c_int, c_int]
+    lib.moe_layer_shared_sets.restype = c_int
+    lib.moe_layer_shared_sets.argtypes = [c_int] * 6
+    lib.moe_layer_forward.restype = c_int
+    lib.moe_layer_forward.argtypes = ([c_vp] * 4 + [c_int] + [c_vp] * 7 + [c_int] * 11 + [c_vp] * 11 + [c_sz, c_vp, c_sz, c_vp,
+                                      c_sz, c_vp])
     lib.moe_residual_norm.restype = c_int
     lib.moe_residual_norm.argtypes = [c_vp, c_vp, c_int, c_int, ctypes.c_float, c_vp, c_vp]
     lib.moe_tile_clock_buffer.restype = c_int
@@ -443,6 +448,57 @@ class LayerBuffers:
                                           device=device))
 
 
+def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, tenant_rows, policy, shared_policy,
+                       shared_stream, fused_gather, seg_offsets, fused_shared) -> bool:
+    """The whole layer through the library's own sequence of its steps: one crossing into native code instead of five to
+    eight.  True when it ran.  It serves the plain case (one block, one stream, buffers of exactly these sizes); everything
+    else, and whatever the library refuses, is left to the step-by-step sequence, which also names the step at fault."""
+    if (groups is not None and len(groups) > 1) or fused_shared:
+        return False
+    if tenant_rows is not None and (bias is None or seg_offsets is None):
+        return False
+    T, H = x.shape
+    E, I, Hg = Wg.shape
+    # Up to 16 tokens the shared expert inside the routed experts' launches beats a second stream (60 experts of H 2048,
+    # I 1408, Is 5632: T = 1 95 -> 43 us, 13 134 -> 126); beyond, its second pass over its weights does not (17: 156, 158).
+    if shared is not None and shared_stream is not None and (T > 16 or policy != 0 or shared_policy != 0 or
+            load().moe_layer_shared_sets(T, H, E, K, I, shared[0].shape[0]) == 0):
+        return False
+    ids, src = buf.topk_ids, buf.src_of_row
+    if (T == 0 or Wr.shape != (E, H) or Hg != H or ids.shape != (T, K) or src.shape[0] != T * K or buf.Yp.shape != (T * K, H)
+            or buf.workspace_permute is None):
+        return False
+    seg, n_seg = None, 0
+    if tenant_rows is not None:
+        n_seg = bias.shape[0]
+        if bias.shape != (n_seg, E) or seg_offsets.numel() != n_seg + 1:
+            return False
+        seg = _ptr(seg_offsets, torch.int32, "seg_offsets")
+    bf, i32, f32 = torch.bfloat16, torch.int32, torch.float32
+    ws, wsp = buf.workspace, buf.workspace_permute
+    if shared is None:
+        sh, Is, S, sg, wss, wss_bytes = (None, None, None, None), 0, None, None, None, 0
+        if buf.S is not None or buf.sg is not None:     # buffers of a layer with a shared expert: the aggregation takes them
+            return False
+    else:
+        Is = shared[0].shape[0]
+        if buf.workspace_shared is None:
+            return False
+        sh = (_ptr(shared[0], bf, "Wsg"), _ptr(shared[1], bf, "Wsu"), _ptr(shared[2], bf, "Wsd"), _ptr(shared[3], bf, "wgate"))
+        S, sg, wss = _ptr(buf.S, bf, "S"), _ptr(buf.sg, f32, "sg"), _ptr(buf.workspace_shared, None, "workspace")
+        wss_bytes = buf.workspace_shared.numel() * buf.workspace_shared.element_size()
+    lo, hi = groups[0] if groups else (0, E)
+    rc = load().moe_layer_forward(
+        _ptr(x, bf, "x"), _ptr(Wr, bf, "Wr"), _ptr(bias, f32, "bias"), seg, n_seg, _ptr(Wg, bf, "Wg"), _ptr(Wu, bf, "Wu"),
+        _ptr(Wd, bf, "Wd"), *sh, T, H, E, K, I, Is, int(bool(renorm)), int(lo), int(hi), int(policy), int(shared_policy),
+        _ptr(ids, i32, "topk_ids"), _ptr(buf.topk_w, f32, "topk_w"), _ptr(buf.expert_offsets, i32, "expert_offsets"),
+        _ptr(src, i32, "src_of_row"), _ptr(buf.row_of_pair, i32, "row_of_pair"),
+        None if fused_gather else _ptr(buf.Xp, bf, "Xp"), _ptr(buf.Yp, bf, "Yp"), S, sg, _ptr(buf.out, bf, "out"),
+        _ptr(wsp, None, "workspace"), wsp.numel() * wsp.element_size(), _ptr(ws, None, "workspace"),
+        ws.numel() * ws.element_size(), wss, wss_bytes, _stream())
+    return rc == 0
+
+
 def moe_layer_forward(x, Wr, bias, Wg, Wu, Wd, shared, K: int, renorm: bool,
                       groups: Optional[Sequence[Tuple[int, int]]] = None, buf: Optional[LayerBuffers] = None,
                       tenant_rows: Optional[List[Tuple[int, int]]] = None, policy: int = 0,
@@ -457,7 +513,8 @@ def moe_layer_forward(x, Wr, bias, Wg, Wu, Wd, shared, K: int, renorm: bool,
     per tenant slice (seg_offsets: the slice bounds on the device, built here when not given; pass
     it when the call is captured into a graph); slices that are not consecutive are gated one by one.
     shared_stream: run the shared expert on this stream, concurrently with gating, permutation and
-    the routed blocks (it depends on x only); the aggregation waits for it.
+    the routed blocks (it depends on x only); the aggregation waits for it.  Batches of up to 16 tokens leave it
+    unused: the shared expert runs inside the routed experts' launches there.
     fused_gather: no permuted copy Xp; the block calls read x through src_of_row.
     fused_shared: the first block call also runs the shared experts (moe_expert_group_forward_fused, which
     reads x through src_of_row) and the aggregation takes their outputs as separate parts; sizes the fused
@@ -467,6 +524,9 @@ def moe_layer_forward(x, Wr, bias, Wg, Wu, Wd, shared, K: int, renorm: bool,
     Is = 0 if shared is None else shared[0].shape[0]
     if buf is None:
         buf = LayerBuffers.allocate(T, H, E, K, I, Is, x.device)
+    if _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, tenant_rows, policy, shared_policy,
+                          shared_stream, fused_gather, seg_offsets, fused_shared):
+        return buf
     main = torch.cuda.current_stream()
     fork = None
     fused_shared = bool(fused_shared and shared is not None and buf.S_parts is not None)

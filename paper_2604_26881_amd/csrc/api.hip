@@ -35,6 +35,10 @@ int shared_parts_room(int T, int H) {
   return parts > 1 ? parts : 0;
 }
 
+// Tokens up to which the shared expert rides along with the routed ones in the streaming kernel: two of its 16-row
+// passes (figures beside that kernel).
+constexpr int RIDE_T_MAX = 32;
+
 struct Plan { bool valid; bool stream; int tile_rows; bool do_gateup; bool do_down; };
 Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
   Plan p{};
@@ -79,11 +83,15 @@ int ffn_forward(const GemmArgs& gu, const GemmArgs& dn, const Plan& p, hipStream
   return rc;
 }
 
+// The shared expert riding along with the routed experts of a few tokens (see expert_stream_lds.hip): `sets` sets of I
+// columns of its hidden layer h [T,Is], and its output as `sets` fp32 parts [T,H].
+struct Riders { const void *x, *Wsg, *Wsu, *Wsd; void* h; float* part; int sets, T, Is; };
+
 int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, const void* A, const int32_t* gather,
                               int gather_div,
                               const int32_t* expert_offsets, const void* Wg, const void* Wu, const void* Wd, int P,
                               int H, int E, int I, void* Yp, void* workspace, size_t workspace_bytes, int policy,
-                              void* stream) {
+                              void* stream, const Riders* riders = nullptr) {
   if (P < 0 || !dims_ok(H) || !dims_ok(I) || E < 1 || E > 256) return MOE_ERR_SHAPE;
   if (group_lo < 0 || group_hi > E || group_lo >= group_hi) return MOE_ERR_SHAPE;
   if ((long long)P * (H > I ? H : I) >= (1ll << 31)) return MOE_ERR_SHAPE;
@@ -93,6 +101,7 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   const int mean_rows = (P + E - 1) / E;
   const Plan plan = make_plan(mean_rows, E, policy);
   if (!plan.valid) return MOE_ERR_SHAPE;
+  if (riders != nullptr && (!plan.stream || mean_rows > STREAM_FEW_ROWS)) return MOE_ERR_SHAPE;
   GemmArgs gu{};
   gu.A = (const bf16_t*)A; gu.B0 = (const bf16_t*)Wg; gu.B1 = (const bf16_t*)Wu; gu.C = (bf16_t*)workspace;
   gu.offsets = expert_offsets; gu.lo = group_lo; gu.hi = group_hi; gu.ids = ids; gu.rows_fixed = 0; gu.rows_total = P;
@@ -101,7 +110,15 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   gu.gather = gather; gu.gather_div = gather_div;   // only the first kernel reads token rows
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wd; dn.B1 = nullptr; dn.C = (bf16_t*)Yp;
   dn.N = H; dn.Kdim = I;
-  int parts;   // (no Cpart: always 1)
+  if (riders != nullptr) {
+    gu.n_shared = dn.n_shared = riders->sets;
+    gu.shared_rows = dn.shared_rows = riders->T;
+    gu.ldb_shared = dn.ldb_shared = riders->Is;
+    gu.As = (const bf16_t*)riders->x; gu.Bs0 = (const bf16_t*)riders->Wsg; gu.Bs1 = (const bf16_t*)riders->Wsu;
+    gu.Cs = (bf16_t*)riders->h;
+    dn.As = (const bf16_t*)riders->h; dn.Bs0 = (const bf16_t*)riders->Wsd; dn.Cpart = riders->part;
+  }
+  int parts;   // (no Cpart of its own: always 1)
   return ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
 }
 }  // namespace
@@ -393,6 +410,47 @@ int moe_combine_parts(const void* Yp, const int32_t* row_of_pair, const float* t
   if (T == 0) return MOE_OK;
   if (!Yp || !row_of_pair || !topk_w || !out || !S_parts || !sg) return MOE_ERR_NULL;
   return launch_combine(Yp, row_of_pair, topk_w, S_parts, n_parts, sg, T, H, K, out, (hipStream_t)stream);
+}
+
+int moe_layer_shared_sets(int T, int H, int E, int K, int I, int Is) {
+  if (T < 1 || T > RIDE_T_MAX || K < 1 || E < 2 || I <= 0 || Is <= 0 || !dims_ok(H) || !dims_ok(I) || !dims_ok(Is)) return 0;
+  if (((long long)T * K + E - 1) / E > STREAM_FEW_ROWS) return 0;
+  const int sets = (Is + I - 1) / I;
+  return sets <= MOE_SHARED_SETS_MAX ? sets : 0;
+}
+
+int moe_layer_forward(const void* x, const void* Wr, const float* bias, const int32_t* seg_offsets, int n_seg, const void* Wg,
+                      const void* Wu, const void* Wd, const void* Wsg, const void* Wsu, const void* Wsd, const void* wgate,
+                      int T, int H, int E, int K, int I, int Is, int renorm, int group_lo, int group_hi, int policy,
+                      int shared_policy, int32_t* topk_ids, float* topk_w, int32_t* expert_offsets, int32_t* src_of_row,
+                      int32_t* row_of_pair, void* Xp, void* Yp, void* S, float* sg, void* out, void* permute_workspace,
+                      size_t permute_workspace_bytes, void* workspace, size_t workspace_bytes, void* shared_workspace,
+                      size_t shared_workspace_bytes, void* stream) {
+  int rc = seg_offsets != nullptr
+               ? moe_route_segments(x, Wr, bias, seg_offsets, n_seg, T, H, E, K, renorm, topk_ids, topk_w, stream)
+               : moe_route(x, Wr, bias, T, H, E, K, renorm, topk_ids, topk_w, stream);
+  if (rc != MOE_OK) return rc;
+  rc = moe_permute(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, permute_workspace,
+                   permute_workspace_bytes, stream);
+  if (rc != MOE_OK) return rc;
+  const int P = T * K, sets = moe_layer_shared_sets(T, H, E, K, I, Is);
+  const size_t h_bytes = sets > 0 ? align256((size_t)T * (size_t)Is * 2) : 0;
+  const bool ride = sets > 0 && policy == 0 && shared_policy == 0 && Wsg && Wsu && Wsd && S && sg && shared_workspace &&
+                    shared_workspace_bytes >= h_bytes + (size_t)sets * (size_t)T * (size_t)H * 4;
+  Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, T, Is};
+  if (ride) riders.part = reinterpret_cast<float*>(static_cast<unsigned char*>(shared_workspace) + h_bytes);
+  const bool copied = Xp != nullptr;
+  rc = expert_group_forward_impl(group_lo, group_hi, nullptr, copied ? Xp : x, copied ? nullptr : src_of_row, copied ? 1 : K,
+                                 expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
+                                 ride ? &riders : nullptr);
+  if (rc != MOE_OK) return rc;
+  if (ride)
+    return launch_combine_forming_s(Yp, row_of_pair, topk_w, riders.part, sets, x, wgate, S, sg, T, H, K, out, (hipStream_t)stream);
+  if (Is > 0) {
+    rc = moe_shared_forward_ex(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, shared_workspace, shared_workspace_bytes, shared_policy, stream);
+    if (rc != MOE_OK) return rc;
+  }
+  return moe_combine(Yp, row_of_pair, topk_w, Is > 0 ? S : nullptr, Is > 0 ? sg : nullptr, T, H, K, out, stream);
 }
 
 int moe_residual_norm(const void* x, const void* y, int T, int H, float eps, void* out, void* stream) {

@@ -12,12 +12,31 @@ namespace moe {
 
 constexpr int COMBINE_KMAX = 16;
 
+// <x[t,:], wgate>: one wave per token, fp32.
+__device__ __forceinline__ float gate_dot(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgate, int t, int H, int lane) {
+  float a = 0.0f;
+  for (int c = lane; c < H / 8; c += 64) {
+    const uint4 v = reinterpret_cast<const uint4*>(x + (size_t)t * H)[c];
+    const uint4 g = reinterpret_cast<const uint4*>(wgate)[c];
+    a = __builtin_fmaf(bf16_lo(v.x), bf16_lo(g.x), a); a = __builtin_fmaf(bf16_hi(v.x), bf16_hi(g.x), a);
+    a = __builtin_fmaf(bf16_lo(v.y), bf16_lo(g.y), a); a = __builtin_fmaf(bf16_hi(v.y), bf16_hi(g.y), a);
+    a = __builtin_fmaf(bf16_lo(v.z), bf16_lo(g.z), a); a = __builtin_fmaf(bf16_hi(v.z), bf16_hi(g.z), a);
+    a = __builtin_fmaf(bf16_lo(v.w), bf16_lo(g.w), a); a = __builtin_fmaf(bf16_hi(v.w), bf16_hi(g.w), a);
+  }
+  return wave_sum(a);
+}
+// What the aggregation of a batch of a few tokens does besides: the shared expert's down projection arrives as fp32
+// parts, which are added in ascending order and rounded to S, and the gate logit is formed from x and wgate (nullptr: it
+// is in sg) and left in sg.  A launch of its own for either costs more than the work.
+struct SharedParts { const float* part; int parts; const bf16_t* x; const bf16_t* wgate; bf16_t* S; float* sg; };
+
+template <bool FORM_S>
 __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__ Yp,
                                                       const int32_t* __restrict__ row_of_pair,
                                                       const float* __restrict__ topk_w,
                                                       const bf16_t* __restrict__ S, int n_parts, long part_stride,
                                                       const float* __restrict__ sg, int H, int K,
-                                                      bf16_t* __restrict__ out) {
+                                                      bf16_t* __restrict__ out, SharedParts form) {
   const int t = blockIdx.x;
   __shared__ int s_row[COMBINE_KMAX];
   __shared__ float s_w[COMBINE_KMAX];
@@ -25,9 +44,19 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
     s_row[threadIdx.x] = row_of_pair[(size_t)t * K + threadIdx.x];
     s_w[threadIdx.x] = topk_w[(size_t)t * K + threadIdx.x];
   }
+  __shared__ float s_gate;
+  if (FORM_S && threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+    const float logit = form.wgate != nullptr ? gate_dot(form.x, form.wgate, t, H, lane) : form.sg[t];
+    if (lane == 0) {
+      s_gate = logit;
+      if (form.wgate != nullptr) form.sg[t] = logit;
+    }
+  }
   __syncthreads();
   float gate = 0.0f;
-  if (S != nullptr) gate = 1.0f / (1.0f + expf(-sg[t]));
+  if (FORM_S) gate = 1.0f / (1.0f + expf(-s_gate));
+  else if (S != nullptr) gate = 1.0f / (1.0f + expf(-sg[t]));
 
   for (int c = threadIdx.x; c < H / 8; c += 256) {
     float acc[8];
@@ -36,7 +65,20 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
     // the shared row and four expert rows at a time are requested before any of them is used
     // (the sum still takes the rows in slot order)
     uint4 vs = {0u, 0u, 0u, 0u};
-    if (S != nullptr) vs = reinterpret_cast<const uint4*>(S + (size_t)t * H)[c];
+    if (FORM_S) {
+      const long row = (long)t * H + 8 * c;
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = form.part[row + i];
+      for (int p = 1; p < form.parts; ++p) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] += form.part[row + (long)p * part_stride + i];
+      }
+      vs = uint4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+      *reinterpret_cast<uint4*>(form.S + row) = vs;
+    } else if (S != nullptr) {
+      vs = reinterpret_cast<const uint4*>(S + (size_t)t * H)[c];
+    }
     float sh[8];
     if (n_parts > 1) {   // the shared experts' outputs come as separate tensors: summed first, in order
       sh[0] = bf16_lo(vs.x); sh[1] = bf16_hi(vs.x); sh[2] = bf16_lo(vs.y); sh[3] = bf16_hi(vs.y);
@@ -64,10 +106,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
         }
       }
     }
-    if (S != nullptr && n_parts > 1) {
+    if (!FORM_S && S != nullptr && n_parts > 1) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(gate, sh[i], acc[i]);
-    } else if (S != nullptr) {
+    } else if (FORM_S || S != nullptr) {
       const uint4 v = vs;
       acc[0] = __builtin_fmaf(gate, bf16_lo(v.x), acc[0]); acc[1] = __builtin_fmaf(gate, bf16_hi(v.x), acc[1]);
       acc[2] = __builtin_fmaf(gate, bf16_lo(v.y), acc[2]); acc[3] = __builtin_fmaf(gate, bf16_hi(v.y), acc[3]);
@@ -83,25 +125,12 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
   }
 }
 
-// sg[t] = <x[t,:], wgate>: one wave per token, fp32.
-__device__ __forceinline__ void gate_dot(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgate, int t, int H, int lane,
-                                         float* __restrict__ sg) {
-  float a = 0.0f;
-  for (int c = lane; c < H / 8; c += 64) {
-    const uint4 v = reinterpret_cast<const uint4*>(x + (size_t)t * H)[c];
-    const uint4 g = reinterpret_cast<const uint4*>(wgate)[c];
-    a = __builtin_fmaf(bf16_lo(v.x), bf16_lo(g.x), a); a = __builtin_fmaf(bf16_hi(v.x), bf16_hi(g.x), a);
-    a = __builtin_fmaf(bf16_lo(v.y), bf16_lo(g.y), a); a = __builtin_fmaf(bf16_hi(v.y), bf16_hi(g.y), a);
-    a = __builtin_fmaf(bf16_lo(v.z), bf16_lo(g.z), a); a = __builtin_fmaf(bf16_hi(v.z), bf16_hi(g.z), a);
-    a = __builtin_fmaf(bf16_lo(v.w), bf16_lo(g.w), a); a = __builtin_fmaf(bf16_hi(v.w), bf16_hi(g.w), a);
-  }
-  a = wave_sum(a);
-  if (lane == 0) sg[t] = a;
-}
 __global__ __launch_bounds__(256) void gate_dot_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ wgate,
                                                        int T, int H, float* __restrict__ sg) {
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t < T) gate_dot(x, wgate, t, H, threadIdx.x & 63, sg);
+  if (t >= T) return;
+  const float logit = gate_dot(x, wgate, t, H, threadIdx.x & 63);
+  if ((threadIdx.x & 63) == 0) sg[t] = logit;
 }
 
 // Second kernel of a down projection whose K was cut: the fp32 parts are added in ascending order and rounded
@@ -113,7 +142,9 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict_
                                                         float* __restrict__ sg) {
   if ((int)blockIdx.x >= sum_groups) {
     const int t = ((int)blockIdx.x - sum_groups) * 4 + (threadIdx.x >> 6);
-    if (t < T) gate_dot(x, wgate, t, H, threadIdx.x & 63, sg);
+    if (t >= T) return;
+    const float logit = gate_dot(x, wgate, t, H, threadIdx.x & 63);
+    if ((threadIdx.x & 63) == 0) sg[t] = logit;
     return;
   }
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
@@ -184,8 +215,17 @@ int launch_residual_norm(const void* x, const void* y, int T, int H, float eps, 
 int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
                    const float* sg, int T, int H, int K, void* out, hipStream_t st) {
   if (T == 0) return 0;
-  hipLaunchKernelGGL(combine_kernel, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w,
-                     (const bf16_t*)S, n_parts, (long)T * H, sg, H, K, (bf16_t*)out);
+  hipLaunchKernelGGL(combine_kernel<false>, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w,
+                     (const bf16_t*)S, n_parts, (long)T * H, sg, H, K, (bf16_t*)out, SharedParts{});
+  return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+int launch_combine_forming_s(const void* Yp, const int32_t* row_of_pair, const float* w, const float* part, int parts,
+                             const void* x, const void* wgate, void* S, float* sg, int T, int H, int K, void* out,
+                             hipStream_t st) {
+  const SharedParts form{part, parts, (const bf16_t*)x, (const bf16_t*)wgate, (bf16_t*)S, sg};
+  hipLaunchKernelGGL(combine_kernel<true>, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w, (const bf16_t*)nullptr, 1,
+                     (long)T * H, (const float*)nullptr, H, K, (bf16_t*)out, form);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 

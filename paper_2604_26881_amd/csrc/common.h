@@ -98,7 +98,8 @@ struct GemmArgs {
   int gather_div;          // (the token rows themselves, addressed through src_of_row: no permuted copy)
   int leave_room;          // 1: no tile shape that takes a whole CU (all registers of every SIMD): kernels of
                            // other streams can then share the CUs with this one
-  // Shared experts riding along with a routed block (tile kernels only; n_shared == 0: none).  They are
+  // Shared experts riding along with a routed block (tile kernels; n_shared == 0: none; the kernel that streams the weights
+  // of a few rows takes them too, as its comment states).  They are
   // n_shared more weight sets, each applied to all shared_rows tokens.  In the row space of A and C
   // the routed rows are [0, rows_routed) and set s owns rows rows_routed + s*shared_rows onwards.
   int n_shared;
@@ -139,6 +140,10 @@ int launch_permute(const int32_t* ids, const void* x, int T, int H, int E, int K
                    int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* workspace, hipStream_t st);
 int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
                    const float* sg, int T, int H, int K, void* out, hipStream_t st);
+// the same with S and sg formed on the way: S = the `parts` fp32 tensors [T,H] added in ascending part, sg = <x, wgate>
+int launch_combine_forming_s(const void* Yp, const int32_t* row_of_pair, const float* w, const float* part, int parts,
+                             const void* x, const void* wgate, void* S, float* sg, int T, int H, int K, void* out,
+                             hipStream_t st);
 int launch_residual_norm(const void* x, const void* y, int T, int H, float eps, void* out, hipStream_t st);
 // C = the `parts` fp32 tensors [T,H] of a K-cut down projection, added in ascending part; with wgate also sg = <x, wgate>
 int launch_sum_parts(const float* part, int parts, int T, int H, void* C, const void* x, const void* wgate, float* sg,
@@ -149,6 +154,7 @@ int launch_mfma_probe(const void* operands, int iters, int workgroups, long long
 int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st);
 int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* parts);
 int tile_down_ksplit(int Kdim);   // most K parts of the down projection
+constexpr int STREAM_FEW_ROWS = 6;   // mean rows per expert up to which the narrow one of them serves a layer
 // Streaming kernels that stage the weights through wave-private LDS rings (whole-line requests): a few rows per
 // expert, and up to a few dozen.
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st);

@@ -50,17 +50,26 @@ __device__ __forceinline__ void stream_tail(F&& step) {
   }
 }
 
-template <int MT, bool GATEUP, int NST>
+// SHARED: the shared expert of a batch of a few tokens rides along.  It is a.n_shared sets of N columns of its hidden
+// layer (gate/up; the last one may be narrower) and as many parts of its contraction (down, left as fp32 partial sums in
+// a.Cpart for the aggregation to add), the first a.n_shared of blockIdx.y; all of them take all tokens.  With one token
+// the routed experts and the shared expert each leave most of the chip idle in a launch of their own: H 2048, 4 of 60
+// experts of I 1408 and Is 5632, gate/up 14.8 + 16.3 us, down 8.3 + 13.3 (tiles with K cut in 8, and their sum); together
+// 19.2 and 11.3.  The layer: T = 1 62.7 -> 46.5 us, 13 (with a second stream before) 134 -> 126.  From 17 tokens on the
+// shared weights are read by two passes; up to 32 tokens that still beats launches of their own on one stream (T = 24
+// 178 -> 171 us, 33 203 without it).
+template <int MT, bool GATEUP, int NST, bool SHARED>
 __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   using S = StreamLdsShape<MT, NST>;
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NPER = GATEUP ? 16 : 32;   // output columns of one item (two 16-row weight blocks)
 
   const int lane = threadIdx.x;
-  const int y = blockIdx.y;
-  const int eg = a.offsets ? (a.ids ? a.ids[a.lo + y] : a.lo + y) : 0;
-  const int rb = a.offsets ? a.offsets[eg] : 0;
-  const int re = a.offsets ? a.offsets[eg + 1] : a.rows_fixed;
+  const bool sh = SHARED && (int)blockIdx.y < a.n_shared;   // eg: the shared set, otherwise the expert id
+  const int y = (int)blockIdx.y - (SHARED && !sh ? a.n_shared : 0);
+  const int eg = sh ? y : a.offsets ? (a.ids ? a.ids[a.lo + y] : a.lo + y) : 0;
+  const int rb = a.offsets && !sh ? a.offsets[eg] : 0;
+  const int re = sh ? a.shared_rows : a.offsets ? a.offsets[eg + 1] : a.rows_fixed;
   const int Me = re - rb;
   // An expert with more rows than one pass covers takes further passes over its weights.  They are dealt
   // round-robin to the gridDim.z workgroups of this (expert, column block): workgroups without a pass leave
@@ -69,8 +78,11 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   const int pass_rows = 16 * MT;
   if (Me <= (int)blockIdx.z * pass_rows) return;
 
-  const int N = a.N, Kdim = a.Kdim;
-  const int nk = Kdim / 64;
+  const int N = a.N;
+  // elements between consecutive weight (and token) rows, and where a shared set's part of the contraction begins
+  const int Kdim = sh && !GATEUP ? a.ldb_shared : a.Kdim;
+  const int kbeg = sh && !GATEUP ? eg * a.Kdim : 0;
+  const int nk = (sh && !GATEUP ? min(a.Kdim, Kdim - kbeg) : a.Kdim) / 64;
   // The walk over K starts at step `rot` and wraps around.  Thousands of these waves start within a
   // few microseconds of each other; if all began at K step 0 their requests of one moment would sit
   // at the same offset inside the weight rows, which for rows of a power-of-two length (4 KB at
@@ -81,11 +93,16 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   const int rot = (int)(((unsigned)blockIdx.x * 3u + (unsigned)eg * 5u) % (unsigned)nk);
   // this wave's output columns: rows [n0, n0+16) of both branches (gate/up) or rows [n0, n0+32) (down)
   const int n0 = (int)blockIdx.x * NPER;
-  if (n0 >= N) return;
-  const unsigned char* W0 = reinterpret_cast<const unsigned char*>(a.B0 + ((size_t)eg * N + n0) * Kdim);
-  const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>(a.B1 + ((size_t)eg * N + n0) * Kdim)
+  if (n0 >= N || (sh && GATEUP && eg * N + n0 >= a.ldb_shared)) return;
+  const size_t wrow = sh && !GATEUP ? (size_t)n0 : (size_t)eg * N + n0;   // first weight row
+  const unsigned char* W0 = reinterpret_cast<const unsigned char*>((sh ? a.Bs0 : a.B0) + wrow * Kdim + kbeg);
+  const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>((sh ? a.Bs1 : a.B1) + wrow * Kdim)
                                    : W0 + (size_t)16 * Kdim * 2;
-  const unsigned char* Ab = reinterpret_cast<const unsigned char*>(a.A);
+  const unsigned char* Ab = reinterpret_cast<const unsigned char*>(sh ? a.As + kbeg : a.A);
+  const bool gathered = a.gather != nullptr && !sh;
+  // gate/up: the shared hidden rows are ldb_shared wide, set eg owns columns [eg*N, (eg+1)*N) of them
+  bf16_t* const Cb = sh && GATEUP ? a.Cs + (size_t)eg * N : a.C;
+  const int ldc = sh && GATEUP ? a.ldb_shared : N;
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
   // copies: lane -> row lane/8 of an 8-row group, slot lane%8 holding chunk slot xor row%8
@@ -106,7 +123,7 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int m = min(m0 + mt * 16 + i * 8 + crow, Me - 1);   // rows past the end repeat the last row
-        const int arow = a.gather ? a.gather[rb + m] / a.gather_div : rb + m;
+        const int arow = gathered ? a.gather[rb + m] / a.gather_div : rb + m;
         coffX[mt][i] = (uint32_t)arow * (uint32_t)Kdim * 2u + (uint32_t)cchunk * 16u;
       }
 
@@ -138,7 +155,13 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
       for (int mt = 0; mt < MT; ++mt) {
         const int m = m0 + r16 + mt * 16;
         if (m < Me) {
-          bf16_t* crow_out = a.C + (size_t)(rb + m) * N + n0 + 4 * q;
+          if (SHARED && !GATEUP && sh) {
+            float* part = a.Cpart + ((size_t)eg * a.shared_rows + m) * N + n0 + 4 * q;
+            *reinterpret_cast<float4*>(part) = make_float4(acc0[mt][0], acc0[mt][1], acc0[mt][2], acc0[mt][3]);
+            *reinterpret_cast<float4*>(part + 16) = make_float4(acc1[mt][0], acc1[mt][1], acc1[mt][2], acc1[mt][3]);
+            continue;
+          }
+          bf16_t* crow_out = Cb + (size_t)(rb + m) * ldc + n0 + 4 * q;
           uint2 o;
           if (GATEUP) {
             float v[4];
@@ -216,11 +239,11 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
 
 constexpr int STREAM_PASS_GROUPS = 8;
 
-template <int MT, bool GATEUP, int NST>
+template <int MT, bool GATEUP, int NST, bool SHARED>
 static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   using S = StreamLdsShape<MT, NST>;
   static_assert(NST * S::STAGE <= 64 * 1024, "dynamic LDS without an opt-in attribute");
-  auto kern = expert_stream_lds_kernel<MT, GATEUP, NST>;
+  auto kern = expert_stream_lds_kernel<MT, GATEUP, NST, SHARED>;
   const int nexp = a.offsets ? a.hi - a.lo : 1;
   const int per = GATEUP ? 16 : 32;
   const int gx = (a.N + per - 1) / per;
@@ -232,7 +255,7 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   // from 250 + 159 to 180 + 98 us at T = 384; 16 and 32 begin to cost the unbiased batches 5 - 20 %.
   const int passes_max = (a.rows_total + 16 * MT - 1) / (16 * MT);
   const int gz = std::max(1, std::min(STREAM_PASS_GROUPS, passes_max / 2));
-  hipLaunchKernelGGL(kern, dim3(gx, nexp, gz), dim3(64), NST * S::STAGE, st, a);
+  hipLaunchKernelGGL(kern, dim3(gx, nexp + (SHARED ? a.n_shared : 0), gz), dim3(64), NST * S::STAGE, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
@@ -245,9 +268,10 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
 template <bool GATEUP>
 static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.N % 32 != 0 || a.Kdim % 64 != 0) return -2;
-  if (a.offsets != nullptr && a.mean_rows > 6 && a.N % 64 == 0)
+  if (a.n_shared > 0) return launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
+  if (a.offsets != nullptr && a.mean_rows > STREAM_FEW_ROWS && a.N % 64 == 0)
     return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
-  return launch_stream_lds_t<1, GATEUP, 4>(a, st);
+  return launch_stream_lds_t<1, GATEUP, 4, false>(a, st);
 }
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st) { return launch_stream_lds_any<true>(a, st); }
 int launch_stream_lds_down(const GemmArgs& a, hipStream_t st) { return launch_stream_lds_any<false>(a, st); }

@@ -182,3 +182,29 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr + r.stdout
+
+
+def test_shared_expert_rides_along_only_with_a_few_tokens():
+    import paper_2604_26881_amd as moe
+    sets = moe.load().moe_layer_shared_sets
+    assert sets(1, 64, 8, 2, 128, 512) == 4
+    assert sets(24, 64, 8, 2, 128, 448) == 4           # a narrower last set
+    assert sets(1, 64, 8, 2, 512, 128) == 1
+    assert sets(33, 64, 60, 4, 128, 512) == 0          # too many tokens
+    assert sets(25, 64, 8, 2, 128, 512) == 0           # 7 rows per expert: another kernel
+    assert sets(1, 64, 8, 2, 64, 576) == 0             # more than 8 sets
+    assert sets(1, 64, 1, 1, 128, 512) == 0
+    assert sets(1, 64, 8, 2, 128, 0) == 0 and sets(0, 64, 8, 2, 128, 512) == 0
+    assert sets(1, 64, 8, 2, 100, 512) == 0 and sets(1, 60, 8, 2, 128, 512) == 0 and sets(1, 64, 8, 0, 128, 512) == 0
+
+
+def test_layer_call_refuses_like_its_steps():
+    import paper_2604_26881_amd as moe
+    lib, p = moe.load(), ctypes.c_void_p(0x1000)
+
+    def call(x=p, T=4, H=64, E=8, K=2, seg=None, n_seg=0):
+        return lib.moe_layer_forward(x, p, p, seg, n_seg, p, p, p, p, p, p, p, T, H, E, K, 128, 128, 0, 0, E, 0, 0, p, p, p, p, p,
+                                     p, p, p, p, p, p, 1 << 20, p, 1 << 20, p, 1 << 20, None)
+    assert call(H=63) == -2 and call(K=9) == -2 and call(E=300) == -2 and call(T=-1) == -2
+    assert call(x=None) == -1
+    assert call(seg=p, n_seg=0) == -2 and call(seg=p, n_seg=5000) == -2

@@ -201,3 +201,35 @@ def test_few_expert_layers_pick_tiles_from_the_whole_layer(moe, oracle64, counts
     check_close(f64(Yp), c["ref"], "Yp")
     Yc = run_blocks(moe, c, 0, [(i, i + 1) for i in range(c["E"])])      # the same bits whatever the block cut
     assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16))
+
+
+@pytest.mark.parametrize("T", [1, 3, 16, 17, 31, 32, 33])
+# sets of I columns of the shared expert: narrower than one, whole, a ragged last one, more than can ride along, none
+@pytest.mark.parametrize("H,E,K,I,Is", [(64, 8, 2, 192, 128), (192, 60, 4, 64, 256), (320, 16, 2, 192, 448), (128, 12, 2, 64, 576),
+                                        (64, 8, 1, 64, 0)])
+@pytest.mark.parametrize("gather,segments", [(False, False), (True, True)])
+def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, gather, segments):
+    print(f"[case] layer in one call T={T} H={H} E={E} K={K} I={I} Is={Is} gather={gather} segments={segments}", flush=True)
+    w = workloads.layer_weights(H, E, I, Is, 11 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    g = torch.Generator().manual_seed(T * 5 + E)
+    x = torch.randn((T, H), generator=g).to(torch.bfloat16)
+    cut = [(0, T // 2), (T // 2, T)] if segments else None
+    bias = torch.randn((2, E), generator=g) if segments else torch.randn((E,), generator=g)
+    d = {k: None if v is None else v.cuda() for k, v in w.items()}
+    shared = None if Is == 0 else (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"])
+    seg = moe.segment_offsets(cut, T, "cuda") if segments else None
+    run = lambda groups: moe.moe_layer_forward(x.cuda(), d["Wr"], bias.cuda(), d["Wg"], d["Wu"], d["Wd"], shared, K, True,
+                                               groups=groups, tenant_rows=cut, fused_gather=gather, seg_offsets=seg)
+    one, steps = run(None), run([(0, 1), (1, E)])       # two blocks take the step-by-step sequence
+    torch.cuda.synchronize()
+    for name in ("topk_ids", "topk_w", "expert_offsets", "src_of_row", "row_of_pair", "Yp") + (() if gather else ("Xp",)):
+        a, b = getattr(one, name), getattr(steps, name)
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+    if Is == 0:
+        assert torch.equal(one.out.view(torch.int16), steps.out.view(torch.int16))
+    else:
+        assert torch.equal(one.sg, steps.sg)
+        f32 = {k: v.float().numpy() for k, v in w.items() if v is not None}
+        S_ref, _ = oracle64.shared_forward(x.float().numpy(), f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
+        check_close(f64(one.S), S_ref, "S")
+        check_close(f64(one.out), f64(steps.out), "out")     # both within the bound of the oracle's: the steps are pinned elsewhere
