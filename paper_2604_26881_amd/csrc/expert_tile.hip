@@ -608,7 +608,7 @@ static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
   return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, false>(a, st);
 }
 
-// Tile shape codes: 256 = 256x256, 160 = 160 token rows x 256 weight rows, 128/129 = 128 x 256,
+// Tile shape codes: 256 = 256x256, 192 = 192x256 (one weight set), 160 = 160 token rows x 256 weight rows, 128/129 = 128 x 256,
 // 130 = 128x128, 64 = 128x64 (the last two also with the K of a down projection cut into parts, whose fp32
 // sums a second kernel adds in order, when the caller provides room for them); 0 = choose from layer-wide
 // sizes only (never from the block bounds).
@@ -616,17 +616,19 @@ static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
 // One weight set on a known number of rows (the shared expert): the shape with the least estimated
 // time.  A launch takes ceil(items / CUs) rounds of one tile each, a tile costs rows x columns x K
 // times a per-shape factor (smaller tiles move more bytes per flop through LDS).  The factors come
-// from timing the five shapes at T = 128 ... 16384 on the Qwen shape; the K cut pays a reduction
+// from timing the six shapes at T = 128 ... 16384 on the Qwen shape; the K cut pays a reduction
 // pass over its fp32 partial sums (5 us and their bytes, written and read, at 5 TB/s).  What the choice is
 // about is filling the chip in whole rounds: gate/up at T = 777 is 176 tiles of 256 rows or 220 of 160 (58 and
 // 46 us), the down projection there 112 tiles of 128x128 or twice as many of half the K (44 and 29 us), at
-// T = 512 64 tiles or 256 quarters (42 and 25 us).
+// T = 512 64 tiles or 256 quarters (42 and 25 us); 192 rows: gate/up at T = 2048 484 tiles, two rounds (100 -> 94 us), at 3000
+// 152 -> 136, the down projection at 6000 256 tiles (125 -> 115).
 static int largest_ksplit(int Kdim) { return Kdim % 512 == 0 ? 8 : Kdim % 256 == 0 ? 4 : Kdim % 128 == 0 ? 2 : 1; }
 int tile_down_ksplit(int Kdim) { return largest_ksplit(Kdim); }
 struct TileChoice { int code, parts; };
 static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int parts_max, bool leave_room) {
   struct Cand { int code, bm, nout; double c; bool cut; };
-  const Cand cands[5] = {{256, 256, gateup ? 128 : 256, 1.0, false}, {160, 160, gateup ? 128 : 256, 1.07, false},
+  const Cand cands[6] = {{256, 256, gateup ? 128 : 256, 1.0, false}, {192, 192, gateup ? 128 : 256, 1.03, false},
+                         {160, 160, gateup ? 128 : 256, 1.07, false},
                          {129, 128, gateup ? 128 : 256, 1.1, false}, {130, 128, gateup ? 64 : 128, 1.42, true},
                          {64, 128, gateup ? 32 : 64, 1.77, true}};
   const double cus = (double)num_cus();
@@ -634,7 +636,7 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
   TileChoice best{129, 1};
   double best_cost = 0.0;
   for (const Cand& k : cands) {
-    if (k.code == 256 && leave_room) continue;   // 256x256 holds all 512 registers of every SIMD
+    if (k.bm >= 192 && leave_room) continue;   // 256x256 holds all 512 registers of every SIMD, 192x256 426 of them
     const int most = gateup || !k.cut ? 1 : std::max(1, std::min(parts_max, largest_ksplit(Kdim)));
     for (int parts = 1; parts <= most; parts *= 2) {
       if (k.code == 64 && !gateup && parts == 1) continue;   // (128x128 serves such a batch better)
@@ -700,6 +702,7 @@ int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st) {
   if (t == 64) return launch_tile_t<128, 64, 4, 1, true, 6, 1>(a, st);
   if (t == 130) return launch_tile_t<128, 128, 2, 2, true, 4, 1>(a, st);
   if (t >= 256) return launch_tile_t<256, 256, 2, 2, true, 2, 1>(a, st);
+  if (t == 192) return launch_tile_s<192, 256, 2, 2, true, 2, 1, 1, false>(a, st);   // (one weight set only)
   if (t == 160) return launch_tile_t<160, 256, 1, 4, true, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, true, 3, 1>(a, st);
 }
@@ -725,6 +728,7 @@ int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* part
     }
   }
   if (t >= 256) return launch_tile_t<256, 256, 2, 2, false, 2, 1>(a, st);
+  if (t == 192) return launch_tile_s<192, 256, 2, 2, false, 2, 1, 1, false>(a, st);
   if (t == 160) return launch_tile_t<160, 256, 1, 4, false, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, false, 3, 1>(a, st);
 }

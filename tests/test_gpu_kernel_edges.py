@@ -233,3 +233,19 @@ def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, ga
         S_ref, _ = oracle64.shared_forward(x.float().numpy(), f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
         check_close(f64(one.S), S_ref, "S")
         check_close(f64(one.out), f64(steps.out), "out")     # both within the bound of the oracle's: the steps are pinned elsewhere
+
+
+@pytest.mark.parametrize("T,H,Is", [(383, 64, 11264), (384, 192, 11200), (385, 64, 11264), (6000, 2048, 64)])
+def test_shared_expert_in_192_row_tiles(moe, oracle64, T, H, Is):
+    # sizes at which the choice falls on 192-row tiles (gate/up of a wide hidden layer; down of many rows), and one beside them
+    print(f"[case] shared expert T={T} H={H} Is={Is}", flush=True)
+    w = workloads.layer_weights(H, 2, 64, Is, T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
+    d = {k: v.cuda() for k, v in w.items()}
+    S, sg = torch.empty((T, H), dtype=torch.bfloat16, device="cuda"), torch.empty(T, device="cuda")
+    ws = torch.empty(int(moe.load().moe_shared_workspace_bytes(T, H, Is)), dtype=torch.uint8, device="cuda")
+    moe.moe_shared_forward(x.cuda(), d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"], S, sg, ws)
+    torch.cuda.synchronize()
+    S_ref, sg_ref = oracle64.shared_forward(x.float().numpy(), *[w[k].float().numpy() for k in ("Wsg", "Wsu", "Wsd", "wgate")])
+    check_close(f64(S), S_ref, "S")
+    assert np.allclose(sg.cpu().numpy(), sg_ref, rtol=1e-4, atol=1e-5)
