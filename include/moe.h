@@ -186,7 +186,8 @@ int moe_combine(const void* Yp, const int32_t* row_of_pair, const float* topk_w,
  * permuted copy, the block reads x through src_of_row.  The outputs of every step are written as the steps write them.
  * Small batches (moe_layer_shared_sets > 0, policy == shared_policy == 0) run the shared expert inside the block's
  * launches when shared_workspace has room for its parts (moe_shared_workspace_bytes includes it): S then differs from
- * moe_shared_forward's in the order of its fp32 sum only.  A step that refuses its arguments ends the call with that
+ * moe_shared_forward's in the order of its fp32 sum only.  next (NULL: off; may be x): also moe_residual_norm(x, out, next_eps),
+ * from the aggregation itself, with the bits of that call.  A step that refuses its arguments ends the call with that
  * step's status; the steps before it have been enqueued.
  */
 int moe_layer_shared_sets(int T, int H, int E, int K, int I, int Is);   /* 0: the shared expert has launches of its own */
@@ -197,7 +198,7 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                       int32_t* expert_offsets, int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* Yp,
                       void* S, float* sg, void* out, void* permute_workspace, size_t permute_workspace_bytes,
                       void* workspace, size_t workspace_bytes, void* shared_workspace,
-                      size_t shared_workspace_bytes, void* stream);
+                      size_t shared_workspace_bytes, float next_eps, void* next, void* stream);
 
 /*
  * Step between two MoE layers when layers are chained without the attention blocks that sit

@@ -99,7 +99,7 @@ def load() -> ctypes.CDLL:
     lib.moe_layer_shared_sets.argtypes = [c_int] * 6
     lib.moe_layer_forward.restype = c_int
     lib.moe_layer_forward.argtypes = ([c_vp] * 4 + [c_int] + [c_vp] * 7 + [c_int] * 11 + [c_vp] * 11 + [c_sz, c_vp, c_sz, c_vp,
-                                      c_sz, c_vp])
+                                      c_sz, ctypes.c_float, c_vp, c_vp])
     lib.moe_residual_norm.restype = c_int
     lib.moe_residual_norm.argtypes = [c_vp, c_vp, c_int, c_int, ctypes.c_float, c_vp, c_vp]
     lib.moe_tile_clock_buffer.restype = c_int
@@ -449,7 +449,7 @@ class LayerBuffers:
 
 
 def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, tenant_rows, policy, shared_policy,
-                       shared_stream, fused_gather, seg_offsets, fused_shared) -> bool:
+                       shared_stream, fused_gather, seg_offsets, fused_shared, next_out=None, eps=0.0) -> bool:
     """The whole layer through the library's own sequence of its steps: one crossing into native code instead of five to
     eight.  True when it ran.  It serves the plain case (one block, one stream, buffers of exactly these sizes); everything
     else, and whatever the library refuses, is left to the step-by-step sequence, which also names the step at fault."""
@@ -495,7 +495,7 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
         _ptr(src, i32, "src_of_row"), _ptr(buf.row_of_pair, i32, "row_of_pair"),
         None if fused_gather else _ptr(buf.Xp, bf, "Xp"), _ptr(buf.Yp, bf, "Yp"), S, sg, _ptr(buf.out, bf, "out"),
         _ptr(wsp, None, "workspace"), wsp.numel() * wsp.element_size(), _ptr(ws, None, "workspace"),
-        ws.numel() * ws.element_size(), wss, wss_bytes, _stream())
+        ws.numel() * ws.element_size(), wss, wss_bytes, float(eps), _ptr(next_out, bf, "x_out"), _stream())
     return rc == 0
 
 
@@ -594,7 +594,10 @@ def moe_stack_forward(x, layers, K: int, renorm: bool, buf: Optional[LayerBuffer
         x_out = torch.empty_like(x)
     for w in layers:
         shared = None if w.get("Wsg") is None else (w["Wsg"], w["Wsu"], w["Wsd"], w["wgate"])
-        moe_layer_forward(cur, w["Wr"], w.get("bias"), w["Wg"], w["Wu"], w["Wd"], shared, K, renorm, buf=buf)
-        moe_residual_norm(cur, buf.out, x_out, eps)
+        if not (x_out.shape == cur.shape and
+                _layer_in_one_call(cur, w["Wr"], w.get("bias"), w["Wg"], w["Wu"], w["Wd"], shared, K, renorm, None, buf, None, 0, 0,
+                                   None, False, None, False, next_out=x_out, eps=eps)):
+            moe_layer_forward(cur, w["Wr"], w.get("bias"), w["Wg"], w["Wu"], w["Wd"], shared, K, renorm, buf=buf)
+            moe_residual_norm(cur, buf.out, x_out, eps)
         cur = x_out
     return x_out

@@ -351,9 +351,12 @@ int moe_expert_group_forward(int group_lo, int group_hi, const void* Xp, const i
                                      workspace_bytes, 0, stream);
 }
 
-int moe_shared_forward_ex(const void* x, const void* Wsg, const void* Wsu, const void* Wsd, const void* wgate, int T,
-                          int H, int Is, void* S, float* sg, void* workspace, size_t workspace_bytes, int policy,
-                          void* stream) {
+}  // extern "C"
+
+// gate_formed (nullptr: here): set to whether sg was formed; the caller then forms it where it was not
+static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, const void* Wsd, const void* wgate, int T,
+                               int H, int Is, void* S, float* sg, void* workspace, size_t workspace_bytes, int policy,
+                               void* stream, bool* gate_formed) {
   if (T < 0 || !dims_ok(H) || !dims_ok(Is)) return MOE_ERR_SHAPE;
   if ((long long)T * (H > Is ? H : Is) >= (1ll << 31)) return MOE_ERR_SHAPE;
   if (T == 0) return MOE_OK;
@@ -386,8 +389,20 @@ int moe_shared_forward_ex(const void* x, const void* Wsg, const void* Wsu, const
   const int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   if (rc != 0) return rc;
   if (parts > 1) return launch_sum_parts(part, parts, T, H, S, x, wgate, sg, (hipStream_t)stream);
+  if (gate_formed != nullptr) {
+    *gate_formed = false;
+    return MOE_OK;
+  }
   if (wgate && plan.do_down) return launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
   return MOE_OK;
+}
+
+extern "C" {
+
+int moe_shared_forward_ex(const void* x, const void* Wsg, const void* Wsu, const void* Wsd, const void* wgate, int T,
+                          int H, int Is, void* S, float* sg, void* workspace, size_t workspace_bytes, int policy,
+                          void* stream) {
+  return shared_forward_impl(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, workspace, workspace_bytes, policy, stream, nullptr);
 }
 
 int moe_shared_forward(const void* x, const void* Wsg, const void* Wsu, const void* Wsd, const void* wgate, int T,
@@ -425,7 +440,8 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                       int shared_policy, int32_t* topk_ids, float* topk_w, int32_t* expert_offsets, int32_t* src_of_row,
                       int32_t* row_of_pair, void* Xp, void* Yp, void* S, float* sg, void* out, void* permute_workspace,
                       size_t permute_workspace_bytes, void* workspace, size_t workspace_bytes, void* shared_workspace,
-                      size_t shared_workspace_bytes, void* stream) {
+                      size_t shared_workspace_bytes, float next_eps, void* next, void* stream) {
+  if (next != nullptr && (H > 8192 || !(next_eps >= 0.0f))) return MOE_ERR_SHAPE;
   int rc = seg_offsets != nullptr
                ? moe_route_segments(x, Wr, bias, seg_offsets, n_seg, T, H, E, K, renorm, topk_ids, topk_w, stream)
                : moe_route(x, Wr, bias, T, H, E, K, renorm, topk_ids, topk_w, stream);
@@ -444,13 +460,16 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                                  expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
                                  ride ? &riders : nullptr);
   if (rc != MOE_OK) return rc;
-  if (ride)
-    return launch_combine_forming_s(Yp, row_of_pair, topk_w, riders.part, sets, x, wgate, S, sg, T, H, K, out, (hipStream_t)stream);
-  if (Is > 0) {
-    rc = moe_shared_forward_ex(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, shared_workspace, shared_workspace_bytes, shared_policy, stream);
+  bool gate_formed = true;   // sg complete (or no shared expert)
+  if (!ride && Is > 0) {
+    rc = shared_forward_impl(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, shared_workspace, shared_workspace_bytes, shared_policy,
+                             stream, T > 0 && (shared_policy & 0x300) == 0 ? &gate_formed : nullptr);
     if (rc != MOE_OK) return rc;
   }
-  return moe_combine(Yp, row_of_pair, topk_w, Is > 0 ? S : nullptr, Is > 0 ? sg : nullptr, T, H, K, out, stream);
+  if (T == 0) return MOE_OK;
+  if (!out || (Is > 0 && (!S || !sg))) return MOE_ERR_NULL;
+  return launch_combine_layer(Yp, row_of_pair, topk_w, ride ? riders.part : nullptr, sets, x, ride || !gate_formed ? wgate : nullptr,
+                              Is > 0 ? S : nullptr, sg, T, H, K, out, next_eps, next, (hipStream_t)stream);
 }
 
 int moe_residual_norm(const void* x, const void* y, int T, int H, float eps, void* out, void* stream) {

@@ -25,18 +25,40 @@ __device__ __forceinline__ float gate_dot(const bf16_t* __restrict__ x, const bf
   }
   return wave_sum(a);
 }
-// What the aggregation of a batch of a few tokens does besides: the shared expert's down projection arrives as fp32
-// parts, which are added in ascending order and rounded to S, and the gate logit is formed from x and wgate (nullptr: it
-// is in sg) and left in sg.  A launch of its own for either costs more than the work.
-struct SharedParts { const float* part; int parts; const bf16_t* x; const bf16_t* wgate; bf16_t* S; float* sg; };
+// u = x + y of eight columns; 1 / sqrt(mean(u^2) + eps) of a row from its 256 threads' sums of squares; u * scale in bf16.
+__device__ __forceinline__ void residual(uint4 a, uint4 b, float (&u)[8]) {
+  u[0] = bf16_lo(a.x) + bf16_lo(b.x); u[1] = bf16_hi(a.x) + bf16_hi(b.x);
+  u[2] = bf16_lo(a.y) + bf16_lo(b.y); u[3] = bf16_hi(a.y) + bf16_hi(b.y);
+  u[4] = bf16_lo(a.z) + bf16_lo(b.z); u[5] = bf16_hi(a.z) + bf16_hi(b.z);
+  u[6] = bf16_lo(a.w) + bf16_lo(b.w); u[7] = bf16_hi(a.w) + bf16_hi(b.w);
+}
+__device__ __forceinline__ float row_scale(float ss, int H, float eps) {
+  __shared__ float s_part[4];
+  ss = wave_sum(ss);
+  if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = ss;
+  __syncthreads();
+  const float total = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
+  return 1.0f / sqrtf(total / (float)H + eps);
+}
+__device__ __forceinline__ uint4 scaled(const float (&u)[8], float scale) {
+  return uint4{pack_bf16x2(u[0] * scale, u[1] * scale), pack_bf16x2(u[2] * scale, u[3] * scale),
+               pack_bf16x2(u[4] * scale, u[5] * scale), pack_bf16x2(u[6] * scale, u[7] * scale)};
+}
 
-template <bool FORM_S>
+// What the aggregation may do besides, where a launch of its own costs more than the work: FORM & 1: the gate logit is
+// formed from x and wgate (nullptr: it is in sg) and left in sg (4.8 us and a gap for 2048 tokens as a launch, 1 us here);
+// FORM & 2: the shared expert's down projection arrives as fp32 parts, which are added in ascending order and rounded to S
+// (a few tokens); FORM & 4: the residual step behind the layer, next = bf16(u / sqrt(mean(u^2) + eps)) with u = x + out as
+// residual_norm_kernel forms it, from the values at hand (6.2 us and a gap for 2048 tokens of H 2048, 2 us here).
+struct CombineExtra { const float* part; int parts; const bf16_t* x; const bf16_t* wgate; bf16_t* S; float* sg; float eps; bf16_t* next; };
+
+template <int FORM>
 __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__ Yp,
                                                       const int32_t* __restrict__ row_of_pair,
                                                       const float* __restrict__ topk_w,
                                                       const bf16_t* __restrict__ S, int n_parts, long part_stride,
                                                       const float* __restrict__ sg, int H, int K,
-                                                      bf16_t* __restrict__ out, SharedParts form) {
+                                                      bf16_t* __restrict__ out, CombineExtra form) {
   const int t = blockIdx.x;
   __shared__ int s_row[COMBINE_KMAX];
   __shared__ float s_w[COMBINE_KMAX];
@@ -45,7 +67,7 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
     s_w[threadIdx.x] = topk_w[(size_t)t * K + threadIdx.x];
   }
   __shared__ float s_gate;
-  if (FORM_S && threadIdx.x < 64) {
+  if ((FORM & 1) && threadIdx.x < 64) {
     const int lane = threadIdx.x;
     const float logit = form.wgate != nullptr ? gate_dot(form.x, form.wgate, t, H, lane) : form.sg[t];
     if (lane == 0) {
@@ -55,17 +77,19 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
   }
   __syncthreads();
   float gate = 0.0f;
-  if (FORM_S) gate = 1.0f / (1.0f + expf(-s_gate));
+  if (FORM & 1) gate = 1.0f / (1.0f + expf(-s_gate));
   else if (S != nullptr) gate = 1.0f / (1.0f + expf(-sg[t]));
 
-  for (int c = threadIdx.x; c < H / 8; c += 256) {
+  float u[4][8];      // (FORM & 4: x + out of this thread's columns; H <= 8192)
+  float ss = 0.0f;
+  auto columns = [&](int c, float (&uc)[8]) {
     float acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.0f;
     // the shared row and four expert rows at a time are requested before any of them is used
     // (the sum still takes the rows in slot order)
     uint4 vs = {0u, 0u, 0u, 0u};
-    if (FORM_S) {
+    if (FORM & 2) {
       const long row = (long)t * H + 8 * c;
       float v[8];
 #pragma unroll
@@ -106,10 +130,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
         }
       }
     }
-    if (!FORM_S && S != nullptr && n_parts > 1) {
+    if (!(FORM & 2) && S != nullptr && n_parts > 1) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = __builtin_fmaf(gate, sh[i], acc[i]);
-    } else if (FORM_S || S != nullptr) {
+    } else if ((FORM & 2) || S != nullptr) {
       const uint4 v = vs;
       acc[0] = __builtin_fmaf(gate, bf16_lo(v.x), acc[0]); acc[1] = __builtin_fmaf(gate, bf16_hi(v.x), acc[1]);
       acc[2] = __builtin_fmaf(gate, bf16_lo(v.y), acc[2]); acc[3] = __builtin_fmaf(gate, bf16_hi(v.y), acc[3]);
@@ -122,6 +146,23 @@ __global__ __launch_bounds__(256) void combine_kernel(const bf16_t* __restrict__
     o.z = pack_bf16x2(acc[4], acc[5]);
     o.w = pack_bf16x2(acc[6], acc[7]);
     reinterpret_cast<uint4*>(out + (size_t)t * H)[c] = o;
+    if (FORM & 4) {
+      const uint4 xv = reinterpret_cast<const uint4*>(form.x + (size_t)t * H)[c];
+      residual(xv, o, uc);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss = __builtin_fmaf(uc[i], uc[i], ss);
+    }
+  };
+  if constexpr ((FORM & 4) != 0) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (threadIdx.x + 256 * r < H / 8) columns(threadIdx.x + 256 * r, u[r]);
+    const float scale = row_scale(ss, H, form.eps);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (threadIdx.x + 256 * r < H / 8) reinterpret_cast<uint4*>(form.next + (size_t)t * H)[threadIdx.x + 256 * r] = scaled(u[r], scale);
+  } else {
+    for (int c = threadIdx.x; c < H / 8; c += 256) columns(c, u[0]);
   }
 }
 
@@ -166,42 +207,23 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict_
 // registers between the two passes (H <= 8192).
 __global__ __launch_bounds__(256) void residual_norm_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ y,
                                                             int H, float eps, bf16_t* __restrict__ out) {
-  __shared__ float s_part[4];
-  const int t = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t = blockIdx.x;
   float u[4][8];
   float ss = 0.0f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int c = threadIdx.x + 256 * r;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) u[r][i] = 0.0f;
     if (c < H / 8) {
-      const uint4 a = reinterpret_cast<const uint4*>(x + (size_t)t * H)[c];
-      const uint4 b = reinterpret_cast<const uint4*>(y + (size_t)t * H)[c];
-      u[r][0] = bf16_lo(a.x) + bf16_lo(b.x); u[r][1] = bf16_hi(a.x) + bf16_hi(b.x);
-      u[r][2] = bf16_lo(a.y) + bf16_lo(b.y); u[r][3] = bf16_hi(a.y) + bf16_hi(b.y);
-      u[r][4] = bf16_lo(a.z) + bf16_lo(b.z); u[r][5] = bf16_hi(a.z) + bf16_hi(b.z);
-      u[r][6] = bf16_lo(a.w) + bf16_lo(b.w); u[r][7] = bf16_hi(a.w) + bf16_hi(b.w);
+      residual(reinterpret_cast<const uint4*>(x + (size_t)t * H)[c], reinterpret_cast<const uint4*>(y + (size_t)t * H)[c], u[r]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) ss = __builtin_fmaf(u[r][i], u[r][i], ss);
     }
   }
-  ss = wave_sum(ss);
-  if (lane == 0) s_part[wave] = ss;
-  __syncthreads();
-  const float total = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
-  const float scale = 1.0f / sqrtf(total / (float)H + eps);
+  const float scale = row_scale(ss, H, eps);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int c = threadIdx.x + 256 * r;
-    if (c < H / 8) {
-      uint4 o;
-      o.x = pack_bf16x2(u[r][0] * scale, u[r][1] * scale);
-      o.y = pack_bf16x2(u[r][2] * scale, u[r][3] * scale);
-      o.z = pack_bf16x2(u[r][4] * scale, u[r][5] * scale);
-      o.w = pack_bf16x2(u[r][6] * scale, u[r][7] * scale);
-      reinterpret_cast<uint4*>(out + (size_t)t * H)[c] = o;
-    }
+    if (c < H / 8) reinterpret_cast<uint4*>(out + (size_t)t * H)[c] = scaled(u[r], scale);
   }
 }
 
@@ -212,21 +234,34 @@ int launch_residual_norm(const void* x, const void* y, int T, int H, float eps, 
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
-int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
-                   const float* sg, int T, int H, int K, void* out, hipStream_t st) {
+template <int FORM>
+static int launch_combine_t(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts, const float* sg,
+                            int T, int H, int K, void* out, const CombineExtra& form, hipStream_t st) {
   if (T == 0) return 0;
-  hipLaunchKernelGGL(combine_kernel<false>, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w,
-                     (const bf16_t*)S, n_parts, (long)T * H, sg, H, K, (bf16_t*)out, SharedParts{});
+  hipLaunchKernelGGL(combine_kernel<FORM>, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w, (const bf16_t*)S, n_parts,
+                     (long)T * H, sg, H, K, (bf16_t*)out, form);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
-int launch_combine_forming_s(const void* Yp, const int32_t* row_of_pair, const float* w, const float* part, int parts,
-                             const void* x, const void* wgate, void* S, float* sg, int T, int H, int K, void* out,
-                             hipStream_t st) {
-  const SharedParts form{part, parts, (const bf16_t*)x, (const bf16_t*)wgate, (bf16_t*)S, sg};
-  hipLaunchKernelGGL(combine_kernel<true>, dim3(T), dim3(256), 0, st, (const bf16_t*)Yp, row_of_pair, w, (const bf16_t*)nullptr, 1,
-                     (long)T * H, (const float*)nullptr, H, K, (bf16_t*)out, form);
-  return hipGetLastError() == hipSuccess ? 0 : -4;
+int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
+                   const float* sg, int T, int H, int K, void* out, hipStream_t st) {
+  return launch_combine_t<0>(Yp, row_of_pair, w, S, n_parts, sg, T, H, K, out, CombineExtra{}, st);
+}
+
+int launch_combine_layer(const void* Yp, const int32_t* row_of_pair, const float* w, const float* part, int parts,
+                         const void* x, const void* wgate, void* S, float* sg, int T, int H, int K, void* out, float eps,
+                         void* next, hipStream_t st) {
+  const CombineExtra form{part, parts, (const bf16_t*)x, (const bf16_t*)wgate, (bf16_t*)S, sg, eps, (bf16_t*)next};
+  const int what = (wgate != nullptr || part != nullptr ? 1 : 0) + (part != nullptr ? 2 : 0) + (next != nullptr ? 4 : 0);
+  const void* S_in = part != nullptr ? nullptr : S;
+  switch (what) {
+    case 0: return launch_combine_t<0>(Yp, row_of_pair, w, S_in, 1, sg, T, H, K, out, form, st);
+    case 1: return launch_combine_t<1>(Yp, row_of_pair, w, S_in, 1, sg, T, H, K, out, form, st);
+    case 3: return launch_combine_t<3>(Yp, row_of_pair, w, S_in, 1, sg, T, H, K, out, form, st);
+    case 4: return launch_combine_t<4>(Yp, row_of_pair, w, S_in, 1, sg, T, H, K, out, form, st);
+    case 5: return launch_combine_t<5>(Yp, row_of_pair, w, S_in, 1, sg, T, H, K, out, form, st);
+    default: return launch_combine_t<7>(Yp, row_of_pair, w, S_in, 1, sg, T, H, K, out, form, st);
+  }
 }
 
 int launch_sum_parts(const float* part, int parts, int T, int H, void* C, const void* x, const void* wgate, float* sg,

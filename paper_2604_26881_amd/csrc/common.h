@@ -140,10 +140,11 @@ int launch_permute(const int32_t* ids, const void* x, int T, int H, int E, int K
                    int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* workspace, hipStream_t st);
 int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
                    const float* sg, int T, int H, int K, void* out, hipStream_t st);
-// the same with S and sg formed on the way: S = the `parts` fp32 tensors [T,H] added in ascending part, sg = <x, wgate>
-int launch_combine_forming_s(const void* Yp, const int32_t* row_of_pair, const float* w, const float* part, int parts,
-                             const void* x, const void* wgate, void* S, float* sg, int T, int H, int K, void* out,
-                             hipStream_t st);
+// The aggregation of a layer with what else it can do on the way: with part (not nullptr) S = the `parts` fp32 tensors
+// [T,H] added in ascending part; with wgate sg = <x, wgate>; with next also next = residual_norm(x, out), H <= 8192.
+int launch_combine_layer(const void* Yp, const int32_t* row_of_pair, const float* w, const float* part, int parts,
+                         const void* x, const void* wgate, void* S, float* sg, int T, int H, int K, void* out, float eps,
+                         void* next, hipStream_t st);
 int launch_residual_norm(const void* x, const void* y, int T, int H, float eps, void* out, hipStream_t st);
 // C = the `parts` fp32 tensors [T,H] of a K-cut down projection, added in ascending part; with wgate also sg = <x, wgate>
 int launch_sum_parts(const float* part, int parts, int T, int H, void* C, const void* x, const void* wgate, float* sg,

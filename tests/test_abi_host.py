@@ -202,9 +202,10 @@ def test_layer_call_refuses_like_its_steps():
     import paper_2604_26881_amd as moe
     lib, p = moe.load(), ctypes.c_void_p(0x1000)
 
-    def call(x=p, T=4, H=64, E=8, K=2, seg=None, n_seg=0):
+    def call(x=p, T=4, H=64, E=8, K=2, seg=None, n_seg=0, next_eps=1e-6):
         return lib.moe_layer_forward(x, p, p, seg, n_seg, p, p, p, p, p, p, p, T, H, E, K, 128, 128, 0, 0, E, 0, 0, p, p, p, p, p,
-                                     p, p, p, p, p, p, 1 << 20, p, 1 << 20, p, 1 << 20, None)
+                                     p, p, p, p, p, p, 1 << 20, p, 1 << 20, p, 1 << 20, next_eps, p, None)
     assert call(H=63) == -2 and call(K=9) == -2 and call(E=300) == -2 and call(T=-1) == -2
     assert call(x=None) == -1
     assert call(seg=p, n_seg=0) == -2 and call(seg=p, n_seg=5000) == -2
+    assert call(next_eps=-1.0) == -2

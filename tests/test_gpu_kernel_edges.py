@@ -235,6 +235,24 @@ def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, ga
         check_close(f64(one.out), f64(steps.out), "out")     # both within the bound of the oracle's: the steps are pinned elsewhere
 
 
+@pytest.mark.parametrize("T,H,E,K,I,Is", [(1, 64, 8, 2, 64, 0), (33, 2112, 8, 2, 64, 128), (520, 128, 8, 2, 64, 192), (700, 64, 4, 1, 64, 0),
+                                          (5, 8192, 4, 1, 64, 0)])
+def test_residual_step_from_the_aggregation_has_the_bits_of_its_own_call(moe, T, H, E, K, I, Is):
+    # 520 tokens and 33 form the gate logit in the aggregation or beside the sum of the K parts; the layers run in place
+    print(f"[case] stack against its steps T={T} H={H} E={E} Is={Is}", flush=True)
+    layers = [{k: None if v is None else v.cuda() for k, v in
+               workloads.layer_weights(H, E, I, Is, 5 + i, 0.05, 0.1, torch.bfloat16, device="cpu").items()} for i in range(3)]
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+    out = moe.moe_stack_forward(x, layers, K, False, eps=1e-5)
+    cur = x
+    for w in layers:
+        shared = None if Is == 0 else (w["Wsg"], w["Wsu"], w["Wsd"], w["wgate"])
+        buf = moe.moe_layer_forward(cur, w["Wr"], None, w["Wg"], w["Wu"], w["Wd"], shared, K, False, groups=[(0, 1), (1, E)])
+        cur = moe.moe_residual_norm(cur, buf.out, eps=1e-5)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), cur.view(torch.int16))
+
+
 @pytest.mark.parametrize("T,H,Is", [(383, 64, 11264), (384, 192, 11200), (385, 64, 11264), (6000, 2048, 64)])
 def test_shared_expert_in_192_row_tiles(moe, oracle64, T, H, Is):
     # sizes at which the choice falls on 192-row tiles (gate/up of a wide hidden layer; down of many rows), and one beside them
