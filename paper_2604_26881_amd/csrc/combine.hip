@@ -46,10 +46,10 @@ __device__ __forceinline__ uint4 scaled(const float (&u)[8], float scale) {
 }
 
 // What the aggregation may do besides, where a launch of its own costs more than the work: FORM & 1: the gate logit is
-// formed from x and wgate (nullptr: it is in sg) and left in sg (4.8 us and a gap for 2048 tokens as a launch, 1 us here);
-// FORM & 2: the shared expert's down projection arrives as fp32 parts, which are added in ascending order and rounded to S
-// (a few tokens); FORM & 4: the residual step behind the layer, next = bf16(u / sqrt(mean(u^2) + eps)) with u = x + out as
-// residual_norm_kernel forms it, from the values at hand (6.2 us and a gap for 2048 tokens of H 2048, 2 us here).
+// formed from x and wgate (nullptr: it is in sg) and left in sg; FORM & 2: the shared expert's down projection arrives as
+// fp32 parts, which are added in ascending order and rounded to S (a few tokens); FORM & 4: the residual step behind the
+// layer, next = bf16(u / sqrt(mean(u^2) + eps)) with u = x + out as residual_norm_kernel forms it, from the values at
+// hand.  2048 tokens of H 2048: aggregation, gate logits and residual step 9.7 + 4.8 + 6.2 us in three launches, 16.9 in one.
 struct CombineExtra { const float* part; int parts; const bf16_t* x; const bf16_t* wgate; bf16_t* S; float* sg; float eps; bf16_t* next; };
 
 template <int FORM>
