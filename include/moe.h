@@ -189,6 +189,8 @@ int moe_combine(const void* Yp, const int32_t* row_of_pair, const float* topk_w,
  * moe_shared_forward's in the order of its fp32 sum only.  next (NULL: off; may be x): also moe_residual_norm(x, out, next_eps),
  * from the aggregation itself, with the bits of that call.  A step that refuses its arguments ends the call with that
  * step's status; the steps before it have been enqueued.
+ * Memory may be shared as between the separate calls: one buffer of moe_workspace_bytes may be every workspace, and an
+ * output may lie in memory that no later step reads.  Steps whose memory overlaps are not drawn into one launch.
  */
 int moe_layer_shared_sets(int T, int H, int E, int K, int I, int Is);   /* 0: the shared expert has launches of its own */
 int moe_layer_forward(const void* x, const void* Wr, const float* bias, const int32_t* seg_offsets, int n_seg,

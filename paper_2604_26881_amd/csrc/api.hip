@@ -11,6 +11,12 @@ namespace {
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
+// No byte of [a, a + na) in [b, b + nb)
+bool apart(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return na == 0 || nb == 0 || (p < q ? q - p >= na : p - q >= nb);
+}
+
 bool dims_ok(int H) { return H > 0 && H % 64 == 0; }
 
 // Which kernels serve an FFN with `mean_rows` expected rows per expert.  The choice uses only
@@ -388,7 +394,12 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
   int parts;
   const int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   if (rc != 0) return rc;
-  if (parts > 1) return launch_sum_parts(part, parts, T, H, S, x, wgate, sg, (hipStream_t)stream);
+  if (parts > 1) {   // the gate logits beside the sum, unless they go where it still reads
+    const bool beside = wgate && apart(sg, (size_t)T * 4, part, (size_t)parts * one_part);
+    const int rc_sum = launch_sum_parts(part, parts, T, H, S, x, beside ? wgate : nullptr, sg, (hipStream_t)stream);
+    if (rc_sum != 0 || beside || !wgate) return rc_sum;
+    return launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
+  }
   if (gate_formed != nullptr) {
     *gate_formed = false;
     return MOE_OK;
@@ -451,25 +462,53 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
   if (rc != MOE_OK) return rc;
   const int P = T * K, sets = moe_layer_shared_sets(T, H, E, K, I, Is);
   const size_t h_bytes = sets > 0 ? align256((size_t)T * (size_t)Is * 2) : 0;
+  const size_t part_bytes = (size_t)sets * (size_t)T * (size_t)H * 4;
+  const bool copied = Xp != nullptr;
+  // The steps run one after another, so a caller may hand the same memory to several of them (one buffer as every
+  // workspace, an output in a workspace that no later step reads).  What is done in one launch instead must not overlap:
+  // a riding shared expert writes its hidden rows and parts while the block's launches read and write theirs, and its
+  // parts are read while the aggregation writes.
+  const size_t x_bytes = (size_t)T * (size_t)H * 2, pairs = (size_t)P * 4;
+  const void* const riding = shared_workspace;
+  const size_t riding_bytes = h_bytes + part_bytes;
   const bool ride = sets > 0 && policy == 0 && shared_policy == 0 && Wsg && Wsu && Wsd && S && sg && shared_workspace &&
-                    shared_workspace_bytes >= h_bytes + (size_t)sets * (size_t)T * (size_t)H * 4;
+                    shared_workspace_bytes >= riding_bytes && apart(riding, riding_bytes, workspace, (size_t)P * (size_t)I * 2) &&
+                    (!copied || apart(riding, riding_bytes, Xp, (size_t)P * (size_t)H * 2)) &&
+                    apart(riding, riding_bytes, src_of_row, pairs) &&
+                    apart(riding, riding_bytes, expert_offsets, ((size_t)E + 1) * 4) &&
+                    apart(riding, riding_bytes, sg, (size_t)T * 4) && apart(riding, riding_bytes, out, x_bytes) &&
+                    apart(riding, riding_bytes, next, next ? x_bytes : 0);
   Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, T, Is};
   if (ride) riders.part = reinterpret_cast<float*>(static_cast<unsigned char*>(shared_workspace) + h_bytes);
-  const bool copied = Xp != nullptr;
   rc = expert_group_forward_impl(group_lo, group_hi, nullptr, copied ? Xp : x, copied ? nullptr : src_of_row, copied ? 1 : K,
                                  expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
                                  ride ? &riders : nullptr);
   if (rc != MOE_OK) return rc;
+  // The aggregation forms the gate logit and the residual step where no row that it still reads for another token lies
+  // in what it writes for this one (x itself may be out or next: then the rows are the token's own); otherwise they are
+  // launches of their own in their places.
+  const bool x_kept = (out == x || apart(out, x_bytes, x, x_bytes)) && (!next || next == x || apart(next, x_bytes, x, x_bytes));
+  const bool next_here = next != nullptr && x_kept && out != x && apart(next, x_bytes, Yp, (size_t)P * (size_t)H * 2) &&
+                         apart(next, x_bytes, S, S ? x_bytes : 0) && apart(next, x_bytes, sg, sg ? (size_t)T * 4 : 0) &&
+                         apart(next, x_bytes, row_of_pair, pairs) && apart(next, x_bytes, topk_w, pairs) &&
+                         (next == out || apart(next, x_bytes, out, x_bytes));
   bool gate_formed = true;   // sg complete (or no shared expert)
   if (!ride && Is > 0) {
     rc = shared_forward_impl(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, shared_workspace, shared_workspace_bytes, shared_policy,
-                             stream, T > 0 && (shared_policy & 0x300) == 0 ? &gate_formed : nullptr);
+                             stream, T > 0 && x_kept && (shared_policy & 0x300) == 0 ? &gate_formed : nullptr);
     if (rc != MOE_OK) return rc;
   }
   if (T == 0) return MOE_OK;
   if (!out || (Is > 0 && (!S || !sg))) return MOE_ERR_NULL;
-  return launch_combine_layer(Yp, row_of_pair, topk_w, ride ? riders.part : nullptr, sets, x, ride || !gate_formed ? wgate : nullptr,
-                              Is > 0 ? S : nullptr, sg, T, H, K, out, next_eps, next, (hipStream_t)stream);
+  if (ride && !x_kept && wgate) {
+    rc = launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
+    if (rc != MOE_OK) return rc;
+  }
+  rc = launch_combine_layer(Yp, row_of_pair, topk_w, ride ? riders.part : nullptr, sets, x,
+                            x_kept && (ride || !gate_formed) ? wgate : nullptr, Is > 0 ? S : nullptr, sg, T, H, K, out, next_eps,
+                            next_here ? next : nullptr, (hipStream_t)stream);
+  if (rc != MOE_OK || next == nullptr || next_here) return rc;
+  return launch_residual_norm(x, out, T, H, next_eps, next, (hipStream_t)stream);
 }
 
 int moe_residual_norm(const void* x, const void* y, int T, int H, float eps, void* out, void* stream) {

@@ -235,6 +235,37 @@ def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, ga
         check_close(f64(one.out), f64(steps.out), "out")     # both within the bound of the oracle's: the steps are pinned elsewhere
 
 
+@pytest.mark.parametrize("T", [1, 13, 16, 17, 32, 33])
+@pytest.mark.parametrize("shared_memory", ["workspaces", "Xp", "out", "src_of_row"])
+def test_layer_in_one_call_with_memory_shared_between_its_steps(moe, oracle64, T, shared_memory):
+    # One buffer as every workspace; or the shared expert's scratch in memory of a step that is over by then (the row
+    # copies, the index list) or not yet begun (the output): right when the steps run in turn, so right in one call too.
+    H, E, K, I, Is = 192, 8, 1, 256, 1088
+    print(f"[case] layer in one call, shared memory: {shared_memory}, T={T}", flush=True)
+    w = workloads.layer_weights(H, E, I, Is, 70 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
+    d = {k: v.cuda() for k, v in w.items()}
+    f32 = {k: v.float().numpy() for k, v in w.items()}
+    buf = moe.LayerBuffers.allocate(T, H, E, K, I, Is)
+    need = moe.moe_workspace_bytes(T, H, E, K, I, Is)
+    if shared_memory == "workspaces":
+        buf.workspace = buf.workspace_shared = buf.workspace_permute = torch.empty(need, dtype=torch.uint8, device="cuda")
+    else:
+        whole = torch.empty(need, dtype=torch.uint8, device="cuda")
+        buf.workspace_shared = whole
+        old = getattr(buf, shared_memory)
+        room = whole[:old.numel() * old.element_size()]
+        assert room.numel() == old.numel() * old.element_size()
+        setattr(buf, shared_memory, room.view(old.dtype).view(old.shape))
+    moe.moe_layer_forward(x.cuda(), d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"]), K, False,
+                          buf=buf, fused_gather=shared_memory in ("workspaces", "src_of_row"))
+    torch.cuda.synchronize()
+    ref = oracle64.layer(x.float().numpy(), f32["Wr"], None, f32["Wg"], f32["Wu"], f32["Wd"],
+                         (f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"]), K, False)
+    assert np.array_equal(buf.topk_ids.cpu().numpy(), ref["ids"])
+    check_close(f64(buf.out), ref["out"], f"out, {shared_memory}")
+
+
 @pytest.mark.parametrize("T,H,E,K,I,Is", [(1, 64, 8, 2, 64, 0), (33, 2112, 8, 2, 64, 128), (520, 128, 8, 2, 64, 192), (700, 64, 4, 1, 64, 0),
                                           (5, 8192, 4, 1, 64, 0)])
 def test_residual_step_from_the_aggregation_has_the_bits_of_its_own_call(moe, T, H, E, K, I, Is):
