@@ -488,6 +488,14 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
         S, sg, wss = _ptr(buf.S, bf, "S"), _ptr(buf.sg, f32, "sg"), _ptr(buf.workspace_shared, None, "workspace")
         wss_bytes = buf.workspace_shared.numel() * buf.workspace_shared.element_size()
     lo, hi = groups[0] if groups else (0, E)
+    # A second stream has no work of its own here, but keeps its place in the order: what was enqueued on it before (the
+    # shared expert's weights, say) is waited for, and what follows on it comes after the layer.
+    side = shared_stream if shared is not None else None
+    if side is not None:
+        main, capturing = torch.cuda.current_stream(), torch.cuda.is_current_stream_capturing()
+        if capturing:       # the second stream enters the capture ...
+            side.wait_stream(main)
+        main.wait_stream(side)
     rc = load().moe_layer_forward(
         _ptr(x, bf, "x"), _ptr(Wr, bf, "Wr"), _ptr(bias, f32, "bias"), seg, n_seg, _ptr(Wg, bf, "Wg"), _ptr(Wu, bf, "Wu"),
         _ptr(Wd, bf, "Wd"), *sh, T, H, E, K, I, Is, int(bool(renorm)), int(lo), int(hi), int(policy), int(shared_policy),
@@ -496,6 +504,10 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
         None if fused_gather else _ptr(buf.Xp, bf, "Xp"), _ptr(buf.Yp, bf, "Yp"), S, sg, _ptr(buf.out, bf, "out"),
         _ptr(wsp, None, "workspace"), wsp.numel() * wsp.element_size(), _ptr(ws, None, "workspace"),
         ws.numel() * ws.element_size(), wss, wss_bytes, float(eps), _ptr(next_out, bf, "x_out"), _stream())
+    if side is not None:
+        side.wait_stream(main)
+        if capturing:       # ... and leaves it joined
+            main.wait_stream(side)
     return rc == 0
 
 
@@ -513,8 +525,9 @@ def moe_layer_forward(x, Wr, bias, Wg, Wu, Wd, shared, K: int, renorm: bool,
     per tenant slice (seg_offsets: the slice bounds on the device, built here when not given; pass
     it when the call is captured into a graph); slices that are not consecutive are gated one by one.
     shared_stream: run the shared expert on this stream, concurrently with gating, permutation and
-    the routed blocks (it depends on x only); the aggregation waits for it.  Batches of up to 16 tokens leave it
-    unused: the shared expert runs inside the routed experts' launches there.
+    the routed blocks (it depends on x only); the aggregation waits for it.  In batches of up to 16 tokens the shared
+    expert runs inside the routed experts' launches instead: the whole layer then comes after what is on this stream
+    already, and what follows on it comes after the layer.
     fused_gather: no permuted copy Xp; the block calls read x through src_of_row.
     fused_shared: the first block call also runs the shared experts (moe_expert_group_forward_fused, which
     reads x through src_of_row) and the aggregation takes their outputs as separate parts; sizes the fused

@@ -266,6 +266,72 @@ def test_layer_in_one_call_with_memory_shared_between_its_steps(moe, oracle64, T
     check_close(f64(buf.out), ref["out"], f"out, {shared_memory}")
 
 
+@pytest.mark.parametrize("T", [1, 16, 17])
+def test_a_second_stream_keeps_its_order_whatever_runs_on_it(moe, T):
+    # The shared expert's weights are uploaded on the second stream behind a long copy, and S is read there behind the
+    # layer while the caller's stream is still busy: both were ordered when the shared expert ran on that stream.
+    H, E, K, I, Is = 128, 8, 2, 64, 192
+    print(f"[case] order of the second stream T={T}", flush=True)
+    w = {k: v.cuda() for k, v in workloads.layer_weights(H, E, I, Is, 80 + T, 0.05, 0.1, torch.bfloat16, device="cpu").items()}
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+    run = lambda sh, b, st: moe.moe_layer_forward(x, w["Wr"], None, w["Wg"], w["Wu"], w["Wd"], sh, K, False, buf=b, shared_stream=st)
+    real = (w["Wsg"], w["Wsu"], w["Wsd"], w["wgate"])
+    late = tuple(torch.zeros_like(t) for t in real)
+    bufs = [moe.LayerBuffers.allocate(T, H, E, K, I, Is) for _ in range(2)]
+    a, b = (torch.zeros(1 << 28, dtype=torch.uint8, device="cuda") for _ in range(2))
+    side, seen = torch.cuda.Stream(), torch.zeros_like(bufs[1].S)
+    run(real, bufs[0], side)                  # (kernels loaded, expected result)
+    torch.cuda.synchronize()
+    bufs[1].S.fill_(768.0)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(40):                   # some milliseconds
+            b.copy_(a)
+        for t, r in zip(late, real):
+            t.copy_(r)
+    run(late, bufs[1], side)
+    torch.cuda.synchronize()
+    assert torch.equal(bufs[0].out.view(torch.int16), bufs[1].out.view(torch.int16)), "ran before the upload"
+    bufs[1].S.fill_(768.0)
+    torch.cuda.synchronize()
+    for _ in range(40):
+        b.copy_(a)
+    run(real, bufs[1], side)
+    with torch.cuda.stream(side):
+        seen.copy_(bufs[1].S)
+    torch.cuda.synchronize()
+    assert torch.equal(bufs[0].S.view(torch.int16), seen.view(torch.int16)), "read before it was written"
+
+
+@pytest.mark.parametrize("T", [1, 16, 17])
+def test_capture_with_a_second_stream_at_few_tokens(moe, T):
+    H, E, K, I, Is = 128, 8, 2, 64, 192
+    print(f"[case] capture with a second stream T={T}", flush=True)
+    w = {k: v.cuda() for k, v in workloads.layer_weights(H, E, I, Is, 90 + T, 0.05, 0.1, torch.bfloat16, device="cpu").items()}
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+    side, buf = torch.cuda.Stream(), moe.LayerBuffers.allocate(T, H, E, K, I, Is)
+    run = lambda b, st: moe.moe_layer_forward(x, w["Wr"], None, w["Wg"], w["Wu"], w["Wd"], (w["Wsg"], w["Wsu"], w["Wsd"], w["wgate"]),
+                                              K, False, buf=b, shared_stream=st)
+    warm = torch.cuda.Stream()
+    warm.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(warm):
+        run(buf, side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(buf, side)
+        run(buf, side)      # the second stream is in the capture already
+    for i in range(3):
+        x.copy_(torch.randn((T, H), generator=torch.Generator().manual_seed(50 + i)).to(torch.bfloat16))
+        buf.out.fill_(768.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        eager = run(None, side)
+        torch.cuda.synchronize()
+        assert torch.equal(buf.out.view(torch.int16), eager.out.view(torch.int16)), f"replay {i}"
+        assert torch.equal(buf.S.view(torch.int16), eager.S.view(torch.int16)), f"replay {i}"
+
+
 @pytest.mark.parametrize("T,H,E,K,I,Is", [(1, 64, 8, 2, 64, 0), (33, 2112, 8, 2, 64, 128), (520, 128, 8, 2, 64, 192), (700, 64, 4, 1, 64, 0),
                                           (5, 8192, 4, 1, 64, 0)])
 def test_residual_step_from_the_aggregation_has_the_bits_of_its_own_call(moe, T, H, E, K, I, Is):
