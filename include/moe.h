@@ -185,10 +185,10 @@ int moe_combine(const void* Yp, const int32_t* row_of_pair, const float* topk_w,
  * Is is 0 without a shared expert; seg_offsets selects moe_route_segments (bias is then its bias_rows); Xp NULL: no
  * permuted copy, the block reads x through src_of_row.  The outputs of every step are written as the steps write them.
  * Small batches (moe_layer_shared_sets > 0, policy == shared_policy == 0) run the shared expert inside the block's
- * launches when shared_workspace has room for its parts (moe_shared_workspace_bytes includes it): S then differs from
- * moe_shared_forward's in the order of its fp32 sum only.  next (NULL: off; may be x): also moe_residual_norm(x, out, next_eps),
- * from the aggregation itself, with the bits of that call.  A step that refuses its arguments ends the call with that
- * step's status; the steps before it have been enqueued.
+ * launches when shared_workspace has room for its parts (moe_shared_workspace_bytes includes it); S keeps the bits of
+ * moe_shared_forward, so that out depends neither on the block cut nor on how the steps are called.
+ * next (NULL: off; may be x): also moe_residual_norm(x, out, next_eps), from the aggregation itself, with the bits of that
+ * call.  A step that refuses its arguments ends the call with that step's status; the steps before it have been enqueued.
  * Memory may be shared as between the separate calls: one buffer of moe_workspace_bytes may be every workspace, and an
  * output may lie in memory that no later step reads.  Steps whose memory overlaps are not drawn into one launch.
  */

@@ -459,11 +459,17 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
         return False
     T, H = x.shape
     E, I, Hg = Wg.shape
-    # Up to 16 tokens the shared expert inside the routed experts' launches beats a second stream (60 experts of H 2048,
-    # I 1408, Is 5632: T = 1 95 -> 43 us, 13 134 -> 126); beyond, its second pass over its weights does not (17: 156, 158).
-    if shared is not None and shared_stream is not None and (T > 16 or policy != 0 or shared_policy != 0 or
-            load().moe_layer_shared_sets(T, H, E, K, I, shared[0].shape[0]) == 0):
-        return False
+    # With a second stream the shared expert inside the routed experts' launches is the faster way up to 16 tokens of a
+    # captured layer (60 experts of H 2048, I 1408, Is 5632: T = 1 58 -> 44 us; 17: 144 against 151).  In eager launches
+    # the waits that keep the second stream's order cost 23 us: there it pays where the kernels take less time than the
+    # 97 us of host work of the calls one by one, up to about 240 MB of weights (same layer, the calls one by one against
+    # one: T = 1 100 and 67 us, 8 105 and 120, 13 129 and 147).
+    if shared is not None and shared_stream is not None:
+        if T > 16 or policy != 0 or shared_policy != 0 or load().moe_layer_shared_sets(T, H, E, K, I, shared[0].shape[0]) == 0:
+            return False
+        weights = 6 * H * (min(E, T * K) * I + shared[0].shape[0])
+        if weights > 240e6 and not torch.cuda.is_current_stream_capturing():
+            return False
     ids, src = buf.topk_ids, buf.src_of_row
     if (T == 0 or Wr.shape != (E, H) or Hg != H or ids.shape != (T, K) or src.shape[0] != T * K or buf.Yp.shape != (T * K, H)
             or buf.workspace_permute is None):
@@ -525,9 +531,9 @@ def moe_layer_forward(x, Wr, bias, Wg, Wu, Wd, shared, K: int, renorm: bool,
     per tenant slice (seg_offsets: the slice bounds on the device, built here when not given; pass
     it when the call is captured into a graph); slices that are not consecutive are gated one by one.
     shared_stream: run the shared expert on this stream, concurrently with gating, permutation and
-    the routed blocks (it depends on x only); the aggregation waits for it.  In batches of up to 16 tokens the shared
-    expert runs inside the routed experts' launches instead: the whole layer then comes after what is on this stream
-    already, and what follows on it comes after the layer.
+    the routed blocks (it depends on x only); the aggregation waits for it.  Where the shared expert runs inside the
+    routed experts' launches instead (a few tokens), the whole layer comes after what is on this stream already, and
+    what follows on it comes after the layer.
     fused_gather: no permuted copy Xp; the block calls read x through src_of_row.
     fused_shared: the first block call also runs the shared experts (moe_expert_group_forward_fused, which
     reads x through src_of_row) and the aggregation takes their outputs as separate parts; sizes the fused

@@ -1,5 +1,6 @@
 // C entry points of the MoE-layer library: argument checks and the choice of kernel shapes.
 // Semantics of every call are stated in include/moe.h.
+#include <algorithm>
 #include <atomic>
 #include "../../include/moe.h"
 #include "../../include/moe_tuning.h"
@@ -41,9 +42,12 @@ int shared_parts_room(int T, int H) {
   return parts > 1 ? parts : 0;
 }
 
-// Tokens up to which the shared expert rides along with the routed ones in the streaming kernel: two of its 16-row
-// passes (figures beside that kernel).
-constexpr int RIDE_T_MAX = 32;
+// Tokens up to which the streaming kernel serves the shared expert, riding along with the routed ones or by itself, and
+// the K parts of its down projection there (of twenty K steps and more; parts of eleven, twice as many, cost a layer of
+// H 2048, Is 5632 about 2 us at 1 to 24 tokens).  Both depend on the shared expert's own sizes alone: its bits are the
+// same in every sequence of calls.  (Figures beside that kernel.)
+constexpr int SHARED_FEW_T = 32;
+int shared_few_parts(int Is) { return std::max(1, std::min(SHARED_KPARTS_MAX, Is / 1280)); }
 
 struct Plan { bool valid; bool stream; int tile_rows; bool do_gateup; bool do_down; };
 Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
@@ -90,8 +94,8 @@ int ffn_forward(const GemmArgs& gu, const GemmArgs& dn, const Plan& p, hipStream
 }
 
 // The shared expert riding along with the routed experts of a few tokens (see expert_stream_lds.hip): `sets` sets of I
-// columns of its hidden layer h [T,Is], and its output as `sets` fp32 parts [T,H].
-struct Riders { const void *x, *Wsg, *Wsu, *Wsd; void* h; float* part; int sets, T, Is; };
+// columns of its hidden layer h [T,Is], and its output as `parts` fp32 parts [T,H].
+struct Riders { const void *x, *Wsg, *Wsu, *Wsd; void* h; float* part; int sets, parts, T, Is; };
 
 int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, const void* A, const int32_t* gather,
                               int gather_div,
@@ -117,7 +121,8 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wd; dn.B1 = nullptr; dn.C = (bf16_t*)Yp;
   dn.N = H; dn.Kdim = I;
   if (riders != nullptr) {
-    gu.n_shared = dn.n_shared = riders->sets;
+    gu.n_shared = riders->sets;
+    dn.n_shared = dn.shared_parts = riders->parts;
     gu.shared_rows = dn.shared_rows = riders->T;
     gu.ldb_shared = dn.ldb_shared = riders->Is;
     gu.As = (const bf16_t*)riders->x; gu.Bs0 = (const bf16_t*)riders->Wsg; gu.Bs1 = (const bf16_t*)riders->Wsu;
@@ -369,19 +374,21 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
   if (!x || !Wsg || !Wsu || !Wsd || !S || !workspace) return MOE_ERR_NULL;
   if (wgate && !sg) return MOE_ERR_NULL;
   if (workspace_bytes < (size_t)T * (size_t)Is * 2) return MOE_ERR_WORKSPACE;   // h, bf16 [T,Is]
-  const Plan plan = make_plan(T, 1, policy);
+  Plan plan = make_plan(T, 1, policy);
   if (!plan.valid) return MOE_ERR_SHAPE;
+  const bool few = (policy & 0xff) == 0 && T <= SHARED_FEW_T;
   const size_t h_bytes = align256((size_t)T * (size_t)Is * 2);
   // Room for K parts of the down projection: the 128x64 shape asked for by the caller and batches up to 512 tokens
   // must bring it; larger ones (sizes the helper reports include it) use what there is.
   const size_t one_part = (size_t)T * (size_t)H * 4;
+  const size_t room = workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0;
   int parts_max = 0;
   if (!plan.stream && (plan.tile_rows == 64 || plan.tile_rows == 0) && tile_down_ksplit(Is) > 1) {
-    const size_t room = workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0;
     const size_t want = plan.tile_rows == 64 || T <= SHARED_SMALL_T ? (size_t)tile_down_ksplit(Is) : (size_t)shared_parts_room(T, H);
     if ((plan.tile_rows == 64 || T <= SHARED_SMALL_T) && room < want) return MOE_ERR_WORKSPACE;
     parts_max = (int)(room < want ? room : want);
   }
+  if (few) parts_max = room >= (size_t)shared_few_parts(Is) ? shared_few_parts(Is) : 1;   // (1: formed one after another)
   float* part = parts_max > 1 ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes) : nullptr;
   GemmArgs gu{};
   gu.A = (const bf16_t*)x; gu.B0 = (const bf16_t*)Wsg; gu.B1 = (const bf16_t*)Wsu; gu.C = (bf16_t*)workspace;
@@ -391,9 +398,20 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wsd; dn.B1 = nullptr; dn.C = (bf16_t*)S;
   dn.N = H; dn.Kdim = Is; dn.Cpart = part; dn.parts_max = part ? parts_max : 0;
   gu.leave_room = (policy >> 10) & 1;
+  if (few) {
+    plan.stream = true;
+    gu.n_shared = 1;
+    dn.n_shared = parts_max;
+    dn.shared_parts = shared_few_parts(Is);
+    gu.shared_rows = dn.shared_rows = T;
+    gu.ldb_shared = dn.ldb_shared = Is;
+    gu.As = gu.A; gu.Bs0 = gu.B0; gu.Bs1 = gu.B1; gu.Cs = gu.C;
+    dn.As = dn.A; dn.Bs0 = dn.B0; dn.Cs = dn.C;
+  }
   int parts;
   const int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   if (rc != 0) return rc;
+  if (few && plan.do_down) parts = parts_max;
   if (parts > 1) {   // the gate logits beside the sum, unless they go where it still reads
     const bool beside = wgate && apart(sg, (size_t)T * 4, part, (size_t)parts * one_part);
     const int rc_sum = launch_sum_parts(part, parts, T, H, S, x, beside ? wgate : nullptr, sg, (hipStream_t)stream);
@@ -439,7 +457,7 @@ int moe_combine_parts(const void* Yp, const int32_t* row_of_pair, const float* t
 }
 
 int moe_layer_shared_sets(int T, int H, int E, int K, int I, int Is) {
-  if (T < 1 || T > RIDE_T_MAX || K < 1 || E < 2 || I <= 0 || Is <= 0 || !dims_ok(H) || !dims_ok(I) || !dims_ok(Is)) return 0;
+  if (T < 1 || T > SHARED_FEW_T || K < 1 || E < 2 || I <= 0 || Is <= 0 || !dims_ok(H) || !dims_ok(I) || !dims_ok(Is)) return 0;
   if (((long long)T * K + E - 1) / E > STREAM_FEW_ROWS) return 0;
   const int sets = (Is + I - 1) / I;
   return sets <= MOE_SHARED_SETS_MAX ? sets : 0;
@@ -462,7 +480,8 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
   if (rc != MOE_OK) return rc;
   const int P = T * K, sets = moe_layer_shared_sets(T, H, E, K, I, Is);
   const size_t h_bytes = sets > 0 ? align256((size_t)T * (size_t)Is * 2) : 0;
-  const size_t part_bytes = (size_t)sets * (size_t)T * (size_t)H * 4;
+  const int parts = shared_few_parts(Is);
+  const size_t part_bytes = (size_t)parts * (size_t)T * (size_t)H * 4;
   const bool copied = Xp != nullptr;
   // The steps run one after another, so a caller may hand the same memory to several of them (one buffer as every
   // workspace, an output in a workspace that no later step reads).  What is done in one launch instead must not overlap:
@@ -478,7 +497,7 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                     apart(riding, riding_bytes, expert_offsets, ((size_t)E + 1) * 4) &&
                     apart(riding, riding_bytes, sg, (size_t)T * 4) && apart(riding, riding_bytes, out, x_bytes) &&
                     apart(riding, riding_bytes, next, next ? x_bytes : 0);
-  Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, T, Is};
+  Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, parts, T, Is};
   if (ride) riders.part = reinterpret_cast<float*>(static_cast<unsigned char*>(shared_workspace) + h_bytes);
   rc = expert_group_forward_impl(group_lo, group_hi, nullptr, copied ? Xp : x, copied ? nullptr : src_of_row, copied ? 1 : K,
                                  expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
@@ -504,7 +523,7 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
     rc = launch_gate_dot(x, wgate, T, H, sg, (hipStream_t)stream);
     if (rc != MOE_OK) return rc;
   }
-  rc = launch_combine_layer(Yp, row_of_pair, topk_w, ride ? riders.part : nullptr, sets, x,
+  rc = launch_combine_layer(Yp, row_of_pair, topk_w, ride ? riders.part : nullptr, parts, x,
                             x_kept && (ride || !gate_formed) ? wgate : nullptr, Is > 0 ? S : nullptr, sg, T, H, K, out, next_eps,
                             next_here ? next : nullptr, (hipStream_t)stream);
   if (rc != MOE_OK || next == nullptr || next_here) return rc;

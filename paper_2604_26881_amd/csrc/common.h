@@ -103,6 +103,7 @@ struct GemmArgs {
   // n_shared more weight sets, each applied to all shared_rows tokens.  In the row space of A and C
   // the routed rows are [0, rows_routed) and set s owns rows rows_routed + s*shared_rows onwards.
   int n_shared;
+  int shared_parts;        // (streaming kernel, down) K parts of the shared contraction
   int shared_rows;         // tokens T
   int rows_routed;         // P
   const bf16_t* Bs0;       // weights of set 0 (gate branch, or the down projection); set s starts s*shared_b_step

@@ -50,14 +50,18 @@ __device__ __forceinline__ void stream_tail(F&& step) {
   }
 }
 
-// SHARED: the shared expert of a batch of a few tokens rides along.  It is a.n_shared sets of N columns of its hidden
-// layer (gate/up; the last one may be narrower) and as many parts of its contraction (down, left as fp32 partial sums in
-// a.Cpart for the aggregation to add), the first a.n_shared of blockIdx.y; all of them take all tokens.  With one token
-// the routed experts and the shared expert each leave most of the chip idle in a launch of their own: H 2048, 4 of 60
-// experts of I 1408 and Is 5632, gate/up 14.8 + 16.3 us, down 8.3 + 13.3 (tiles with K cut in 8, and their sum); together
-// 19.2 and 11.3.  The layer: T = 1 62.7 -> 46.5 us, 13 (with a second stream before) 134 -> 126.  From 17 tokens on the
-// shared weights are read by two passes; up to 32 tokens that still beats launches of their own on one stream (T = 24
-// 178 -> 171 us, 33 203 without it).
+// SHARED: the shared expert of a batch of a few tokens, riding along with the routed experts or (no experts) by itself.
+// Of blockIdx.y the first a.n_shared are its own, and all of them take all tokens.  Gate/up: sets of N columns of its
+// hidden layer (the last one may be narrower).  Down: its contraction is cut into a.shared_parts parts of whole K steps;
+// with a.Cpart each is a set of its own and leaves fp32 partial sums there, which a later kernel adds in ascending order
+// and rounds; without (no room for them) one wave forms the parts one after another and adds them in that same order.
+// The parts and the K starts depend on Is and the column alone, so the shared expert has the same bits alone, riding,
+// beside any block cut, and whatever the workspace.
+// With one token the routed experts and the shared expert each leave most of the chip idle in a launch of their own:
+// H 2048, 4 of 60 experts of I 1408 and Is 5632, gate/up 14.8 + 16.3 us, down 8.3 + 13.3 (tiles with K cut in 8, and their
+// sum); together 19.2 and 11.3.  By itself (beside several blocks or on a second stream), with its sum and gate logits,
+// against those tiles: 1 token 32 -> 21 us, 32 tokens 32 -> 24; H 1024, Is 4032 42 -> 14.  From 17 tokens on a riding shared expert is read by two passes; up to 32 tokens that
+// still beats launches of their own on one stream.
 template <int MT, bool GATEUP, int NST, bool SHARED>
 __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   using S = StreamLdsShape<MT, NST>;
@@ -79,29 +83,32 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   if (Me <= (int)blockIdx.z * pass_rows) return;
 
   const int N = a.N;
-  // elements between consecutive weight (and token) rows, and where a shared set's part of the contraction begins
-  const int Kdim = sh && !GATEUP ? a.ldb_shared : a.Kdim;
-  const int kbeg = sh && !GATEUP ? eg * a.Kdim : 0;
-  const int nk = (sh && !GATEUP ? min(a.Kdim, Kdim - kbeg) : a.Kdim) / 64;
+  constexpr bool CUT = SHARED && !GATEUP;                      // a shared set's contraction comes in parts
+  const int Kdim = CUT && sh ? a.ldb_shared : a.Kdim;          // elements between consecutive weight (and token) rows
+  const int part0 = CUT && sh && a.Cpart != nullptr ? eg : 0;  // the parts this wave forms
+  const int part1 = CUT && sh ? (a.Cpart != nullptr ? eg + 1 : a.shared_parts) : 1;
+  int nk = Kdim / 64;                                          // K steps of a part, and the byte where it begins
+  size_t kofs = 0;
   // The walk over K starts at step `rot` and wraps around.  Thousands of these waves start within a
   // few microseconds of each other; if all began at K step 0 their requests of one moment would sit
   // at the same offset inside the weight rows, which for rows of a power-of-two length (4 KB at
   // K = 2048) lands them in the same memory channels (measured on the decode batch: gate/up 134 us
   // with a common start, 121 us with staggered starts; the 2816-byte rows of the down projection
-  // show no difference).  rot depends on the expert and the column block only, so results do not
-  // depend on the block cut.
-  const int rot = (int)(((unsigned)blockIdx.x * 3u + (unsigned)eg * 5u) % (unsigned)nk);
+  // show no difference).  rot depends on the expert (or the part) and the column block only, so results
+  // do not depend on the block cut.
+  auto start = [&](unsigned column, unsigned set) { return (int)((column * 3u + set * 5u) % (unsigned)nk); };
   // this wave's output columns: rows [n0, n0+16) of both branches (gate/up) or rows [n0, n0+32) (down)
   const int n0 = (int)blockIdx.x * NPER;
   if (n0 >= N || (sh && GATEUP && eg * N + n0 >= a.ldb_shared)) return;
+  int rot = sh && GATEUP ? start((unsigned)(eg * N + n0) / NPER, 0u) : start(blockIdx.x, (unsigned)eg);
   const size_t wrow = sh && !GATEUP ? (size_t)n0 : (size_t)eg * N + n0;   // first weight row
-  const unsigned char* W0 = reinterpret_cast<const unsigned char*>((sh ? a.Bs0 : a.B0) + wrow * Kdim + kbeg);
+  const unsigned char* W0 = reinterpret_cast<const unsigned char*>((sh ? a.Bs0 : a.B0) + wrow * Kdim);
   const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>((sh ? a.Bs1 : a.B1) + wrow * Kdim)
                                    : W0 + (size_t)16 * Kdim * 2;
-  const unsigned char* Ab = reinterpret_cast<const unsigned char*>(sh ? a.As + kbeg : a.A);
+  const unsigned char* Ab = reinterpret_cast<const unsigned char*>(sh ? a.As : a.A);
   const bool gathered = a.gather != nullptr && !sh;
   // gate/up: the shared hidden rows are ldb_shared wide, set eg owns columns [eg*N, (eg+1)*N) of them
-  bf16_t* const Cb = sh && GATEUP ? a.Cs + (size_t)eg * N : a.C;
+  bf16_t* const Cb = sh ? a.Cs + (GATEUP ? (size_t)eg * N : (size_t)0) : a.C;
   const int ldc = sh && GATEUP ? a.ldb_shared : N;
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -128,16 +135,11 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
       }
 
     f32x4 acc0[MT], acc1[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      acc0[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      acc1[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
 
     // K step s into ring slot `slot`: the weights with the read-once hint, the token rows without
     auto issue = [&](int s, int slot) {
       const uint32_t l = lds0 + (uint32_t)slot * S::STAGE;
-      const size_t kb = (size_t)(s + rot >= nk ? s + rot - nk : s + rot) * 128;
+      const size_t kb = kofs + (size_t)(s + rot >= nk ? s + rot - nk : s + rot) * 128;
       copy_to_lds_16(W0 + kb, coffW[0], l, true);
       copy_to_lds_16(W0 + kb, coffW[1], l + 1024u, true);
       copy_to_lds_16(W1 + kb, coffW[0], l + 2048u, true);
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
       for (int mt = 0; mt < MT; ++mt) {
         const int m = m0 + r16 + mt * 16;
         if (m < Me) {
-          if (SHARED && !GATEUP && sh) {
+          if (CUT && sh && a.Cpart != nullptr) {
             float* part = a.Cpart + ((size_t)eg * a.shared_rows + m) * N + n0 + 4 * q;
             *reinterpret_cast<float4*>(part) = make_float4(acc0[mt][0], acc0[mt][1], acc0[mt][2], acc0[mt][3]);
             *reinterpret_cast<float4*>(part + 16) = make_float4(acc1[mt][0], acc1[mt][1], acc1[mt][2], acc1[mt][3]);
@@ -212,25 +214,51 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
         }
     };
 
-    if (nk > S::D) {
-#pragma unroll
-      for (int s = 0; s < S::D; ++s) issue(s, s);
-      int slot = 0;
-      for (int s = 0; s + S::D < nk; ++s) {
-        wait_copies_but<(S::D - 1) * S::NI>();          // step s has landed
-        const int free_slot = slot == 0 ? NST - 1 : slot - 1;   // read one step ago (or never used yet)
-        consume(slot, [&] { issue(s + S::D, free_slot); });
-        slot = slot + 1 == NST ? 0 : slot + 1;
+    f32x4 sum0[MT], sum1[MT];   // (CUT: of the parts before)
+    for (int part = part0; part < part1; ++part) {
+      if (CUT && sh) {
+        const int steps = Kdim / 64, begin = steps * part / a.shared_parts;
+        nk = steps * (part + 1) / a.shared_parts - begin;
+        kofs = (size_t)begin * 128;
+        rot = start(blockIdx.x, (unsigned)part);
       }
-      stream_tail<0, S::D, S::NI>([&](int) {
-        consume(slot, [] {});
-        slot = slot + 1 == NST ? 0 : slot + 1;
-      });
-    } else {   // fewer K steps than ring stages: one stage at a time
-      for (int s = 0; s < nk; ++s) {
-        issue(s, 0);
-        wait_copies_but<0>();
-        consume(0, [] {});
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        acc0[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc1[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      if (nk > S::D) {
+  #pragma unroll
+        for (int s = 0; s < S::D; ++s) issue(s, s);
+        int slot = 0;
+        for (int s = 0; s + S::D < nk; ++s) {
+          wait_copies_but<(S::D - 1) * S::NI>();          // step s has landed
+          const int free_slot = slot == 0 ? NST - 1 : slot - 1;   // read one step ago (or never used yet)
+          consume(slot, [&] { issue(s + S::D, free_slot); });
+          slot = slot + 1 == NST ? 0 : slot + 1;
+        }
+        stream_tail<0, S::D, S::NI>([&](int) {
+          consume(slot, [] {});
+          slot = slot + 1 == NST ? 0 : slot + 1;
+        });
+      } else {   // fewer K steps than ring stages: one stage at a time
+        for (int s = 0; s < nk; ++s) {
+          issue(s, 0);
+          wait_copies_but<0>();
+          consume(0, [] {});
+        }
+      }
+      if constexpr (CUT) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            acc0[mt][j] = part > part0 ? sum0[mt][j] + acc0[mt][j] : acc0[mt][j];
+            acc1[mt][j] = part > part0 ? sum1[mt][j] + acc1[mt][j] : acc1[mt][j];
+          }
+          sum0[mt] = acc0[mt];
+          sum1[mt] = acc1[mt];
+        }
       }
     }
     store();
@@ -244,7 +272,7 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   using S = StreamLdsShape<MT, NST>;
   static_assert(NST * S::STAGE <= 64 * 1024, "dynamic LDS without an opt-in attribute");
   auto kern = expert_stream_lds_kernel<MT, GATEUP, NST, SHARED>;
-  const int nexp = a.offsets ? a.hi - a.lo : 1;
+  const int nexp = (a.offsets ? a.hi - a.lo : SHARED ? 0 : 1) + (SHARED ? a.n_shared : 0);
   const int per = GATEUP ? 16 : 32;
   const int gx = (a.N + per - 1) / per;
   if (gx <= 0 || nexp <= 0) return 0;
@@ -255,7 +283,7 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   // from 250 + 159 to 180 + 98 us at T = 384; 16 and 32 begin to cost the unbiased batches 5 - 20 %.
   const int passes_max = (a.rows_total + 16 * MT - 1) / (16 * MT);
   const int gz = std::max(1, std::min(STREAM_PASS_GROUPS, passes_max / 2));
-  hipLaunchKernelGGL(kern, dim3(gx, nexp + (SHARED ? a.n_shared : 0), gz), dim3(64), NST * S::STAGE, st, a);
+  hipLaunchKernelGGL(kern, dim3(gx, nexp, gz), dim3(64), NST * S::STAGE, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
@@ -268,7 +296,9 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
 template <bool GATEUP>
 static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.N % 32 != 0 || a.Kdim % 64 != 0) return -2;
-  if (a.n_shared > 0) return launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
+  if (a.n_shared > 0)   // by itself one pass over its weights serves 32 tokens
+    return a.offsets == nullptr && a.shared_rows > 16 ? launch_stream_lds_t<2, GATEUP, 4, true>(a, st)
+                                                      : launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
   if (a.offsets != nullptr && a.mean_rows > STREAM_FEW_ROWS && a.N % 64 == 0)
     return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
   return launch_stream_lds_t<1, GATEUP, 4, false>(a, st);

@@ -225,14 +225,47 @@ def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, ga
     for name in ("topk_ids", "topk_w", "expert_offsets", "src_of_row", "row_of_pair", "Yp") + (() if gather else ("Xp",)):
         a, b = getattr(one, name), getattr(steps, name)
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
-    if Is == 0:
-        assert torch.equal(one.out.view(torch.int16), steps.out.view(torch.int16))
-    else:
-        assert torch.equal(one.sg, steps.sg)
+    assert torch.equal(one.out.view(torch.int16), steps.out.view(torch.int16))
+    if Is > 0:
+        assert torch.equal(one.sg, steps.sg) and torch.equal(one.S.view(torch.int16), steps.S.view(torch.int16))
         f32 = {k: v.float().numpy() for k, v in w.items() if v is not None}
         S_ref, _ = oracle64.shared_forward(x.float().numpy(), f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
         check_close(f64(one.S), S_ref, "S")
-        check_close(f64(one.out), f64(steps.out), "out")     # both within the bound of the oracle's: the steps are pinned elsewhere
+
+
+@pytest.mark.parametrize("T", [1, 13, 16, 17, 32, 33])
+# K parts of 20 and 21 steps; three; one; four of 22; one, and more sets than can ride along
+@pytest.mark.parametrize("H,E,K,I,Is", [(512, 12, 2, 384, 2624), (256, 60, 4, 576, 3904), (128, 16, 2, 64, 448), (192, 20, 2, 1408, 5632),
+                                        (320, 16, 1, 64, 1024)])
+def test_output_is_bitwise_independent_of_blocks_streams_and_sequence(moe, oracle64, T, H, E, K, I, Is):
+    print(f"[case] few tokens in every sequence T={T} H={H} E={E} K={K} I={I} Is={Is}", flush=True)
+    w = workloads.layer_weights(H, E, I, Is, 21 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T * 3 + E)).to(torch.bfloat16)
+    d, xg = {k: v.cuda() for k, v in w.items()}, x.cuda()
+    run = lambda **kw: moe.moe_layer_forward(xg, d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"]), K,
+                                             False, **kw)
+    bufs = {"one block": run(), "gathered": run(fused_gather=True), "two blocks": run(groups=[(0, 5), (5, E)]),
+            "a block per expert": run(groups=[(e, e + 1) for e in range(E)]), "two streams": run(shared_stream=torch.cuda.Stream()),
+            "blocks and streams": run(groups=[(0, 1), (1, E)], shared_stream=torch.cuda.Stream())}
+    torch.cuda.synchronize()
+    one = bufs["one block"]
+    f32 = {k: v.float().numpy() for k, v in w.items()}
+    S_ref, sg_ref = oracle64.shared_forward(x.float().numpy(), f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
+    check_close(f64(one.S), S_ref, "S")
+    assert np.allclose(one.sg.cpu().numpy(), sg_ref, rtol=1e-4, atol=1e-5)
+    for name, b in bufs.items():
+        for what in ("S", "sg", "Yp", "out"):
+            assert torch.equal(getattr(b, what).view(torch.uint8), getattr(one, what).view(torch.uint8)), f"{what} of {name}"
+    # the shared expert by hand, in workspaces from the smallest that is taken (K parts where K divides evenly) to the helper's
+    h_only = (T * Is * 2 + 255) // 256 * 256
+    least = h_only + next((p for p in (8, 4, 2) if Is % (64 * p) == 0), 0) * T * H * 4
+    for nbytes in {least, int(moe.load().moe_shared_workspace_bytes(T, H, Is))}:
+        for flags in (0, 0x400):
+            S, sg = torch.full_like(one.S, 768.0), torch.full_like(one.sg, 768.0)
+            moe.moe_shared_forward(xg, d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"], S, sg, torch.empty(nbytes, dtype=torch.uint8, device="cuda"),
+                                   flags)
+            torch.cuda.synchronize()
+            assert torch.equal(S.view(torch.int16), one.S.view(torch.int16)) and torch.equal(sg, one.sg), f"workspace {nbytes}"
 
 
 @pytest.mark.parametrize("T", [1, 13, 16, 17, 32, 33])
