@@ -30,8 +30,9 @@ bool dims_ok(int H) { return H > 0 && H % 64 == 0; }
 // only, 0x200: down projection only), so that each can be timed on its own.  Bit 10 (0x400, shared
 // expert with automatic shapes): its first kernel takes no tile shape that fills a CU completely,
 // so that small kernels of other streams (gating, micro-batch construction) run beside it.
-// Shared expert: parts of its down projection along K that the workspace has room for: 8 up to 512 tokens, beyond
-// that as many (a power of two) as it takes 128x128 tiles to 256 items, one round of the chip.
+// Shared expert: most parts of its down projection along K, for which the workspace helper reports room: 8 up to 512
+// tokens, beyond that as many (a power of two) as it takes 128x128 tiles to 256 items, one round of the chip (the compute
+// units of the MI355X: the helper answers without a device, and the sums must not depend on one).
 constexpr int SHARED_SMALL_T = 512;
 constexpr int SHARED_KPARTS_MAX = 8;
 int shared_parts_room(int T, int H) {
@@ -378,30 +379,31 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
   if (!plan.valid) return MOE_ERR_SHAPE;
   const bool few = (policy & 0xff) == 0 && T <= SHARED_FEW_T;
   const size_t h_bytes = align256((size_t)T * (size_t)Is * 2);
-  // Room for K parts of the down projection: the 128x64 shape asked for by the caller and batches up to 512 tokens
-  // must bring it; larger ones (sizes the helper reports include it) use what there is.
+  // K parts of the down projection: as many as the sizes call for.  The 128x64 shape asked for by the caller and batches up
+  // to 512 tokens must bring room for them; otherwise parts without room are formed in turn, to the same bits.
   const size_t one_part = (size_t)T * (size_t)H * 4;
-  const size_t room = workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0;
+  const int room = (int)std::min<size_t>(SHARED_KPARTS_MAX, workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0);
   int parts_max = 0;
   if (!plan.stream && (plan.tile_rows == 64 || plan.tile_rows == 0) && tile_down_ksplit(Is) > 1) {
-    const size_t want = plan.tile_rows == 64 || T <= SHARED_SMALL_T ? (size_t)tile_down_ksplit(Is) : (size_t)shared_parts_room(T, H);
-    if ((plan.tile_rows == 64 || T <= SHARED_SMALL_T) && room < want) return MOE_ERR_WORKSPACE;
-    parts_max = (int)(room < want ? room : want);
+    const bool must = plan.tile_rows == 64 || T <= SHARED_SMALL_T;
+    parts_max = must ? tile_down_ksplit(Is) : shared_parts_room(T, H);
+    if (must && room < parts_max) return MOE_ERR_WORKSPACE;
   }
-  if (few) parts_max = room >= (size_t)shared_few_parts(Is) ? shared_few_parts(Is) : 1;   // (1: formed one after another)
-  float* part = parts_max > 1 ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes) : nullptr;
+  const int few_parts = few && room >= shared_few_parts(Is) ? shared_few_parts(Is) : 1;   // (1: formed in turn)
+  const bool side_by_side = few ? few_parts > 1 : room > 1 && parts_max > 1;
+  float* part = side_by_side ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes) : nullptr;
   GemmArgs gu{};
   gu.A = (const bf16_t*)x; gu.B0 = (const bf16_t*)Wsg; gu.B1 = (const bf16_t*)Wsu; gu.C = (bf16_t*)workspace;
   gu.offsets = nullptr; gu.lo = 0; gu.hi = 1; gu.rows_fixed = T; gu.rows_total = T; gu.mean_rows = T;
   gu.N = Is; gu.Kdim = H;
   GemmArgs dn = gu;
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wsd; dn.B1 = nullptr; dn.C = (bf16_t*)S;
-  dn.N = H; dn.Kdim = Is; dn.Cpart = part; dn.parts_max = part ? parts_max : 0;
+  dn.N = H; dn.Kdim = Is; dn.Cpart = part; dn.parts_max = parts_max; dn.parts_room = room;
   gu.leave_room = (policy >> 10) & 1;
   if (few) {
     plan.stream = true;
     gu.n_shared = 1;
-    dn.n_shared = parts_max;
+    dn.n_shared = few_parts;
     dn.shared_parts = shared_few_parts(Is);
     gu.shared_rows = dn.shared_rows = T;
     gu.ldb_shared = dn.ldb_shared = Is;
@@ -411,7 +413,7 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
   int parts;
   const int rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   if (rc != 0) return rc;
-  if (few && plan.do_down) parts = parts_max;
+  if (few && plan.do_down) parts = few_parts;
   if (parts > 1) {   // the gate logits beside the sum, unless they go where it still reads
     const bool beside = wgate && apart(sg, (size_t)T * 4, part, (size_t)parts * one_part);
     const int rc_sum = launch_sum_parts(part, parts, T, H, S, x, beside ? wgate : nullptr, sg, (hipStream_t)stream);

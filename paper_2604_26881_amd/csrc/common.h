@@ -93,7 +93,8 @@ struct GemmArgs {
   int N;               // output columns (per branch for gate/up)
   int Kdim;            // contraction length
   float* Cpart;        // room for the fp32 partial outputs [parts, rows_total, N] of kernels that cut K, else unused
-  int parts_max;       // parts that Cpart has room for (0: none)
+  int parts_max;       // most parts the sizes call for (0 and 1: no cut); the number, and with it the result, does not depend
+  int parts_room;      // on the parts that Cpart has room for: without it they are formed in turn
   const int32_t* gather;   // nullptr: row r of A is A[r]; else row r of A is A[gather[r] / gather_div]
   int gather_div;          // (the token rows themselves, addressed through src_of_row: no permuted copy)
   int leave_room;          // 1: no tile shape that takes a whole CU (all registers of every SIMD): kernels of

@@ -90,7 +90,10 @@ __host__ __device__ constexpr int fragment_read_order(int slot, int tb, int nb) 
   return slot == 0 ? tb : (slot == 1 ? 0 : (slot <= nb ? tb + slot - 1 : slot - nb));
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE>
+// KSPLIT > 1: K is cut into that many parts.  Each is a work item whose fp32 sums go to a.Cpart; INTURN: a workgroup forms
+// the parts of a tile one after another and adds them in the order of the kernel that adds them otherwise: the same
+// bits without room for the parts (and the time of the uncut tile).
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE, bool INTURN>
 __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -161,7 +164,8 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   // gap; tiles of a complete index space that do not exist would otherwise push real ones into one more round:
   // 777 tokens on one weight set are 5 tiles of 160 rows by 44 column tiles, 220 for 256 workgroups, and took
   // 73 us as 8 x 44 with gaps.)
-  const int Lend = (grp0 == 0 || grp1 == 0 ? (total0 + total1) * NT : ngrp * groupTiles) * KSPLIT;
+  constexpr int ITEMS = INTURN ? 1 : KSPLIT;     // work items of a tile
+  const int Lend = (grp0 == 0 || grp1 == 0 ? (total0 + total1) * NT : ngrp * groupTiles) * ITEMS;
   // Divisions of the walk, prepared once per workgroup so that finding a tile costs multiplications only:
   // light groups among the first g groups of the merged walk = (g * light_ratio) >> 32, with light_ratio =
   // ceil(grp0 * 2^32 / ngrp): monotone in g, rises by at most one per group, and is exactly grp0 at g = ngrp,
@@ -207,7 +211,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   uint32_t coff[S::NL];   // byte offsets of this lane's 16 bytes for each of the NL copies of a stage (K step 0)
   int krot = 0;           // K step the tile starts at (its walk over K wraps around)
   auto kstep = [&](int kt) -> int { const int k = kt + krot; return k >= nk ? k - nk : k; };
-  int it = 0;
+  int it = 0, turn = 0;   // turn: the K part that comes next (INTURN)
   auto next_tile = [&]() -> TileState {
     TileState t{};
     int L = 0, mrow = 0, nt = 0, cls = 0, ks = 0;
@@ -216,8 +220,8 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
       if (L >= Lend) { t.valid = false; return t; }
       int Lt = L;
       ks = 0;
-      if constexpr (KSPLIT > 1) {   // K parts outermost: the items of an XCD share panels, not only sums
-        const int tiles = Lend / KSPLIT;
+      if constexpr (ITEMS > 1) {   // K parts outermost: the items of an XCD share panels, not only sums
+        const int tiles = Lend / ITEMS;
         while (Lt >= tiles) { Lt -= tiles; ++ks; }
       }
       int grp = Lt, rem = 0;
@@ -240,7 +244,13 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
       }
       if (nt < NT) break;
     }
-    ++it;
+    if constexpr (INTURN) {
+      ks = turn;
+      turn = turn + 1 == KSPLIT ? 0 : turn + 1;
+      if (turn == 0) ++it;
+    } else {
+      ++it;
+    }
     t.valid = true;
     t.ks = ks;   // K part of this work item
 
@@ -327,6 +337,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   long long clk_kloops = 0, clk_tiles = 0;
   const long long clk_begin = clock64(), wall_begin = wall_clock64();
 
+  f32x16 sum[INTURN ? S::NB : 1][INTURN ? S::TB : 1];   // of the K parts before (INTURN)
   TileState cur = next_tile();
   while (cur.valid) {
     const int row0 = cur.row0, rowEnd = cur.rowEnd, rowsValid = cur.rowsValid, n0 = cur.n0, ks = cur.ks;
@@ -479,6 +490,19 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
     // stages now, their way from L2 overlaps the stores below
     const TileState nxt = next_tile();
 
+    // (selected, not branched around: see the clock record above)
+    if constexpr (INTURN) {
+#pragma unroll
+      for (int nb = 0; nb < S::NB; ++nb)
+#pragma unroll
+        for (int tb = 0; tb < S::TB; ++tb) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[nb][tb][i] = ks > 0 ? sum[nb][tb][i] + acc[nb][tb][i] : acc[nb][tb][i];
+          sum[nb][tb] = acc[nb][tb];
+        }
+    }
+    const int rowStop = INTURN && ks + 1 < KSPLIT ? row0 : rowEnd;   // rows of an incomplete sum are not stored
+
     // epilogue: accumulator element i of block (nb, tb) is output column
     // 8*(i/4) + 4*(lane/32) + i%4 of the block, token row lane%32: lanes l and l+32 hold the two
     // halves of every 8-column group of a row.  In the down projection the two lanes trade one
@@ -500,13 +524,13 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
 #pragma unroll
     for (int tb = 0; tb < S::TB; ++tb) {
       const int m = row0 + wm * S::WTM + tb * 32 + frag_row;
-      if (m < rowEnd) {
+      if (m < rowStop) {
         bf16_t* crow_out = cbase + (size_t)(m - cshift) * a.N;
 #pragma unroll
         for (int nb = 0; nb < S::NBH; ++nb) {
           const int nblock = n0 + (GATEUP ? wn * (S::WTN / 2) : wn * S::WTN) + nb * 32;   // first column of the 32-column block
           if (nblock < a.N) {   // N is a multiple of 64 and nblock of 32: the block is inside or outside as a whole
-            if (KSPLIT > 1) {   // fp32 partial sum of K part ks; summed in order by the reduce kernel
+            if (ITEMS > 1) {   // fp32 partial sum of K part ks; summed in order by the reduce kernel
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
                 const int n = nblock + 4 * frag_half + 8 * q;
@@ -567,14 +591,14 @@ static int num_cus() {
   return n;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE, bool INTURN = false>
 static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
-  auto kern = expert_tile_kernel<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, SINGLE>;
+  auto kern = expert_tile_kernel<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, SINGLE, INTURN>;
   static_assert(KSPLIT == 1 || !SINGLE, "a K part of a tile does not wrap around");
   static_assert(KSPLIT == 1 || !GATEUP, "the SwiGLU product needs complete sums");
   if (a.Kdim % (S::BK * KSPLIT) != 0) return -2;
-  if (KSPLIT > 1 && a.Cpart == nullptr) return -3;
+  if (KSPLIT > 1 && !INTURN && a.Cpart == nullptr) return -3;
   static_assert(OCC * (NS * S::STAGE + 3600) <= 160 * 1024, "LDS of the resident workgroups must fit a CU");
   static std::atomic<uint64_t> lds_raised{0};
   const int lds = NS * S::STAGE;
@@ -583,7 +607,7 @@ static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   if (nexp > TILE_EMAX) return -2;
   const int NT = (a.N + S::NOUT - 1) / S::NOUT;
   const long mt_bound = (long)a.rows_total / BM + nexp;
-  const long bound = ((mt_bound + S::GM - 1) / S::GM) * S::GM * NT * KSPLIT;
+  const long bound = ((mt_bound + S::GM - 1) / S::GM) * S::GM * NT * (INTURN ? 1 : KSPLIT);
   // persistent workgroups: as many as fit on the chip at once (two per CU for the smaller tile)
   const long resident = (long)num_cus() * OCC;
   int grid = (int)(bound < resident ? bound : resident);
@@ -599,13 +623,10 @@ static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
 // instance without that path (with it the 256x256 kernels at 16 384 tokens lose 0.6 %, to registers and code
 // that no tile uses), and so does one weight set (the shared expert; with one token its gate/up kernel takes
 // 2 us more with the path than without).  The rule reads layer-wide sizes only.
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT = 1>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC>
 static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
-  if constexpr (KSPLIT == 1) {
-    if (a.offsets && a.mean_rows <= 4 * BM)
-      return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, true>(a, st);
-  }
-  return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, false>(a, st);
+  if (a.offsets && a.mean_rows <= 4 * BM) return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, 1, true>(a, st);
+  return launch_tile_s<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, 1, false>(a, st);
 }
 
 // Tile shape codes: 256 = 256x256, 192 = 192x256 (one weight set), 160 = 160 token rows x 256 weight rows, 128/129 = 128 x 256,
@@ -709,27 +730,30 @@ int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st) {
   if (t == 160) return launch_tile_t<160, 256, 1, 4, true, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, true, 3, 1>(a, st);
 }
+// A down projection in tiles of 128 token rows by BN, whole or in K parts (side by side in a.Cpart, or in turn)
+template <int BN, int WAVES_M, int WAVES_N, int NS>
+static int launch_tile_cut(const GemmArgs& a, int parts, bool in_turn, hipStream_t st) {
+  switch (parts) {
+    case 8:
+      return in_turn ? launch_tile_s<128, BN, WAVES_M, WAVES_N, false, NS, 1, 8, false, true>(a, st)
+                     : launch_tile_s<128, BN, WAVES_M, WAVES_N, false, NS, 1, 8, false>(a, st);
+    case 4:
+      return in_turn ? launch_tile_s<128, BN, WAVES_M, WAVES_N, false, NS, 1, 4, false, true>(a, st)
+                     : launch_tile_s<128, BN, WAVES_M, WAVES_N, false, NS, 1, 4, false>(a, st);
+    case 2:
+      return in_turn ? launch_tile_s<128, BN, WAVES_M, WAVES_N, false, NS, 1, 2, false, true>(a, st)
+                     : launch_tile_s<128, BN, WAVES_M, WAVES_N, false, NS, 1, 2, false>(a, st);
+    default: return launch_tile_t<128, BN, WAVES_M, WAVES_N, false, NS, 1>(a, st);
+  }
+}
 // *parts: in how many K parts the output was left in a.Cpart (1: the output itself is written)
 int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* parts) {
   const TileChoice c = pick_tile(a, tile_rows, false);
   const int t = c.code;
-  *parts = c.parts;
-  if (t == 64) {
-    switch (c.parts) {   // without a buffer for the parts: whole K per tile
-      case 8: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 8>(a, st);
-      case 4: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 4>(a, st);
-      case 2: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 2>(a, st);
-      default: return launch_tile_t<128, 64, 4, 1, false, 6, 1, 1>(a, st);
-    }
-  }
-  if (t == 130) {
-    switch (c.parts) {
-      case 8: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 8>(a, st);
-      case 4: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 4>(a, st);
-      case 2: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 2>(a, st);
-      default: return launch_tile_t<128, 128, 2, 2, false, 4, 1, 1>(a, st);
-    }
-  }
+  const bool in_turn = c.parts > std::max(1, a.parts_room);
+  *parts = in_turn ? 1 : c.parts;
+  if (t == 64) return launch_tile_cut<64, 4, 1, 6>(a, c.parts, in_turn, st);   // (without parts: whole K per tile)
+  if (t == 130) return launch_tile_cut<128, 2, 2, 4>(a, c.parts, in_turn, st);
   if (t >= 256) return launch_tile_t<256, 256, 2, 2, false, 2, 1>(a, st);
   if (t == 192) return launch_tile_s<192, 256, 2, 2, false, 2, 1, 1, false>(a, st);
   if (t == 160) return launch_tile_t<160, 256, 1, 4, false, 3, 1>(a, st);

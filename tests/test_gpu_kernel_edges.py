@@ -112,7 +112,7 @@ def test_block_call_that_hosts_the_shared_experts_on_few_rows(moe, oracle64, T):
         check_close(f64(buf.S_parts[p]), S, f"shared expert {p}")
 
 
-@pytest.mark.parametrize("T,H,Is", [(513, 256, 1024), (640, 1024, 256), (700, 1536, 768), (1000, 128, 640),
+@pytest.mark.parametrize("T,H,Is", [(777, 2048, 5632), (600, 64, 1536), (513, 256, 1024), (640, 1024, 256), (700, 1536, 768), (1000, 128, 640),
                                           (129, 512, 1024), (300, 2048, 512), (1100, 3072, 128)])
 def test_shared_expert_with_the_down_projection_cut_along_k(moe, oracle64, T, H, Is):
     # the parts that the workspace has room for (at most; K must also divide into them), and none of them
@@ -123,7 +123,8 @@ def test_shared_expert_with_the_down_projection_cut_along_k(moe, oracle64, T, H,
     if T > 512:
         assert full in (h_only, h_only + 2 * T * H * 4, h_only + 4 * T * H * 4, h_only + 8 * T * H * 4)
     S_ref, sg_ref = oracle64.shared_forward(d["x"], d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"])
-    for nbytes in {full, h_only} if T > 512 else {full}:
+    first = None     # beyond 512 tokens: the same bits with room for every part, for some, for none
+    for nbytes in sorted({full, h_only, h_only + T * H * 4, min(full, h_only + 2 * T * H * 4)}) if T > 512 else {full}:
         print(f"[case] shared expert T={T} H={H} Is={Is}, workspace {nbytes}", flush=True)
         ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
         S = torch.full((T, H), 768.0, dtype=torch.bfloat16, device="cuda")
@@ -132,6 +133,8 @@ def test_shared_expert_with_the_down_projection_cut_along_k(moe, oracle64, T, H,
         torch.cuda.synchronize()
         check_close(f64(S), S_ref, f"S, workspace {nbytes}")
         assert np.allclose(sg.cpu().numpy(), sg_ref, rtol=1e-4, atol=1e-5)
+        first = S if first is None else first
+        assert torch.equal(S.view(torch.int16), first.view(torch.int16)), f"bits depend on the workspace ({nbytes})"
 
 
 @pytest.mark.parametrize("T", [33, 160, 161, 640, 641, 700])     # 1, 2, 4, 5 token tiles of 160 rows and one row more
