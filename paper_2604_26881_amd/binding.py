@@ -24,6 +24,9 @@ SYMBOLS = ["moe_status_string", "moe_build_id", "moe_route", "moe_route_segments
            "moe_workspace_bytes", "moe_layer_forward", "moe_layer_shared_sets", "moe_residual_norm", "moe_probe_mfma", "moe_tile_clock_buffer"]
 
 
+REFUSALS = (-1, -2, -3)     # MOE_ERR_NULL, MOE_ERR_SHAPE, MOE_ERR_WORKSPACE: the call does not take these arguments
+
+
 class MoeError(RuntimeError):
     pass
 
@@ -452,7 +455,8 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
                        shared_stream, fused_gather, seg_offsets, fused_shared, next_out=None, eps=0.0) -> bool:
     """The whole layer through the library's own sequence of its steps: one crossing into native code instead of five to
     eight.  True when it ran.  It serves the plain case (one block, one stream, buffers of exactly these sizes); everything
-    else, and whatever the library refuses, is left to the step-by-step sequence, which also names the step at fault."""
+    else, and arguments that the library refuses, are left to the step-by-step sequence, which also names the step at
+    fault.  A launch that fails raises MoeError."""
     if (groups is not None and len(groups) > 1) or fused_shared:
         return False
     if tenant_rows is not None and (bias is None or seg_offsets is None):
@@ -471,6 +475,9 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
         if weights > 240e6 and not torch.cuda.is_current_stream_capturing():
             return False
     ids, src = buf.topk_ids, buf.src_of_row
+    if any(t is None for t in (ids, buf.topk_w, buf.expert_offsets, src, buf.row_of_pair, x if fused_gather else buf.Xp, buf.Yp,
+                               buf.out, buf.workspace)):
+        return False        # buffers with gaps: every step knows what it allocates and what it refuses
     if (T == 0 or Wr.shape != (E, H) or Hg != H or ids.shape != (T, K) or src.shape[0] != T * K or buf.Yp.shape != (T * K, H)
             or buf.workspace_permute is None):
         return False
@@ -514,6 +521,8 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
         side.wait_stream(main)
         if capturing:       # ... and leaves it joined
             main.wait_stream(side)
+    if rc not in REFUSALS:      # (a launch that failed is no refusal: the steps would only be enqueued a second time)
+        _check(rc, "moe_layer_forward")
     return rc == 0
 
 

@@ -209,3 +209,52 @@ def test_layer_call_refuses_like_its_steps():
     assert call(x=None) == -1
     assert call(seg=p, n_seg=0) == -2 and call(seg=p, n_seg=5000) == -2
     assert call(next_eps=-1.0) == -2
+
+
+class _FakeLibrary:
+    def __init__(self, status):
+        self.status, self.calls = status, 0
+
+    def moe_layer_forward(self, *args):
+        self.calls += 1
+        return self.status
+
+    def moe_status_string(self, status):
+        return b"status text"
+
+
+def _one_call(monkeypatch, status, **without):
+    """binding._layer_in_one_call on CPU tensors with a library that returns `status`."""
+    import torch
+    from paper_2604_26881_amd import binding
+    T, H, E, K, I = 4, 64, 8, 2, 64
+    lib = _FakeLibrary(status)
+    monkeypatch.setattr(binding, "load", lambda: lib)
+    monkeypatch.setattr(binding, "_ptr", lambda t, dtype, name: None if t is None else 1)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    bf, i32 = dict(dtype=torch.bfloat16), dict(dtype=torch.int32)
+    buf = dict(topk_ids=torch.empty((T, K), **i32), topk_w=torch.empty((T, K)), expert_offsets=torch.empty(E + 1, **i32),
+               src_of_row=torch.empty(T * K, **i32), row_of_pair=torch.empty(T * K, **i32), Xp=torch.empty((T * K, H), **bf),
+               Yp=torch.empty((T * K, H), **bf), S=None, sg=None, out=torch.empty((T, H), **bf), workspace=torch.empty(4096),
+               workspace_shared=None, workspace_permute=torch.empty(4096))
+    buf.update(without)
+    w = torch.empty((E, I, H), **bf)
+    ran = binding._layer_in_one_call(torch.empty((T, H), **bf), torch.empty((E, H), **bf), None, w, w, torch.empty((E, H, I), **bf), None,
+                                     K, False, None, binding.LayerBuffers(**buf), None, 0, 0, None, False, None, False)
+    return ran, lib.calls
+
+
+def test_layer_in_one_call_leaves_refusals_to_the_steps_and_raises_failures(monkeypatch):
+    from paper_2604_26881_amd import MoeError
+    assert _one_call(monkeypatch, 0) == (True, 1)
+    for refused in (-1, -2, -3):
+        assert _one_call(monkeypatch, refused) == (False, 1)
+    for failed in (-4, -99):        # not enqueued a second time, and the first status is what the caller sees
+        with pytest.raises(MoeError, match=f"status {failed}"):
+            _one_call(monkeypatch, failed)
+
+
+@pytest.mark.parametrize("name", ["topk_ids", "topk_w", "expert_offsets", "src_of_row", "row_of_pair", "Xp", "Yp", "out", "workspace",
+                                  "workspace_permute"])
+def test_layer_in_one_call_leaves_buffers_with_gaps_to_the_steps(monkeypatch, name):
+    assert _one_call(monkeypatch, 0, **{name: None}) == (False, 0)
