@@ -137,6 +137,23 @@ def test_shared_expert_with_the_down_projection_cut_along_k(moe, oracle64, T, H,
         assert torch.equal(S.view(torch.int16), first.view(torch.int16)), f"bits depend on the workspace ({nbytes})"
 
 
+@pytest.mark.parametrize("T", [1, 16, 17, 31, 32, 33, 65])     # one and two tiles of 16 rows per pass, further passes
+@pytest.mark.parametrize("H,Is", [(64, 192), (448, 576)])
+def test_shared_expert_streamed_on_request(moe, oracle64, T, H, Is):
+    print(f"[case] shared expert streamed T={T} H={H} Is={Is}", flush=True)
+    w = workloads.layer_weights(H, 2, 64, Is, T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
+    d = {k: v.cuda() for k, v in w.items()}
+    ws = torch.empty((T * Is * 2 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    run = lambda n: moe.moe_shared_forward(x[:n].cuda(), d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"], torch.empty((n, H), dtype=torch.bfloat16,
+                                           device="cuda"), torch.empty(n, device="cuda"), ws, 9)[0]
+    S, S16 = run(T), run(min(T, 16))
+    torch.cuda.synchronize()
+    S_ref, _ = oracle64.shared_forward(x.float().numpy(), *[w[k].float().numpy() for k in ("Wsg", "Wsu", "Wsd", "wgate")])
+    check_close(f64(S), S_ref, "S")
+    assert torch.equal(S[:16].view(torch.int16), S16.view(torch.int16)), "a row depends on the rows of its pass"
+
+
 @pytest.mark.parametrize("T", [33, 160, 161, 640, 641, 700])     # 1, 2, 4, 5 token tiles of 160 rows and one row more
 def test_shared_expert_walk_over_incomplete_tile_groups(moe, oracle64, T):
     wl = workloads.qwen_layer(T, 950 + T, H=128, E=4, K=1, I=64, Is=448, renorm=False)
