@@ -234,16 +234,18 @@ int moe_expert_group_forward_gather(int group_lo, int group_hi, const void* x,
  * experts per layer beside the 60 routed ones; Sec. 3: a block packages a configurable set of
  * experts behind one function).  The shared FFN of intermediate size Is is taken as Is / I experts
  * of the routed experts' size I (gate/up rows [s*I, (s+1)*I) of Wsg, Wsu and columns [s*I, (s+1)*I)
- * of Wsd are shared expert s), each applied to every token.  Their tiles join the routed experts'
- * tiles in the same two kernel launches, so the launch has no idle tail between the routed and the
- * shared part and compute-bound shared tiles run beside memory-bound tiles of small experts.
+ * of Wsd are shared expert s), each applied to every token.  They join the routed experts in the same
+ * two kernel launches, so the launch has no idle tail between the routed and the shared part and
+ * compute-bound shared tiles run beside memory-bound tiles of small experts.  (With few rows per
+ * routed expert and many tokens, a mean of up to 32 rows and more than 192 tokens, the two parts take
+ * two launches each: different kernels serve them best.)
  *   Yp rows of the experts in [group_lo, group_hi): as moe_expert_group_forward_gather, bit for bit;
  *   S_parts[s,t,:] = FFN of shared expert s on x[t,:]  (bf16 [n_sets,T,H]; their sum over s is the
  *                    shared FFN's output, which moe_combine_parts forms in fp32);
  *   sg[t] = <x[t,:], wgate> (fp32) when wgate is not NULL.
  * Supported when moe_fused_shared_sets(T,H,E,K,I,Is) returns n_sets > 0: Is a multiple of I with
- * at most MOE_SHARED_SETS_MAX sets, E + n_sets <= 256, and a batch large enough for the MFMA tile
- * kernels (more than 26 rows per routed expert on average); otherwise MOE_ERR_SHAPE, and the
+ * at most MOE_SHARED_SETS_MAX sets, E + n_sets <= 256, and fewer than 16 experts or more than 26
+ * rows per routed expert on average; otherwise MOE_ERR_SHAPE, and the
  * caller uses moe_expert_group_forward(_gather) and moe_shared_forward.  When the routed experts
  * are cut into several blocks, one of the calls carries the shared experts and the others are
  * plain block calls.  x [T,H]; src_of_row [T*K]; weights as in the separate calls.

@@ -44,11 +44,21 @@ int shared_parts_room(int T, int H) {
 }
 
 // Tokens up to which the streaming kernel serves the shared expert, riding along with the routed ones or by itself, and
-// the K parts of its down projection there (of twenty K steps and more; parts of eleven, twice as many, cost a layer of
-// H 2048, Is 5632 about 2 us at 1 to 24 tokens).  Both depend on the shared expert's own sizes alone: its bits are the
-// same in every sequence of calls.  (Figures beside that kernel.)
+// the K parts of its down projection there: up to four of eight K steps and more, then parts of 22.  (A layer of H 2048,
+// Is 5632: four parts, with eight it takes about 2 us more at 1 to 24 tokens; 12 experts of H 1024 and Is 1536 at 24
+// tokens: 33 us in two parts, 38 in one.)  Both depend on the shared expert's own sizes alone: its bits are the same in
+// every sequence of calls.  (More figures beside that kernel.)
 constexpr int SHARED_FEW_T = 32;
-int shared_few_parts(int Is) { return std::max(1, std::min(SHARED_KPARTS_MAX, Is / 1280)); }
+int shared_few_parts(int Is) { return std::max({1, std::min(4, Is / 512), std::min(SHARED_KPARTS_MAX, Is / 1408)}); }
+
+// Tokens up to which the streaming kernels take the sets of a block call that hosts the shared experts along: four passes
+// of the narrow one, two of the wide one.  A layer in us, taken along | in tiles of their own | before routed rows of
+// these sizes were streamed (all in tiles): 12 experts of H 1024, I 768, Is 1536 at 20 tokens, top 4 36 | 56 | 44, at 36,
+// top 2 34 | 50 | 44, at 150 43 | 63 | 51; 15 of H 2048, I 512, Is 2048, top 1 at 60 tokens 52 | 60 | 65, at 90 (narrow)
+// 62 | 61 | 68; 8 of H 2560, I and Is 4096, top 1 at 200 (wide, three passes) 165 | 158 | 183.  What stays slower than all
+// in tiles are 27 to 32 rows per expert of more tokens (60 experts of H 2048 at T = 470 284 | 274, 15 at 400 78 | 71), for
+// the routed rows must keep the bits of the plain call, which is faster there than in tiles (285 | 307, 78 | 110).
+constexpr int FUSED_NARROW_T = 64, FUSED_WIDE_T = 192;
 
 struct Plan { bool valid; bool stream; int tile_rows; bool do_gateup; bool do_down; };
 Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
@@ -295,7 +305,7 @@ int moe_fused_shared_sets(int T, int H, int E, int K, int I, int Is) {
   if (ns > MOE_SHARED_SETS_MAX || E + ns > 256) return 0;
   const long long P = (long long)T * K;
   if ((P + (long long)ns * T) * (H > I ? H : I) >= (1ll << 31)) return 0;
-  return E < 16 || (P + E - 1) / E > 26 ? ns : 0;     // decode-sized batches keep the separate calls
+  return E < 16 || (P + E - 1) / E > 26 ? ns : 0;     // decode-sized batches of many experts keep the separate calls
 }
 
 size_t moe_fused_workspace_bytes(int T, int K, int I, int Is) {
@@ -336,9 +346,19 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
   dn.Bs0 = (const bf16_t*)Wsd; dn.shared_b_step = I; dn.ldb_shared = Is;   // set s: columns [s*I, (s+1)*I) of Wsd [H,Is]
   dn.Cs = (bf16_t*)S_parts;
   int rc = 0, parts;
-  if (plan.stream) {
-    // few rows per routed expert: the routed rows go through the streaming kernels (the bits of the plain block
-    // call), the shared sets through tiles of their own
+  const bool narrow = mean_rows <= STREAM_FEW_ROWS;
+  if (plan.stream && T <= (narrow ? FUSED_NARROW_T : FUSED_WIDE_T)) {
+    // few rows per routed expert: the streaming kernels, whose launches take the shared sets along (the hidden rows of the
+    // sets lie behind the routed ones: as one [T,Is] for the narrow kernel, as a [T,I] per set for the wide one)
+    gu.rows_total = dn.rows_total = P;
+    gu.Cs = (bf16_t*)workspace + (size_t)P * I;
+    dn.As = gu.Cs;
+    dn.shared_parts = ns;
+    if (narrow) gu.ldb_shared = Is;
+    rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
+  } else if (plan.stream) {
+    // the routed rows go through the streaming kernels all the same (the bits of the plain block call), the shared sets,
+    // with more tokens than passes over their weights pay for, through tiles of their own
     Plan tiles = plan;
     tiles.stream = false;
     GemmArgs sgu = gu, sdn = dn;

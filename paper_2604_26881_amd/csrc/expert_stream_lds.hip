@@ -54,7 +54,9 @@ __device__ __forceinline__ void stream_tail(F&& step) {
 // Of blockIdx.y the first a.n_shared are its own, and all of them take all tokens.  Gate/up: sets of N columns of its
 // hidden layer (the last one may be narrower).  Down: its contraction is cut into a.shared_parts parts of whole K steps;
 // with a.Cpart each is a set of its own and leaves fp32 partial sums there, which a later kernel adds in ascending order
-// and rounds; without (no room for them) one wave forms the parts one after another and adds them in that same order.
+// and rounds; with one set (no room for them) one wave forms the parts one after another and adds them in that same order.
+// (With as many sets as parts and no a.Cpart every part is an output of its own, bf16 in a.Cs: the block call that hosts
+// the shared experts.)
 // The parts and the K starts depend on Is and the column alone, so the shared expert has the same bits alone, riding,
 // beside any block cut, and whatever the workspace.
 // With one token the routed experts and the shared expert each leave most of the chip idle in a launch of their own:
@@ -85,8 +87,9 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   const int N = a.N;
   constexpr bool CUT = SHARED && !GATEUP;                      // a shared set's contraction comes in parts
   const int Kdim = CUT && sh ? a.ldb_shared : a.Kdim;          // elements between consecutive weight (and token) rows
-  const int part0 = CUT && sh && a.Cpart != nullptr ? eg : 0;  // the parts this wave forms
-  const int part1 = CUT && sh ? (a.Cpart != nullptr ? eg + 1 : a.shared_parts) : 1;
+  const bool in_turn = CUT && sh && a.n_shared != a.shared_parts;
+  const int part0 = CUT && sh && !in_turn ? eg : 0;            // the parts this wave forms
+  const int part1 = in_turn ? a.shared_parts : part0 + 1;
   int nk = Kdim / 64;                                          // K steps of a part, and the byte where it begins
   size_t kofs = 0;
   // The walk over K starts at step `rot` and wraps around.  Thousands of these waves start within a
@@ -108,7 +111,7 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   const unsigned char* Ab = reinterpret_cast<const unsigned char*>(sh ? a.As : a.A);
   const bool gathered = a.gather != nullptr && !sh;
   // gate/up: the shared hidden rows are ldb_shared wide, set eg owns columns [eg*N, (eg+1)*N) of them
-  bf16_t* const Cb = sh ? a.Cs + (GATEUP ? (size_t)eg * N : (size_t)0) : a.C;
+  bf16_t* const Cb = sh ? a.Cs + (GATEUP ? (size_t)eg * N : (size_t)eg * a.shared_rows * N) : a.C;
   const int ldc = sh && GATEUP ? a.ldb_shared : N;
 
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
@@ -297,10 +300,10 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
 template <bool GATEUP>
 static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.N % 32 != 0 || a.Kdim % 64 != 0) return -2;
-  const bool two = a.offsets == nullptr && (a.n_shared > 0 ? a.shared_rows : a.rows_fixed) > 16;
-  if (a.n_shared > 0) return two ? launch_stream_lds_t<2, GATEUP, 4, true>(a, st) : launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
   if (a.offsets != nullptr && a.mean_rows > STREAM_FEW_ROWS)
     return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
+  const bool two = a.offsets == nullptr && (a.n_shared > 0 ? a.shared_rows : a.rows_fixed) > 16;
+  if (a.n_shared > 0) return two ? launch_stream_lds_t<2, GATEUP, 4, true>(a, st) : launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
   return two ? launch_stream_lds_t<2, GATEUP, 4, false>(a, st) : launch_stream_lds_t<1, GATEUP, 4, false>(a, st);
 }
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st) { return launch_stream_lds_any<true>(a, st); }

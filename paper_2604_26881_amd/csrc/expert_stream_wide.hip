@@ -52,27 +52,30 @@ __device__ __forceinline__ void drain(F&& step) {
   }
 }
 
+// Where the rows of a pass come from and go: token rows A (through gather, if any), output C, elements between weight rows.
+struct WideRows { const bf16_t* A; const int32_t* gather; bf16_t* C; int ldw; };
+
 // One pass: TB token blocks (rows m0 .. of the expert's rows [rb, rb + Me)) by the 64 weight rows at W0, W1.
 template <int TB, bool GATEUP>
-__device__ __forceinline__ void wide_pass(const GemmArgs& a, unsigned char* ring, int rb, int Me, int m0, int mend, int n0,
-                                          int rot, const unsigned char* W0, const unsigned char* W1) {
+__device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, unsigned char* ring, int rb, int Me, int m0, int mend,
+                                          int n0, int rot, const unsigned char* W0, const unsigned char* W1) {
   constexpr int STAGE = (2 + TB) * 4096;   // 64 weight rows, then TB x 32 token rows, 128 bytes each
   constexpr int NS = WIDE_LDS / STAGE;     // 3, 2, 2
   constexpr int NI = (2 + TB) * 4;         // 1 KB copies per stage
   static_assert(NS >= 2 && (NS - 1) * NI < 64, "the wait counter holds 6 bits");
   const int lane = threadIdx.x & 63;
   const int N = a.N, Kdim = a.Kdim, nk = Kdim / 64;
-  const unsigned char* Ab = reinterpret_cast<const unsigned char*>(a.A);
+  const unsigned char* Ab = reinterpret_cast<const unsigned char*>(r.A);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
   // copies: lane -> row lane/8 of an 8-row group, slot lane%8 holding chunk slot xor row%8
   const int crow = lane >> 3, cchunk = (lane & 7) ^ crow;
   uint32_t coffW[4], coffX[TB * 4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) coffW[i] = (uint32_t)(i * 8 + crow) * (uint32_t)Kdim * 2u + (uint32_t)cchunk * 16u;
+  for (int i = 0; i < 4; ++i) coffW[i] = (uint32_t)(i * 8 + crow) * (uint32_t)r.ldw * 2u + (uint32_t)cchunk * 16u;
 #pragma unroll
   for (int i = 0; i < TB * 4; ++i) {
     const int m = min(m0 + i * 8 + crow, Me - 1);   // rows past the end repeat the last row
-    const int arow = a.gather ? a.gather[rb + m] / a.gather_div : rb + m;
+    const int arow = r.gather ? r.gather[rb + m] / a.gather_div : rb + m;
     coffX[i] = (uint32_t)arow * (uint32_t)Kdim * 2u + (uint32_t)cchunk * 16u;
   }
   const int r32 = lane & 31, half = lane >> 5, swz = lane & 7;
@@ -154,7 +157,7 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, unsigned char* ring
   for (int t = 0; t < TB; ++t) {
     const int m = m0 + t * 32 + r32;
     if (m < mend) {
-      bf16_t* out = a.C + (size_t)(rb + m) * N + n0;
+      bf16_t* out = r.C + (size_t)(rb + m) * N + n0;
 #pragma unroll
       for (int b = 0; b < (GATEUP ? 1 : 2); ++b) {
 #pragma unroll
@@ -176,13 +179,16 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, unsigned char* ring
   }
 }
 
-template <bool GATEUP>
+// SHARED: a.n_shared more weight sets of N by Kdim ride along, each applied to all a.shared_rows tokens (the block call that
+// hosts the shared experts); their items come first, for they have the most rows.
+template <bool GATEUP, bool SHARED>
 __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(GemmArgs a, int groups) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NPER = GATEUP ? 32 : 64;   // output columns of a wave
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nexp = a.hi - a.lo;
+  const int nsets = SHARED ? a.n_shared : 0;
+  const int nexp = nsets + a.hi - a.lo;
 
   // passes of the experts (four per lane) and their exclusive prefix
   int eid[4], rb[4], me[4], np[4], sum = 0;
@@ -190,8 +196,12 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
   for (int i = 0; i < 4; ++i) {
     const int e = lane * 4 + i;
     eid[i] = 0; rb[i] = 0; me[i] = 0; np[i] = 0;
-    if (e < nexp) {
-      eid[i] = a.ids ? a.ids[a.lo + e] : a.lo + e;
+    if (SHARED && e < nsets) {
+      eid[i] = -1 - e;
+      me[i] = a.shared_rows;
+      np[i] = (me[i] + WIDE_ROWS - 1) / WIDE_ROWS;
+    } else if (e < nexp) {
+      eid[i] = a.ids ? a.ids[a.lo + e - nsets] : a.lo + e - nsets;
       rb[i] = a.offsets[eid[i]];
       me[i] = a.offsets[eid[i] + 1] - rb[i];
       np[i] = (max(me[i], 0) + WIDE_ROWS - 1) / WIDE_ROWS;
@@ -218,7 +228,9 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
     const int next = base + lnp * groups;
     if (item >= next) { base = next; le = eid[i]; lrb = rb[i]; lme = me[i]; lnp = np[i]; }
   }
-  const int eg = __builtin_amdgcn_readlane(le, src);
+  const int id = __builtin_amdgcn_readlane(le, src);
+  const bool sh = SHARED && id < 0;
+  const int eg = sh ? -1 - id : id;     // the expert, or the number of the shared set
   const int erb = __builtin_amdgcn_readlane(lrb, src);
   const int Me = __builtin_amdgcn_readlane(lme, src);
   const int passes = __builtin_amdgcn_readlane(lnp, src);
@@ -236,28 +248,35 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
   // the walk over K starts at a step of its own (see expert_stream_lds.hip); it depends on the expert and the
   // column only, so results depend neither on the block cut nor on the passes
   const int rot = (int)(((unsigned)col * 3u + (unsigned)eg * 5u) % (unsigned)nk);
-  const unsigned char* W0 = reinterpret_cast<const unsigned char*>(a.B0 + ((size_t)eg * N + n0) * Kdim);
-  const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>(a.B1 + ((size_t)eg * N + n0) * Kdim)
-                                   : W0 + (size_t)32 * Kdim * 2;
+  WideRows r{a.A, a.gather, a.C, Kdim};
+  const bf16_t *B0 = a.B0 + (size_t)eg * N * Kdim, *B1 = GATEUP ? a.B1 + (size_t)eg * N * Kdim : nullptr;
+  if (sh) {    // gate/up: every set reads the tokens; down: its own hidden rows
+    r = WideRows{a.As + (GATEUP ? (size_t)0 : (size_t)eg * a.shared_rows * Kdim), nullptr, a.Cs + (size_t)eg * a.shared_rows * N, a.ldb_shared};
+    B0 = a.Bs0 + (size_t)eg * a.shared_b_step;
+    B1 = GATEUP ? a.Bs1 + (size_t)eg * a.shared_b_step : nullptr;
+  }
+  const unsigned char* W0 = reinterpret_cast<const unsigned char*>(B0 + (size_t)n0 * r.ldw);
+  const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>(B1 + (size_t)n0 * r.ldw) : W0 + (size_t)32 * r.ldw * 2;
   unsigned char* ring = smem + wave * WIDE_LDS;
   const int m0 = b0 * 32, mend = min(b1 * 32, Me);
   switch (b1 - b0) {
-    case 1: wide_pass<1, GATEUP>(a, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
-    case 2: wide_pass<2, GATEUP>(a, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
-    default: wide_pass<3, GATEUP>(a, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
+    case 1: wide_pass<1, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
+    case 2: wide_pass<2, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
+    default: wide_pass<3, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
   }
 }
 
-template <bool GATEUP>
+template <bool GATEUP, bool SHARED>
 int launch_wide(const GemmArgs& a, hipStream_t st) {
-  auto kern = expert_stream_wide_kernel<GATEUP>;
+  auto kern = expert_stream_wide_kernel<GATEUP, SHARED>;
   constexpr int lds = WIDE_WAVES * WIDE_LDS;
-  const int nexp = a.hi - a.lo;
-  if (a.offsets == nullptr || nexp > WIDE_EMAX || a.N % 64 != 0 || a.Kdim % 64 != 0) return -2;
+  const int nexp = a.hi - a.lo, nsets = SHARED ? a.n_shared : 0;
+  if (a.offsets == nullptr || nexp + nsets > WIDE_EMAX || a.N % 64 != 0 || a.Kdim % 64 != 0) return -2;
   const int per = WIDE_WAVES * (GATEUP ? 32 : 64);
   const int groups = (a.N + per - 1) / per;
   // an upper bound of the passes: every expert's last pass may be partial
-  const long passes = (long)a.rows_total / WIDE_ROWS + std::min((long)nexp, (long)a.rows_total);
+  const long passes = (long)a.rows_total / WIDE_ROWS + std::min((long)nexp, (long)a.rows_total) +
+                      (long)nsets * ((a.shared_rows + WIDE_ROWS - 1) / WIDE_ROWS);
   constexpr long runs = 8l * WIDE_RUN;
   const long grid = (passes * groups + runs - 1) / runs * runs;
   if (grid <= 0) return 0;
@@ -269,7 +288,11 @@ int launch_wide(const GemmArgs& a, hipStream_t st) {
 
 }  // namespace
 
-int launch_stream_wide_gateup(const GemmArgs& a, hipStream_t st) { return launch_wide<true>(a, st); }
-int launch_stream_wide_down(const GemmArgs& a, hipStream_t st) { return launch_wide<false>(a, st); }
+int launch_stream_wide_gateup(const GemmArgs& a, hipStream_t st) {
+  return a.n_shared > 0 ? launch_wide<true, true>(a, st) : launch_wide<true, false>(a, st);
+}
+int launch_stream_wide_down(const GemmArgs& a, hipStream_t st) {
+  return a.n_shared > 0 ? launch_wide<false, true>(a, st) : launch_wide<false, false>(a, st);
+}
 
 }  // namespace moe

@@ -112,6 +112,38 @@ def test_block_call_that_hosts_the_shared_experts_on_few_rows(moe, oracle64, T):
         check_close(f64(buf.S_parts[p]), S, f"shared expert {p}")
 
 
+# mean rows per expert and tokens at the lines between narrow, wide and separate launches: (64, 65 | 6 rows), (192, 193 | 32 rows)
+@pytest.mark.parametrize("T,E,K,n_sets", [(1, 12, 2, 3), (16, 12, 4, 1), (36, 12, 2, 3), (37, 12, 2, 3), (64, 12, 1, 8), (65, 12, 1, 8),
+                                          (96, 12, 2, 2), (97, 12, 2, 2), (192, 12, 2, 3), (193, 12, 2, 3), (200, 15, 1, 3), (410, 60, 4, 2)])
+@pytest.mark.parametrize("H,I", [(128, 64), (192, 320)])
+def test_block_call_that_hosts_the_shared_experts_in_every_launch_form(moe, oracle64, T, E, K, n_sets, H, I):
+    print(f"[case] hosted shared experts T={T} E={E} K={K} sets={n_sets} H={H} I={I}", flush=True)
+    Is = n_sets * I
+    w = workloads.layer_weights(H, E, I, Is, 31 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
+    d, xg = {k: v.cuda() for k, v in w.items()}, x.cuda()
+    assert moe.moe_fused_shared_sets(T, H, E, K, I, Is) == n_sets
+    ids, _ = moe.moe_route(xg, d["Wr"], None, K, False)
+    off, src, rowp, _ = moe.moe_permute(ids, xg, E, materialize=False)
+    buf = moe.LayerBuffers.allocate(T, H, E, K, I, Is)
+    Y = torch.full_like(buf.Yp, 768.0)
+    lo, hi = 1, E - 1       # a block that is not the whole layer
+    moe.moe_expert_group_forward_gather(lo, hi, xg, src, K, off, d["Wg"], d["Wu"], d["Wd"], Y, buf.workspace)
+    buf.Yp.fill_(768.0)
+    buf.S_parts.fill_(768.0)
+    moe.moe_expert_group_forward_fused(lo, hi, xg, src, K, off, d["Wg"], d["Wu"], d["Wd"], d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"], buf.Yp,
+                                       buf.S_parts, buf.sg, buf.workspace_fused)
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(torch.int16), buf.Yp.view(torch.int16))
+    f32 = {k: v.float().numpy() for k, v in w.items()}
+    for p in range(n_sets):
+        sl = slice(p * I, (p + 1) * I)
+        S, sg = oracle64.shared_forward(x.float().numpy(), f32["Wsg"][sl], f32["Wsu"][sl], np.ascontiguousarray(f32["Wsd"][:, sl]),
+                                        f32["wgate"])
+        check_close(f64(buf.S_parts[p]), S, f"shared expert {p}")
+    assert np.allclose(buf.sg.cpu().numpy(), sg, rtol=1e-4, atol=1e-5)
+
+
 @pytest.mark.parametrize("T,H,Is", [(777, 2048, 5632), (600, 64, 1536), (513, 256, 1024), (640, 1024, 256), (700, 1536, 768), (1000, 128, 640),
                                           (129, 512, 1024), (300, 2048, 512), (1100, 3072, 128)])
 def test_shared_expert_with_the_down_projection_cut_along_k(moe, oracle64, T, H, Is):
