@@ -104,6 +104,12 @@ int ffn_forward(const GemmArgs& gu, const GemmArgs& dn, const Plan& p, hipStream
   return rc;
 }
 
+void set_shared_parts(GemmArgs& dn, int parts, int Is) {
+  dn.shared_parts = parts;
+  dn.part_steps = Is / 64 / parts;
+  dn.part_extra = Is / 64 % parts;
+}
+
 // The shared expert riding along with the routed experts of a few tokens (see expert_stream_lds.hip): `sets` sets of I
 // columns of its hidden layer h [T,Is], and its output as `parts` fp32 parts [T,H].
 struct Riders { const void *x, *Wsg, *Wsu, *Wsd; void* h; float* part; int sets, parts, T, Is; };
@@ -133,7 +139,8 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   dn.N = H; dn.Kdim = I;
   if (riders != nullptr) {
     gu.n_shared = riders->sets;
-    dn.n_shared = dn.shared_parts = riders->parts;
+    dn.n_shared = riders->parts;
+    set_shared_parts(dn, riders->parts, riders->Is);
     gu.shared_rows = dn.shared_rows = riders->T;
     gu.ldb_shared = dn.ldb_shared = riders->Is;
     gu.As = (const bf16_t*)riders->x; gu.Bs0 = (const bf16_t*)riders->Wsg; gu.Bs1 = (const bf16_t*)riders->Wsu;
@@ -353,7 +360,7 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
     gu.rows_total = dn.rows_total = P;
     gu.Cs = (bf16_t*)workspace + (size_t)P * I;
     dn.As = gu.Cs;
-    dn.shared_parts = ns;
+    set_shared_parts(dn, ns, Is);
     if (narrow) gu.ldb_shared = Is;
     rc = ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
   } else if (plan.stream) {
@@ -424,7 +431,7 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
     plan.stream = true;
     gu.n_shared = 1;
     dn.n_shared = few_parts;
-    dn.shared_parts = shared_few_parts(Is);
+    set_shared_parts(dn, shared_few_parts(Is), Is);
     gu.shared_rows = dn.shared_rows = T;
     gu.ldb_shared = dn.ldb_shared = Is;
     gu.As = gu.A; gu.Bs0 = gu.B0; gu.Bs1 = gu.B1; gu.Cs = gu.C;

@@ -94,7 +94,7 @@ struct GemmArgs {
   int Kdim;            // contraction length
   float* Cpart;        // room for the fp32 partial outputs [parts, rows_total, N] of kernels that cut K, else unused
   int parts_max;       // most parts the sizes call for (0 and 1: no cut); the number, and with it the result, does not depend
-  int parts_room;      // on the parts that Cpart has room for: without it they are formed in turn
+                       // on the parts that Cpart has room for (parts_room)
   const int32_t* gather;   // nullptr: row r of A is A[r]; else row r of A is A[gather[r] / gather_div]
   int gather_div;          // (the token rows themselves, addressed through src_of_row: no permuted copy)
   int leave_room;          // 1: no tile shape that takes a whole CU (all registers of every SIMD): kernels of
@@ -104,7 +104,6 @@ struct GemmArgs {
   // n_shared more weight sets, each applied to all shared_rows tokens.  In the row space of A and C
   // the routed rows are [0, rows_routed) and set s owns rows rows_routed + s*shared_rows onwards.
   int n_shared;
-  int shared_parts;        // (streaming kernel, down) K parts of the shared contraction
   int shared_rows;         // tokens T
   int rows_routed;         // P
   const bf16_t* Bs0;       // weights of set 0 (gate branch, or the down projection); set s starts s*shared_b_step
@@ -118,6 +117,10 @@ struct GemmArgs {
   // ticks it spent inside the K loops of its tiles, and the number of its tiles.
   long long* clocks;
   int clock_groups;
+  int parts_room;          // parts that Cpart has room for; more of them are formed in turn
+  int shared_parts;        // (streaming kernel, down) K parts of the shared contraction, of part_steps steps of 64 each,
+  int part_steps;          // the first part_extra of them one more
+  int part_extra;
 };
 // Raises a kernel's dynamic LDS limit once per device: one bit per device id in `done` (the kernel's own),
 // set after the call has succeeded there (two threads may both make the call; it is idempotent).

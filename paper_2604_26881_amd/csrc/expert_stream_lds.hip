@@ -220,9 +220,8 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
     f32x4 sum0[MT], sum1[MT];   // (CUT: of the parts before)
     for (int part = part0; part < part1; ++part) {
       if (CUT && sh) {
-        const int steps = Kdim / 64, begin = steps * part / a.shared_parts;
-        nk = steps * (part + 1) / a.shared_parts - begin;
-        kofs = (size_t)begin * 128;
+        nk = a.part_steps + (part < a.part_extra ? 1 : 0);
+        kofs = (size_t)(part * a.part_steps + min(part, a.part_extra)) * 128;
         rot = start(blockIdx.x, (unsigned)part);
       }
 #pragma unroll
