@@ -13,7 +13,6 @@
 //   with the same ballots, and has row = offsets[e] + earlier[e] + rank.  It writes row_of_pair and
 //   src_of_row and copies the 64 token rows with 16-byte loads and stores.  The table is P/64 x E
 //   ints (61 KB at 16 384 pairs), read from L2 by every workgroup.
-#include <algorithm>
 #include "common.h"
 
 namespace moe {
@@ -218,6 +217,7 @@ __global__ __launch_bounds__(PERM_SMALL_MAX) void permute_small_kernel(const int
 // 10.5 -> 8.4, 8000 pairs 9.9 -> 9.3 | 14.8 -> 16.8 (every workgroup reads every id: that is where the table wins).
 constexpr int PERM_ONE_MAX = 4096;
 constexpr int PERM_ONE_WAVES = 16;
+constexpr int PERM_ONE_SPLIT = 4;   // workgroups that copy the rows of one chunk: one row per wave
 __global__ __launch_bounds__(64 * PERM_ONE_WAVES) void permute_one_kernel(const int32_t* __restrict__ ids,
                                                                           const bf16_t* __restrict__ x, int P, int E, int K,
                                                                           int H, int split, int32_t* __restrict__ offsets,
@@ -228,10 +228,11 @@ __global__ __launch_bounds__(64 * PERM_ONE_WAVES) void permute_one_kernel(const 
   __shared__ int s_total[PERM_EMAX];       // pairs of expert e
   __shared__ int s_base[PERM_EMAX];        // those in earlier chunks; then: first row of expert e for this chunk
   __shared__ int s_row[64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = (int)(blockDim.x >> 6);
+  constexpr int nwaves = PERM_ONE_WAVES;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = blockIdx.x / split, part = blockIdx.x % split;
   const int chunks = (P + 63) / 64, nbits = bits_for(E);
-  for (int i = tid; i < PERM_EMAX; i += blockDim.x) s_total[i] = s_base[i] = 0;
+  for (int i = tid; i < PERM_EMAX; i += 64 * nwaves) s_total[i] = s_base[i] = 0;
   const int own = c * 64 + lane < P ? min(max(ids[c * 64 + lane], 0), E - 1) : -1;   // (used by wave 0)
   __syncthreads();
   for (int c0 = wave; c0 < chunks; c0 += AHEAD * nwaves) {
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(64 * PERM_ONE_WAVES) void permute_one_kernel(const 
       base += v[i];
     }
     if (blockIdx.x == 0 && lane == 63) offsets[E] = incl;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the bases are written before other lanes read them
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the bases are written before other lanes read them
     const unsigned long long match = match_expert(max(own, 0), own >= 0, nbits);
     int row = -1;
     if (own >= 0) {
@@ -319,11 +320,9 @@ int launch_permute(const int32_t* ids, const void* x, int T, int H, int E, int K
     return hipGetLastError() == hipSuccess ? 0 : -4;
   }
   if (P <= PERM_ONE_MAX) {
-    const int chunks = (P + 63) / 64;
-    const int waves = std::min(PERM_ONE_WAVES, Xp == nullptr ? chunks : PERM_ONE_WAVES);
-    const int split = Xp == nullptr ? 1 : std::max(1, std::min(4, 512 / chunks));   // four rows of Xp per wave at least
-    hipLaunchKernelGGL(permute_one_kernel, dim3(chunks * split), dim3(64 * waves), 0, st, ids, (const bf16_t*)x, P, E, K, H,
-                       split, offsets, src_of_row, row_of_pair, (bf16_t*)Xp);
+    const int split = Xp == nullptr ? 1 : PERM_ONE_SPLIT;
+    hipLaunchKernelGGL(permute_one_kernel, dim3((P + 63) / 64 * split), dim3(64 * PERM_ONE_WAVES), 0, st, ids, (const bf16_t*)x, P, E, K,
+                       H, split, offsets, src_of_row, row_of_pair, (bf16_t*)Xp);
     return hipGetLastError() == hipSuccess ? 0 : -4;
   }
   int32_t* hist = static_cast<int32_t*>(workspace);
