@@ -255,12 +255,25 @@ def test_few_expert_layers_pick_tiles_from_the_whole_layer(moe, oracle64, counts
     assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16))
 
 
+def record_one_calls(monkeypatch):
+    """Whether each layer from here on ran as one native call (a sequence that fell back to its steps would pass every
+    comparison with them)."""
+    from paper_2604_26881_amd import binding
+    inner, served = binding._layer_in_one_call, []
+
+    def recorded(*args, **kw):
+        served.append(inner(*args, **kw))
+        return served[-1]
+    monkeypatch.setattr(binding, "_layer_in_one_call", recorded)
+    return served
+
+
 @pytest.mark.parametrize("T", [1, 3, 16, 17, 31, 32, 33])
 # sets of I columns of the shared expert: narrower than one, whole, a ragged last one, more than can ride along, none
 @pytest.mark.parametrize("H,E,K,I,Is", [(64, 8, 2, 192, 128), (192, 60, 4, 64, 256), (320, 16, 2, 192, 448), (128, 12, 2, 64, 576),
                                         (64, 8, 1, 64, 0)])
 @pytest.mark.parametrize("gather,segments", [(False, False), (True, True)])
-def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, gather, segments):
+def test_layer_in_one_call_equals_its_steps(moe, oracle64, monkeypatch, T, H, E, K, I, Is, gather, segments):
     print(f"[case] layer in one call T={T} H={H} E={E} K={K} I={I} Is={Is} gather={gather} segments={segments}", flush=True)
     w = workloads.layer_weights(H, E, I, Is, 11 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
     g = torch.Generator().manual_seed(T * 5 + E)
@@ -272,8 +285,10 @@ def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, ga
     seg = moe.segment_offsets(cut, T, "cuda") if segments else None
     run = lambda groups: moe.moe_layer_forward(x.cuda(), d["Wr"], bias.cuda(), d["Wg"], d["Wu"], d["Wd"], shared, K, True,
                                                groups=groups, tenant_rows=cut, fused_gather=gather, seg_offsets=seg)
+    served = record_one_calls(monkeypatch)
     one, steps = run(None), run([(0, 1), (1, E)])       # two blocks take the step-by-step sequence
     torch.cuda.synchronize()
+    assert served == [True, False]
     for name in ("topk_ids", "topk_w", "expert_offsets", "src_of_row", "row_of_pair", "Yp") + (() if gather else ("Xp",)):
         a, b = getattr(one, name), getattr(steps, name)
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
@@ -289,17 +304,19 @@ def test_layer_in_one_call_equals_its_steps(moe, oracle64, T, H, E, K, I, Is, ga
 # K parts of 20 and 21 steps; three; one; four of 22; one, and more sets than can ride along
 @pytest.mark.parametrize("H,E,K,I,Is", [(512, 12, 2, 384, 2624), (256, 60, 4, 576, 3904), (128, 16, 2, 64, 448), (192, 20, 2, 1408, 5632),
                                         (320, 16, 1, 64, 1024)])
-def test_output_is_bitwise_independent_of_blocks_streams_and_sequence(moe, oracle64, T, H, E, K, I, Is):
+def test_output_is_bitwise_independent_of_blocks_streams_and_sequence(moe, oracle64, monkeypatch, T, H, E, K, I, Is):
     print(f"[case] few tokens in every sequence T={T} H={H} E={E} K={K} I={I} Is={Is}", flush=True)
     w = workloads.layer_weights(H, E, I, Is, 21 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
     x = torch.randn((T, H), generator=torch.Generator().manual_seed(T * 3 + E)).to(torch.bfloat16)
     d, xg = {k: v.cuda() for k, v in w.items()}, x.cuda()
     run = lambda **kw: moe.moe_layer_forward(xg, d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"]), K,
                                              False, **kw)
+    served = record_one_calls(monkeypatch)
     bufs = {"one block": run(), "gathered": run(fused_gather=True), "two blocks": run(groups=[(0, 5), (5, E)]),
             "a block per expert": run(groups=[(e, e + 1) for e in range(E)]), "two streams": run(shared_stream=torch.cuda.Stream()),
             "blocks and streams": run(groups=[(0, 1), (1, E)], shared_stream=torch.cuda.Stream())}
     torch.cuda.synchronize()
+    assert served[:3] == [True, True, False]
     one = bufs["one block"]
     f32 = {k: v.float().numpy() for k, v in w.items()}
     S_ref, sg_ref = oracle64.shared_forward(x.float().numpy(), f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
@@ -418,14 +435,18 @@ def test_capture_with_a_second_stream_at_few_tokens(moe, T):
 
 
 @pytest.mark.parametrize("T,H,E,K,I,Is", [(1, 64, 8, 2, 64, 0), (33, 2112, 8, 2, 64, 128), (520, 128, 8, 2, 64, 192), (700, 64, 4, 1, 64, 0),
-                                          (5, 8192, 4, 1, 64, 0)])
-def test_residual_step_from_the_aggregation_has_the_bits_of_its_own_call(moe, T, H, E, K, I, Is):
-    # 520 tokens and 33 form the gate logit in the aggregation or beside the sum of the K parts; the layers run in place
+                                          (5, 8192, 4, 1, 64, 0), (1, 320, 16, 2, 384, 2624), (16, 192, 12, 2, 256, 1088),
+                                          (32, 128, 20, 2, 64, 448)])
+def test_residual_step_from_the_aggregation_has_the_bits_of_its_own_call(moe, monkeypatch, T, H, E, K, I, Is):
+    # 520 tokens and 33 form the gate logit in the aggregation or beside the sum of the K parts; up to 32 tokens the shared
+    # expert rides along and the aggregation adds its parts as well; the layers run in place
     print(f"[case] stack against its steps T={T} H={H} E={E} Is={Is}", flush=True)
     layers = [{k: None if v is None else v.cuda() for k, v in
                workloads.layer_weights(H, E, I, Is, 5 + i, 0.05, 0.1, torch.bfloat16, device="cpu").items()} for i in range(3)]
     x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+    served = record_one_calls(monkeypatch)
     out = moe.moe_stack_forward(x, layers, K, False, eps=1e-5)
+    assert served == [True] * 3
     cur = x
     for w in layers:
         shared = None if Is == 0 else (w["Wsg"], w["Wsu"], w["Wsd"], w["wgate"])
