@@ -536,7 +536,7 @@ def run_layer_workload(args, moe, cpu_baseline: bool):
     # fraction of the bf16 MFMA peak); at decode sizes the same kernels stream weights (HBM).
     # Both figures of every kernel are in "kernels".
     # (the library's own switch to the weight-streaming kernels, or the caller's choice of them)
-    streaming = (args.policy & 0xff) == 9 or ((args.policy & 0xff) == 0 and -(-P // s.E) <= 32)
+    streaming = (args.policy & 0xff) == 9 or ((args.policy & 0xff) == 0 and s.E > 1 and -(-P // s.E) <= 32)
     if streaming:
         achieved = alg_bytes[dom] / launches / dur_s / 1e9
         roof = {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
