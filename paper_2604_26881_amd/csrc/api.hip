@@ -20,19 +20,9 @@ bool apart(const void* a, size_t na, const void* b, size_t nb) {
 
 bool dims_ok(int H) { return H > 0 && H % 64 == 0; }
 
-// Which kernels serve an FFN with `mean_rows` expected rows per expert.  The choice uses only
-// layer-wide sizes (never the block bounds), so a row's result does not depend on the block cut.
-// policy: 0 = automatic; 3 and 5 = MFMA tiles of 128 token rows by 256 weight rows; 4 = 256 by 256;
-//         8 = 128 by 64, the down projection cut along K (few rows in all, one weight set);
-//         9 = weight streaming through wave-private LDS rings (few rows per expert);
-//         10 = 128 by 128; 11 = 160 by 256.  Any other number is refused.
-// Bits 8 and 9 of the policy word restrict a call to one of its two kernels (0x100: gate/up
-// only, 0x200: down projection only), so that each can be timed on its own.  Bit 10 (0x400, shared
-// expert with automatic shapes): its first kernel takes no tile shape that fills a CU completely,
-// so that small kernels of other streams (gating, micro-batch construction) run beside it.
 // Shared expert: most parts of its down projection along K, for which the workspace helper reports room: 8 up to 512
 // tokens, beyond that as many (a power of two) as it takes 128x128 tiles to 256 items, one round of the chip (the compute
-// units of the MI355X: the helper answers without a device, and the sums must not depend on one).
+// units of the MI355X: the helper answers without a device).
 constexpr int SHARED_SMALL_T = 512;
 constexpr int SHARED_KPARTS_MAX = 8;
 int shared_parts_room(int T, int H) {
@@ -46,7 +36,7 @@ int shared_parts_room(int T, int H) {
 // Tokens up to which the streaming kernel serves the shared expert, riding along with the routed ones or by itself, and
 // the K parts of its down projection there: up to four of eight K steps and more, then parts of 22.  (A layer of H 2048,
 // Is 5632: four parts, with eight it takes about 2 us more at 1 to 24 tokens; 12 experts of H 1024 and Is 1536 at 24
-// tokens: 33 us in two parts, 38 in one.)  Both depend on the shared expert's own sizes alone: its bits are the same in
+// tokens: 32 us in three parts, 38 in one.)  Both depend on the shared expert's own sizes alone: its bits are the same in
 // every sequence of calls.  (More figures beside that kernel.)
 constexpr int SHARED_FEW_T = 32;
 int shared_few_parts(int Is) { return std::max({1, std::min(4, Is / 512), std::min(SHARED_KPARTS_MAX, Is / 1408)}); }
@@ -56,10 +46,21 @@ int shared_few_parts(int Is) { return std::max({1, std::min(4, Is / 512), std::m
 // these sizes were streamed (all in tiles): 12 experts of H 1024, I 768, Is 1536 at 20 tokens, top 4 36 | 56 | 44, at 36,
 // top 2 34 | 50 | 44, at 150 43 | 63 | 51; 15 of H 2048, I 512, Is 2048, top 1 at 60 tokens 52 | 60 | 65, at 90 (narrow)
 // 62 | 61 | 68; 8 of H 2560, I and Is 4096, top 1 at 200 (wide, three passes) 165 | 158 | 183.  What stays slower than all
-// in tiles are 27 to 32 rows per expert of more tokens (60 experts of H 2048 at T = 470 284 | 274, 15 at 400 78 | 71), for
-// the routed rows must keep the bits of the plain call, which is faster there than in tiles (285 | 307, 78 | 110).
+// in tiles: 27 to 32 rows per expert with more tokens than that (60 experts of H 2048 at T = 470 284 against 274, 15 at 400
+// 78 against 71), for the routed rows must keep the bits of the plain block call, whose layer is the faster one for it
+// (284 against 307, 78 against 110).
 constexpr int FUSED_NARROW_T = 64, FUSED_WIDE_T = 192;
 
+// Which kernels serve an FFN with `mean_rows` expected rows per expert.  The choice uses only
+// layer-wide sizes (never the block bounds), so a row's result does not depend on the block cut.
+// policy: 0 = automatic; 3 and 5 = MFMA tiles of 128 token rows by 256 weight rows; 4 = 256 by 256;
+//         8 = 128 by 64, the down projection cut along K (few rows in all, one weight set);
+//         9 = weight streaming through wave-private LDS rings (few rows per expert);
+//         10 = 128 by 128; 11 = 160 by 256.  Any other number is refused.
+// Bits 8 and 9 of the policy word restrict a call to one of its two kernels (0x100: gate/up
+// only, 0x200: down projection only), so that each can be timed on its own.  Bit 10 (0x400, shared
+// expert with automatic shapes): its first kernel takes no tile shape that keeps small kernels of
+// other streams (gating, micro-batch construction) off the CUs (pick_tile_shape says which).
 struct Plan { bool valid; bool stream; int tile_rows; bool do_gateup; bool do_down; };
 Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
   Plan p{};

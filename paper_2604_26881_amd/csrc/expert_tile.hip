@@ -664,7 +664,7 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
       const double items = (double)((rows + k.bm - 1) / k.bm) * (double)((N + k.nout - 1) / k.nout) * parts;
       const double rounds = (double)(long)((items + cus - 1) / cus);
       // 160x256 leaves registers but no LDS beside it: the small kernels of the other stream wait for it, which a launch of
-      // many rounds must not make them (16 384 tokens: the row sort waited 750 us behind it; layer 2417 us, start 2397)
+      // many rounds must not make them (16 384 tokens: the row sort waited 750 us behind it; layer 2417 us, without 2362)
       if (k.code == 160 && leave_room && rounds > 2.0) continue;
       double cost = rounds * k.bm * k.nout * ((double)Kdim / parts) * k.c;
       if (parts > 1) cost += (5.0 + (double)rows * N * parts * 8.0 / 5.0e6) * units_per_us;
