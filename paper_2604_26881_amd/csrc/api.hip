@@ -410,13 +410,16 @@ static int shared_forward_impl(const void* x, const void* Wsg, const void* Wsu, 
   // K parts of the down projection: as many as the sizes call for.  The 128x64 shape asked for by the caller and batches up
   // to 512 tokens must bring room for them; otherwise parts without room are formed in turn, to the same bits.
   const size_t one_part = (size_t)T * (size_t)H * 4;
-  const int room = (int)std::min<size_t>(SHARED_KPARTS_MAX, workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0);
+  int room = (int)std::min<size_t>(SHARED_KPARTS_MAX, workspace_bytes > h_bytes ? (workspace_bytes - h_bytes) / one_part : 0);
   int parts_max = 0;
   if (!plan.stream && (plan.tile_rows == 64 || plan.tile_rows == 0) && tile_down_ksplit(Is) > 1) {
     const bool must = plan.tile_rows == 64 || T <= SHARED_SMALL_T;
     parts_max = must ? tile_down_ksplit(Is) : shared_parts_room(T, H);
     if (must && room < parts_max) return MOE_ERR_WORKSPACE;
   }
+  // (memory behind h that holds the tokens or the output is no room)
+  const void* const behind = static_cast<const unsigned char*>(workspace) + h_bytes;
+  if (!apart(S, one_part / 2, behind, room * one_part) || !apart(x, one_part / 2, behind, room * one_part)) room = 0;
   const int few_parts = few && room >= shared_few_parts(Is) ? shared_few_parts(Is) : 1;   // (1: formed in turn)
   const bool side_by_side = few ? few_parts > 1 : room > 1 && parts_max > 1;
   float* part = side_by_side ? reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + h_bytes) : nullptr;
@@ -525,7 +528,8 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                     (!copied || apart(riding, riding_bytes, Xp, (size_t)P * (size_t)H * 2)) &&
                     apart(riding, riding_bytes, src_of_row, pairs) &&
                     apart(riding, riding_bytes, expert_offsets, ((size_t)E + 1) * 4) &&
-                    apart(riding, riding_bytes, sg, (size_t)T * 4) && apart(riding, riding_bytes, out, x_bytes) &&
+                    apart(riding, riding_bytes, sg, (size_t)T * 4) && apart(riding, riding_bytes, S, x_bytes) &&
+                    apart(riding, riding_bytes, x, x_bytes) && apart(riding, riding_bytes, out, x_bytes) &&
                     apart(riding, riding_bytes, next, next ? x_bytes : 0);
   Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, parts, T, Is};
   if (ride) riders.part = reinterpret_cast<float*>(static_cast<unsigned char*>(shared_workspace) + h_bytes);

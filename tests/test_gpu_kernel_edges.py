@@ -338,15 +338,16 @@ def test_output_is_bitwise_independent_of_blocks_streams_and_sequence(moe, oracl
 
 
 @pytest.mark.parametrize("T", [1, 13, 16, 17, 32, 33])
-@pytest.mark.parametrize("shared_memory", ["workspaces", "Xp", "out", "src_of_row"])
+@pytest.mark.parametrize("shared_memory", ["workspaces", "Xp", "out", "src_of_row", "S", "x"])
 def test_layer_in_one_call_with_memory_shared_between_its_steps(moe, oracle64, T, shared_memory):
     # One buffer as every workspace; or the shared expert's scratch in memory of a step that is over by then (the row
-    # copies, the index list) or not yet begun (the output): right when the steps run in turn, so right in one call too.
+    # copies, the index list) or not yet begun (the output), or S or the tokens behind the hidden rows, in room that this K is
+    # not cut for (17 steps): right when the steps run in turn, so right in one call too.
     H, E, K, I, Is = 192, 8, 1, 256, 1088
     print(f"[case] layer in one call, shared memory: {shared_memory}, T={T}", flush=True)
     w = workloads.layer_weights(H, E, I, Is, 70 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
     x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16)
-    d = {k: v.cuda() for k, v in w.items()}
+    d, xg = {k: v.cuda() for k, v in w.items()}, x.cuda()
     f32 = {k: v.float().numpy() for k, v in w.items()}
     buf = moe.LayerBuffers.allocate(T, H, E, K, I, Is)
     need = moe.moe_workspace_bytes(T, H, E, K, I, Is)
@@ -355,11 +356,17 @@ def test_layer_in_one_call_with_memory_shared_between_its_steps(moe, oracle64, T
     else:
         whole = torch.empty(need, dtype=torch.uint8, device="cuda")
         buf.workspace_shared = whole
-        old = getattr(buf, shared_memory)
-        room = whole[:old.numel() * old.element_size()]
+        old = xg if shared_memory == "x" else getattr(buf, shared_memory)
+        at = (T * Is * 2 + 255) // 256 * 256 if shared_memory in ("S", "x") else 0
+        room = whole[at:at + old.numel() * old.element_size()]
         assert room.numel() == old.numel() * old.element_size()
-        setattr(buf, shared_memory, room.view(old.dtype).view(old.shape))
-    moe.moe_layer_forward(x.cuda(), d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"]), K, False,
+        new = room.view(old.dtype).view(old.shape)
+        if shared_memory == "x":
+            new.copy_(xg)
+            xg = new
+        else:
+            setattr(buf, shared_memory, new)
+    moe.moe_layer_forward(xg, d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"]), K, False,
                           buf=buf, fused_gather=shared_memory in ("workspaces", "src_of_row"))
     torch.cuda.synchronize()
     ref = oracle64.layer(x.float().numpy(), f32["Wr"], None, f32["Wg"], f32["Wu"], f32["Wd"],
