@@ -354,8 +354,8 @@ int moe_expert_group_forward_fused(int group_lo, int group_hi, const void* x, co
   dn.Bs0 = (const bf16_t*)Wsd; dn.shared_b_step = I; dn.ldb_shared = Is;   // set s: columns [s*I, (s+1)*I) of Wsd [H,Is]
   dn.Cs = (bf16_t*)S_parts;
   int rc = 0, parts;
-  const bool narrow = mean_rows <= STREAM_FEW_ROWS;
-  if (plan.stream && T <= (narrow ? FUSED_NARROW_T : FUSED_WIDE_T)) {
+  const bool narrow = stream_narrow(mean_rows, H);     // (of gate/up; the down projection must be served alike)
+  if (plan.stream && narrow == stream_narrow(mean_rows, I) && T <= (narrow ? FUSED_NARROW_T : FUSED_WIDE_T)) {
     // few rows per routed expert: the streaming kernels, whose launches take the shared sets along (the hidden rows of the
     // sets lie behind the routed ones: as one [T,Is] for the narrow kernel, as a [T,I] per set for the wide one)
     gu.rows_total = dn.rows_total = P;

@@ -294,14 +294,14 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
 // workgroups per CU.  Larger experts go to the wide kernels: from a mean of 6 rows on, where both read the
 // weights at the same rate when the batch is even (8.5 rows: 116 + 62 here, 118 + 60 us there) and a hot
 // expert of 127 rows, eight passes here and two there, makes 137 + 70 of it here and 122 + 65 us there.
-// One weight set (the shared expert) stays here, with two tiles per pass beyond 16 rows: gate/up + down at 32 rows of
-// H 2048, Is 5632 12 + 24 us, with one tile 20 + 42.
+// One weight set (the shared expert) stays here, with two tiles per pass beyond 16 rows (gate/up + down at 32 rows of
+// H 2048, Is 5632 12 + 24 us, with one tile 20 + 42), and so do short contractions, with two beyond a mean of 10.
 template <bool GATEUP>
 static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.N % 32 != 0 || a.Kdim % 64 != 0) return -2;
-  if (a.offsets != nullptr && a.mean_rows > STREAM_FEW_ROWS)
+  if (a.offsets != nullptr && !stream_narrow(a.mean_rows, a.Kdim))
     return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
-  const bool two = a.offsets == nullptr && (a.n_shared > 0 ? a.shared_rows : a.rows_fixed) > 16;
+  const bool two = a.offsets != nullptr ? a.mean_rows > 10 : (a.n_shared > 0 ? a.shared_rows : a.rows_fixed) > 16;
   if (a.n_shared > 0) return two ? launch_stream_lds_t<2, GATEUP, 4, true>(a, st) : launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
   return two ? launch_stream_lds_t<2, GATEUP, 4, false>(a, st) : launch_stream_lds_t<1, GATEUP, 4, false>(a, st);
 }

@@ -10,6 +10,7 @@
 // Every staged byte is then read from LDS exactly once, the copies of token rows (which come from L2 and
 // share its path to LDS with the weights) are at most 1.5 times those of the weights, and an expert takes one
 // pass over its weights up to 96 rows.
+// (That is the coarse form; launches of few waves take 32 weight rows per wave, see launch_wide_any.)
 //
 // Work decomposition.  A pass is up to 96 rows of one expert; an item is one pass by 128 weight rows, one
 // workgroup of two waves that share nothing but the item.  The number of passes depends on expert_offsets:
@@ -36,11 +37,13 @@ namespace moe {
 namespace {
 
 constexpr int WIDE_EMAX = 256;      // experts of a block: four per lane
-constexpr int WIDE_LDS = 40 * 1024; // ring of one wave: four waves fill the 160 KB of a CU
-constexpr int WIDE_TB = 3;          // token blocks of 32 rows per pass; a stage of three is 20 KB: two in the ring
-constexpr int WIDE_ROWS = 32 * WIDE_TB;
-constexpr int WIDE_WAVES = 2;       // waves (column blocks) per workgroup; 1 and 4 measured the same within 3 %, but four
-                                    // leave the chip half empty on 8 experts of H 4096 (down 76 -> 107 us)
+// A wave's weight rows and its ring (the choice: launch_wide_any).  COARSE: 64 rows, 40 KB: four waves fill the 160 KB of a
+// CU.  FINE: 32 rows in the same ring.  FINEST: 32 rows in 24 KB: six waves fill a CU.
+enum WideForm { COARSE, FINE, FINEST };
+constexpr int wide_blocks(WideForm f) { return f == COARSE ? 2 : 1; }          // of 32 weight rows
+constexpr int wide_ring(WideForm f) { return (f == FINEST ? 24 : 40) * 1024; }
+constexpr int wide_rows(WideForm f) { return f == FINEST ? 64 : 96; }          // token rows per pass: two stages of them fit the ring
+constexpr int wide_waves(WideForm f) { return f == COARSE ? 2 : 1; }           // waves (column blocks) per workgroup
 constexpr int WIDE_RUN = 8;         // consecutive items of one XCD (4 ... 64 measured the same within 2 %)
 
 template <int J, int NS, int NI, class F>
@@ -55,13 +58,17 @@ __device__ __forceinline__ void drain(F&& step) {
 // Where the rows of a pass come from and go: token rows A (through gather, if any), output C, elements between weight rows.
 struct WideRows { const bf16_t* A; const int32_t* gather; bf16_t* C; int ldw; };
 
-// One pass: TB token blocks (rows m0 .. of the expert's rows [rb, rb + Me)) by the 64 weight rows at W0, W1.
-template <int TB, bool GATEUP>
+// One pass: TB token blocks (rows m0 .. of the expert's rows [rb, rb + Me)) by the weight rows at W0, W1: WB = 2: 32 at each;
+// WB = 1: 16 at each (gate/up: the gate rows, then the up rows, in one MFMA block).  A product does not depend on its
+// place in a block, so both give the same bits.
+template <WideForm FORM, int TB, bool GATEUP>
 __device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, unsigned char* ring, int rb, int Me, int m0, int mend,
                                           int n0, int rot, const unsigned char* W0, const unsigned char* W1) {
-  constexpr int STAGE = (2 + TB) * 4096;   // 64 weight rows, then TB x 32 token rows, 128 bytes each
-  constexpr int NS = WIDE_LDS / STAGE;     // 3, 2, 2
-  constexpr int NI = (2 + TB) * 4;         // 1 KB copies per stage
+  constexpr int WB = wide_blocks(FORM);
+  constexpr int STAGE = (WB + TB) * 4096;  // 32 * WB weight rows, then TB x 32 token rows, 128 bytes each
+  constexpr int NS = wide_ring(FORM) / STAGE;   // COARSE 3, 2, 2; FINE 5, 3, 2; FINEST 3, 2
+  constexpr int NI = (WB + TB) * 4;        // 1 KB copies per stage
+  constexpr int NW0 = 2 * WB;              // of which the first are the rows at W0, as many those at W1
   static_assert(NS >= 2 && (NS - 1) * NI < 64, "the wait counter holds 6 bits");
   const int lane = threadIdx.x & 63;
   const int N = a.N, Kdim = a.Kdim, nk = Kdim / 64;
@@ -69,9 +76,9 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, 
   const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
   // copies: lane -> row lane/8 of an 8-row group, slot lane%8 holding chunk slot xor row%8
   const int crow = lane >> 3, cchunk = (lane & 7) ^ crow;
-  uint32_t coffW[4], coffX[TB * 4];
+  uint32_t coffW[NW0], coffX[TB * 4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) coffW[i] = (uint32_t)(i * 8 + crow) * (uint32_t)r.ldw * 2u + (uint32_t)cchunk * 16u;
+  for (int i = 0; i < NW0; ++i) coffW[i] = (uint32_t)(i * 8 + crow) * (uint32_t)r.ldw * 2u + (uint32_t)cchunk * 16u;
 #pragma unroll
   for (int i = 0; i < TB * 4; ++i) {
     const int m = min(m0 + i * 8 + crow, Me - 1);   // rows past the end repeat the last row
@@ -79,9 +86,9 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, 
     coffX[i] = (uint32_t)arow * (uint32_t)Kdim * 2u + (uint32_t)cchunk * 16u;
   }
   const int r32 = lane & 31, half = lane >> 5, swz = lane & 7;
-  f32x16 acc[2][TB];
+  f32x16 acc[WB][TB];
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < WB; ++b)
 #pragma unroll
     for (int t = 0; t < TB; ++t)
 #pragma unroll
@@ -90,67 +97,58 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, 
   auto kbyte = [&](int s) -> size_t { return (size_t)(s + rot >= nk ? s + rot - nk : s + rot) * 128; };
   auto request1 = [&](size_t kb, int slot, int i) {   // copy i of the stage of the K step at byte kb of the rows
     const uint32_t l = lds0 + (uint32_t)slot * STAGE + (uint32_t)i * 1024u;
-    if (i < 4) copy_to_lds_16(W0 + kb, coffW[i], l, true);
-    else if (i < 8) copy_to_lds_16(W1 + kb, coffW[i - 4], l, true);
-    else copy_to_lds_16(Ab + kb, coffX[i - 8], l);
+    if (i < NW0) copy_to_lds_16(W0 + kb, coffW[i], l, true);
+    else if (i < 2 * NW0) copy_to_lds_16(W1 + kb, coffW[i - NW0], l, true);
+    else copy_to_lds_16(Ab + kb, coffX[i - 2 * NW0], l);
   };
   // Multiply the stage in `slot`: all operands go to registers first (the empty asm makes the compiler wait for
   // them), so the slot is free and takes, request by request between the MFMAs, the stage NS steps ahead.
   auto consume = [&](int slot, bool more, size_t kb) {
     const unsigned char* st = ring + slot * STAGE + r32 * 128;
-    u32x4 w[2][4], x[TB][4];
+    u32x4 w[WB][4], x[TB][4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       const int c = ((2 * kk + half) ^ swz) << 4;
 #pragma unroll
-      for (int b = 0; b < 2; ++b) w[b][kk] = *reinterpret_cast<const u32x4*>(st + b * 4096 + c);
+      for (int b = 0; b < WB; ++b) w[b][kk] = *reinterpret_cast<const u32x4*>(st + b * 4096 + c);
 #pragma unroll
-      for (int t = 0; t < TB; ++t) x[t][kk] = *reinterpret_cast<const u32x4*>(st + (2 + t) * 4096 + c);
+      for (int t = 0; t < TB; ++t) x[t][kk] = *reinterpret_cast<const u32x4*>(st + (WB + t) * 4096 + c);
     }
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
 #pragma unroll
-      for (int b = 0; b < 2; ++b) asm volatile("" : "+v"(w[b][kk]));
+      for (int b = 0; b < WB; ++b) asm volatile("" : "+v"(w[b][kk]));
 #pragma unroll
       for (int t = 0; t < TB; ++t) asm volatile("" : "+v"(x[t][kk]));
     }
 #pragma unroll
-    for (int j = 0; j < 8 * TB; ++j) {
-      const int kk = j / (2 * TB), b = j % 2, t = (j / 2) % TB;
+    for (int j = 0; j < 4 * WB * TB; ++j) {
+      const int kk = j / (WB * TB), b = j % WB, t = (j / WB) % TB;
       acc[b][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(w[b][kk]), as_bf16x8(x[t][kk]), acc[b][t], 0, 0, 0);
       if (more) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-          if (i * 8 * TB / NI == j) request1(kb, slot, i);
+          if (i * 4 * WB * TB / NI == j) request1(kb, slot, i);
       }
       __builtin_amdgcn_sched_barrier(0x6);
     }
   };
-  if (nk >= NS) {
-    for (int s = 0; s < NS; ++s) {
-      const size_t kb = kbyte(s);
+  // (nk >= NS: shorter contractions go to the narrow kernel)
+  for (int s = 0; s < NS; ++s) {
+    const size_t kb = kbyte(s);
 #pragma unroll
-      for (int i = 0; i < NI; ++i) request1(kb, s, i);
-    }
-    int slot = 0;
-    for (int s = 0; s + NS < nk; ++s) {
-      wait_copies_but<(NS - 1) * NI>();   // step s has landed
-      consume(slot, true, kbyte(s + NS));
-      slot = slot + 1 == NS ? 0 : slot + 1;
-    }
-    drain<0, NS, NI>([&]() {
-      consume(slot, false, 0);
-      slot = slot + 1 == NS ? 0 : slot + 1;
-    });
-  } else {   // fewer K steps than ring stages: one at a time
-    for (int s = 0; s < nk; ++s) {
-      const size_t kb = kbyte(s);
-#pragma unroll
-      for (int i = 0; i < NI; ++i) request1(kb, 0, i);
-      wait_copies_but<0>();
-      consume(0, false, 0);
-    }
+    for (int i = 0; i < NI; ++i) request1(kb, s, i);
   }
+  int slot = 0;
+  for (int s = 0; s + NS < nk; ++s) {
+    wait_copies_but<(NS - 1) * NI>();   // step s has landed
+    consume(slot, true, kbyte(s + NS));
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  }
+  drain<0, NS, NI>([&]() {
+    consume(slot, false, 0);
+    slot = slot + 1 == NS ? 0 : slot + 1;
+  });
   // accumulator element i of block (b, t): weight row (output column) 8*(i/4) + 4*(lane/32) + i%4 of the block,
   // token row lane%32; lanes l and l+32 trade column groups, so each stores 16 bytes
 #pragma unroll
@@ -159,14 +157,14 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, 
     if (m < mend) {
       bf16_t* out = r.C + (size_t)(rb + m) * N + n0;
 #pragma unroll
-      for (int b = 0; b < (GATEUP ? 1 : 2); ++b) {
+      for (int b = 0; b < (GATEUP ? 1 : WB); ++b) {
 #pragma unroll
-        for (int q = 0; q < 4; q += 2) {
+        for (int q = 0; q < (GATEUP && WB == 1 ? 2 : 4); q += 2) {
           float v[8];
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             const float g = acc[b][t][4 * q + i];
-            v[i] = GATEUP ? __fdividef(g, 1.0f + __expf(-g)) * acc[1][t][4 * q + i] : g;
+            v[i] = GATEUP ? __fdividef(g, 1.0f + __expf(-g)) * (WB == 1 ? acc[0][t][8 + i] : acc[WB - 1][t][4 * q + i]) : g;
           }
           uint32_t ox = pack_bf16x2(v[0], v[1]), oy = pack_bf16x2(v[2], v[3]);
           uint32_t oz = pack_bf16x2(v[4], v[5]), ow = pack_bf16x2(v[6], v[7]);
@@ -181,10 +179,11 @@ __device__ __forceinline__ void wide_pass(const GemmArgs& a, const WideRows& r, 
 
 // SHARED: a.n_shared more weight sets of N by Kdim ride along, each applied to all a.shared_rows tokens (the block call that
 // hosts the shared experts); their items come first, for they have the most rows.
-template <bool GATEUP, bool SHARED>
-__global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(GemmArgs a, int groups) {
+template <bool GATEUP, bool SHARED, WideForm FORM>
+__global__ __launch_bounds__(64 * wide_waves(FORM)) void expert_stream_wide_kernel(GemmArgs a, int groups) {
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NPER = GATEUP ? 32 : 64;   // output columns of a wave
+  constexpr int WB = wide_blocks(FORM), ROWS = wide_rows(FORM);
+  constexpr int NPER = (GATEUP ? 16 : 32) * WB;   // output columns of a wave
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nsets = SHARED ? a.n_shared : 0;
@@ -199,12 +198,12 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
     if (SHARED && e < nsets) {
       eid[i] = -1 - e;
       me[i] = a.shared_rows;
-      np[i] = (me[i] + WIDE_ROWS - 1) / WIDE_ROWS;
+      np[i] = (me[i] + ROWS - 1) / ROWS;
     } else if (e < nexp) {
       eid[i] = a.ids ? a.ids[a.lo + e - nsets] : a.lo + e - nsets;
       rb[i] = a.offsets[eid[i]];
       me[i] = a.offsets[eid[i] + 1] - rb[i];
-      np[i] = (max(me[i], 0) + WIDE_ROWS - 1) / WIDE_ROWS;
+      np[i] = (max(me[i], 0) + ROWS - 1) / ROWS;
     }
     sum += np[i];
   }
@@ -239,7 +238,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
   const int pass = rem - group * passes;
 
   const int N = a.N, Kdim = a.Kdim, nk = Kdim / 64;
-  const int col = group * WIDE_WAVES + wave;
+  const int col = group * wide_waves(FORM) + wave;
   const int n0 = col * NPER;
   if (n0 >= N) return;
   // rows of the pass: the expert's 32-row blocks dealt evenly to its passes
@@ -247,7 +246,7 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
   const int b0 = blocks * pass / passes, b1 = blocks * (pass + 1) / passes;
   // the walk over K starts at a step of its own (see expert_stream_lds.hip); it depends on the expert and the
   // column only, so results depend neither on the block cut nor on the passes
-  const int rot = (int)(((unsigned)col * 3u + (unsigned)eg * 5u) % (unsigned)nk);
+  const int rot = (int)(((unsigned)(WB == 1 ? col >> 1 : col) * 3u + (unsigned)eg * 5u) % (unsigned)nk);   // (32 or 64 columns)
   WideRows r{a.A, a.gather, a.C, Kdim};
   const bf16_t *B0 = a.B0 + (size_t)eg * N * Kdim, *B1 = GATEUP ? a.B1 + (size_t)eg * N * Kdim : nullptr;
   if (sh) {    // gate/up: every set reads the tokens; down: its own hidden rows
@@ -256,43 +255,55 @@ __global__ __launch_bounds__(64 * WIDE_WAVES) void expert_stream_wide_kernel(Gem
     B1 = GATEUP ? a.Bs1 + (size_t)eg * a.shared_b_step : nullptr;
   }
   const unsigned char* W0 = reinterpret_cast<const unsigned char*>(B0 + (size_t)n0 * r.ldw);
-  const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>(B1 + (size_t)n0 * r.ldw) : W0 + (size_t)32 * r.ldw * 2;
-  unsigned char* ring = smem + wave * WIDE_LDS;
+  const unsigned char* W1 = GATEUP ? reinterpret_cast<const unsigned char*>(B1 + (size_t)n0 * r.ldw) : W0 + (size_t)(16 * WB) * r.ldw * 2;
+  unsigned char* ring = smem + wave * wide_ring(FORM);
   const int m0 = b0 * 32, mend = min(b1 * 32, Me);
   switch (b1 - b0) {
-    case 1: wide_pass<1, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
-    case 2: wide_pass<2, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
-    default: wide_pass<3, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
+    case 1: wide_pass<FORM, 1, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
+    case 2: wide_pass<FORM, 2, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
+    default: if constexpr (ROWS > 64) wide_pass<FORM, 3, GATEUP>(a, r, ring, erb, Me, m0, mend, n0, rot, W0, W1); break;
   }
 }
 
-template <bool GATEUP, bool SHARED>
+template <bool GATEUP, bool SHARED, WideForm FORM>
 int launch_wide(const GemmArgs& a, hipStream_t st) {
-  auto kern = expert_stream_wide_kernel<GATEUP, SHARED>;
-  constexpr int lds = WIDE_WAVES * WIDE_LDS;
+  auto kern = expert_stream_wide_kernel<GATEUP, SHARED, FORM>;
+  constexpr int lds = wide_waves(FORM) * wide_ring(FORM), ROWS = wide_rows(FORM);
   const int nexp = a.hi - a.lo, nsets = SHARED ? a.n_shared : 0;
-  if (a.offsets == nullptr || nexp + nsets > WIDE_EMAX || a.N % 64 != 0 || a.Kdim % 64 != 0) return -2;
-  const int per = WIDE_WAVES * (GATEUP ? 32 : 64);
+  if (a.offsets == nullptr || nexp + nsets > WIDE_EMAX || a.N % 64 != 0 || a.Kdim % 64 != 0 || a.Kdim < 5 * 64) return -2;   // (the deepest ring)
+  const int per = wide_waves(FORM) * (GATEUP ? 16 : 32) * wide_blocks(FORM);
   const int groups = (a.N + per - 1) / per;
   // an upper bound of the passes: every expert's last pass may be partial
-  const long passes = (long)a.rows_total / WIDE_ROWS + std::min((long)nexp, (long)a.rows_total) +
-                      (long)nsets * ((a.shared_rows + WIDE_ROWS - 1) / WIDE_ROWS);
+  const long passes = (long)a.rows_total / ROWS + std::min((long)nexp, (long)a.rows_total) +
+                      (long)nsets * ((a.shared_rows + ROWS - 1) / ROWS);
   constexpr long runs = 8l * WIDE_RUN;
   const long grid = (passes * groups + runs - 1) / runs * runs;
   if (grid <= 0) return 0;
   static std::atomic<uint64_t> lds_raised{0};
   if (raise_lds_limit((const void*)kern, lds, lds_raised) != 0) return -4;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * WIDE_WAVES), lds, st, a, groups);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * wide_waves(FORM)), lds, st, a, groups);
   return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+// The forms give the same bits, so the choice may look at the call (a few experts of a layer cut into blocks).  By waves of 64
+// weight rows, counting one pass per expert, on 256 CUs: up to 1.5 per CU a launch is bound by the latency of its few
+// waves, and twice as many of half the rows are faster (4 of 16 experts, H 3072, I 2048, 16 rows, gate/up: 256 waves, 27.4
+// -> 19.7 us; 352: 35.6 -> 34.5; 440: 22.0 -> 23.8); up to 2 every CU has one coarse workgroup at most; up to 3 some have
+// two and the rest one, while the six finest waves that fit a CU come out even (15 of 60, H 2048, I 1408, 11 rows, gate/up:
+// 660 waves, 37.5 -> 31.9 us; 768, H 1024: 21.7 -> 18.8; 880: 40.1 -> 41.9); beyond, the token rows, which the fine forms copy
+// twice as often, cost more than that.
+template <bool GATEUP>
+int launch_wide_any(const GemmArgs& a, hipStream_t st) {
+  if (a.n_shared > 0) return launch_wide<GATEUP, true, COARSE>(a, st);
+  const long waves = std::min((long)(a.hi - a.lo), (long)a.rows_total) * (a.N / (GATEUP ? 32 : 64));
+  if (waves <= 384) return launch_wide<GATEUP, false, FINE>(a, st);
+  if (waves > 512 && waves <= 768) return launch_wide<GATEUP, false, FINEST>(a, st);
+  return launch_wide<GATEUP, false, COARSE>(a, st);
 }
 
 }  // namespace
 
-int launch_stream_wide_gateup(const GemmArgs& a, hipStream_t st) {
-  return a.n_shared > 0 ? launch_wide<true, true>(a, st) : launch_wide<true, false>(a, st);
-}
-int launch_stream_wide_down(const GemmArgs& a, hipStream_t st) {
-  return a.n_shared > 0 ? launch_wide<false, true>(a, st) : launch_wide<false, false>(a, st);
-}
+int launch_stream_wide_gateup(const GemmArgs& a, hipStream_t st) { return launch_wide_any<true>(a, st); }
+int launch_stream_wide_down(const GemmArgs& a, hipStream_t st) { return launch_wide_any<false>(a, st); }
 
 }  // namespace moe

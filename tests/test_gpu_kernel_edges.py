@@ -58,7 +58,8 @@ def test_single_tile_experts_start_anywhere_in_k(moe, oracle64, policy, H, I):
     assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16))
 
 
-@pytest.mark.parametrize("H,I", [(64, 64), (128, 192), (320, 448)])     # one K step ... more than the ring; a lone column block
+# contractions of up to four steps (the narrow kernel), five (the deepest ring), seven
+@pytest.mark.parametrize("H,I", [(64, 64), (128, 192), (320, 448), (448, 320)])
 @pytest.mark.parametrize("counts", [
     [0, 1, 31, 32, 33, 63, 64, 65, 0, 0, 2, 5],                 # one, two, three token blocks
     [95, 96, 97, 0, 0, 0, 0, 1, 0, 0, 0, 0],                    # the last row of one pass and the first of two
@@ -83,14 +84,33 @@ def test_wide_streaming_at_block_and_pass_borders(moe, oracle64, counts, H, I):
     assert torch.equal(Yp.view(torch.int16), Yl.view(torch.int16)), "depends on list or gather"
 
 
+# waves of 64 weight rows at the lines between the kernel's forms: gate/up 384 | 390, 512 | 520, 768 | 780; down 384 | 385, 510 | 516, 768 | 774
+@pytest.mark.parametrize("E,H,I", [(24, 320, 512), (39, 320, 320), (32, 320, 512), (26, 320, 640), (32, 384, 768), (26, 320, 960),
+                                   (32, 768, 320), (35, 704, 320), (34, 960, 320), (43, 768, 384), (32, 1536, 320), (43, 1152, 320)])
+def test_wide_streaming_forms_give_the_same_bits(moe, oracle64, E, H, I):
+    print(f"[case] forms of the wide kernel E={E} H={H} I={I}", flush=True)
+    pattern = [1, 31, 32, 33, 0, 64, 65, 7, 96, 97, 5, 129, 12, 193, 8, 9]      # one to three blocks, one to four passes
+    counts = [pattern[e % len(pattern)] for e in range(E)]
+    c = block_case(oracle64, counts, H, I, E + H)
+    Yp = run_blocks(moe, c, 9)
+    check_close(f64(Yp), c["ref"], "Yp")
+    for cuts in ([(e, e + 1) for e in range(E)], [(E // 2, E), (0, E // 2)], [(0, E - 1), (E - 1, E)]):
+        Yc = run_blocks(moe, c, 9, cuts)
+        assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16)), f"{len(cuts)} blocks"
+
+
 @pytest.mark.parametrize("E,rows", [(8, 5), (8, 32), (8, 33), (20, 6), (20, 7), (20, 32), (20, 33), (1, 20)])
-def test_automatic_choice_around_its_lines(moe, oracle64, E, rows):
+@pytest.mark.parametrize("H,I", [(192, 128), (320, 384), (256, 320)])     # contractions for the narrow kernel, the wide one, one each
+def test_automatic_choice_around_its_lines(moe, oracle64, E, rows, H, I):
     # mean rows per expert 6 | 7: narrow or wide streaming; 32 | 33: streaming or tiles
     g = torch.Generator().manual_seed(E * 100 + rows)
     cut = torch.sort(torch.randint(0, E * rows + 1, (E - 1,), generator=g)).values.tolist()
     counts = np.diff([0] + cut + [E * rows])
-    c = block_case(oracle64, counts, 192, 128, rows)
-    check_close(f64(run_blocks(moe, c, 0)), c["ref"], f"Yp, {E} experts of {rows} rows on average")
+    c = block_case(oracle64, counts, H, I, rows)
+    Yp = run_blocks(moe, c, 0)
+    check_close(f64(Yp), c["ref"], f"Yp, {E} experts of {rows} rows on average")
+    Yc = run_blocks(moe, c, 0, [(e, e + 1) for e in range(E)])
+    assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16))
 
 
 @pytest.mark.parametrize("T", [12, 56])     # 8 experts, top-2: 3 and 14 rows per expert
@@ -115,7 +135,7 @@ def test_block_call_that_hosts_the_shared_experts_on_few_rows(moe, oracle64, T):
 # mean rows per expert and tokens at the lines between narrow, wide and separate launches: (64, 65 | 6 rows), (192, 193 | 32 rows)
 @pytest.mark.parametrize("T,E,K,n_sets", [(1, 12, 2, 3), (16, 12, 4, 1), (36, 12, 2, 3), (37, 12, 2, 3), (64, 12, 1, 8), (65, 12, 1, 8),
                                           (96, 12, 2, 2), (97, 12, 2, 2), (192, 12, 2, 3), (193, 12, 2, 3), (200, 15, 1, 3), (410, 60, 4, 2)])
-@pytest.mark.parametrize("H,I", [(128, 64), (192, 320)])
+@pytest.mark.parametrize("H,I", [(128, 64), (192, 320), (384, 320)])     # narrow, one kernel each, wide where the rows call for it
 def test_block_call_that_hosts_the_shared_experts_in_every_launch_form(moe, oracle64, T, E, K, n_sets, H, I):
     print(f"[case] hosted shared experts T={T} E={E} K={K} sets={n_sets} H={H} I={I}", flush=True)
     Is = n_sets * I
