@@ -420,18 +420,28 @@ static int launch_route_many(MOE_ROUTE_PARAMS) {
 //   8 tokens, 4 waves in pairs: T = 2048 18.8 | 24.1; 3000 25.3 | 32.2; 4096 26.0 | 32.9; 16384 90.6 | 112
 // Before, with one token per workgroup below 1024 and every wave on tokens of its own from there on: T = 301 13.7 | 18.5;
 // 777 18.3 | 25.9; 2048 22.9 | 28.5; 4096 30.2 | 36.9.
-// Rows beyond 2048 elements hold half as many tokens in registers; H 4096, 60 experts: T = 301 18.7 -> 13.5,
+// Rows of up to 1536 elements have instances of their own (as padded rows of 2048: H 1536, 60 experts, T = 384 11.4 us, 8.1 now; 4096
+// 28.7 -> 21.4).  Rows beyond 2048 elements hold half as many tokens in registers; H 4096, 60 experts: T = 301 18.7 -> 13.5,
 // 777 26.2 -> 20.6, 4096 77 -> 71, 16384 288 -> 277 (up to 256 tokens the widening kernel above is still the fastest).
 int launch_route(MOE_ROUTE_PARAMS) {
   const int chunks = (H + 511) / 512;
   const int size = T <= 256 ? 0 : T <= 512 ? 1 : T <= 1024 ? 2 : T <= 2048 ? 3 : T < 4096 ? 4 : 5;
+  // (up to 8 experts are two batches: two of the four waves would have none)
+  const bool pairs = E <= 8 && size >= 3;
   if (chunks <= 1) {
+    if (pairs) return launch_route_many<1, 4, 4, 4, 2, 2>(MOE_ROUTE_ARGS);
     if (size == 0) return launch_route_many<1, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
     return size == 1 ? launch_route_many<1, 2, 4, 4, 1, 2>(MOE_ROUTE_ARGS) : launch_route_many<1, 4, 4, 4, 1, 2>(MOE_ROUTE_ARGS);
   }
   if (chunks <= 2) {
+    if (pairs) return launch_route_many<2, 4, 4, 4, 2, 2>(MOE_ROUTE_ARGS);
     if (size == 0) return launch_route_many<2, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
     return size == 1 ? launch_route_many<2, 2, 4, 4, 1, 2>(MOE_ROUTE_ARGS) : launch_route_many<2, 4, 4, 4, 1, 2>(MOE_ROUTE_ARGS);
+  }
+  if (chunks <= 3) {
+    if (size == 0) return launch_route_many<3, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
+    if (size == 1) return launch_route_many<3, 2, 2, 4, 1, 2>(MOE_ROUTE_ARGS);
+    return size < 5 ? launch_route_many<3, 4, 2, 4, 1, 2>(MOE_ROUTE_ARGS) : launch_route_many<3, 4, 2, 4, 2, 2>(MOE_ROUTE_ARGS);
   }
   if (chunks <= 4) {
     if (size == 0) return launch_route_many<4, 1, 4, 16, 1, 1>(MOE_ROUTE_ARGS);
@@ -442,7 +452,11 @@ int launch_route(MOE_ROUTE_PARAMS) {
     if (size == 0) return launch_route_t<8, 2, 8>(MOE_ROUTE_ARGS);
     if (size == 1) return launch_route_many<8, 2, 2, 4, 1, 1>(MOE_ROUTE_ARGS);
     if (size == 2) return launch_route_many<8, 2, 2, 4, 2, 1>(MOE_ROUTE_ARGS);
-    return size == 3 ? launch_route_many<8, 2, 2, 4, 4, 1>(MOE_ROUTE_ARGS) : launch_route_many<8, 4, 1, 4, 4, 1>(MOE_ROUTE_ARGS);
+    // 8 or 16 tokens of a workgroup: whichever takes less in whole rounds of the 256 CUs (a round of 16 takes 1.85 times a
+    // round of 8; 128 experts of H 4096: 75 and 138 us; T = 3000 one round against two, 9000 three against five)
+    const int rounds8 = (T + 2047) / 2048, rounds16 = (T + 4095) / 4096;
+    return 1.85 * rounds16 > rounds8 ? launch_route_many<8, 2, 2, 4, 4, 1>(MOE_ROUTE_ARGS)
+                                     : launch_route_many<8, 4, 1, 4, 4, 1>(MOE_ROUTE_ARGS);
   }
   if (chunks <= 16) return launch_route_t<16, 1, 4>(MOE_ROUTE_ARGS);
   return -2;

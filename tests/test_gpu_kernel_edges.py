@@ -220,13 +220,10 @@ def test_shared_expert_walk_over_incomplete_tile_groups(moe, oracle64, T):
         check_close(f64(S), S_ref, f"S, T={T} policy {policy}")
 
 
-@pytest.mark.parametrize("H", [64, 960, 1024, 1984, 2048, 3072, 4096])
-@pytest.mark.parametrize("T", [1, 255, 256, 257, 511, 512, 513, 1024, 1025, 2049, 4095, 4097])
-def test_router_sums_keep_their_order_in_every_variant(moe, oracle64, T, H):
+def router_bits(moe, oracle64, T, H, E, K):
     # The batch repeats one token and bias[e] = -(the oracle's fp32 logit of e): every logit becomes exactly 0 when it
     # has the oracle's bits, and ids 0..K-1 win the tie at weight 1/E; one ulp anywhere changes the ids.
-    E, K = (61, 4) if H % 512 else (66, 7)      # ragged last batches of experts
-    print(f"[case] router variants T={T} H={H}", flush=True)
+    print(f"[case] router variants T={T} H={H} E={E}", flush=True)
     g = torch.Generator().manual_seed(T * 7 + H)
     x = ((torch.rand((1, H), generator=g) - 0.5) * torch.pow(2.0, torch.randint(-8, 9, (1, H), generator=g).float())).to(torch.bfloat16)
     Wr = (torch.randn((E, H), generator=g) * 0.05).to(torch.bfloat16)
@@ -238,6 +235,20 @@ def test_router_sums_keep_their_order_in_every_variant(moe, oracle64, T, H):
         torch.cuda.synchronize()
         assert np.array_equal(ids.cpu().numpy(), expect), sign
         assert np.allclose(w.cpu().numpy(), 1.0 / E, rtol=1e-6)
+
+
+@pytest.mark.parametrize("H", [64, 960, 1024, 1088, 1536, 1984, 2048, 3072, 4096])
+@pytest.mark.parametrize("T", [1, 255, 256, 257, 511, 512, 513, 1024, 1025, 2049, 4095, 4097])
+def test_router_sums_keep_their_order_in_every_variant(moe, oracle64, T, H):
+    E, K = (61, 4) if H % 512 else (66, 7)      # ragged last batches of experts
+    router_bits(moe, oracle64, T, H, E, K)
+
+
+# few experts, whose waves work on pairs of token groups; rounds of 8 and of 16 tokens per workgroup (4096 | 4097, 8192 | 8193)
+@pytest.mark.parametrize("T,H,E,K", [(1025, 64, 8, 3), (1031, 320, 3, 1), (2049, 1024, 5, 2), (4099, 512, 8, 8), (1024, 64, 8, 3), (1030, 64, 9, 3),
+                                     (4096, 2560, 6, 2), (4098, 2112, 6, 2), (8192, 2112, 5, 2), (8193, 4096, 4, 1)])
+def test_router_sums_keep_their_order_with_few_experts_and_in_whole_rounds(moe, oracle64, T, H, E, K):
+    router_bits(moe, oracle64, T, H, E, K)
 
 
 @pytest.mark.parametrize("T,H,E,K", [(1, 64, 8, 2), (64, 64, 3, 1), (65, 128, 61, 1), (1023, 64, 256, 1), (257, 192, 60, 4), (341, 64, 256, 3),
