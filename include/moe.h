@@ -162,7 +162,7 @@ int moe_expert_group_forward(int group_lo, int group_hi, const void* Xp,
  * workspace: moe_shared_workspace_bytes(T, H, Is) bytes: h as bf16 [T,Is], then up to 8 fp32 tensors
  * [T,H], the partial sums of a down projection that is cut along K (batches that leave the chip part
  * empty otherwise).  Beyond 512 tokens h alone is enough: the parts are then formed one after another,
- * which takes longer and gives the same bits.
+ * which fills less of the chip and gives the same bits.
  */
 int moe_shared_forward(const void* x, const void* Wsg, const void* Wsu, const void* Wsd,
                        const void* wgate, int T, int H, int Is, void* S, float* sg,

@@ -90,9 +90,9 @@ __host__ __device__ constexpr int fragment_read_order(int slot, int tb, int nb) 
   return slot == 0 ? tb : (slot == 1 ? 0 : (slot <= nb ? tb + slot - 1 : slot - nb));
 }
 
-// KSPLIT > 1: K is cut into that many parts.  Each is a work item whose fp32 sums go to a.Cpart; INTURN: a workgroup forms
-// the parts of a tile one after another and adds them in the order of the kernel that adds them otherwise: the same
-// bits without room for the parts (and the time of the uncut tile).
+// KSPLIT > 1: K is cut into that many parts.  Each is a work item whose fp32 sums go to a.Cpart; INTURN: a tile walks all of
+// K, sets its sums aside at the end of a part and adds them in the order of the kernel that adds the parts otherwise:
+// the same bits without room for the parts, in the time of the uncut tile.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE, bool INTURN>
 __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
@@ -158,13 +158,13 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   const int ngrp = grp0 + grp1;
   const int NT = (a.N + S::NOUT - 1) / S::NOUT;
   const int Kdim = a.Kdim;
-  const int nk = Kdim / S::BK / KSPLIT;          // K steps of one work item (a tile, or a K part of it)
+  constexpr int ITEMS = INTURN ? 1 : KSPLIT;     // work items of a tile
+  const int nk = Kdim / S::BK / ITEMS;           // K steps of one work item (a tile, or a K part of it)
   const int groupTiles = S::GM * NT;
   // With one class the walk ends with its last tile.  (With two, the incomplete last group of each leaves a
   // gap; tiles of a complete index space that do not exist would otherwise push real ones into one more round:
   // 777 tokens on one weight set are 5 tiles of 160 rows by 44 column tiles, 220 for 256 workgroups, and took
   // 73 us as 8 x 44 with gaps.)
-  constexpr int ITEMS = INTURN ? 1 : KSPLIT;     // work items of a tile
   const int Lend = (grp0 == 0 || grp1 == 0 ? (total0 + total1) * NT : ngrp * groupTiles) * ITEMS;
   // Divisions of the walk, prepared once per workgroup so that finding a tile costs multiplications only:
   // light groups among the first g groups of the merged walk = (g * light_ratio) >> 32, with light_ratio =
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
   uint32_t coff[S::NL];   // byte offsets of this lane's 16 bytes for each of the NL copies of a stage (K step 0)
   int krot = 0;           // K step the tile starts at (its walk over K wraps around)
   auto kstep = [&](int kt) -> int { const int k = kt + krot; return k >= nk ? k - nk : k; };
-  int it = 0, turn = 0;   // turn: the K part that comes next (INTURN)
+  int it = 0;
   auto next_tile = [&]() -> TileState {
     TileState t{};
     int L = 0, mrow = 0, nt = 0, cls = 0, ks = 0;
@@ -244,13 +244,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
       }
       if (nt < NT) break;
     }
-    if constexpr (INTURN) {
-      ks = turn;
-      turn = turn + 1 == KSPLIT ? 0 : turn + 1;
-      if (turn == 0) ++it;
-    } else {
-      ++it;
-    }
+    ++it;
     t.valid = true;
     t.ks = ks;   // K part of this work item
 
@@ -432,6 +426,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
       bf16x8 faA[S::TB], fbA[S::NB], faB[S::TB], fbB[S::NB];
       MOE_TILE_READ(faA, fbA, 0, 0);
       int st = 0;                                  // buffer of the stage being multiplied: kt % NS
+      int part_end = nk / KSPLIT;                  // (INTURN) K step at which the part ends
       for (int kt = 0; kt + 1 < nk; ++kt) {
         const int st1 = st + 1 == NS ? 0 : st + 1;
         // the rest of the copies of K step kt-1+NS, whose first part went out during the last slice
@@ -451,6 +446,22 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
         wait_copies_but<(S::DIST - 1) * S::NL>();
         workgroup_barrier();  // stage kt+1 is complete for everyone; stage kt is free for everyone
         MOE_TILE_SLICE_LAST(st1, ONCE ? kstep(min(kt + NS, nk - 1)) : min(kt + NS, nk - 1), st);
+        if constexpr (INTURN) {
+          if (kt + 1 == part_end) {   // (the wait states between the slice's last MFMAs and their results: the branch hides the pair)
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int nb = 0; nb < S::NB; ++nb)
+#pragma unroll
+              for (int tb = 0; tb < S::TB; ++tb)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                  sum[nb][tb][i] = part_end == nk / KSPLIT ? acc[nb][tb][i] : sum[nb][tb][i] + acc[nb][tb][i];
+                  acc[nb][tb][i] = 0.0f;
+                }
+            part_end += nk / KSPLIT;
+          }
+        }
         st = st1;
       }
       MOE_TILE_SLICE(faA, fbA, faB, fbB, st, 1);
@@ -490,18 +501,14 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
     // stages now, their way from L2 overlaps the stores below
     const TileState nxt = next_tile();
 
-    // (selected, not branched around: see the clock record above)
-    if constexpr (INTURN) {
+    if constexpr (INTURN) {   // the last part
 #pragma unroll
       for (int nb = 0; nb < S::NB; ++nb)
 #pragma unroll
-        for (int tb = 0; tb < S::TB; ++tb) {
+        for (int tb = 0; tb < S::TB; ++tb)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[nb][tb][i] = ks > 0 ? sum[nb][tb][i] + acc[nb][tb][i] : acc[nb][tb][i];
-          sum[nb][tb] = acc[nb][tb];
-        }
+          for (int i = 0; i < 16; ++i) acc[nb][tb][i] = sum[nb][tb][i] + acc[nb][tb][i];
     }
-    const int rowStop = INTURN && ks + 1 < KSPLIT ? row0 : rowEnd;   // rows of an incomplete sum are not stored
 
     // epilogue: accumulator element i of block (nb, tb) is output column
     // 8*(i/4) + 4*(lane/32) + i%4 of the block, token row lane%32: lanes l and l+32 hold the two
@@ -524,7 +531,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
 #pragma unroll
     for (int tb = 0; tb < S::TB; ++tb) {
       const int m = row0 + wm * S::WTM + tb * 32 + frag_row;
-      if (m < rowStop) {
+      if (m < rowEnd) {
         bf16_t* crow_out = cbase + (size_t)(m - cshift) * a.N;
 #pragma unroll
         for (int nb = 0; nb < S::NBH; ++nb) {
