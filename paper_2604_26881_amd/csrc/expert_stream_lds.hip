@@ -54,8 +54,8 @@ __device__ __forceinline__ void stream_tail(F&& step) {
 // Of blockIdx.y the first a.n_shared are its own, and all of them take all tokens.  Gate/up: sets of N columns of its
 // hidden layer (the last one may be narrower).  Down: its contraction is cut into a.shared_parts parts of whole K steps;
 // with a.Cpart each is a set of its own and leaves fp32 partial sums there, which a later kernel adds in ascending order
-// and rounds; with one set (no room for them) one wave forms the parts one after another and adds them in that same order.
-// (With as many sets as parts and no a.Cpart every part is an output of its own, bf16 in a.Cs: the block call that hosts
+// and rounds; without room for them there is one set (TURN) and one wave forms the parts one after another and adds them in
+// that same order.  (With as many sets as parts and no a.Cpart every part is an output of its own, bf16 in a.Cs: the block call that hosts
 // the shared experts.)
 // The parts and the K starts depend on Is and the column alone, so the shared expert has the same bits alone, riding,
 // beside any block cut, and whatever the workspace.
@@ -64,7 +64,7 @@ __device__ __forceinline__ void stream_tail(F&& step) {
 // sum); together 19.2 and 11.3.  By itself (beside several blocks or on a second stream), with its sum and gate logits,
 // against those tiles: 1 token 32 -> 21 us, 32 tokens 32 -> 24; H 1024, Is 4032 42 -> 14.  From 17 tokens on a riding shared expert is read by two passes; up to 32 tokens that
 // still beats launches of their own on one stream.
-template <int MT, bool GATEUP, int NST, bool SHARED>
+template <int MT, bool GATEUP, int NST, bool SHARED, bool TURN>
 __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   using S = StreamLdsShape<MT, NST>;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -87,9 +87,9 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   const int N = a.N;
   constexpr bool CUT = SHARED && !GATEUP;                      // a shared set's contraction comes in parts
   const int Kdim = CUT && sh ? a.ldb_shared : a.Kdim;          // elements between consecutive weight (and token) rows
-  const bool in_turn = CUT && sh && a.n_shared != a.shared_parts;
-  const int part0 = CUT && sh && !in_turn ? eg : 0;            // the parts this wave forms
-  const int part1 = in_turn ? a.shared_parts : part0 + 1;
+  static_assert(!TURN || CUT, "parts of the shared contraction");
+  const int part0 = CUT && sh && !TURN ? eg : 0;               // the parts this wave forms
+  const int part1 = TURN ? a.shared_parts : part0 + 1;
   int nk = Kdim / 64;                                          // K steps of a part, and the byte where it begins
   size_t kofs = 0;
   // The walk over K starts at step `rot` and wraps around.  Thousands of these waves start within a
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
         }
     };
 
-    f32x4 sum0[MT], sum1[MT];   // (CUT: of the parts before)
+    f32x4 sum0[MT], sum1[MT];   // (TURN: of the parts before)
     for (int part = part0; part < part1; ++part) {
       if (CUT && sh) {
         nk = a.part_steps + (part < a.part_extra ? 1 : 0);
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
           consume(0, [] {});
         }
       }
-      if constexpr (CUT) {
+      if constexpr (TURN) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
@@ -269,11 +269,11 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
 
 constexpr int STREAM_PASS_GROUPS = 8;
 
-template <int MT, bool GATEUP, int NST, bool SHARED>
+template <int MT, bool GATEUP, int NST, bool SHARED, bool TURN = false>
 static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   using S = StreamLdsShape<MT, NST>;
   static_assert(NST * S::STAGE <= 64 * 1024, "dynamic LDS without an opt-in attribute");
-  auto kern = expert_stream_lds_kernel<MT, GATEUP, NST, SHARED>;
+  auto kern = expert_stream_lds_kernel<MT, GATEUP, NST, SHARED, TURN>;
   const int nexp = (a.offsets ? a.hi - a.lo : SHARED ? 0 : 1) + (SHARED ? a.n_shared : 0);
   const int per = GATEUP ? 16 : 32;
   const int gx = (a.N + per - 1) / per;
@@ -302,6 +302,10 @@ static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.offsets != nullptr && !stream_narrow(a.mean_rows, a.Kdim))
     return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
   const bool two = a.offsets != nullptr ? a.mean_rows > 10 : (a.n_shared > 0 ? a.shared_rows : a.rows_fixed) > 16;
+  if constexpr (!GATEUP) {
+    if (a.n_shared > 0 && a.n_shared != a.shared_parts)
+      return two ? launch_stream_lds_t<2, GATEUP, 4, true, true>(a, st) : launch_stream_lds_t<1, GATEUP, 4, true, true>(a, st);
+  }
   if (a.n_shared > 0) return two ? launch_stream_lds_t<2, GATEUP, 4, true>(a, st) : launch_stream_lds_t<1, GATEUP, 4, true>(a, st);
   return two ? launch_stream_lds_t<2, GATEUP, 4, false>(a, st) : launch_stream_lds_t<1, GATEUP, 4, false>(a, st);
 }
