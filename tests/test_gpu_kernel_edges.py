@@ -369,11 +369,11 @@ def test_output_is_bitwise_independent_of_blocks_streams_and_sequence(moe, oracl
 
 
 @pytest.mark.parametrize("T", [1, 13, 16, 17, 32, 33])
-@pytest.mark.parametrize("shared_memory", ["workspaces", "Xp", "out", "src_of_row", "S", "x"])
+@pytest.mark.parametrize("shared_memory", ["workspaces", "Xp", "out", "src_of_row", "S", "x", "out over x"])
 def test_layer_in_one_call_with_memory_shared_between_its_steps(moe, oracle64, T, shared_memory):
     # One buffer as every workspace; or the shared expert's scratch in memory of a step that is over by then (the row
     # copies, the index list) or not yet begun (the output), or S or the tokens behind the hidden rows, in room that this K is
-    # not cut for (17 steps): right when the steps run in turn, so right in one call too.
+    # not cut for (17 steps); or the output one row behind the tokens: right when the steps run in turn, so right in one call too.
     H, E, K, I, Is = 192, 8, 1, 256, 1088
     print(f"[case] layer in one call, shared memory: {shared_memory}, T={T}", flush=True)
     w = workloads.layer_weights(H, E, I, Is, 70 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
@@ -384,6 +384,10 @@ def test_layer_in_one_call_with_memory_shared_between_its_steps(moe, oracle64, T
     need = moe.moe_workspace_bytes(T, H, E, K, I, Is)
     if shared_memory == "workspaces":
         buf.workspace = buf.workspace_shared = buf.workspace_permute = torch.empty(need, dtype=torch.uint8, device="cuda")
+    elif shared_memory == "out over x":
+        both = torch.empty((T + 1, H), dtype=torch.bfloat16, device="cuda")
+        both[:T] = xg
+        xg, buf.out = both[:T], both[1:]
     else:
         whole = torch.empty(need, dtype=torch.uint8, device="cuda")
         buf.workspace_shared = whole
@@ -492,6 +496,23 @@ def test_residual_step_from_the_aggregation_has_the_bits_of_its_own_call(moe, mo
         cur = moe.moe_residual_norm(cur, buf.out, eps=1e-5)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int16), cur.view(torch.int16))
+
+
+@pytest.mark.parametrize("T", [1, 5, 33, 130])
+@pytest.mark.parametrize("where", ["x", "out", "Yp", "S", "Xp"])
+def test_residual_step_into_memory_of_the_layer(moe, T, where):
+    # the next layer's tokens may take the place of anything that is over by then, also of rows the aggregation still reads
+    H, E, K, I, Is = 192, 8, 2, 64, 128
+    print(f"[case] residual step into {where} T={T}", flush=True)
+    w = {k: v.cuda() for k, v in workloads.layer_weights(H, E, I, Is, 40 + T, 0.05, 0.1, torch.bfloat16, device="cpu").items()}
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+    expect = moe.moe_stack_forward(x, [w], K, False)
+    buf = moe.LayerBuffers.allocate(T, H, E, K, I, Is)
+    cur = x.clone()
+    into = cur if where == "x" else getattr(buf, where)[:T]
+    got = moe.moe_stack_forward(cur, [w], K, False, buf=buf, x_out=into)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), expect.view(torch.int16))
 
 
 @pytest.mark.parametrize("T,H,Is", [(383, 64, 11264), (384, 192, 11200), (385, 64, 11264), (6000, 2048, 64)])
