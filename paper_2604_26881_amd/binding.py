@@ -466,13 +466,13 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
     # With a second stream the shared expert inside the routed experts' launches is the faster way up to 16 tokens of a
     # captured layer (60 experts of H 2048, I 1408, Is 5632: T = 1 58 -> 44 us; 17: 144 against 151).  In eager launches
     # the waits that keep the second stream's order cost 23 us: there it pays where the kernels take less time than the
-    # 97 us of host work of the calls one by one, up to about 240 MB of weights (same layer, the calls one by one against
-    # one: T = 1 100 and 67 us, 8 105 and 120, 13 129 and 147).
+    # 97 us of host work of the calls one by one, up to about 330 MB of weights (same layer, the calls one by one against
+    # one: T = 1 93 and 74 us, 3 92 and 88, 4 92 and 92, 5 92 and 97, 13 129 and 147).
     if shared is not None and shared_stream is not None:
         if T > 16 or policy != 0 or shared_policy != 0 or load().moe_layer_shared_sets(T, H, E, K, I, shared[0].shape[0]) == 0:
             return False
         weights = 6 * H * (min(E, T * K) * I + shared[0].shape[0])
-        if weights > 240e6 and not torch.cuda.is_current_stream_capturing():
+        if weights > 330e6 and not torch.cuda.is_current_stream_capturing():
             return False
     ids, src = buf.topk_ids, buf.src_of_row
     if any(t is None for t in (ids, buf.topk_w, buf.expert_offsets, src, buf.row_of_pair, x if fused_gather else buf.Xp, buf.Yp,
