@@ -466,7 +466,7 @@ def _layer_in_one_call(x, Wr, bias, Wg, Wu, Wd, shared, K, renorm, groups, buf, 
     # With a second stream the shared expert inside the routed experts' launches is the faster way up to 16 tokens of a
     # captured layer (60 experts of H 2048, I 1408, Is 5632: T = 1 58 -> 44 us; 17: 144 against 151).  In eager launches
     # the waits that keep the second stream's order cost 23 us: there it pays where the kernels take less time than the
-    # 97 us of host work of the calls one by one, up to about 330 MB of weights (same layer, the calls one by one against
+    # 92 us of host work of the calls one by one, up to about 330 MB of weights (same layer, the calls one by one against
     # one: T = 1 93 and 74 us, 3 92 and 88, 4 92 and 92, 5 92 and 97, 13 129 and 147).
     if shared is not None and shared_stream is not None:
         if T > 16 or policy != 0 or shared_policy != 0 or load().moe_layer_shared_sets(T, H, E, K, I, shared[0].shape[0]) == 0:
