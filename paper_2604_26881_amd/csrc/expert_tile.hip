@@ -16,7 +16,7 @@
 // b mod 8; the index walk hands each XCD runs of consecutive tiles that share weight and token
 // panels, so they meet in that XCD's L2.
 //
-// Inside a tile: 4 waves, K steps of 64 through a ring of NS LDS stages.  Both panels are copied
+// Inside a tile: 4 waves (8 for 256x256, below), K steps of 64 through a ring of NS LDS stages.  Both panels are copied
 // from global memory straight into LDS (global_load_lds, 16 bytes per lane, no registers in
 // between).  Eight lanes fetch one row's 128 bytes, so every request is a whole cache line: with
 // 64-byte requests the L2-to-LDS path delivered 27 B/clk per CU, with 128-byte requests 47 B/clk
@@ -39,6 +39,13 @@
 // -> 80-84); 52 rows: 152-174 -> 138.  Experts of several tiles share weight panels through L2, which the
 // hint throws away (60 experts of 273 rows: 256 -> 293 us): those keep the plain requests.  The start
 // depends on nothing but the expert, the column and the tile shape, so results do not depend on the block cut.
+// Waves: one per SIMD with up to 512 registers, except 256x256: two per SIMD (2x4 waves of 128x64).  These read 1.5 times as
+// much from LDS (192 of the 256 KB a stage's 2048 MFMA clocks allow for), but tile border and epilogue, which one wave per SIMD
+// walks through alone, take half the time: K loops are 90 % of a workgroup's time instead of 83 %.  Gate/up, 4 -> 8 waves:
+// 16 384 rows of the shared expert 643 -> 607 us (1.25 PFLOP/s), 60 experts of 1092 rows 788 -> 727, of 300 344 -> 305, of 200
+// 212 -> 191; the down projection 297 -> 295, 422 -> 412, 172 -> 166, 104 -> 100.  Smaller shapes gain nothing (128x256 as
+// 2x4, 1x8 or 4x2 waves: equal within 2 %, 192x256 slower for the down projection: 87 -> 103 us at 4096 rows): their LDS reads
+// grow past the MFMA time, and where experts stream weights the waves wait for memory.
 // Rows past the end of an expert are clamped on load (they recompute the expert's last row) and
 // masked on store, which keeps the K loop free of branches.
 #include <math.h>
@@ -59,8 +66,9 @@ struct TileShape {
   static constexpr int NB = WTN / 32;             // 32-row weight blocks per wave
   static constexpr int NBH = GATEUP ? NB / 2 : NB;
   static constexpr int STAGE = (BM + BN) * ROWB;  // bytes per LDS stage
-  static constexpr int NL = (BM + BN) / 32;       // 1 KB (8-row) copies per wave and stage
-  static constexpr int NLA = BM / 32;             // the first NLA of them are token rows
+  static constexpr int NW = WAVES_M * WAVES_N;      // waves per workgroup
+  static constexpr int NL = (BM + BN) / (8 * NW);  // 1 KB (8-row) copies per wave and stage
+  static constexpr int NLA = BM / (8 * NW);        // the first NLA of them are token rows
   static constexpr int NF = TB + NB;              // operand fragments per wave and 16-wide K slice
   static constexpr int NM = TB * NB;              // MFMAs per wave and 16-wide K slice
   static constexpr int DIST = NS - 1;             // stages in flight while one is being multiplied
@@ -73,10 +81,10 @@ struct TileShape {
   static constexpr int ISSUE0 = NL - 2 * (NL / 3);
   static constexpr int ISSUE1 = NL / 3;
   static constexpr int ISSUE2 = NL / 3;
-  static_assert(WAVES_M * WAVES_N == 4, "four waves per workgroup");
+  static_assert(NW == 4 || NW == 8, "one or two waves per SIMD");
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of 32x32 blocks");
   static_assert(!GATEUP || NB % 2 == 0, "gate and up blocks come in pairs");
-  static_assert(BM % 32 == 0 && BN % 64 == 0, "copies of 8 rows are dealt to 4 waves");
+  static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0, "copies of 8 rows are dealt to the waves");
   static_assert((NS - 1) * NL < 64, "the wait counter holds 6 bits");
 };
 
@@ -94,7 +102,7 @@ __host__ __device__ constexpr int fragment_read_order(int slot, int tb, int nb) 
 // K, sets its sums aside at the end of a part and adds them in the order of the kernel that adds the parts otherwise:
 // the same bits without room for the parts, in the time of the uncut tile.
 template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC, int KSPLIT, bool SINGLE, bool INTURN>
-__global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4) void expert_tile_kernel(GemmArgs a) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
   extern __shared__ __align__(16) unsigned char smem[];
   // Experts come in two classes.  One with at least HEAVY_MIN token tiles reuses every weight panel
@@ -201,7 +209,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
 #define MOE_TILE_ISSUE1(kt, st, i, once_)                                                           \
     copy_to_lds_16(                                                                                 \
         ((i) < S::NLA ? Ag : ((GATEUP && (i) >= S::NLA + (S::NL - S::NLA) / 2) ? Bg1 : Bg0)) + (size_t)(kt) * S::ROWB, \
-        coff[i], lds0 + (uint32_t)(st) * S::STAGE + (uint32_t)wave * 1024u + (uint32_t)(i) * 4096u, (once_) && (i) >= S::NLA);
+        coff[i], lds0 + (uint32_t)(st) * S::STAGE + (uint32_t)wave * 1024u + (uint32_t)(i) * (S::NW * 1024u), (once_) && (i) >= S::NLA);
 
   // State of a tile: the current one (being multiplied, then stored) and, while the current one is
   // stored, the next one, whose first NS stages are already requested: the latency of those copies
@@ -283,7 +291,7 @@ __global__ __launch_bounds__(256, OCC) void expert_tile_kernel(GemmArgs a) {
                  : nullptr;
 #pragma unroll
     for (int i = 0; i < S::NL; ++i) {
-      const int row = (i * 4 + wave) * 8 + crow;        // row inside the stage: tokens first, then weights
+      const int row = (i * S::NW + wave) * 8 + crow;        // row inside the stage: tokens first, then weights
       int grow;
       uint32_t ld = (uint32_t)Kdim;
       if (i < S::NLA) {
@@ -622,7 +630,7 @@ static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   GemmArgs launched = a;
   launched.clocks = t_clock_buffer;
   launched.clock_groups = t_clock_groups;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), lds, st, launched);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * S::NW), lds, st, launched);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
@@ -664,7 +672,9 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
   TileChoice best{129, 1};
   double best_cost = 0.0;
   for (const Cand& k : cands) {
-    if (k.bm >= 192 && leave_room) continue;   // 256x256 holds all 512 registers of every SIMD, 192x256 426 of them
+    // 192x256 leaves other kernels 86 registers of a SIMD and 45 KB of LDS.  (256x256, two waves of 210 registers per SIMD
+    // and 128 KB, does not keep the row sort waiting: 16 384 tokens beside gating and sort 2312 us with 128x256, 2220 with it.)
+    if (k.bm == 192 && leave_room) continue;
     const int most = gateup || !k.cut ? 1 : std::max(1, std::min(parts_max, largest_ksplit(Kdim)));
     for (int parts = 1; parts <= most; parts *= 2) {
       if (k.code == 64 && !gateup && parts == 1) continue;   // (128x128 serves such a batch better)
@@ -732,7 +742,7 @@ int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st) {
   const int t = pick_tile(a, tile_rows, true).code;
   if (t == 64) return launch_tile_t<128, 64, 4, 1, true, 6, 1>(a, st);
   if (t == 130) return launch_tile_t<128, 128, 2, 2, true, 4, 1>(a, st);
-  if (t >= 256) return launch_tile_t<256, 256, 2, 2, true, 2, 1>(a, st);
+  if (t >= 256) return launch_tile_t<256, 256, 2, 4, true, 2, 1>(a, st);
   if (t == 192) return launch_tile_s<192, 256, 2, 2, true, 2, 1, 1, false>(a, st);   // (one weight set only)
   if (t == 160) return launch_tile_t<160, 256, 1, 4, true, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, true, 3, 1>(a, st);
@@ -761,7 +771,7 @@ int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* part
   *parts = in_turn ? 1 : c.parts;
   if (t == 64) return launch_tile_cut<64, 4, 1, 6>(a, c.parts, in_turn, st);   // (without parts: whole K per tile)
   if (t == 130) return launch_tile_cut<128, 2, 2, 4>(a, c.parts, in_turn, st);
-  if (t >= 256) return launch_tile_t<256, 256, 2, 2, false, 2, 1>(a, st);
+  if (t >= 256) return launch_tile_t<256, 256, 2, 4, false, 2, 1>(a, st);
   if (t == 192) return launch_tile_s<192, 256, 2, 2, false, 2, 1, 1, false>(a, st);
   if (t == 160) return launch_tile_t<160, 256, 1, 4, false, 3, 1>(a, st);
   return launch_tile_t<128, 256, 1, 4, false, 3, 1>(a, st);
