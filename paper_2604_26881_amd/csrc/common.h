@@ -121,6 +121,7 @@ struct GemmArgs {
   int shared_parts;        // (streaming kernel, down) K parts of the shared contraction, of part_steps steps of 64 each,
   int part_steps;          // the first part_extra of them one more
   int part_extra;
+  int rot_shift;           // (tile kernels) log2 of the output columns that share a K start: those of a tile of the layer's shape
 };
 // Raises a kernel's dynamic LDS limit once per device: one bit per device id in `done` (the kernel's own),
 // set after the call has succeeded there (two threads may both make the call; it is idempotent).

@@ -38,7 +38,7 @@
 // without either, 166-177 with the rotation alone, 180 with the hint alone, 153-158 with both (down 88-96
 // -> 80-84); 52 rows: 152-174 -> 138.  Experts of several tiles share weight panels through L2, which the
 // hint throws away (60 experts of 273 rows: 256 -> 293 us): those keep the plain requests.  The start
-// depends on nothing but the expert, the column and the tile shape, so results do not depend on the block cut.
+// depends on nothing but the expert, the column and the tile shape of the layer, so results do not depend on the block cut.
 // Waves: one per SIMD with up to 512 registers, except 256x256: two per SIMD (2x4 waves of 128x64).  These read 1.5 times as
 // much from LDS (192 of the 256 KB a stage's 2048 MFMA clocks allow for), but tile border and epilogue, which one wave per SIMD
 // walks through alone, take half the time: K loops are 90 % of a workgroup's time instead of 83 %.  Gate/up, 4 -> 8 waves:
@@ -64,7 +64,10 @@ struct TileShape {
   static constexpr int WTN = BN / WAVES_N;        // weight rows per wave
   static constexpr int TB = WTM / 32;             // 32-row token blocks per wave
   static constexpr int NB = WTN / 32;             // 32-row weight blocks per wave
-  static constexpr int NBH = GATEUP ? NB / 2 : NB;
+  // Gate/up with one weight block per wave: its 32 rows are 8 gate rows, the matching 8 up rows, and both again
+  // (16 output columns per wave), so a lane still holds gate and up of a column (elements i and i + 4).
+  static constexpr bool MIXED = GATEUP && NB == 1;
+  static constexpr int NBH = GATEUP && !MIXED ? NB / 2 : NB;
   static constexpr int STAGE = (BM + BN) * ROWB;  // bytes per LDS stage
   static constexpr int NW = WAVES_M * WAVES_N;      // waves per workgroup
   static constexpr int NL = (BM + BN) / (8 * NW);  // 1 KB (8-row) copies per wave and stage
@@ -83,7 +86,7 @@ struct TileShape {
   static constexpr int ISSUE2 = NL / 3;
   static_assert(NW == 4 || NW == 8, "one or two waves per SIMD");
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of 32x32 blocks");
-  static_assert(!GATEUP || NB % 2 == 0, "gate and up blocks come in pairs");
+  static_assert(!GATEUP || NB == 1 || NB % 2 == 0, "gate and up blocks come in pairs");
   static_assert(BM % (8 * NW) == 0 && BN % (16 * NW) == 0, "copies of 8 rows are dealt to the waves");
   static_assert((NS - 1) * NL < 64, "the wait counter holds 6 bits");
 };
@@ -192,6 +195,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   const int cchunk = (lane & 7) ^ (lane >> 3);
   // operand reads: row lane%32 of a 32-row block, chunk 2*kk + lane/32 of the row
   const int frag_row = lane & 31;
+  const int wfrag_row = S::MIXED ? ((frag_row >> 3) & 1) * (BN / 2) + (frag_row >> 4) * 8 + (frag_row & 7) : frag_row;
   const int frag_half = lane >> 5;
   const int frag_swz = lane & 7;
 
@@ -323,7 +327,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
       }
     };
     if (SINGLE && t.once) {
-      krot = (int)((unsigned)(eg * 5 + nt * 3) % (unsigned)nk);
+      krot = (int)((unsigned)(eg * 5 + (t.n0 >> a.rot_shift) * 3) % (unsigned)nk);
       request(std::true_type{});
     } else {
       request(std::false_type{});
@@ -365,10 +369,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
             As_ + (wm * S::WTM + (f_) * 32 + frag_row) * S::ROWB + cr_));                            \
       } else {                                                                                      \
         const int nb_ = (f_) < TBc ? 0 : (f_) - TBc;                                                \
-        const int brow_ = GATEUP ? ((nb_ < S::NBH ? 0 : BN / 2) + wn * (S::WTN / 2) + (nb_ % S::NBH) * 32) \
+        const int brow_ = S::MIXED ? wn * 16 : GATEUP ? ((nb_ < S::NBH ? 0 : BN / 2) + wn * (S::WTN / 2) + (nb_ % S::NBH) * 32) \
                                  : (wn * S::WTN + nb_ * 32);                                         \
         fb_[nb_] = as_bf16x8(*reinterpret_cast<const u32x4*>(                                        \
-            As_ + BM * S::ROWB + (brow_ + frag_row) * S::ROWB + cr_));                               \
+            As_ + BM * S::ROWB + (brow_ + wfrag_row) * S::ROWB + cr_));                              \
       }                                                                                             \
     }
 #define MOE_TILE_READ(fa_, fb_, stage_, kk_)                                                        \
@@ -531,7 +535,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     auto out_value = [&](int nb, int tb, int i) -> float {
       if (GATEUP) {
         const float g = acc[nb][tb][i];
-        const float u = acc[nb + S::NBH][tb][i];
+        const float u = S::MIXED ? acc[nb][tb][i + 4 < 16 ? i + 4 : i] : acc[S::MIXED ? nb : nb + S::NBH][tb][i];
         return __fdividef(g, 1.0f + __expf(-g)) * u;
       }
       return acc[nb][tb][i];
@@ -544,7 +548,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
 #pragma unroll
         for (int nb = 0; nb < S::NBH; ++nb) {
           const int nblock = n0 + (GATEUP ? wn * (S::WTN / 2) : wn * S::WTN) + nb * 32;   // first column of the 32-column block
-          if (nblock < a.N) {   // N is a multiple of 64 and nblock of 32: the block is inside or outside as a whole
+          if (nblock < a.N) {   // N is a multiple of 64, nblock of 32 (of 16, and 16 columns, for MIXED): inside or outside as a whole
             if (ITEMS > 1) {   // fp32 partial sum of K part ks; summed in order by the reduce kernel
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
@@ -555,11 +559,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
               }
             } else if (GATEUP) {
 #pragma unroll
-              for (int q = 0; q < 4; ++q) {
+              for (int q = 0; q < 4; q += S::MIXED ? 2 : 1) {
                 uint2 o;
                 o.x = pack_bf16x2(out_value(nb, tb, 4 * q), out_value(nb, tb, 4 * q + 1));
                 o.y = pack_bf16x2(out_value(nb, tb, 4 * q + 2), out_value(nb, tb, 4 * q + 3));
-                *reinterpret_cast<uint2*>(crow_out + nblock + 4 * frag_half + 8 * q) = o;
+                *reinterpret_cast<uint2*>(crow_out + nblock + 4 * frag_half + (S::MIXED ? 4 : 8) * q) = o;
               }
             } else {
 #pragma unroll
@@ -661,6 +665,7 @@ static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
 static int largest_ksplit(int Kdim) { return Kdim % 512 == 0 ? 8 : Kdim % 256 == 0 ? 4 : Kdim % 128 == 0 ? 2 : 1; }
 int tile_down_ksplit(int Kdim) { return largest_ksplit(Kdim); }
 struct TileChoice { int code, parts; };
+constexpr int NARROW_160 = 1601, NARROW_256 = 2561;   // 160x128 and 256x128: only launched in place of the wider ones (pick_tile)
 static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int parts_max, bool leave_room) {
   struct Cand { int code, bm, nout; double c; bool cut; };
   const Cand cands[6] = {{256, 256, gateup ? 128 : 256, 1.0, false}, {192, 192, gateup ? 128 : 256, 1.03, false},
@@ -699,7 +704,7 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
 // Measured on uniform routing at T = 768 ... 8192 the pick is the fastest shape or within 3 % of
 // it; Zipf-skewed routing (mean 273, median 130) and the multi-tenant batch (mean 137) also run
 // fastest on its choice (160).
-static TileChoice pick_tile(const GemmArgs& a, int tile_rows, bool gateup) {
+static TileChoice pick_layer_tile(const GemmArgs& a, int tile_rows, bool gateup) {
   if (tile_rows == 64 && !gateup && a.parts_max > 0) return TileChoice{64, std::min(a.parts_max, largest_ksplit(a.Kdim))};
   if (tile_rows != 0) return TileChoice{tile_rows, 1};
   if (a.offsets == nullptr) return pick_tile_shape(a.rows_total, a.N, a.Kdim, gateup, a.parts_max, a.leave_room != 0);
@@ -738,8 +743,49 @@ static TileChoice pick_tile(const GemmArgs& a, int tile_rows, bool gateup) {
   }
   return TileChoice{best, 1};
 }
-int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st) {
+// What a call launches for the layer's tile shape.  A call on a block of a few experts can have fewer tiles than the chip
+// has compute units; narrower tiles of the same height then give more of them work.  Every output element is summed in the
+// same order whatever the tile's columns (the K start of a single-tile expert goes by the columns of the layer's shape), so
+// the bits stay those of the uncut layer.  cost = rounds x columns x factor (a step of a tile of half the columns takes
+// more than half the time), the rounds counted for even routing and, weighing more, for skewed routing: with a mean of r
+// tiles of rows, experts then take 1 + 1.15 (r - 0.3) tiles on average (r + 0.8 beyond one; four tenants with normal router
+// biases, 700 to 3000 tokens).  The skew decides close cases: 15 experts of 137 rows even are 120 tiles of the down
+// projection, 240 half ones take 27 instead of 34 us, but skewed they are 152-192 and the half ones take two rounds.  What
+// wins by less than a tenth is left alone (16 of 64 experts of H 1536, I 1024 at 84 rows, 128x64 for 128x128: 3 us more).
+// us, one call per block, 256 -> narrower: 60 experts of H 2048, I 1408 in blocks of 7 at 137 rows 41+31 -> 32+23, of 15
+// at 200 rows 69+47 -> 61+31, at 52 rows 39+28 -> 39+22; 16 of H 3072, I 4096 at 100 rows in blocks of 4 63+58 -> 46+36,
+// of 2 54+56 -> 32+31; 8 of H 4096, I 7168 in blocks of 2 at 60 rows 61+62 -> 45+45, at 250 rows 88+103 -> 88+76.
+static int tile_columns(int code, bool gateup) {
+  const int bn = code == 64 ? 64 : code == 130 || code == NARROW_160 || code == NARROW_256 ? 128 : 256;
+  return gateup ? bn / 2 : bn;
+}
+static TileChoice pick_tile(GemmArgs& a, int tile_rows, bool gateup) {
+  TileChoice c = pick_layer_tile(a, tile_rows, gateup);
+  a.rot_shift = __builtin_ctz(tile_columns(c.code, gateup));
+  if (tile_rows != 0 || a.offsets == nullptr || a.n_shared > 0) return c;
+  const int layer = c.code;
+  const int f = layer == 256 ? 0 : layer == 160 ? 1 : 2;
+  const int family[3][3] = {{256, NARROW_256, 0}, {160, NARROW_160, 0}, {129, 130, 64}};
+  const double factor[3] = {1.0, 1.29, 1.75};
+  const int heights[3] = {256, 160, 128};
+  const double r = (double)a.mean_rows / heights[f], cus = (double)num_cus();
+  const double even = ceil(((double)a.mean_rows + 1.5 * sqrt((double)a.mean_rows)) / heights[f]);
+  const double skewed = r < 0.3 ? 1.0 : r < 1.0 ? 1.0 + 1.15 * (r - 0.3) : r + 0.8;
+  double best = 0.0;
+  for (int i = 0; i < 3 && family[f][i] != 0; ++i) {
+    const int nout = tile_columns(family[f][i], gateup);
+    if (nout > tile_columns(layer, gateup)) continue;
+    const double per_row_tile = (double)(a.hi - a.lo) * (double)((a.N + nout - 1) / nout);
+    const double cost = (ceil(per_row_tile * even / cus) + 2.0 * ceil(per_row_tile * skewed / cus)) * nout * factor[i];
+    if (best == 0.0 || cost < 0.9 * best) { best = cost; c.code = family[f][i]; }
+  }
+  return c;
+}
+int launch_tile_gateup(const GemmArgs& layer, int tile_rows, hipStream_t st) {
+  GemmArgs a = layer;
   const int t = pick_tile(a, tile_rows, true).code;
+  if (t == NARROW_160) return launch_tile_t<160, 128, 1, 4, true, 4, 1>(a, st);
+  if (t == NARROW_256) return launch_tile_t<256, 128, 2, 2, true, 3, 1>(a, st);
   if (t == 64) return launch_tile_t<128, 64, 4, 1, true, 6, 1>(a, st);
   if (t == 130) return launch_tile_t<128, 128, 2, 2, true, 4, 1>(a, st);
   if (t >= 256) return launch_tile_t<256, 256, 2, 4, true, 2, 1>(a, st);
@@ -764,11 +810,14 @@ static int launch_tile_cut(const GemmArgs& a, int parts, bool in_turn, hipStream
   }
 }
 // *parts: in how many K parts the output was left in a.Cpart (1: the output itself is written)
-int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* parts) {
+int launch_tile_down(const GemmArgs& layer, int tile_rows, hipStream_t st, int* parts) {
+  GemmArgs a = layer;
   const TileChoice c = pick_tile(a, tile_rows, false);
   const int t = c.code;
   const bool in_turn = c.parts > std::max(1, a.parts_room);
   *parts = in_turn ? 1 : c.parts;
+  if (t == NARROW_160) return launch_tile_t<160, 128, 1, 4, false, 4, 1>(a, st);
+  if (t == NARROW_256) return launch_tile_t<256, 128, 2, 2, false, 3, 1>(a, st);
   if (t == 64) return launch_tile_cut<64, 4, 1, 6>(a, c.parts, in_turn, st);   // (without parts: whole K per tile)
   if (t == 130) return launch_tile_cut<128, 2, 2, 4>(a, c.parts, in_turn, st);
   if (t >= 256) return launch_tile_t<256, 256, 2, 4, false, 2, 1>(a, st);

@@ -529,3 +529,22 @@ def test_shared_expert_in_192_row_tiles(moe, oracle64, T, H, Is):
     S_ref, sg_ref = oracle64.shared_forward(x.float().numpy(), *[w[k].float().numpy() for k in ("Wsg", "Wsu", "Wsd", "wgate")])
     check_close(f64(S), S_ref, "S")
     assert np.allclose(sg.cpu().numpy(), sg_ref, rtol=1e-4, atol=1e-5)
+
+
+@pytest.mark.parametrize("mean,bm", [(60, 128), (140, 160), (232, 256)])     # the height of the layer's tiles
+@pytest.mark.parametrize("H,I", [(256, 1152), (2304, 64)])                   # full width in gate/up, in the down projection
+def test_calls_on_a_few_experts_take_narrower_tiles_to_the_same_bits(moe, oracle64, mean, bm, H, I):
+    # 60 experts: the uncut call has two rounds of whole tiles, calls on a few of them have compute units to spare
+    E = 60
+    edges = [bm - 1, bm, bm + 1, 0, 1, 31, 32, 33, 64, bm - 32, 2 * bm + 1]
+    counts = (edges * 6)[:E]
+    rest = (mean * E - sum(counts)) // 20
+    counts = [n + (rest if i % 3 == 2 else 0) for i, n in enumerate(counts)]
+    counts = [max(0, n) for n in counts]
+    print(f"[case] narrower tiles mean={mean} H={H} I={I}", flush=True)
+    c = block_case(oracle64, counts, H, I, 300 + mean)
+    Yp = run_blocks(moe, c, 0)
+    check_close(f64(Yp), c["ref"], f"Yp mean {mean}")
+    for cuts in ([(i, i + 1) for i in range(E)], [(0, 3), (3, 10), (10, 17), (17, 32), (32, 40), (40, 60)]):
+        Yc = run_blocks(moe, c, 0, cuts)
+        assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16)), cuts[:2]
