@@ -115,11 +115,18 @@ void set_shared_parts(GemmArgs& dn, int parts, int Is) {
 // columns of its hidden layer h [T,Is], and its output as `parts` fp32 parts [T,H].
 struct Riders { const void *x, *Wsg, *Wsu, *Wsd; void* h; float* part; int sets, parts, T, Is; };
 
+// The micro-batch of a layer with few pairs, constructed inside the first launch of its experts (see expert_stream_lds.hip)
+struct Sort { const int32_t* ids; int32_t *offsets, *src, *rows; void* Xp; };
+bool sort_in_gateup(int P, int H, int E) {
+  const int mean_rows = (P + E - 1) / E;
+  return P <= SORT_HERE_MAX && E > 1 && make_plan(mean_rows, E, 0).stream && stream_narrow(mean_rows, H);
+}
+
 int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, const void* A, const int32_t* gather,
                               int gather_div,
                               const int32_t* expert_offsets, const void* Wg, const void* Wu, const void* Wd, int P,
                               int H, int E, int I, void* Yp, void* workspace, size_t workspace_bytes, int policy,
-                              void* stream, const Riders* riders = nullptr) {
+                              void* stream, const Riders* riders = nullptr, const Sort* sort = nullptr) {
   if (P < 0 || !dims_ok(H) || !dims_ok(I) || E < 1 || E > 256) return MOE_ERR_SHAPE;
   if (group_lo < 0 || group_hi > E || group_lo >= group_hi) return MOE_ERR_SHAPE;
   if ((long long)P * (H > I ? H : I) >= (1ll << 31)) return MOE_ERR_SHAPE;
@@ -138,6 +145,10 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
   gu.gather = gather; gu.gather_div = gather_div;   // only the first kernel reads token rows
   dn.A = (const bf16_t*)workspace; dn.B0 = (const bf16_t*)Wd; dn.B1 = nullptr; dn.C = (bf16_t*)Yp;
   dn.N = H; dn.Kdim = I;
+  if (sort != nullptr) {
+    gu.sort_ids = sort->ids; gu.n_pairs = P; gu.sort_offsets = sort->offsets; gu.sort_src = sort->src; gu.sort_rows = sort->rows;
+    gu.sort_copy = (bf16_t*)sort->Xp;
+  }
   if (riders != nullptr) {
     gu.n_shared = riders->sets;
     dn.n_shared = riders->parts;
@@ -248,15 +259,23 @@ int moe_route_segments(const void* x, const void* Wr, const float* bias_rows, co
                       (hipStream_t)stream);
 }
 
-int moe_permute(const int32_t* topk_ids, const void* x, int T, int H, int E, int K, int32_t* expert_offsets,
-                int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* workspace, size_t workspace_bytes,
-                void* stream) {
+static int permute_refusal(const int32_t* topk_ids, const void* x, int T, int H, int E, int K, const int32_t* expert_offsets,
+                           const int32_t* src_of_row, const int32_t* row_of_pair, const void* Xp, const void* workspace,
+                           size_t workspace_bytes) {
   if (T < 0 || !dims_ok(H) || E < 1 || E > 256 || K < 1 || K > 16 || K > E) return MOE_ERR_SHAPE;
   if ((long long)T * K * H >= (1ll << 31)) return MOE_ERR_SHAPE;
   if (!expert_offsets) return MOE_ERR_NULL;
   if (T > 0 && (!topk_ids || !src_of_row || !row_of_pair || !workspace)) return MOE_ERR_NULL;
   if (T > 0 && Xp && !x) return MOE_ERR_NULL;   // Xp == NULL: index arrays only, x is not read
   if (T > 0 && workspace_bytes < (((size_t)T * K + 63) / 64) * (size_t)E * 4) return MOE_ERR_WORKSPACE;
+  return MOE_OK;
+}
+
+int moe_permute(const int32_t* topk_ids, const void* x, int T, int H, int E, int K, int32_t* expert_offsets,
+                int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* workspace, size_t workspace_bytes,
+                void* stream) {
+  const int rc = permute_refusal(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, workspace, workspace_bytes);
+  if (rc != MOE_OK) return rc;
   return launch_permute(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, workspace,
                         (hipStream_t)stream);
 }
@@ -508,8 +527,8 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                ? moe_route_segments(x, Wr, bias, seg_offsets, n_seg, T, H, E, K, renorm, topk_ids, topk_w, stream)
                : moe_route(x, Wr, bias, T, H, E, K, renorm, topk_ids, topk_w, stream);
   if (rc != MOE_OK) return rc;
-  rc = moe_permute(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, permute_workspace,
-                   permute_workspace_bytes, stream);
+  rc = permute_refusal(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, permute_workspace,
+                       permute_workspace_bytes);
   if (rc != MOE_OK) return rc;
   const int P = T * K, sets = moe_layer_shared_sets(T, H, E, K, I, Is);
   const size_t h_bytes = sets > 0 ? align256((size_t)T * (size_t)Is * 2) : 0;
@@ -531,11 +550,28 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                     apart(riding, riding_bytes, sg, (size_t)T * 4) && apart(riding, riding_bytes, S, x_bytes) &&
                     apart(riding, riding_bytes, x, x_bytes) && apart(riding, riding_bytes, out, x_bytes) &&
                     apart(riding, riding_bytes, next, next ? x_bytes : 0);
+  // The sort inside the experts' first launch: that launch then reads the ids and x, and writes the sorted arrays, beside
+  // the hidden rows (and those of a riding shared expert).
+  const size_t h_routed = (size_t)P * (size_t)I * 2, offsets_bytes = ((size_t)E + 1) * 4;
+  const auto beside_hidden = [&](const void* p, size_t n) {
+    return apart(p, n, workspace, h_routed) && (!ride || apart(p, n, riding, riding_bytes));
+  };
+  const bool sort_here = T > 0 && policy == 0 && sort_in_gateup(P, H, E) && beside_hidden(topk_ids, pairs) && beside_hidden(x, x_bytes) &&
+                         beside_hidden(expert_offsets, offsets_bytes) && beside_hidden(src_of_row, pairs) &&
+                         beside_hidden(row_of_pair, pairs) && apart(topk_ids, pairs, expert_offsets, offsets_bytes) &&
+                         apart(topk_ids, pairs, src_of_row, pairs) && apart(topk_ids, pairs, row_of_pair, pairs) &&
+                         (!copied || (apart(Xp, (size_t)P * (size_t)H * 2, x, x_bytes) && beside_hidden(Xp, (size_t)P * (size_t)H * 2)));
+  if (!sort_here) {
+    rc = launch_permute(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, permute_workspace, (hipStream_t)stream);
+    if (rc != 0) return rc;
+  }
+  const Sort sort{topk_ids, expert_offsets, src_of_row, row_of_pair, Xp};
   Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, parts, T, Is};
   if (ride) riders.part = reinterpret_cast<float*>(static_cast<unsigned char*>(shared_workspace) + h_bytes);
-  rc = expert_group_forward_impl(group_lo, group_hi, nullptr, copied ? Xp : x, copied ? nullptr : src_of_row, copied ? 1 : K,
+  const bool from_x = sort_here || !copied;
+  rc = expert_group_forward_impl(group_lo, group_hi, nullptr, from_x ? x : Xp, from_x ? src_of_row : nullptr, from_x ? K : 1,
                                  expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
-                                 ride ? &riders : nullptr);
+                                 ride ? &riders : nullptr, sort_here ? &sort : nullptr);
   if (rc != MOE_OK) return rc;
   // The aggregation forms the gate logit and the residual step where no row that it still reads for another token lies
   // in what it writes for this one (x itself may be out or next: then the rows are the token's own); otherwise they are

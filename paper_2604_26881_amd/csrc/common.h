@@ -121,6 +121,14 @@ struct GemmArgs {
   int shared_parts;        // (streaming kernel, down) K parts of the shared contraction, of part_steps steps of 64 each,
   int part_steps;          // the first part_extra of them one more
   int part_extra;
+  // (narrow streaming kernel, gate/up of a few pairs) not nullptr: the micro-batch is constructed in this launch, from these
+  // expert ids of the n_pairs = T * K pairs; offsets and gather are written by it, and read by later launches only
+  const int32_t* sort_ids;
+  int n_pairs;
+  int32_t* sort_offsets;   // [experts_layer + 1]
+  int32_t* sort_src;       // src_of_row
+  int32_t* sort_rows;      // row_of_pair
+  bf16_t* sort_copy;       // not nullptr: the permuted copy Xp of the token rows (A)
   int rot_shift;           // (tile kernels) log2 of the output columns that share a K start: those of a tile of the layer's shape
 };
 // Raises a kernel's dynamic LDS limit once per device: one bit per device id in `done` (the kernel's own),
@@ -142,6 +150,20 @@ void set_tile_clock_buffer(long long* clocks, int groups);
 // bias [E] for all tokens (seg == nullptr), or bias [n_seg, E] with seg [n_seg + 1] segment bounds on the device
 int launch_route(const void* x, const void* Wr, const float* bias, const int32_t* seg, int n_seg, int T, int H, int E,
                  int K, int renorm, int32_t* ids, float* w, hipStream_t st);
+// Lanes of the wave whose (valid) pair has the same expert id as this lane's
+__device__ __forceinline__ unsigned long long match_expert(int e, bool valid, int nbits) {
+  unsigned long long match = __ballot(valid);
+  for (int b = 0; b < nbits; ++b) {
+    const unsigned long long bal = __ballot(valid && ((e >> b) & 1));
+    match &= ((e >> b) & 1) ? bal : ~bal;
+  }
+  return match;
+}
+__device__ __forceinline__ int bits_for(int E) {
+  int nbits = 0;
+  while ((1 << nbits) < E) ++nbits;
+  return nbits;
+}
 int launch_permute(const int32_t* ids, const void* x, int T, int H, int E, int K, int32_t* offsets,
                    int32_t* src_of_row, int32_t* row_of_pair, void* Xp, void* workspace, hipStream_t st);
 int launch_combine(const void* Yp, const int32_t* row_of_pair, const float* w, const void* S, int n_parts,
@@ -165,6 +187,7 @@ constexpr int STREAM_FEW_ROWS = 6;   // mean rows per expert up to which the nar
 // It also serves contractions of up to four K steps, where what counts is how soon a wave starts: 16 experts of H 256, I 256
 // at 7 to 26 rows, gate/up + down: 7.4-8.7 us narrow, 9.1-11 wide.
 inline bool stream_narrow(int mean_rows, int Kdim) { return mean_rows <= STREAM_FEW_ROWS || Kdim <= 256; }
+constexpr int SORT_HERE_MAX = 128;   // pairs up to which that kernel's gate/up launch constructs the micro-batch as well
 // Streaming kernels that stage the weights through wave-private LDS rings (whole-line requests): a few rows per
 // expert, and up to a few dozen.
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st);

@@ -41,6 +41,86 @@ struct StreamLdsShape {
   static_assert(D >= 1 && D * NI < 64, "the wait counter holds 6 bits");
 };
 
+// SORT (gate/up of a layer with few pairs): the launch constructs the micro-batch as well.  A wave needs little of it: how
+// many pairs chose its expert, how many a lower one, and which pairs its rows are.  Each reads that off the expert ids
+// themselves with a ballot per 64 pairs (in the place of two dependent loads of the sorted arrays), and the workgroups of
+// blockIdx.y == 0 write the arrays, and the row copies where asked for, for the launches that follow: the same stable
+// counting sort as in permute.hip, by one wave.
+// It saves a launch of 3-4 us and the gap before it, and costs every wave its look at the ids, also those of experts without
+// rows.  A layer, us, sorted in a launch of its own -> here: H 64, 16 tokens, top 2 25.8 -> 22.7; 60 experts of H 2048, I 1408,
+// top 4 at 1 token 46.4 -> 42.6, at 13 125.4 -> 122.9, at 30 (120 pairs) 182.2 -> 180.1; 256 of H 1024, I 256, top 8 at 8
+// tokens 39.6 -> 36.1, at 16 (128 pairs) 54.5 -> 52.9.  Beyond 128 pairs it turns: 160 pairs of the 60 experts 194 -> 198, 180
+// of 64 experts of H 1536 114 -> 118, 1024 of the 256 96 -> 148.
+constexpr int SORT_SPLIT = 16;   // waves that share the row copies of 64 pairs
+__device__ __forceinline__ int pair_expert(const GemmArgs& a, int p) {   // -1 past the last pair
+  return p < a.n_pairs ? min(max(a.sort_ids[p], 0), a.experts_layer - 1) : -1;   // (an id outside [0,E) stays in the tables)
+}
+__device__ __forceinline__ void sort_pairs(const GemmArgs& a, int* lds) {
+  int* const s_total = lds;          // pairs of expert e
+  int* const s_base = lds + 256;     // those in earlier chunks; then: first row of expert e for this chunk
+  int* const s_row = lds + 512;
+  const int lane = threadIdx.x, E = a.experts_layer, nbits = bits_for(E);
+  const int chunks = (a.n_pairs + 63) / 64, split = a.sort_copy != nullptr ? SORT_SPLIT : 1;
+  for (int item = blockIdx.x; item < chunks * split; item += gridDim.x) {
+    const int c = item / split, part = item % split;
+    for (int i = lane; i < 512; i += 64) lds[i] = 0;
+    __syncthreads();
+    for (int cc = 0; cc < chunks; ++cc) {
+      const int e = pair_expert(a, cc * 64 + lane);
+      const unsigned long long match = match_expert(max(e, 0), e >= 0, nbits);
+      if (e >= 0 && (match & ((1ull << lane) - 1ull)) == 0ull) {   // one lane per expert
+        s_total[e] += __popcll(match);
+        if (cc < c) s_base[e] += __popcll(match);
+      }
+      __syncthreads();
+    }
+    int v[4], sum = 0;   // exclusive scan of the totals over experts, four experts per lane
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[i] = s_total[lane * 4 + i];   // (zero beyond E)
+      sum += v[i];
+    }
+    int incl = sum;
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+      const int o = __shfl_up(incl, s, WAVE);
+      if (lane >= s) incl += o;
+    }
+    int base = incl - sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = lane * 4 + i;
+      s_base[e] += base;
+      if (item == 0 && e < E) a.sort_offsets[e] = base;
+      base += v[i];
+    }
+    if (item == 0 && lane == 63) a.sort_offsets[E] = incl;
+    __syncthreads();
+    const int p = c * 64 + lane, own = pair_expert(a, p);
+    const unsigned long long match = match_expert(max(own, 0), own >= 0, nbits);
+    int row = -1;
+    if (own >= 0) {
+      row = s_base[own] + __popcll(match & ((1ull << lane) - 1ull));
+      if (part == 0) {
+        a.sort_rows[p] = row;
+        a.sort_src[row] = p;
+      }
+    }
+    s_row[lane] = row;
+    __syncthreads();
+    if (a.sort_copy != nullptr) {
+      for (int i = part; i < 64; i += split) {
+        const int to = s_row[i];
+        if (to < 0) break;                      // pairs past the last sit at the end of the last chunk
+        const u32x4* src = reinterpret_cast<const u32x4*>(a.A + (size_t)((c * 64 + i) / a.gather_div) * a.Kdim);
+        u32x4* dst = reinterpret_cast<u32x4*>(a.sort_copy + (size_t)to * a.Kdim);
+        for (int j = lane; j < a.Kdim / 8; j += 64) dst[j] = src[j];
+      }
+    }
+    __syncthreads();
+  }
+}
+
 template <int J, int D, int NI, class F>
 __device__ __forceinline__ void stream_tail(F&& step) {
   if constexpr (J < D) {
@@ -64,19 +144,48 @@ __device__ __forceinline__ void stream_tail(F&& step) {
 // sum); together 19.2 and 11.3.  By itself (beside several blocks or on a second stream), with its sum and gate logits,
 // against those tiles: 1 token 32 -> 21 us, 32 tokens 32 -> 24; H 1024, Is 4032 42 -> 14.  From 17 tokens on a riding shared expert is read by two passes; up to 32 tokens that
 // still beats launches of their own on one stream.
-template <int MT, bool GATEUP, int NST, bool SHARED, bool TURN>
+template <int MT, bool GATEUP, int NST, bool SHARED, bool TURN, bool SORT>
 __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   using S = StreamLdsShape<MT, NST>;
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NPER = GATEUP ? 16 : 32;   // output columns of one item (two 16-row weight blocks)
 
+  static_assert(!SORT || GATEUP, "the micro-batch is constructed beside the first kernel of the layer");
   const int lane = threadIdx.x;
-  const bool sh = SHARED && (int)blockIdx.y < a.n_shared;   // eg: the shared set, otherwise the expert id
-  const int y = (int)blockIdx.y - (SHARED && !sh ? a.n_shared : 0);
+  if (SORT && blockIdx.y == 0) {
+    if (blockIdx.z == 0) sort_pairs(a, reinterpret_cast<int*>(smem));
+    return;
+  }
+  const int by = (int)blockIdx.y - (SORT ? 1 : 0);
+  const bool sh = SHARED && by < a.n_shared;   // eg: the shared set, otherwise the expert id
+  const int y = by - (SHARED && !sh ? a.n_shared : 0);
   const int eg = sh ? y : a.offsets ? (a.ids ? a.ids[a.lo + y] : a.lo + y) : 0;
-  const int rb = a.offsets && !sh ? a.offsets[eg] : 0;
-  const int re = sh ? a.shared_rows : a.offsets ? a.offsets[eg + 1] : a.rows_fixed;
-  const int Me = re - rb;
+  // SORT: pairs [m0, m0 + pass_rows) of this expert, in order, into s_pair; the pairs of lower experts and of this one
+  int* const s_pair = reinterpret_cast<int*>(smem);   // (the ring is free whenever this is called)
+  auto own_pairs = [&](int first, int& lower, int& mine) {
+    lower = mine = 0;
+    for (int p0 = 0; p0 < a.n_pairs; p0 += 128) {   // two requests at a time
+      int e[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) e[u] = pair_expert(a, p0 + u * 64 + lane);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const unsigned long long match = __ballot(e[u] == eg);
+        const int rank = mine + __popcll(match & ((1ull << lane) - 1ull)) - first;
+        if (e[u] == eg && rank >= 0 && rank < 16 * MT) s_pair[rank] = p0 + u * 64 + lane;
+        mine += __popcll(match);
+        lower += __popcll(__ballot(e[u] >= 0 && e[u] < eg));
+      }
+    }
+    __syncthreads();   // (one wave: orders the writes above before the reads of other lanes)
+  };
+  int rb = 0, Me = 0;
+  if (SORT && !sh) {
+    own_pairs((int)blockIdx.z * 16 * MT, rb, Me);
+  } else {
+    rb = a.offsets && !sh ? a.offsets[eg] : 0;
+    Me = (sh ? a.shared_rows : a.offsets ? a.offsets[eg + 1] : a.rows_fixed) - rb;
+  }
   // An expert with more rows than one pass covers takes further passes over its weights.  They are dealt
   // round-robin to the gridDim.z workgroups of this (expert, column block): workgroups without a pass leave
   // at once (they cost nothing measurable), and a hot expert of a skewed batch no longer runs all its passes
@@ -127,13 +236,17 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
   const int swz = r16 & 7;
 
   for (int m0 = (int)blockIdx.z * pass_rows; m0 < Me; m0 += pass_rows * (int)gridDim.z) {
+    if (SORT && !sh && m0 != (int)blockIdx.z * pass_rows) {
+      int lower, mine;
+      own_pairs(m0, lower, mine);
+    }
     uint32_t coffX[MT][2];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int m = min(m0 + mt * 16 + i * 8 + crow, Me - 1);   // rows past the end repeat the last row
-        const int arow = gathered ? a.gather[rb + m] / a.gather_div : rb + m;
+        const int arow = SORT && !sh ? s_pair[m - m0] / a.gather_div : gathered ? a.gather[rb + m] / a.gather_div : rb + m;
         coffX[mt][i] = (uint32_t)arow * (uint32_t)Kdim * 2u + (uint32_t)cchunk * 16u;
       }
 
@@ -269,11 +382,11 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
 
 constexpr int STREAM_PASS_GROUPS = 8;
 
-template <int MT, bool GATEUP, int NST, bool SHARED, bool TURN = false>
+template <int MT, bool GATEUP, int NST, bool SHARED, bool TURN = false, bool SORT = false>
 static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   using S = StreamLdsShape<MT, NST>;
   static_assert(NST * S::STAGE <= 64 * 1024, "dynamic LDS without an opt-in attribute");
-  auto kern = expert_stream_lds_kernel<MT, GATEUP, NST, SHARED, TURN>;
+  auto kern = expert_stream_lds_kernel<MT, GATEUP, NST, SHARED, TURN, SORT>;
   const int nexp = (a.offsets ? a.hi - a.lo : SHARED ? 0 : 1) + (SHARED ? a.n_shared : 0);
   const int per = GATEUP ? 16 : 32;
   const int gx = (a.N + per - 1) / per;
@@ -285,7 +398,7 @@ static int launch_stream_lds_t(const GemmArgs& a, hipStream_t st) {
   // from 250 + 159 to 180 + 98 us at T = 384; 16 and 32 begin to cost the unbiased batches 5 - 20 %.
   const int passes_max = (a.rows_total + 16 * MT - 1) / (16 * MT);
   const int gz = std::max(1, std::min(STREAM_PASS_GROUPS, passes_max / 2));
-  hipLaunchKernelGGL(kern, dim3(gx, nexp, gz), dim3(64), NST * S::STAGE, st, a);
+  hipLaunchKernelGGL(kern, dim3(gx, nexp + (SORT ? 1 : 0), gz), dim3(64), NST * S::STAGE, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -4;
 }
 
@@ -300,8 +413,15 @@ template <bool GATEUP>
 static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if (a.N % 32 != 0 || a.Kdim % 64 != 0) return -2;
   if (a.offsets != nullptr && !stream_narrow(a.mean_rows, a.Kdim))
-    return GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
+    return a.sort_ids != nullptr ? -2 : GATEUP ? launch_stream_wide_gateup(a, st) : launch_stream_wide_down(a, st);
   const bool two = a.offsets != nullptr ? a.mean_rows > 10 : (a.n_shared > 0 ? a.shared_rows : a.rows_fixed) > 16;
+  if constexpr (GATEUP) {
+    if (a.sort_ids != nullptr) {
+      if (a.offsets == nullptr || a.ids != nullptr || a.n_pairs > SORT_HERE_MAX) return -2;
+      if (a.n_shared > 0) return two ? launch_stream_lds_t<2, true, 4, true, false, true>(a, st) : launch_stream_lds_t<1, true, 4, true, false, true>(a, st);
+      return two ? launch_stream_lds_t<2, true, 4, false, false, true>(a, st) : launch_stream_lds_t<1, true, 4, false, false, true>(a, st);
+    }
+  }
   if constexpr (!GATEUP) {
     if (a.n_shared > 0 && a.n_shared != a.shared_parts)
       return two ? launch_stream_lds_t<2, GATEUP, 4, true, true>(a, st) : launch_stream_lds_t<1, GATEUP, 4, true, true>(a, st);

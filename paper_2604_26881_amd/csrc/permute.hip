@@ -3,6 +3,7 @@
 // (token, slot) pairs by expert id, followed by a coalesced gather of the token rows.
 // No atomics anywhere, so the result is deterministic; every step runs on many CUs.
 //
+// (A layer of up to 128 pairs whose experts stream their weights is sorted inside their first launch: expert_stream_lds.hip.)
 // The pairs are cut into chunks of 64 (one wave).
 // permute_hist_kernel: one wave per chunk.  Lanes with the same expert find each other with
 //   bit-sliced ballots (log2 E ballots); the first lane of each group writes the group size:
@@ -18,21 +19,6 @@
 namespace moe {
 
 constexpr int PERM_EMAX = 256;
-
-// match set of each lane: the lanes of the wave whose (valid) pair has the same expert id
-__device__ __forceinline__ unsigned long long match_expert(int e, bool valid, int nbits) {
-  unsigned long long match = __ballot(valid);
-  for (int b = 0; b < nbits; ++b) {
-    const unsigned long long bal = __ballot(valid && ((e >> b) & 1));
-    match &= ((e >> b) & 1) ? bal : ~bal;
-  }
-  return match;
-}
-__device__ __forceinline__ int bits_for(int E) {
-  int nbits = 0;
-  while ((1 << nbits) < E) ++nbits;
-  return nbits;
-}
 
 __global__ __launch_bounds__(256) void permute_hist_kernel(const int32_t* __restrict__ ids, int P, int E,
                                                            int32_t* __restrict__ hist) {

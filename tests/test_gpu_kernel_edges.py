@@ -548,3 +548,31 @@ def test_calls_on_a_few_experts_take_narrower_tiles_to_the_same_bits(moe, oracle
     for cuts in ([(i, i + 1) for i in range(E)], [(0, 3), (3, 10), (10, 17), (17, 32), (32, 40), (40, 60)]):
         Yc = run_blocks(moe, c, 0, cuts)
         assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16)), cuts[:2]
+
+
+@pytest.mark.parametrize("T,K,E", [(63, 1, 12), (64, 1, 256), (65, 1, 256), (127, 1, 200), (64, 2, 33), (128, 1, 64), (129, 1, 64)])
+@pytest.mark.parametrize("gather,ids_in", [(False, "their own memory"), (True, "their own memory"), (False, "the hidden rows"),
+                                           (True, "row_of_pair")])
+def test_micro_batch_constructed_beside_gate_up_equals_the_sort(moe, oracle64, monkeypatch, T, K, E, gather, ids_in):
+    # up to 128 pairs the sort is part of the experts' first launch; most tokens choose the same expert, so that its rows
+    # take several passes over the ids; ids in memory that this launch writes keep the sort's own launch
+    H, I = 64, 64
+    print(f"[case] sort beside gate/up T={T} K={K} E={E} gather={gather} ids in {ids_in}", flush=True)
+    w = workloads.layer_weights(H, E, I, 0, 90 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T + E)).to(torch.bfloat16)
+    bias = torch.zeros(E)
+    bias[E // 2] = 3.0
+    d, xg = {k: None if v is None else v.cuda() for k, v in w.items()}, x.cuda()
+    run = lambda buf, groups: moe.moe_layer_forward(xg, d["Wr"], bias.cuda(), d["Wg"], d["Wu"], d["Wd"], None, K, True, groups=groups,
+                                                    buf=buf, fused_gather=gather)
+    one, steps = (moe.LayerBuffers.allocate(T, H, E, K, I, 0) for _ in range(2))
+    if ids_in != "their own memory":
+        one.topk_ids = (one.workspace if ids_in == "the hidden rows" else one.row_of_pair).view(torch.int32)[:T * K].view(T, K)
+    served = record_one_calls(monkeypatch)
+    run(one, None), run(steps, [(0, 1), (1, E)])
+    torch.cuda.synchronize()
+    assert served == [True, False]
+    assert int((steps.expert_offsets[1:] - steps.expert_offsets[:-1]).max()) > 16
+    for name in ("topk_w", "expert_offsets", "src_of_row", "row_of_pair", "Yp", "out") + (() if gather else ("Xp",)):
+        a, b = getattr(one, name), getattr(steps, name)
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
