@@ -158,7 +158,9 @@ def _ptr(t: Optional[torch.Tensor], dtype: Optional[torch.dtype], name: str) -> 
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The raw handle of the current stream.  (A torch.cuda.Stream object made for it costs 3.1 us, on every library call:
+    a layer of 16 tokens, H 64, in one call 22.5 -> 20.4 us.)"""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def moe_workspace_bytes(T: int, H: int, E: int, K: int, I: int, Is: int) -> int:
