@@ -115,6 +115,9 @@ void set_shared_parts(GemmArgs& dn, int parts, int Is) {
 // columns of its hidden layer h [T,Is], and its output as `parts` fp32 parts [T,H].
 struct Riders { const void *x, *Wsg, *Wsu, *Wsd; void* h; float* part; int sets, parts, T, Is; };
 
+// The shared expert's gate/up tiles in the launch of the routed experts' (see expert_tile.hip): h is its hidden layer [T,Is].
+struct Hosted { const void *x, *Wsg, *Wsu; void* h; int T, Is; };
+
 // The micro-batch of a layer with few pairs, constructed inside the first launch of its experts (see expert_stream_lds.hip)
 struct Sort { const int32_t* ids; int32_t *offsets, *src, *rows; void* Xp; };
 bool sort_in_gateup(int P, int H, int E) {
@@ -126,7 +129,8 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
                               int gather_div,
                               const int32_t* expert_offsets, const void* Wg, const void* Wu, const void* Wd, int P,
                               int H, int E, int I, void* Yp, void* workspace, size_t workspace_bytes, int policy,
-                              void* stream, const Riders* riders = nullptr, const Sort* sort = nullptr) {
+                              void* stream, const Riders* riders = nullptr, const Sort* sort = nullptr, const Hosted* hosted = nullptr,
+                              bool* is_hosted = nullptr) {
   if (P < 0 || !dims_ok(H) || !dims_ok(I) || E < 1 || E > 256) return MOE_ERR_SHAPE;
   if (group_lo < 0 || group_hi > E || group_lo >= group_hi) return MOE_ERR_SHAPE;
   if ((long long)P * (H > I ? H : I) >= (1ll << 31)) return MOE_ERR_SHAPE;
@@ -158,6 +162,19 @@ int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, co
     gu.As = (const bf16_t*)riders->x; gu.Bs0 = (const bf16_t*)riders->Wsg; gu.Bs1 = (const bf16_t*)riders->Wsu;
     gu.Cs = (bf16_t*)riders->h;
     dn.As = (const bf16_t*)riders->h; dn.Bs0 = (const bf16_t*)riders->Wsd; dn.Cpart = riders->part;
+  }
+  if (hosted != nullptr && !plan.stream && tile_hosts_shared(gu, hosted->T, hosted->Is)) {
+    gu.n_shared = (hosted->Is + I - 1) / I;
+    gu.shared_rows = hosted->T;
+    gu.rows_routed = P;
+    gu.rows_total = P + gu.n_shared * hosted->T;
+    gu.Bs0 = (const bf16_t*)hosted->Wsg; gu.Bs1 = (const bf16_t*)hosted->Wsu;
+    gu.shared_b_step = (long)I * H;
+    gu.ldb_shared = H;
+    gu.As = (const bf16_t*)hosted->x;
+    gu.Cs = (bf16_t*)hosted->h;
+    gu.shared_cols = hosted->Is;
+    *is_hosted = true;
   }
   int parts;   // (no Cpart of its own: always 1)
   return ffn_forward(gu, dn, plan, (hipStream_t)stream, &parts);
@@ -568,10 +585,23 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
   const Sort sort{topk_ids, expert_offsets, src_of_row, row_of_pair, Xp};
   Riders riders{x, Wsg, Wsu, Wsd, shared_workspace, nullptr, sets, parts, T, Is};
   if (ride) riders.part = reinterpret_cast<float*>(static_cast<unsigned char*>(shared_workspace) + h_bytes);
+  // The shared expert's hidden rows formed beside the routed ones: nothing that the routed experts still read or write may
+  // lie there, and everything its own call would refuse is left to that call.
+  const size_t shared_h = (size_t)T * (size_t)Is * 2;
+  const bool host = !ride && T > 0 && Is > 0 && dims_ok(H) && dims_ok(Is) && policy == 0 && shared_policy == 0 && Wsg && Wsu && Wsd && S &&
+                    shared_workspace && shared_workspace_bytes >= shared_h && (!wgate || sg) && (Is + I - 1) / I <= MOE_SHARED_SETS_MAX &&
+                    (long long)T * (H > Is ? H : Is) < (1ll << 31) &&
+                    apart(shared_workspace, shared_h, workspace, h_routed) && apart(shared_workspace, shared_h, x, x_bytes) &&
+                    apart(shared_workspace, shared_h, Yp, (size_t)P * (size_t)H * 2) && apart(workspace, h_routed, x, x_bytes) &&
+                    apart(Yp, (size_t)P * (size_t)H * 2, x, x_bytes) &&
+                    (!copied || apart(shared_workspace, shared_h, Xp, (size_t)P * (size_t)H * 2)) &&
+                    apart(shared_workspace, shared_h, src_of_row, pairs) && apart(shared_workspace, shared_h, expert_offsets, offsets_bytes);
+  const Hosted hosted{x, Wsg, Wsu, shared_workspace, T, Is};
+  bool is_hosted = false;
   const bool from_x = sort_here || !copied;
   rc = expert_group_forward_impl(group_lo, group_hi, nullptr, from_x ? x : Xp, from_x ? src_of_row : nullptr, from_x ? K : 1,
                                  expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
-                                 ride ? &riders : nullptr, sort_here ? &sort : nullptr);
+                                 ride ? &riders : nullptr, sort_here ? &sort : nullptr, host ? &hosted : nullptr, &is_hosted);
   if (rc != MOE_OK) return rc;
   // The aggregation forms the gate logit and the residual step where no row that it still reads for another token lies
   // in what it writes for this one (x itself may be out or next: then the rows are the token's own); otherwise they are
@@ -583,8 +613,8 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
                          (next == out || apart(next, x_bytes, out, x_bytes));
   bool gate_formed = true;   // sg complete (or no shared expert)
   if (!ride && Is > 0) {
-    rc = shared_forward_impl(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, shared_workspace, shared_workspace_bytes, shared_policy,
-                             stream, T > 0 && x_kept && (shared_policy & 0x300) == 0 ? &gate_formed : nullptr);
+    rc = shared_forward_impl(x, Wsg, Wsu, Wsd, wgate, T, H, Is, S, sg, shared_workspace, shared_workspace_bytes,
+                             is_hosted ? shared_policy | 0x200 : shared_policy, stream, T > 0 && x_kept && (shared_policy & 0x300) == 0 ? &gate_formed : nullptr);
     if (rc != MOE_OK) return rc;
   }
   if (T == 0) return MOE_OK;

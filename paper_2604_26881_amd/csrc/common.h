@@ -112,6 +112,8 @@ struct GemmArgs {
   int ldb_shared;
   const bf16_t* As;        // not nullptr: set s reads its token rows from As[0 .. shared_rows) instead of A (gate/up: x)
   bf16_t* Cs;              // not nullptr: row r of set s goes to Cs[s*shared_rows + r] instead of C (down: the S parts)
+  int shared_cols;         // (tile kernels, gate/up) not 0: set s is columns [s*N, (s+1)*N) of one hidden layer of this many, in
+                           // Cs [shared_rows, shared_cols] (the last set may be narrower)
   // Measurement aid (tile kernels; nullptr: off): workgroup b < clock_groups writes four values at clocks[4*b]:
   // shader-clock ticks and ticks of the constant 100 MHz clock between its start and its end, the shader-clock
   // ticks it spent inside the K loops of its tiles, and the number of its tiles.
@@ -182,6 +184,8 @@ int launch_mfma_probe(const void* operands, int iters, int workgroups, long long
 // Tiled MFMA kernels (many rows per expert) and streaming kernels (few rows per expert).
 int launch_tile_gateup(const GemmArgs& a, int tile_rows, hipStream_t st);
 int launch_tile_down(const GemmArgs& a, int tile_rows, hipStream_t st, int* parts);
+// Whether the gate/up launch of a layer takes the shared expert's gate/up tiles along (a: the routed experts' arguments)
+bool tile_hosts_shared(const GemmArgs& a, int tokens, int Is);
 int tile_down_ksplit(int Kdim);   // most K parts of the down projection
 constexpr int STREAM_FEW_ROWS = 6;   // mean rows per expert up to which the narrow one of them serves a layer
 // It also serves contractions of up to four K steps, where what counts is how soon a wave starts: 16 experts of H 256, I 256

@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   // State of a tile: the current one (being multiplied, then stored) and, while the current one is
   // stored, the next one, whose first NS stages are already requested: the latency of those copies
   // hides behind the epilogue instead of opening every tile.
-  struct TileState { int row0, rowEnd, rowsValid, n0, ks, cshift; bf16_t* cbase; bool once, valid; };
+  struct TileState { int row0, rowEnd, rowsValid, n0, ks, cshift, ncols, ldc; bf16_t* cbase; bool once, valid; };
   const unsigned char *Ag = nullptr, *Bg0 = nullptr, *Bg1 = nullptr;
   uint32_t coff[S::NL];   // byte offsets of this lane's 16 bytes for each of the NL copies of a stage (K step 0)
   int krot = 0;           // K step the tile starts at (its walk over K wraps around)
@@ -279,8 +279,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     t.once = SINGLE && t.rowEnd - rb <= BM;
     // where this tile's rows go: a shared set may have an output tensor of its own
     const bool own_c = sh && a.Cs != nullptr;
-    t.cbase = own_c ? a.Cs : a.C;
-    t.cshift = own_c ? a.rows_routed : 0;
+    const bool of_one = GATEUP && own_c && a.shared_cols != 0;    // the sets are columns of one hidden layer
+    t.cbase = own_c ? a.Cs + (of_one ? (size_t)eg * a.N : (size_t)0) : a.C;
+    t.cshift = of_one ? rb : own_c ? a.rows_routed : 0;
+    t.ldc = of_one ? a.shared_cols : a.N;
+    // (a column tile of a narrower last set may lie past its columns: it repeats the last one and stores nothing)
+    t.ncols = of_one ? min(a.N, a.shared_cols - eg * a.N) : a.N;
 
     const size_t kbeg = (size_t)t.ks * nk * S::BK;
     // token rows: with a gather list they are addressed from the start of A, through the list; a
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
       } else {
         int r = row - BM;
         if (GATEUP && i >= S::NLA + (S::NL - S::NLA) / 2) r -= BN / 2;   // second half: the up branch
-        grow = min(t.n0 + r, a.N - 1);
+        grow = min(t.n0 + r, t.ncols - 1);
         ld = ldb;
       }
       coff[i] = (uint32_t)grow * ld * 2u + (uint32_t)cchunk * 16u;
@@ -348,7 +352,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   while (cur.valid) {
     const int row0 = cur.row0, rowEnd = cur.rowEnd, rowsValid = cur.rowsValid, n0 = cur.n0, ks = cur.ks;
     bf16_t* const cbase = cur.cbase;
-    const int cshift = cur.cshift;
+    const int cshift = cur.cshift, ldc = cur.ldc, ncols = cur.ncols;
     f32x16 acc[S::NB][S::TB];
 #pragma unroll
     for (int nb = 0; nb < S::NB; ++nb)
@@ -544,11 +548,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     for (int tb = 0; tb < S::TB; ++tb) {
       const int m = row0 + wm * S::WTM + tb * 32 + frag_row;
       if (m < rowEnd) {
-        bf16_t* crow_out = cbase + (size_t)(m - cshift) * a.N;
+        bf16_t* crow_out = cbase + (size_t)(m - cshift) * ldc;
 #pragma unroll
         for (int nb = 0; nb < S::NBH; ++nb) {
           const int nblock = n0 + (GATEUP ? wn * (S::WTN / 2) : wn * S::WTN) + nb * 32;   // first column of the 32-column block
-          if (nblock < a.N) {   // N is a multiple of 64, nblock of 32 (of 16, and 16 columns, for MIXED): inside or outside as a whole
+          if (nblock < ncols) {   // N is a multiple of 64, nblock of 32 (of 16, and 16 columns, for MIXED): inside or outside as a whole
             if (ITEMS > 1) {   // fp32 partial sum of K part ks; summed in order by the reduce kernel
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
@@ -780,6 +784,29 @@ static TileChoice pick_tile(GemmArgs& a, int tile_rows, bool gateup) {
     if (best == 0.0 || cost < 0.9 * best) { best = cost; c.code = family[f][i]; }
   }
   return c;
+}
+// The shared expert's gate/up tiles in the launch of the routed experts': both contract over H, so they are alike, and the
+// walk draws them alternately.  What it saves is rounds that are not full (2048 tokens of H 2048, 60 experts of I 1408, top
+// 4, Is 5632: 660 tiles run as three rounds and 484 as two; together 1232 of 160 rows as five) and tiles that wait for weights
+// while nothing multiplies.  us, two launches -> one: 777 tokens 175 -> 162, 1400 210 -> 193, 2048 252 -> 219 (with skewed
+// routing 256 -> 262), 3000 327 -> 299, 4096 426 -> 396 (skewed 416 -> 401), 8192 765 -> 744.  The down projections stay apart:
+// their contractions differ (22 and 88 K steps), and the shared expert cut into sets gains nothing (136 -> 132 at 2048).
+// Only with full-width tiles: layers of few or small experts take narrower ones, which the shared expert's many rows do
+// not want; only with more tokens than a tile has rows, for the K start of single tiles is not the shared expert's; and
+// only where the tiles together leave no more of a round empty than apart, where the shared expert's own launch leaves about a
+// tenth of its tiles' time and costs a tenth of a round (64 experts of H 1536, I 1024 at 66 rows are two full rounds: with
+// the 96 tiles of Is 2048 a layer takes 200 us, apart 195).
+bool tile_hosts_shared(const GemmArgs& a, int tokens, int Is) {
+  const int code = pick_layer_tile(a, 0, true).code;
+  if (code != 256 && code != 160 && code != 129) return false;
+  const int sets = (Is + a.N - 1) / a.N;
+  if (tokens <= 256 || a.hi - a.lo + sets > TILE_EMAX) return false;
+  const double bm = code == 129 ? 128.0 : code, cus = (double)num_cus();
+  const double m = (double)a.mean_rows + 1.5 * sqrt((double)a.mean_rows);
+  const double routed = (double)(a.hi - a.lo) * ceil(m / bm) * (double)((a.N + 127) / 128);
+  const double shared = ceil(tokens / bm) * (double)sets * (double)((a.N + 127) / 128);
+  auto empty = [&](double tiles) { return ceil(tiles / cus) * cus - tiles; };
+  return empty(routed + shared) <= empty(routed) + 0.1 * shared + 0.1 * cus;
 }
 int launch_tile_gateup(const GemmArgs& layer, int tile_rows, hipStream_t st) {
   GemmArgs a = layer;

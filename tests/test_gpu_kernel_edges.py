@@ -576,3 +576,29 @@ def test_micro_batch_constructed_beside_gate_up_equals_the_sort(moe, oracle64, m
     for name in ("topk_w", "expert_offsets", "src_of_row", "row_of_pair", "Yp", "out") + (() if gather else ("Xp",)):
         a, b = getattr(one, name), getattr(steps, name)
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+
+
+# 60 experts take tiles of 128, 160 and 256 rows; the shared hidden layer is whole sets of I columns, or ends in a
+# narrower one that covers less than the column tiles of a set, or is narrower than one; too many sets for one launch
+@pytest.mark.parametrize("T", [640, 2100, 3000])
+@pytest.mark.parametrize("Is", [2304, 1216, 64, 10432])
+@pytest.mark.parametrize("gather", [False, True])
+def test_shared_expert_formed_beside_the_routed_gate_up_has_the_bits_of_its_own_call(moe, oracle64, monkeypatch, T, Is, gather):
+    H, E, K, I = 128, 60, 4, 1152
+    print(f"[case] shared gate/up beside the routed T={T} Is={Is} gather={gather}", flush=True)
+    w = workloads.layer_weights(H, E, I, Is, 120 + T, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T + Is)).to(torch.bfloat16)
+    d, xg = {k: v.cuda() for k, v in w.items()}, x.cuda()
+    sh = (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"])
+    run = lambda groups: moe.moe_layer_forward(xg, d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], sh, K, True, groups=groups, fused_gather=gather)
+    served = record_one_calls(monkeypatch)
+    one, steps = run(None), run([(0, 25), (25, E)])
+    torch.cuda.synchronize()
+    assert served == [True, False]
+    for name in ("Yp", "S", "sg", "out"):
+        a, b = getattr(one, name), getattr(steps, name)
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), name
+    f32 = {k: v.float().numpy() for k, v in w.items()}
+    rows = np.arange(0, T, 7)
+    S_ref, _ = oracle64.shared_forward(x.float().numpy()[rows], f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
+    check_close(f64(one.S)[rows], S_ref, "S")
