@@ -11,7 +11,7 @@
 // Work decomposition.  A tile is BM token rows of ONE expert by BN weight rows (gate/up: BN/2 gate
 // rows and the matching BN/2 up rows, so the SwiGLU product is formed in registers).  The number
 // of tiles depends on expert_offsets, which only the device knows: the kernel is persistent, every
-// workgroup first builds the per-expert tile prefix in LDS and then walks tile indices with a
+// wave first forms the per-expert tile prefix in registers and then walks tile indices with a
 // fixed stride, so there is no host synchronisation and no atomic.  Workgroup b runs on XCD
 // b mod 8; the index walk hands each XCD runs of consecutive tiles that share weight and token
 // panels, so they meet in that XCD's L2.
@@ -115,11 +115,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   // of each class are listed separately (experts in order inside a class) and the walk draws
   // locality groups from the two lists in proportion, so both kinds are in flight at any time.
   constexpr int HEAVY_MIN = 3;
-  __shared__ int s_pref[2][TILE_EMAX];    // token tiles of the same class before expert i of the block
-  __shared__ int s_rb[TILE_EMAX];         // first row of expert i of the block
-  __shared__ uint8_t s_eid[TILE_EMAX];    // its expert id (E <= 256)
-  __shared__ int s_total[2];              // token tiles per class
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -127,44 +122,46 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   const int nrouted = a.offsets ? a.hi - a.lo : (a.n_shared > 0 ? 0 : 1);
   const int nexp = nrouted + a.n_shared;     // at most TILE_EMAX (checked by the caller)
 
-  // per-expert row range and number of token tiles -> exclusive prefix per class in LDS
-  if (wave == 0) {
-    int v[4], cnt[2] = {0, 0};
+  // Row range and token tiles of four experts per lane: [first[i], last[i]) in the tiles of the expert's class, rows
+  // [rb[i], re[i]).  Every wave keeps all of it in registers, where finding the expert of a tile is a handful of compares and
+  // ballots: a workgroup has one wave per SIMD, so what it waits for at a tile border nothing else fills.  (As prefixes in LDS
+  // and a binary search, with the expert's end re-read from memory: gate/up + down in us
+  // 60 experts of H 2048, I 1408 at 33, 51, 273 and 546 rows 131+67, 138+73, 257+135, 421+246; so 128+66, 134+71, 255+133, 415+241.)
+  int first[4], last[4], rb[4], re[4], cnt[2] = {0, 0};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = lane * 4 + i;
-      v[i] = 0;
-      if (e < nexp) {
-        const bool sh = e >= nrouted;
-        const int eid = sh ? e - nrouted : (a.offsets ? (a.ids ? a.ids[a.lo + e] : a.lo + e) : 0);
-        const int rb = sh ? a.rows_routed + eid * a.shared_rows : (a.offsets ? a.offsets[eid] : 0);
-        const int re = sh ? rb + a.shared_rows : (a.offsets ? a.offsets[eid + 1] : a.rows_fixed);
-        s_eid[e] = (uint8_t)eid;
-        s_rb[e] = rb;
-        v[i] = (max(re - rb, 0) + BM - 1) / BM;
-      }
-      cnt[v[i] >= HEAVY_MIN] += v[i];
+  for (int i = 0; i < 4; ++i) {
+    const int e = lane * 4 + i;
+    rb[i] = re[i] = 0;
+    if (e < nexp) {
+      const bool sh = e >= nrouted;
+      const int eid = sh ? e - nrouted : (a.offsets ? (a.ids ? a.ids[a.lo + e] : a.lo + e) : 0);
+      rb[i] = sh ? a.rows_routed + eid * a.shared_rows : (a.offsets ? a.offsets[eid] : 0);
+      re[i] = sh ? rb[i] + a.shared_rows : (a.offsets ? a.offsets[eid + 1] : a.rows_fixed);
     }
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      int incl = cnt[c];
-#pragma unroll
-      for (int s = 1; s < 64; s <<= 1) {
-        const int o = __shfl_up(incl, s, WAVE);
-        if (lane >= s) incl += o;
-      }
-      int base = incl - cnt[c];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = lane * 4 + i;
-        if (e < nexp) s_pref[c][e] = base;
-        if ((v[i] >= HEAVY_MIN) == (c == 1)) base += v[i];
-      }
-      if (lane == 63) s_total[c] = incl;
-    }
+    last[i] = (max(re[i] - rb[i], 0) + BM - 1) / BM;      // (a count so far)
+    cnt[last[i] >= HEAVY_MIN] += last[i];
   }
-  __syncthreads();
-  const int total0 = s_total[0], total1 = s_total[1];
+  int total[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    int incl = cnt[c];
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+      const int o = __shfl_up(incl, s, WAVE);
+      if (lane >= s) incl += o;
+    }
+    total[c] = __builtin_amdgcn_readlane(incl, 63);
+    cnt[c] = incl - cnt[c];                               // tiles of this class before this lane's experts
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool heavy = last[i] >= HEAVY_MIN;
+    first[i] = heavy ? cnt[1] : cnt[0];
+    last[i] += first[i];
+    cnt[0] = heavy ? cnt[0] : last[i];
+    cnt[1] = heavy ? last[i] : cnt[1];
+  }
+  const int total0 = total[0], total1 = total[1];
   const int grp0 = (total0 + S::GM - 1) / S::GM, grp1 = (total1 + S::GM - 1) / S::GM;   // locality groups per class
   const int ngrp = grp0 + grp1;
   const int NT = (a.N + S::NOUT - 1) / S::NOUT;
@@ -225,6 +222,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   auto kstep = [&](int kt) -> int { const int k = kt + krot; return k >= nk ? k - nk : k; };
   int it = 0;
   auto next_tile = [&]() -> TileState {
+    // The arguments are read again for every tile: kept over the K loops they would not fit the scalar registers, and what is
+    // set aside in vector lanes comes back one wait at a time.
+    const __attribute__((address_space(4))) GemmArgs* args = (const __attribute__((address_space(4))) GemmArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const auto& a = *args;
     TileState t{};
     int L = 0, mrow = 0, nt = 0, cls = 0, ks = 0;
     for (;; ++it) {
@@ -260,28 +262,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     t.valid = true;
     t.ks = ks;   // K part of this work item
 
-    // expert of this token tile: last e with s_pref[cls][e] <= mrow (an expert of the other class
-    // repeats its successor's prefix, so the last one is of this class)
-    int elo = 0, ehi = nexp;
-    while (ehi - elo > 1) {
-      const int mid = (elo + ehi) >> 1;
-      if (s_pref[cls][mid] <= mrow) elo = mid; else ehi = mid;
+    // the expert of this token tile: exactly one lane and i (the same in every lane: scalar registers)
+    int at = 0, vf = 0, vb = 0, ve = 0;
+    unsigned long long found = 0ull;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool own = (last[i] - first[i] >= HEAVY_MIN) == (cls == 1) && first[i] <= mrow && mrow < last[i];
+      found |= __ballot(own);
+      at = own ? i : at;
+      vf = own ? first[i] : vf;
+      vb = own ? rb[i] : vb;
+      ve = own ? re[i] : ve;
     }
-    // (the same in every lane: readfirstlane keeps them in scalar registers)
-    const int e = __builtin_amdgcn_readfirstlane(elo);
-    const int eg = __builtin_amdgcn_readfirstlane((int)s_eid[e]);   // expert id, or the number of the shared set
+    const int owner = __builtin_ctzll(found);
+    const int e = owner * 4 + __builtin_amdgcn_readlane(at, owner);
     const bool sh = e >= nrouted;
-    const int rb = __builtin_amdgcn_readfirstlane(s_rb[e]);
-    t.row0 = __builtin_amdgcn_readfirstlane(rb + (mrow - s_pref[cls][e]) * BM);
-    t.rowEnd = sh ? rb + a.shared_rows : (a.offsets ? a.offsets[eg + 1] : a.rows_fixed);
+    const int eg = sh ? e - nrouted : a.ids ? a.ids[a.lo + e] : a.offsets ? a.lo + e : 0;   // expert id, or the number of the shared set
+    const int rb_e = __builtin_amdgcn_readlane(vb, owner);
+    t.row0 = rb_e + (mrow - __builtin_amdgcn_readlane(vf, owner)) * BM;
+    t.rowEnd = __builtin_amdgcn_readlane(ve, owner);
     t.rowsValid = min(BM, t.rowEnd - t.row0);
     t.n0 = nt * S::NOUT;
-    t.once = SINGLE && t.rowEnd - rb <= BM;
+    t.once = SINGLE && t.rowEnd - rb_e <= BM;
     // where this tile's rows go: a shared set may have an output tensor of its own
     const bool own_c = sh && a.Cs != nullptr;
     const bool of_one = GATEUP && own_c && a.shared_cols != 0;    // the sets are columns of one hidden layer
     t.cbase = own_c ? a.Cs + (of_one ? (size_t)eg * a.N : (size_t)0) : a.C;
-    t.cshift = of_one ? rb : own_c ? a.rows_routed : 0;
+    t.cshift = of_one ? rb_e : own_c ? a.rows_routed : 0;
     t.ldc = of_one ? a.shared_cols : a.N;
     // (a column tile of a narrower last set may lie past its columns: it repeats the last one and stores nothing)
     t.ncols = of_one ? min(a.N, a.shared_cols - eg * a.N) : a.N;
@@ -292,7 +299,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     const bool own_a = sh && a.As != nullptr;
     const bool gathered = a.gather != nullptr && !own_a;
     Ag = reinterpret_cast<const unsigned char*>(
-        own_a ? a.As + (size_t)(t.row0 - rb) * Kdim + kbeg : a.A + (gathered ? (size_t)0 : (size_t)t.row0 * Kdim) + kbeg);
+        own_a ? a.As + (size_t)(t.row0 - rb_e) * Kdim + kbeg : a.A + (gathered ? (size_t)0 : (size_t)t.row0 * Kdim) + kbeg);
     const uint32_t ldb = sh ? (uint32_t)a.ldb_shared : (uint32_t)Kdim;   // elements between consecutive weight rows
     Bg0 = reinterpret_cast<const unsigned char*>((sh ? a.Bs0 + (size_t)eg * a.shared_b_step : a.B0 + (size_t)eg * a.N * Kdim) + kbeg);
     Bg1 = GATEUP ? reinterpret_cast<const unsigned char*>((sh ? a.Bs1 + (size_t)eg * a.shared_b_step : a.B1 + (size_t)eg * a.N * Kdim) + kbeg)
@@ -622,7 +629,7 @@ static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   static_assert(KSPLIT == 1 || !GATEUP, "the SwiGLU product needs complete sums");
   if (a.Kdim % (S::BK * KSPLIT) != 0) return -2;
   if (KSPLIT > 1 && !INTURN && a.Cpart == nullptr) return -3;
-  static_assert(OCC * (NS * S::STAGE + 3600) <= 160 * 1024, "LDS of the resident workgroups must fit a CU");
+  static_assert(OCC * NS * S::STAGE <= 160 * 1024, "LDS of the resident workgroups must fit a CU");
   static std::atomic<uint64_t> lds_raised{0};
   const int lds = NS * S::STAGE;
   if (raise_lds_limit((const void*)kern, lds, lds_raised) != 0) return -4;
