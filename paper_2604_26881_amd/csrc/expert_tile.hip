@@ -46,6 +46,10 @@
 // 212 -> 191; the down projection 297 -> 295, 422 -> 412, 172 -> 166, 104 -> 100.  Smaller shapes gain nothing (128x256 as
 // 2x4, 1x8 or 4x2 waves: equal within 2 %, 192x256 slower for the down projection: 87 -> 103 us at 4096 rows): their LDS reads
 // grow past the MFMA time, and where experts stream weights the waves wait for memory.
+// The 32-row blocks of a tile are dealt to the WAVES_M rows of waves in turn, so that a tile of few rows is halved between
+// them (an expert's last tile: 70 of 256 rows are two blocks per wave instead of three and none), and
+// blocks of padding are not copied either where a copy belongs to one row of waves.  60 experts of 1092 rows, gate/up + down in
+// us: 722 + 405 -> 702 + 397; where experts stream their weights, up to 1 %.
 // Rows past the end of an expert are clamped on load (they recompute the expert's last row) and
 // masked on store, which keeps the K loop free of branches.
 #include <math.h>
@@ -81,9 +85,14 @@ struct TileShape {
   // (one copy instruction of 1 KB keeps it busy for about 16 clocks) is not asked for a whole stage
   // within one K slice: ISSUE0 of them while the last slice of the stage that frees the buffer is
   // multiplied, ISSUE1 and ISSUE2 during the first two slices of the next K step.
-  static constexpr int ISSUE0 = NL - 2 * (NL / 3);
-  static constexpr int ISSUE1 = NL / 3;
-  static constexpr int ISSUE2 = NL / 3;
+  // (the pipeline counts with the copies its token blocks need)
+  // With four waves side by side copy i < NLA of a wave is part of the i-th token block of the wave's own row of waves: blocks of
+  // padding need not be copied either.
+  static constexpr bool TRIM = WAVES_N == 4;
+  static constexpr int tokens(int tbc) { return TRIM ? tbc : NLA; }             // token copies of a wave with tbc token blocks
+  static constexpr int copies(int tbc) { return tokens(tbc) + NL - NLA; }
+  static constexpr int copy(int tbc, int q) { return q < tokens(tbc) ? q : q - tokens(tbc) + NLA; }   // its q-th one
+  static_assert(!TRIM || NLA == WTM / 32, "a copy of the token rows is a block of the wave's row");
   static_assert(NW == 4 || NW == 8, "one or two waves per SIMD");
   static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile is made of 32x32 blocks");
   static_assert(!GATEUP || NB == 1 || NB % 2 == 0, "gate and up blocks come in pairs");
@@ -215,7 +224,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   // State of a tile: the current one (being multiplied, then stored) and, while the current one is
   // stored, the next one, whose first NS stages are already requested: the latency of those copies
   // hides behind the epilogue instead of opening every tile.
-  struct TileState { int row0, rowEnd, rowsValid, n0, ks, cshift, ncols, ldc; bf16_t* cbase; bool once, valid; };
+  struct TileState { int row0, rowEnd, rowsValid, tbv, n0, ks, cshift, ncols, ldc; bf16_t* cbase; bool once, valid; };
   const unsigned char *Ag = nullptr, *Bg0 = nullptr, *Bg1 = nullptr;
   uint32_t coff[S::NL];   // byte offsets of this lane's 16 bytes for each of the NL copies of a stage (K step 0)
   int krot = 0;           // K step the tile starts at (its walk over K wraps around)
@@ -282,6 +291,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     t.row0 = rb_e + (mrow - __builtin_amdgcn_readlane(vf, owner)) * BM;
     t.rowEnd = __builtin_amdgcn_readlane(ve, owner);
     t.rowsValid = min(BM, t.rowEnd - t.row0);
+    // token blocks of this wave that hold rows of the expert (at least one, so that the copies and
+    // operand reads keep their places between MFMAs)
+    t.tbv = min(S::TB, max(1, (((t.rowsValid + 31) >> 5) - wm + WAVES_M - 1) / WAVES_M));
     t.n0 = nt * S::NOUT;
     t.once = SINGLE && t.rowEnd - rb_e <= BM;
     // where this tile's rows go: a shared set may have an output tensor of its own
@@ -334,7 +346,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
       for (int s = 0; s < NS; ++s) {
         const int k = decltype(once_)::value ? kstep(min(s, nk - 1)) : min(s, nk - 1);
 #pragma unroll
-        for (int i = 0; i < S::NL; ++i) MOE_TILE_ISSUE1(k, s, i, decltype(once_)::value);
+        for (int i = 0; i < S::NL; ++i)
+          if (!S::TRIM || i >= S::NLA || i < t.tbv) MOE_TILE_ISSUE1(k, s, i, decltype(once_)::value);
       }
     };
     if (SINGLE && t.once) {
@@ -357,7 +370,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
   f32x16 sum[INTURN ? S::NB : 1][INTURN ? S::TB : 1];   // of the K parts before (INTURN)
   TileState cur = next_tile();
   while (cur.valid) {
-    const int row0 = cur.row0, rowEnd = cur.rowEnd, rowsValid = cur.rowsValid, n0 = cur.n0, ks = cur.ks;
+    const int row0 = cur.row0, rowEnd = cur.rowEnd, n0 = cur.n0, ks = cur.ks;
     bf16_t* const cbase = cur.cbase;
     const int cshift = cur.cshift, ldc = cur.ldc, ncols = cur.ncols;
     f32x16 acc[S::NB][S::TB];
@@ -377,7 +390,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
       const int cr_ = (((kk_) * 2 + frag_half) ^ frag_swz) << 4;                                     \
       if ((f_) < TBc) {                                                                             \
         fa_[(f_) < TBc ? (f_) : 0] = as_bf16x8(*reinterpret_cast<const u32x4*>(                    \
-            As_ + (wm * S::WTM + (f_) * 32 + frag_row) * S::ROWB + cr_));                            \
+            As_ + (((f_) * WAVES_M + wm) * 32 + frag_row) * S::ROWB + cr_));                         \
       } else {                                                                                      \
         const int nb_ = (f_) < TBc ? 0 : (f_) - TBc;                                                \
         const int brow_ = S::MIXED ? wn * 16 : GATEUP ? ((nb_ < S::NBH ? 0 : BN / 2) + wn * (S::WTN / 2) + (nb_ % S::NBH) * 32) \
@@ -412,7 +425,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
             constexpr int NE_ = S::NB + 1 < NFc ? S::NB + 1 : NFc;   /* reads needed early: before the copies */ \
             constexpr int NC_ = (I1) - (I0);                                                        \
             if (q < NE_) MOE_TILE_READ1(faY, fbY, stage_, kk_, fragment_read_order(q < NE_ ? q : 0, TBc, S::NB)) \
-            else if (q < NE_ + NC_) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, ((q >= NE_ && q < NE_ + NC_) ? (I0) + q - NE_ : 0), ONCE); } \
+            else if (q < NE_ + NC_) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, S::copy(TBc, (q >= NE_ && q < NE_ + NC_) ? (I0) + q - NE_ : 0), ONCE); } \
             else MOE_TILE_READ1(faY, fbY, stage_, kk_, fragment_read_order(q >= NE_ + NC_ ? q - NC_ : 0, TBc, S::NB)) \
           }                                                                                         \
         __builtin_amdgcn_sched_barrier(0x6);                                                        \
@@ -422,12 +435,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
 #define MOE_TILE_SLICE_LAST(next_stage_, kt_issue_, st_issue_)                                      \
     { _Pragma("unroll") for (int j = 0; j < NMc; ++j) {                                             \
         MOE_TILE_MFMA1(faB, fbB, j);                                                                \
-        _Pragma("unroll") for (int q = 0; q < S::ISSUE0 + NFc; ++q)                                 \
-          if (q * NMc / (S::ISSUE0 + NFc) == j) {                                                   \
+        _Pragma("unroll") for (int q = 0; q < ISSUE0 + NFc; ++q)                                    \
+          if (q * NMc / (ISSUE0 + NFc) == j) {                                                      \
             constexpr int NE_ = S::NB + 1 < NFc ? S::NB + 1 : NFc;                                  \
             if (q < NE_) MOE_TILE_READ1(faA, fbA, next_stage_, 0, fragment_read_order(q < NE_ ? q : 0, TBc, S::NB)) \
-            else if (q < NE_ + S::ISSUE0) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, ((q >= NE_ && q < NE_ + S::ISSUE0) ? q - NE_ : 0), ONCE); } \
-            else MOE_TILE_READ1(faA, fbA, next_stage_, 0, fragment_read_order(q >= NE_ + S::ISSUE0 ? q - S::ISSUE0 : 0, TBc, S::NB)) \
+            else if (q < NE_ + ISSUE0) { MOE_TILE_ISSUE1(kt_issue_, st_issue_, S::copy(TBc, (q >= NE_ && q < NE_ + ISSUE0) ? q - NE_ : 0), ONCE); } \
+            else MOE_TILE_READ1(faA, fbA, next_stage_, 0, fragment_read_order(q >= NE_ + ISSUE0 ? q - ISSUE0 : 0, TBc, S::NB)) \
           }                                                                                         \
         __builtin_amdgcn_sched_barrier(0x6);                                                        \
     } }
@@ -444,7 +457,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
       constexpr bool ONCE = decltype(once_)::value;
       constexpr int NMc = TBc * S::NB;   // MFMAs per 16-wide K slice
       constexpr int NFc = TBc + S::NB;   // operand fragments per slice
-      wait_copies_but<S::DIST * S::NL>();   // stage 0 (requested before the previous tile was stored) has landed
+      constexpr int NLc = S::copies(TBc);   // copies per stage
+      constexpr int ISSUE0 = NLc - 2 * (NLc / 3), ISSUE1 = NLc / 3;
+      wait_copies_but<S::DIST * NLc>();   // stage 0 (requested before the previous tile was stored) has landed
       workgroup_barrier();
       bf16x8 faA[S::TB], fbA[S::NB], faB[S::TB], fbB[S::NB];
       MOE_TILE_READ(faA, fbA, 0, 0);
@@ -456,8 +471,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
         // of K step kt-1 (at kt = 0 this repeats copies of the prologue: same bytes, same place)
         const int ktd = ONCE ? kstep(min(kt - 1 + NS, nk - 1)) : min(kt - 1 + NS, nk - 1);
         const int std_ = st == 0 ? NS - 1 : st - 1;
-        MOE_TILE_SLICE_ISSUE(faA, fbA, faB, fbB, st, 1, ktd, std_, S::ISSUE0, S::ISSUE0 + S::ISSUE1);
-        MOE_TILE_SLICE_ISSUE(faB, fbB, faA, fbA, st, 2, ktd, std_, S::ISSUE0 + S::ISSUE1, S::NL);
+        MOE_TILE_SLICE_ISSUE(faA, fbA, faB, fbB, st, 1, ktd, std_, ISSUE0, ISSUE0 + ISSUE1);
+        MOE_TILE_SLICE_ISSUE(faB, fbB, faA, fbA, st, 2, ktd, std_, ISSUE0 + ISSUE1, NLc);
         MOE_TILE_SLICE(faA, fbA, faB, fbB, st, 3);
         // this wave has finished reading stage kt once the last-slice fragments are in registers
         // (the empty asm makes the compiler wait for them; the fence keeps that wait behind the MFMAs)
@@ -466,7 +481,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
         for (int tb = 0; tb < TBc; ++tb) asm volatile("" : "+v"(faB[tb]));
 #pragma unroll
         for (int nb = 0; nb < S::NB; ++nb) asm volatile("" : "+v"(fbB[nb]));
-        wait_copies_but<(S::DIST - 1) * S::NL>();
+        wait_copies_but<(S::DIST - 1) * NLc>();
         workgroup_barrier();  // stage kt+1 is complete for everyone; stage kt is free for everyone
         MOE_TILE_SLICE_LAST(st1, ONCE ? kstep(min(kt + NS, nk - 1)) : min(kt + NS, nk - 1), st);
         if constexpr (INTURN) {
@@ -495,9 +510,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
       wait_copies_but<0>();  // the repeated last-step copies of the final iterations: none may outlive the tile
       workgroup_barrier();   // the next tile's first copies overwrite stages other waves may still read
     };
-    // token blocks of this wave that hold rows of the expert (at least one, so that the copies and
-    // operand reads keep their places between MFMAs)
-    const int tbv = min(S::TB, max(1, (rowsValid - wm * S::WTM + 31) >> 5));
+    const int tbv = cur.tbv;
     const long long clk_k0 = clock64();
     auto run_pipeline = [&](auto once_) {
       switch (tbv) {
@@ -553,7 +566,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
     };
 #pragma unroll
     for (int tb = 0; tb < S::TB; ++tb) {
-      const int m = row0 + wm * S::WTM + tb * 32 + frag_row;
+      const int m = row0 + (tb * WAVES_M + wm) * 32 + frag_row;
       if (m < rowEnd) {
         bf16_t* crow_out = cbase + (size_t)(m - cshift) * ldc;
 #pragma unroll
