@@ -602,6 +602,10 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
   rc = expert_group_forward_impl(group_lo, group_hi, nullptr, from_x ? x : Xp, from_x ? src_of_row : nullptr, from_x ? K : 1,
                                  expert_offsets, Wg, Wu, Wd, P, H, E, I, Yp, workspace, workspace_bytes, policy, stream,
                                  ride ? &riders : nullptr, sort_here ? &sort : nullptr, host ? &hosted : nullptr, &is_hosted);
+  if (sort_here && (rc == MOE_ERR_NULL || rc == MOE_ERR_SHAPE || rc == MOE_ERR_WORKSPACE)) {   // refused: the step before it stands
+    const int rc_sort = launch_permute(topk_ids, x, T, H, E, K, expert_offsets, src_of_row, row_of_pair, Xp, permute_workspace, (hipStream_t)stream);
+    if (rc_sort != 0) return rc_sort;
+  }
   if (rc != MOE_OK) return rc;
   // The aggregation forms the gate logit and the residual step where no row that it still reads for another token lies
   // in what it writes for this one (x itself may be out or next: then the rows are the token's own); otherwise they are

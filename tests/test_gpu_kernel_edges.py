@@ -602,3 +602,23 @@ def test_shared_expert_formed_beside_the_routed_gate_up_has_the_bits_of_its_own_
     rows = np.arange(0, T, 7)
     S_ref, _ = oracle64.shared_forward(x.float().numpy()[rows], f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
     check_close(f64(one.S)[rows], S_ref, "S")
+
+
+def test_a_layer_whose_block_is_refused_leaves_the_steps_before_it(moe):
+    T, H, E, K, I = 5, 64, 8, 2, 64
+    print("[case] refused block behind gating and sort", flush=True)
+    w = {k: None if v is None else v.cuda() for k, v in workloads.layer_weights(H, E, I, 0, 7, 0.05, 0.1, torch.bfloat16, device="cpu").items()}
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(2)).to(torch.bfloat16).cuda()
+    want = moe.moe_layer_forward(x, w["Wr"], None, w["Wg"], w["Wu"], w["Wd"], None, K, True)
+    b = moe.LayerBuffers.allocate(T, H, E, K, I, 0)
+    b.src_of_row.fill_(-1)
+    p = lambda t: t.data_ptr()
+    rc = moe.load().moe_layer_forward(
+        p(x), p(w["Wr"]), None, None, 0, p(w["Wg"]), p(w["Wu"]), p(w["Wd"]), None, None, None, None, T, H, E, K, I, 0, 1, 0, E, 0, 0,
+        p(b.topk_ids), p(b.topk_w), p(b.expert_offsets), p(b.src_of_row), p(b.row_of_pair), p(b.Xp), None, None, None, p(b.out),
+        p(b.workspace_permute), b.workspace_permute.numel(), p(b.workspace), b.workspace.numel(), None, 0, 0.0, None,
+        torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert rc == -1     # MOE_ERR_NULL: no Yp
+    for name in ("topk_ids", "expert_offsets", "src_of_row", "row_of_pair", "Xp"):
+        assert torch.equal(getattr(b, name).view(torch.uint8), getattr(want, name).view(torch.uint8)), name
