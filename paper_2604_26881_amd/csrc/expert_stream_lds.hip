@@ -249,6 +249,8 @@ __global__ __launch_bounds__(64) void expert_stream_lds_kernel(GemmArgs a) {
         const int arow = SORT && !sh ? s_pair[m - m0] / a.gather_div : gathered ? a.gather[rb + m] / a.gather_div : rb + m;
         coffX[mt][i] = (uint32_t)arow * (uint32_t)Kdim * 2u + (uint32_t)cchunk * 16u;
       }
+    // s_pair lies in ring slot 0, and the first copies into that slot, of weights, do not depend on what is read from it here
+    if (SORT && !sh) wait_lds_reads();
 
     f32x4 acc0[MT], acc1[MT];
 

@@ -1,4 +1,4 @@
-"""Build-time check of the kernels' own assembly for two hazards the hardware does not interlock.
+"""Build-time check of the kernels' own assembly for three hazards the hardware does not interlock.
 
 On CDNA an MFMA's result registers may not be read or overwritten by a non-MFMA instruction until
 the matrix pipe has written them back: the ISA asks for a number of wait states (independent
@@ -13,6 +13,11 @@ instruction that touches an MFMA's result and fails the build if fewer wait stat
 A second, simpler check covers the other pair this library's code can get wrong: a load that writes LDS
 (global_load_lds_*) takes its LDS address from m0 and needs one wait state after a scalar write of m0.
 The compiler pads the pairs it emits itself, but the copies here are asm statements it does not look into.
+
+The third concerns kernels whose wave reuses its own LDS without a barrier (the weight-streaming ones): a load that
+writes LDS may not be issued while an LDS read or write of the same wave is still in flight, for the two are not
+ordered and the place may be the same.  The compiler puts its wait where a read's result is used, which can be
+behind such a copy: the wait belongs into the source, and this check sees to it that it is in the code.
 
 It reads the device assembly hipcc writes for this library's own sources (-save-temps), nothing else.
 """
@@ -58,8 +63,8 @@ def _kernels(path: str) -> Iterator[Tuple[str, List[str]]]:
                 name = None
 
 
-def hazards_in_kernel(body: List[str]) -> List[Tuple[str, str, int, int]]:
-    """(mfma, touching instruction, wait states found, wait states needed) for every violation."""
+def _flow(body: List[str]) -> Tuple[List[str], List[List[int]]]:
+    """The instructions of a kernel, and for each the numbers of those that may follow it."""
     ins: List[str] = []
     labels: Dict[str, int] = {}
     for t in body:
@@ -70,15 +75,25 @@ def hazards_in_kernel(body: List[str]) -> List[Tuple[str, str, int, int]]:
         if t.startswith(".") or t.endswith(":"):
             continue
         ins.append(t)
-    preds: Dict[int, List[int]] = {i: [] for i in range(len(ins))}
+    succs: List[List[int]] = [[] for _ in ins]
     for i, t in enumerate(ins):
         op = t.split()[0]
         if op.startswith("s_cbranch") or op == "s_branch":
             tgt = re.search(r"(\.L\w+)", t)
             if tgt and labels.get(tgt.group(1), len(ins)) < len(ins):
-                preds[labels[tgt.group(1)]].append(i)
+                succs[i].append(labels[tgt.group(1)])
         if op != "s_branch" and not op.startswith("s_endpgm") and i + 1 < len(ins):
-            preds[i + 1].append(i)
+            succs[i].append(i + 1)
+    return ins, succs
+
+
+def hazards_in_kernel(body: List[str]) -> List[Tuple[str, str, int, int]]:
+    """(mfma, touching instruction, wait states found, wait states needed) for every violation."""
+    ins, succs = _flow(body)
+    preds: List[List[int]] = [[] for _ in ins]
+    for i, after in enumerate(succs):
+        for j in after:
+            preds[j].append(i)
 
     def dest(i: int) -> Optional[Tuple[str, int, int]]:
         regs = _registers(ins[i].split(None, 1)[1].split(",")[0]) if " " in ins[i] else []
@@ -127,6 +142,39 @@ def m0_hazards_in_kernel(body: List[str]) -> List[Tuple[str, str]]:
     return found
 
 
+# kernels in which every LDS access of a wave must have finished before the wave issues its next copy into LDS (the tile
+# kernels copy into one stage while they read another, behind barriers)
+_WAVE_PRIVATE_RING = "expert_stream"
+
+
+def ring_hazards_in_kernel(body: List[str]) -> List[Tuple[str, str]]:
+    """(LDS access, LDS-writing load) pairs where the access may still be in flight, on some path, when the load is issued."""
+    ins, succs = _flow(body)
+    if not ins:
+        return []
+    before: List[set] = [set() for _ in ins]      # LDS accesses that may be in flight at an instruction
+    seen = [False] * len(ins)
+    seen[0] = True
+    found, work = set(), [0]
+    while work:
+        i = work.pop()
+        flying, op = set(before[i]), ins[i].split()[0]
+        if "_lds_" in op and op.startswith(("global_load", "buffer_load")):
+            found.update((j, i) for j in flying)
+        elif op.startswith("ds_"):
+            flying.add(i)
+        elif op == "s_waitcnt":
+            m = re.search(r"lgkmcnt\((\d+)\)", ins[i])
+            if m and int(m.group(1)) == 0:        # (a wait for some of them is taken for none: straight-line order does not tell which)
+                flying = set()
+        for j in succs[i]:
+            if not seen[j] or not flying <= before[j]:
+                before[j] |= flying
+                seen[j] = True
+                work.append(j)
+    return [(ins[j], ins[i]) for j, i in sorted(found)]
+
+
 def check_file(path: str) -> List[str]:
     """One line per kernel of the assembly file that has a violation."""
     out = []
@@ -139,4 +187,8 @@ def check_file(path: str) -> List[str]:
         m0 = m0_hazards_in_kernel(body)
         if m0:
             out.append(f"{name}: {len(m0)} LDS-writing load(s) directly behind the write of m0, e.g. `{m0[0][0]}` / `{m0[0][1]}`")
+        ring = ring_hazards_in_kernel(body) if _WAVE_PRIVATE_RING in name else []
+        if ring:
+            out.append(f"{name}: {len(ring)} pair(s) of an LDS access and a copy into LDS issued before it has finished, "
+                       f"e.g. `{ring[0][0]}` / `{ring[0][1]}`")
     return out

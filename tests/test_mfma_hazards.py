@@ -1,6 +1,6 @@
-"""The build-time check for MFMA results touched before write-back (paper_2604_26881_amd/mfma_hazards.py), on
-hand-written assembly: the control-flow case the compiler's own padding misses, the padded forms, and a result
-in ordinary vector registers."""
+"""The build-time checks of the emitted code (paper_2604_26881_amd/mfma_hazards.py) on hand-written assembly: MFMA results
+touched before write-back (the control-flow case the compiler's own padding misses, the padded forms, a result in ordinary
+vector registers), copies into LDS behind the write of m0, and copies into LDS that overtake a wave's own LDS accesses."""
 import textwrap
 
 from paper_2604_26881_amd import mfma_hazards as H
@@ -71,3 +71,27 @@ def test_lds_writing_load_directly_behind_the_write_of_m0(tmp_path):
     assert flagged(tmp_path, "\ts_mov_b32 m0, s5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 v2, s[4:5]\n") == []
     assert flagged(tmp_path, "\ts_add_i32 m0, s0, 0x400\n\tglobal_load_lds_dwordx4 v[2:3], off\n") != []
     assert flagged(tmp_path, "\ts_mov_b32 m0, s5\n\tv_mov_b32_e32 v1, v2\n\tglobal_load_lds_dwordx4 v2, s[4:5] nt\n") == []
+
+
+def test_copy_into_lds_while_an_lds_access_of_the_same_wave_is_in_flight(tmp_path):
+    # the weight-streaming kernels reuse their ring without a barrier: an index read from the place that a copy which does
+    # not depend on it then overwrites (the wait where the index is used comes behind that copy)
+    copy = "\ts_mov_b32 m0, s5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 v2, s[4:5] nt\n"
+    read, use, wait = "\tds_read_b32 v3, v1\n", "\tv_lshlrev_b32_e32 v4, 12, v3\n", "\ts_waitcnt lgkmcnt(0)\n"
+
+    def stream(body):
+        p = tmp_path / "s.s"
+        p.write_text(kernel(body).replace("kern:", "expert_stream_kern:"))
+        return H.check_file(str(p))
+
+    out = stream(read + copy + wait + use)
+    assert len(out) == 1 and "ds_read_b32" in out[0]
+    assert stream(read + wait + use + copy) == []
+    assert len(stream(read + "\ts_waitcnt vmcnt(0)\n" + copy + wait)) == 1
+    assert len(stream("\tds_write_b32 v1, v3\n" + copy)) == 1
+    # through a branch that goes round the wait, and through a loop back-edge
+    assert len(stream(read + "\ts_cbranch_vccnz .LBB0_2\n" + wait + ".LBB0_2:\n" + copy)) == 1
+    assert len(stream(".LBB0_1:\n" + copy + read + "\ts_cbranch_scc1 .LBB0_1\n" + wait)) == 1
+    assert stream(".LBB0_1:\n" + copy + read + wait + "\ts_cbranch_scc1 .LBB0_1\n") == []
+    # the tile kernels read one stage while they copy into another
+    assert flagged(tmp_path, read + copy + wait + use) == []
