@@ -688,8 +688,9 @@ static int launch_tile_t(const GemmArgs& a, hipStream_t st) {
 // 152 -> 136, the down projection at 6000 256 tiles (125 -> 115).
 static int largest_ksplit(int Kdim) { return Kdim % 512 == 0 ? 8 : Kdim % 256 == 0 ? 4 : Kdim % 128 == 0 ? 2 : 1; }
 int tile_down_ksplit(int Kdim) { return largest_ksplit(Kdim); }
-struct TileChoice { int code, parts; };
+struct TileChoice { int code, parts; double cost; };   // (cost: of one weight set, as estimated)
 constexpr int NARROW_160 = 1601, NARROW_256 = 2561;   // 160x128 and 256x128: only launched in place of the wider ones (pick_tile)
+constexpr double UNITS_PER_US = 3.0e6;   // 256x256x2048 tile: 45 us (a gate/up tile, which counts the columns of one branch, takes twice as long)
 static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int parts_max, bool leave_room) {
   struct Cand { int code, bm, nout; double c; bool cut; };
   const Cand cands[6] = {{256, 256, gateup ? 128 : 256, 1.0, false}, {192, 192, gateup ? 128 : 256, 1.03, false},
@@ -697,9 +698,7 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
                          {129, 128, gateup ? 128 : 256, 1.1, false}, {130, 128, gateup ? 64 : 128, 1.42, true},
                          {64, 128, gateup ? 32 : 64, 1.77, true}};
   const double cus = (double)num_cus();
-  const double units_per_us = 3.0e6;   // 256x256x2048 tile: 45 us
-  TileChoice best{129, 1};
-  double best_cost = 0.0;
+  TileChoice best{129, 1, 0.0};
   for (const Cand& k : cands) {
     // 192x256 leaves other kernels 86 registers of a SIMD and 45 KB of LDS.  (256x256, two waves of 210 registers per SIMD
     // and 128 KB, does not keep the row sort waiting: 16 384 tokens beside gating and sort 2312 us with 128x256, 2220 with it.)
@@ -713,8 +712,8 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
       // many rounds must not make them (16 384 tokens: the row sort waited 750 us behind it; layer 2417 us, without 2362)
       if (k.code == 160 && leave_room && rounds > 2.0) continue;
       double cost = rounds * k.bm * k.nout * ((double)Kdim / parts) * k.c;
-      if (parts > 1) cost += (5.0 + (double)rows * N * parts * 8.0 / 5.0e6) * units_per_us;
-      if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = TileChoice{k.code, parts}; }
+      if (parts > 1) cost += (5.0 + (double)rows * N * parts * 8.0 / 5.0e6) * UNITS_PER_US;
+      if (best.cost == 0.0 || cost < best.cost) best = TileChoice{k.code, parts, cost};
     }
   }
   return best;
@@ -729,8 +728,8 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
 // it; Zipf-skewed routing (mean 273, median 130) and the multi-tenant batch (mean 137) also run
 // fastest on its choice (160).
 static TileChoice pick_layer_tile(const GemmArgs& a, int tile_rows, bool gateup) {
-  if (tile_rows == 64 && !gateup && a.parts_max > 0) return TileChoice{64, std::min(a.parts_max, largest_ksplit(a.Kdim))};
-  if (tile_rows != 0) return TileChoice{tile_rows, 1};
+  if (tile_rows == 64 && !gateup && a.parts_max > 0) return TileChoice{64, std::min(a.parts_max, largest_ksplit(a.Kdim)), 0.0};
+  if (tile_rows != 0) return TileChoice{tile_rows, 1, 0.0};
   if (a.offsets == nullptr) return pick_tile_shape(a.rows_total, a.N, a.Kdim, gateup, a.parts_max, a.leave_room != 0);
   const double m = (double)a.mean_rows + 1.5 * sqrt((double)a.mean_rows);
   const int heights[3] = {129, 160, 256};
@@ -765,7 +764,7 @@ static TileChoice pick_layer_tile(const GemmArgs& a, int tile_rows, bool gateup)
       if (best_cost == 0.0 || cost < best_cost) { best_cost = cost; best = k.code; }
     }
   }
-  return TileChoice{best, 1};
+  return TileChoice{best, 1, 0.0};
 }
 // What a call launches for the layer's tile shape.  A call on a block of a few experts can have fewer tiles than the chip
 // has compute units; narrower tiles of the same height then give more of them work.  Every output element is summed in the
@@ -809,24 +808,30 @@ static TileChoice pick_tile(GemmArgs& a, int tile_rows, bool gateup) {
 // walk draws them alternately.  What it saves is rounds that are not full (2048 tokens of H 2048, 60 experts of I 1408, top
 // 4, Is 5632: 660 tiles run as three rounds and 484 as two; together 1232 of 160 rows as five) and tiles that wait for weights
 // while nothing multiplies.  us, two launches -> one: 777 tokens 175 -> 162, 1400 210 -> 193, 2048 252 -> 219 (with skewed
-// routing 256 -> 262), 3000 327 -> 299, 4096 426 -> 396 (skewed 416 -> 401), 8192 765 -> 744.  The down projections stay apart:
+// routing 256 -> 262), 3000 327 -> 299, 4096 426 -> 396 (skewed 416 -> 401), 8192 765 -> 744; the whole layer at 2048 skewed tokens 459 -> 437.  The down projections stay apart:
 // their contractions differ (22 and 88 K steps), and the shared expert cut into sets gains nothing (136 -> 132 at 2048).
-// Only with full-width tiles: layers of few or small experts take narrower ones, which the shared expert's many rows do
-// not want; only with more tokens than a tile has rows, for the K start of single tiles is not the shared expert's; and
-// only where the tiles together leave no more of a round empty than apart, where the shared expert's own launch leaves about a
-// tenth of its tiles' time and costs a tenth of a round (64 experts of H 1536, I 1024 at 66 rows are two full rounds: with
-// the 96 tiles of Is 2048 a layer takes 200 us, apart 195).
+// Only with full-width tiles: layers of few or small experts and calls on a few of them take narrower ones, which the shared
+// expert's many rows do not want; only with more tokens than a tile has rows, for the K start of single tiles is not the shared expert's; only
+// where the rounds that its tiles add cost no more than its own launch in the shape that it takes there (both in the units
+// and factors of pick_tile_shape), and about 6 us for the launch: with even routing, and as a share of a round per tile, for
+// skewed routing fills the last round differently.  Counted are all column tiles of all sets: one past the columns of a
+// narrower last set walks K like any other and stores nothing.  A layer in us, apart -> in one launch: 60 experts of H 2048, I
+// 1152, Is 1216 at 2100 tokens, half of whose shared tiles hold columns, 330 -> 322; what the line keeps apart: 16 of H 1024, I
+// 4096, Is 192 at 4513 (58 of 928 tiles hold columns) 233 -> 279, 48 of H 1024, I 4032, Is 512 at 9015 437 -> 543, 64 of H
+// 1536, I 1024 at 66 rows (two full rounds, and 0.4 of Is 2048) 195 -> 200.  Near the line both cost the same: 32 of H 1024, I
+// 2048, Is 8192 at 4007 344 -> 352 on one card, 362 -> 361 on another, 32 of H 1024, I 960, Is 1984 at 6000 351 -> 347 and 364 -> 368.
 bool tile_hosts_shared(const GemmArgs& a, int tokens, int Is) {
-  const int code = pick_layer_tile(a, 0, true).code;
+  GemmArgs apart = a;
+  const int code = pick_tile(apart, 0, true).code;
   if (code != 256 && code != 160 && code != 129) return false;
-  const int sets = (Is + a.N - 1) / a.N;
+  const int sets = (Is + a.N - 1) / a.N, columns = (a.N + 127) / 128;      // sets, and column tiles of one
   if (tokens <= 256 || a.hi - a.lo + sets > TILE_EMAX) return false;
-  const double bm = code == 129 ? 128.0 : code, cus = (double)num_cus();
+  const double bm = code == 129 ? 128.0 : code, cus = (double)num_cus(), factor = code == 256 ? 1.0 : code == 160 ? 1.07 : 1.1;
   const double m = (double)a.mean_rows + 1.5 * sqrt((double)a.mean_rows);
-  const double routed = (double)(a.hi - a.lo) * ceil(m / bm) * (double)((a.N + 127) / 128);
-  const double shared = ceil(tokens / bm) * (double)sets * (double)((a.N + 127) / 128);
-  auto empty = [&](double tiles) { return ceil(tiles / cus) * cus - tiles; };
-  return empty(routed + shared) <= empty(routed) + 0.1 * shared + 0.1 * cus;
+  const double routed = (double)(a.hi - a.lo) * ceil(m / bm) * (double)columns;
+  const double shared = ceil(tokens / bm) * (double)(sets * columns);
+  const double rounds = std::max(ceil((routed + shared) / cus) - ceil(routed / cus), shared / cus);
+  return rounds * bm * 128.0 * (double)a.Kdim * factor <= pick_tile_shape(tokens, Is, a.Kdim, true, 0, false).cost + 3.0 * UNITS_PER_US;
 }
 int launch_tile_gateup(const GemmArgs& layer, int tile_rows, hipStream_t st) {
   GemmArgs a = layer;

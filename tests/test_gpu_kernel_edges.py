@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import workloads
+from tests.test_launch_routes_host import SHARED_BESIDE
 from tests.test_gpu_parity import check_close, f64, moe  # noqa: F401  (moe is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -580,8 +581,8 @@ def test_micro_batch_constructed_beside_gate_up_equals_the_sort(moe, oracle64, m
 
 # 60 experts take tiles of 128, 160 and 256 rows; the shared hidden layer is whole sets of I columns, or ends in a
 # narrower one that covers less than the column tiles of a set, or is narrower than one; too many sets for one launch
-@pytest.mark.parametrize("T", [640, 2100, 3000])
-@pytest.mark.parametrize("Is", [2304, 1216, 64, 10432])
+# (which of these sizes take the one launch: the table says so, and test_launch_routes_host.py holds the library to it)
+@pytest.mark.parametrize("T,Is", [(T, Is) for T, Is, _ in SHARED_BESIDE])
 @pytest.mark.parametrize("gather", [False, True])
 def test_shared_expert_formed_beside_the_routed_gate_up_has_the_bits_of_its_own_call(moe, oracle64, monkeypatch, T, Is, gather):
     H, E, K, I = 128, 60, 4, 1152

@@ -97,3 +97,36 @@ def test_experts_without_columns_are_refused_behind_the_sort(record, T, I):
     (rc, launches), = record([layer(T, 64, 8, 2, I, 64)])
     assert rc == SHAPE
     assert named(launches, "route") and named(launches, "permute") and not named(launches, "expert")
+
+
+def gate_up(launches):
+    """The tile kernels' gate/up launches: their sixth argument says which projection"""
+    return [l for l in named(launches, "expert_tile_kernel") if l.split("<")[1].split(",")[4] == "1"]
+
+
+# one (T, Is, hosted) each, for 60 experts of H 128, I 1152, top 4 (tiles of 128, 160 and 256 rows): whole sets of I columns, a
+# narrower last set that covers all column tiles of a set or fewer, one set narrower than I; too many sets.  What the path computes is compared at the same sizes in test_gpu_kernel_edges.py.
+SHARED_BESIDE = [(640, 2304, True), (640, 2240, True), (640, 1216, True), (640, 64, True), (640, 10432, False),
+                 (2100, 2304, True), (2100, 2240, True), (2100, 1088, True), (2100, 1216, True), (2100, 64, True), (2100, 10432, False),
+                 (3000, 2304, True), (3000, 2240, True), (3000, 1088, True), (3000, 1216, True), (3000, 64, True), (3000, 10432, False)]
+# the benchmark's layer at every tile height; layers whose shared tiles are mostly empty, or fill more rounds beside the
+# routed ones than alone; too few tokens
+OTHERS = [(777, 2048, 60, 4, 1408, 5632, True), (2048, 2048, 60, 4, 1408, 5632, True), (3000, 2048, 60, 4, 1408, 5632, True),
+          (2000, 1024, 200, 8, 512, 1728, True), (2100, 2048, 60, 4, 1152, 1216, True), (6000, 1024, 32, 4, 960, 1984, False),
+          (4513, 1024, 16, 1, 4096, 192, False), (9015, 1024, 48, 1, 4032, 512, False), (1449, 1024, 24, 2, 3840, 26880, False),
+          (4007, 1024, 32, 1, 2048, 8192, False), (700, 1536, 64, 6, 1024, 2048, False), (256, 2048, 8, 4, 1408, 5632, False)]
+
+
+@pytest.mark.parametrize("T,H,E,K,I,Is,hosted", [(T, 128, 60, 4, 1152, Is, hosted) for T, Is, hosted in SHARED_BESIDE] + OTHERS)
+@pytest.mark.parametrize("gather", [False, True])
+def test_shared_gate_up_joins_the_routed_launch_where_its_tiles_cost_no_more_there(record, T, H, E, K, I, Is, hosted, gather):
+    (rc, launches), = record([layer(T, H, E, K, I, Is, gather)])
+    assert rc == 0
+    assert len(gate_up(launches)) == (1 if hosted else 2), launches
+
+
+def test_a_call_on_a_few_experts_keeps_its_narrower_tiles_for_itself(record):
+    (rc, whole), (rc_few, few) = record([layer(2048, 2048, 60, 4, 1408, 5632), layer(2048, 2048, 60, 4, 1408, 5632, lo=7, hi=14)])
+    assert rc == rc_few == 0
+    assert len(gate_up(whole)) == 1 and "<160,256," in gate_up(whole)[0]
+    assert len(gate_up(few)) == 2 and "<160,128," in gate_up(few)[0]
