@@ -30,11 +30,13 @@ extern "C" {
  * Adding 0x100 to policy runs only the first kernel of the call (gate/up projections and SwiGLU
  * into the workspace), adding 0x200 only the second (down projection from the workspace, and for
  * the shared expert the gate logit): the two halves of one call, so each can be timed alone.
- * Adding 0x400 to the policy of moe_shared_forward_ex (automatic shapes) keeps its first kernel off
- * the tile shapes that fill a CU (256 and 192 token rows by 256: its registers; 160 by 256: its LDS,
- * allowed in launches of up to two rounds of tiles), so that small kernels issued on other streams at
- * the same time (gating, micro-batch construction) are not held up behind it.  The result has the
- * same bits with and without it.
+ * Adding 0x400 to the policy of moe_shared_forward_ex (automatic shapes) says that small kernels run on
+ * other streams at the same time (gating, micro-batch construction): its first kernel then keeps off
+ * the tile shapes behind which they wait so long that both streams together lose (192 token rows by
+ * 256, which fills a CU's registers; 160 by 256, which fills its LDS, in launches of more than two
+ * rounds of tiles).  256 by 256 is taken: its two waves per SIMD leave registers and LDS for them;
+ * they do run slower beside it than beside narrower tiles, but the streams together end earlier.
+ * The result has the same bits with and without it.
  */
 int moe_expert_group_forward_ex(int group_lo, int group_hi, const void* Xp,
                                 const int32_t* expert_offsets, const void* Wg, const void* Wu,

@@ -598,7 +598,7 @@ def moe_layer_forward(x, Wr, bias, Wg, Wu, Wd, shared, K: int, renorm: bool,
         # hardware queue with the aggregation and the step's critical path crosses no queue boundary
         shared_stream.wait_event(fork)
         with torch.cuda.stream(shared_stream):
-            # 0x400: leave room on the CUs for the small kernels of the routed path running beside it
+            # 0x400: the small kernels of the routed path run beside it: no tile shape that holds them up for long
             moe_shared_forward(x, shared[0], shared[1], shared[2], shared[3], buf.S, buf.sg, buf.workspace_shared,
                                shared_policy | 0x400)
         main.wait_stream(shared_stream)

@@ -60,7 +60,7 @@ constexpr int FUSED_NARROW_T = 64, FUSED_WIDE_T = 192;
 // Bits 8 and 9 of the policy word restrict a call to one of its two kernels (0x100: gate/up
 // only, 0x200: down projection only), so that each can be timed on its own.  Bit 10 (0x400, shared
 // expert with automatic shapes): its first kernel takes no tile shape that keeps small kernels of
-// other streams (gating, micro-batch construction) off the CUs (pick_tile_shape says which).
+// other streams (gating, micro-batch construction) off the CUs for long (pick_tile_shape says which).
 struct Plan { bool valid; bool stream; int tile_rows; bool do_gateup; bool do_down; };
 Plan make_plan(int mean_rows, int n_experts_layer, int policy_word) {
   Plan p{};

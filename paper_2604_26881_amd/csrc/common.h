@@ -97,8 +97,8 @@ struct GemmArgs {
                        // on the parts that Cpart has room for (parts_room)
   const int32_t* gather;   // nullptr: row r of A is A[r]; else row r of A is A[gather[r] / gather_div]
   int gather_div;          // (the token rows themselves, addressed through src_of_row: no permuted copy)
-  int leave_room;          // 1: no tile shape that takes a whole CU (all registers of every SIMD): kernels of
-                           // other streams can then share the CUs with this one
+  int leave_room;          // 1: small kernels run on other streams meanwhile: no tile shape that holds them up for long
+                           // (pick_tile_shape says which)
   // Shared experts riding along with a routed block (tile kernels; n_shared == 0: none; the kernel that streams the weights
   // of a few rows takes them too, as its comment states).  They are
   // n_shared more weight sets, each applied to all shared_rows tokens.  In the row space of A and C

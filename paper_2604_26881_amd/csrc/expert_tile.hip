@@ -48,7 +48,7 @@
 // grow past the MFMA time, and where experts stream weights the waves wait for memory.
 // The 32-row blocks of a tile are dealt to the WAVES_M rows of waves in turn, so that a tile of few rows is halved between
 // them (an expert's last tile: 70 of 256 rows are two blocks per wave instead of three and none), and
-// blocks of padding are not copied either where a copy belongs to one row of waves.  60 experts of 1092 rows, gate/up + down in
+// blocks of padding are not copied either where a copy belongs to one row of waves (the shapes with four waves side by side).  60 experts of 1092 rows, gate/up + down in
 // us: 722 + 405 -> 702 + 397; where experts stream their weights, up to 1 %.
 // Rows past the end of an expert are clamped on load (they recompute the expert's last row) and
 // masked on store, which keeps the K loop free of branches.
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, OCC * WAVES_M * WAVES_N / 4
 
   // Row range and token tiles of four experts per lane: [first[i], last[i]) in the tiles of the expert's class, rows
   // [rb[i], re[i]).  Every wave keeps all of it in registers, where finding the expert of a tile is a handful of compares and
-  // ballots: a workgroup has one wave per SIMD, so what it waits for at a tile border nothing else fills.  (As prefixes in LDS
+  // ballots: a workgroup has one or two waves per SIMD, so what it waits for at a tile border little else fills.  (As prefixes in LDS
   // and a binary search, with the expert's end re-read from memory: gate/up + down in us
   // 60 experts of H 2048, I 1408 at 33, 51, 273 and 546 rows 131+67, 138+73, 257+135, 421+246; so 128+66, 134+71, 255+133, 415+241.)
   int first[4], last[4], rb[4], re[4], cnt[2] = {0, 0};
@@ -700,8 +700,11 @@ static TileChoice pick_tile_shape(int rows, int N, int Kdim, bool gateup, int pa
   const double cus = (double)num_cus();
   TileChoice best{129, 1, 0.0};
   for (const Cand& k : cands) {
-    // 192x256 leaves other kernels 86 registers of a SIMD and 45 KB of LDS.  (256x256, two waves of 210 registers per SIMD
-    // and 128 KB, does not keep the row sort waiting: 16 384 tokens beside gating and sort 2312 us with 128x256, 2220 with it.)
+    // 192x256 leaves other kernels 86 registers of a SIMD and 45 KB of LDS.  256x256, two waves of 210 registers per SIMD and
+    // 128 KB, slows them down (16 384 tokens, each kernel's time: row sort 152 -> 243 us, gate logits 45 -> 67), but its own
+    // time outweighs that: layers of H 2048, 60 experts, Is 5632 beside gating and sort, us, without it -> with it: 4096 tokens
+    // 700 -> 682 (skewed, captured 677 -> 665), 8192 1254 -> 1214, 12 000 skewed 1783 -> 1722, 16 384 2355 -> 2269; 32 experts of
+    // H 2560, Is 4096 at 12 000 1964 -> 1903; where it is not picked, and at 3000 and 6000, equal.
     if (k.bm == 192 && leave_room) continue;
     const int most = gateup || !k.cut ? 1 : std::max(1, std::min(parts_max, largest_ksplit(Kdim)));
     for (int parts = 1; parts <= most; parts *= 2) {
@@ -778,6 +781,12 @@ static TileChoice pick_layer_tile(const GemmArgs& a, int tile_rows, bool gateup)
 // us, one call per block, 256 -> narrower: 60 experts of H 2048, I 1408 in blocks of 7 at 137 rows 41+31 -> 32+23, of 15
 // at 200 rows 69+47 -> 61+31, at 52 rows 39+28 -> 39+22; 16 of H 3072, I 4096 at 100 rows in blocks of 4 63+58 -> 46+36,
 // of 2 54+56 -> 32+31; 8 of H 4096, I 7168 in blocks of 2 at 60 rows 61+62 -> 45+45, at 250 rows 88+103 -> 88+76.
+// The line was fitted to the tenants' routing; against the build without the rule (and a few other changes worth 1 to 2 %)
+// layers in blocks gain with every other kind that was timed, us, Zipf unless said: 60 experts of H 2048, I 1408 in blocks of
+// 7 at 1500 tokens 605 -> 497, at 2048 652 -> 544, of 5 at 6000 1430 -> 1159, of 6 at 3000 (even) 1116 -> 665, of 15 at 600 to 3000
+// 287 -> 275, 321 -> 314, 404 -> 396, 559 -> 501; 64 of H 1536, I 1024 in blocks of 8 at 3000 590 -> 563, of 16 at 900 252 ->
+// 246; 32 of H 2560, I 1536 in blocks of 8 at 1500 545 -> 456; 8 of H 4096, I 7168 in blocks of 2 at 1000 836 -> 768; 16 of H
+// 3072, I 4096 in blocks of 4 at 600 746 -> 537.
 static int tile_columns(int code, bool gateup) {
   const int bn = code == 64 ? 64 : code == 130 || code == NARROW_160 || code == NARROW_256 ? 128 : 256;
   return gateup ? bn / 2 : bn;
@@ -808,7 +817,8 @@ static TileChoice pick_tile(GemmArgs& a, int tile_rows, bool gateup) {
 // walk draws them alternately.  What it saves is rounds that are not full (2048 tokens of H 2048, 60 experts of I 1408, top
 // 4, Is 5632: 660 tiles run as three rounds and 484 as two; together 1232 of 160 rows as five) and tiles that wait for weights
 // while nothing multiplies.  us, two launches -> one: 777 tokens 175 -> 162, 1400 210 -> 193, 2048 252 -> 219 (with skewed
-// routing 256 -> 262), 3000 327 -> 299, 4096 426 -> 396 (skewed 416 -> 401), 8192 765 -> 744; the whole layer at 2048 skewed tokens 459 -> 437.  The down projections stay apart:
+// routing 256 -> 262), 3000 327 -> 299, 4096 426 -> 396 (skewed 416 -> 401), 8192 765 -> 744; a whole layer at
+// 2048 skewed tokens 458 -> 442, with four tenants 468 -> 442.  The down projections stay apart:
 // their contractions differ (22 and 88 K steps), and the shared expert cut into sets gains nothing (136 -> 132 at 2048).
 // Only with full-width tiles: layers of few or small experts and calls on a few of them take narrower ones, which the shared
 // expert's many rows do not want; only with more tokens than a tile has rows, for the K start of single tiles is not the shared expert's; only

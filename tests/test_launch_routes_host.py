@@ -130,3 +130,18 @@ def test_a_call_on_a_few_experts_keeps_its_narrower_tiles_for_itself(record):
     assert rc == rc_few == 0
     assert len(gate_up(whole)) == 1 and "<160,256," in gate_up(whole)[0]
     assert len(gate_up(few)) == 2 and "<160,128," in gate_up(few)[0]
+
+
+@pytest.mark.parametrize("H,Is", [(2048, 5632), (1024, 8192), (2560, 4096)])
+def test_shared_expert_beside_small_kernels_keeps_off_the_tiles_that_hold_them_up(record, H, Is):
+    p = [["p", 1 << 40]]
+    call = lambda T, policy: ["moe_shared_forward_ex", p * 5 + [["i", T], ["i", H], ["i", Is]] + p * 3 + [["z", 1 << 38], ["i", policy], ["p", None]]]
+    sizes = list(range(64, 16385, 160))
+    alone, beside = record([call(T, 0) for T in sizes]), record([call(T, 0x400) for T in sizes])
+    assert any("<192,256," in gate_up(l)[0] for _, l in alone if gate_up(l))
+    for T, (rc, launches) in zip(sizes, beside):
+        assert rc == 0 and len(gate_up(launches)) == 1, T
+        assert "<192,256," not in launches[0], T
+        if "<160,256," in launches[0]:
+            assert -(-T // 160) * -(-Is // 128) <= 512, T
+    assert any("<256,256," in l[0] for _, l in beside)
