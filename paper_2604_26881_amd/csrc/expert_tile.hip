@@ -638,6 +638,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, bool GATEUP, int NS, int OCC
 static int launch_tile_s(const GemmArgs& a, hipStream_t st) {
   using S = TileShape<BM, BN, WAVES_M, WAVES_N, GATEUP, NS>;
   auto kern = expert_tile_kernel<BM, BN, WAVES_M, WAVES_N, GATEUP, NS, OCC, KSPLIT, SINGLE, INTURN>;
+  static_assert(std::is_same<decltype(kern), void (*)(GemmArgs)>::value, "next_tile reads the arguments at the start of the kernel's");
   static_assert(KSPLIT == 1 || !SINGLE, "a K part of a tile does not wrap around");
   static_assert(KSPLIT == 1 || !GATEUP, "the SwiGLU product needs complete sums");
   if (a.Kdim % (S::BK * KSPLIT) != 0) return -2;
