@@ -420,7 +420,7 @@ static int launch_stream_lds_any(const GemmArgs& a, hipStream_t st) {
   if constexpr (GATEUP) {
     if (a.sort_ids != nullptr) {
       if (a.offsets == nullptr || a.ids != nullptr || a.n_pairs > SORT_HERE_MAX) return -2;
-      if (a.n_shared > 0) return two ? launch_stream_lds_t<2, true, 4, true, false, true>(a, st) : launch_stream_lds_t<1, true, 4, true, false, true>(a, st);
+      if (a.n_shared > 0) return two ? -2 : launch_stream_lds_t<1, true, 4, true, false, true>(a, st);   // (it rides up to a mean of 6 rows)
       return two ? launch_stream_lds_t<2, true, 4, false, false, true>(a, st) : launch_stream_lds_t<1, true, 4, false, false, true>(a, st);
     }
   }

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import workloads
-from tests.test_launch_routes_host import SHARED_BESIDE
+from tests.test_launch_routes_host import SHARED_BESIDE, SORT_BESIDE
 from tests.test_gpu_parity import check_close, f64, moe  # noqa: F401  (moe is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -533,7 +533,8 @@ def test_shared_expert_in_192_row_tiles(moe, oracle64, T, H, Is):
 
 
 @pytest.mark.parametrize("mean,bm", [(60, 128), (140, 160), (232, 256)])     # the height of the layer's tiles
-@pytest.mark.parametrize("H,I", [(256, 1152), (2304, 64)])                   # full width in gate/up, in the down projection
+# full width in gate/up, in the down projection; one K step, four, and seven (longer than every ring and no multiple of one)
+@pytest.mark.parametrize("H,I", [(256, 1152), (448, 1152), (2304, 64), (2304, 448)])
 def test_calls_on_a_few_experts_take_narrower_tiles_to_the_same_bits(moe, oracle64, mean, bm, H, I):
     # 60 experts: the uncut call has two rounds of whole tiles, calls on a few of them have compute units to spare
     E = 60
@@ -551,7 +552,8 @@ def test_calls_on_a_few_experts_take_narrower_tiles_to_the_same_bits(moe, oracle
         assert torch.equal(Yp.view(torch.int16), Yc.view(torch.int16)), cuts[:2]
 
 
-@pytest.mark.parametrize("T,K,E", [(63, 1, 12), (64, 1, 256), (65, 1, 256), (127, 1, 200), (64, 2, 33), (128, 1, 64), (129, 1, 64)])
+# (which of these sizes are sorted there: test_launch_routes_host.py holds the library to it, as to the memory)
+@pytest.mark.parametrize("T,K,E", [(T, K, E) for T, K, E, _ in SORT_BESIDE])
 @pytest.mark.parametrize("gather,ids_in", [(False, "their own memory"), (True, "their own memory"), (False, "the hidden rows"),
                                            (True, "row_of_pair")])
 def test_micro_batch_constructed_beside_gate_up_equals_the_sort(moe, oracle64, monkeypatch, T, K, E, gather, ids_in):
@@ -603,6 +605,29 @@ def test_shared_expert_formed_beside_the_routed_gate_up_has_the_bits_of_its_own_
     rows = np.arange(0, T, 7)
     S_ref, _ = oracle64.shared_forward(x.float().numpy()[rows], f32["Wsg"], f32["Wsu"], f32["Wsd"], f32["wgate"])
     check_close(f64(one.S)[rows], S_ref, "S")
+
+
+@pytest.mark.parametrize("memory", ["workspaces", "Xp", "src_of_row", "expert_offsets"])
+def test_shared_expert_whose_rows_lie_in_memory_of_the_routed_ones_has_its_own_launch(moe, memory):
+    # right when the steps run in turn: each of these is of no further use when the shared expert's own call begins
+    T, H, E, K, I, Is = 640, 128, 60, 4, 1152, 2304
+    print(f"[case] shared hidden rows in memory of the routed experts: {memory}", flush=True)
+    w = workloads.layer_weights(H, E, I, Is, 17, 0.05, 0.1, torch.bfloat16, device="cpu")
+    x = torch.randn((T, H), generator=torch.Generator().manual_seed(T)).to(torch.bfloat16).cuda()
+    d = {k: v.cuda() for k, v in w.items()}
+    apart, one = (moe.LayerBuffers.allocate(T, H, E, K, I, Is) for _ in range(2))
+    if memory == "workspaces":
+        need = moe.moe_workspace_bytes(T, H, E, K, I, Is)
+        one.workspace = one.workspace_shared = one.workspace_permute = torch.empty(need, dtype=torch.uint8, device="cuda")
+    else:
+        old = getattr(one, memory)
+        setattr(one, memory, one.workspace_shared[:old.numel() * old.element_size()].view(old.dtype).view(old.shape))
+    for buf in (apart, one):
+        moe.moe_layer_forward(x, d["Wr"], None, d["Wg"], d["Wu"], d["Wd"], (d["Wsg"], d["Wsu"], d["Wsd"], d["wgate"]), K, True, buf=buf,
+                              fused_gather=memory != "Xp")
+    torch.cuda.synchronize()
+    for name in ("Yp", "S", "sg", "out"):
+        assert torch.equal(getattr(one, name).view(torch.uint8), getattr(apart, name).view(torch.uint8)), name
 
 
 def test_a_layer_whose_block_is_refused_leaves_the_steps_before_it(moe):

@@ -59,7 +59,7 @@ def short(mangled):
 
 def layer(T, H, E, K, I, Is, gather=False, lo=0, hi=None, policy=0, shared_policy=0, wgate=True, **memory):
     """moe_layer_forward on memory of its own for every operand (terabytes apart), but for what `memory` says: name ->
-    (name of another operand, byte offset in it) or a size"""
+    (name of another operand, byte offset in it), None (NULL) or a workspace's size"""
     names = ["x", "Wr", "bias", "Wg", "Wu", "Wd", "Wsg", "Wsu", "Wsd", "wgate", "topk_ids", "topk_w", "expert_offsets", "src_of_row",
              "row_of_pair", "Xp", "Yp", "S", "sg", "out", "permute_workspace", "workspace", "shared_workspace", "next"]
     at = {n: (i + 1) << 40 for i, n in enumerate(names)}
@@ -73,7 +73,9 @@ def layer(T, H, E, K, I, Is, gather=False, lo=0, hi=None, policy=0, shared_polic
         at["wgate"] = None
     size = {n: 1 << 38 for n in ("permute_workspace", "workspace", "shared_workspace")}
     for n, v in memory.items():
-        if isinstance(v, tuple):
+        if v is None:
+            at[n] = None
+        elif isinstance(v, tuple):
             at[n] = at[v[0]] + v[1]
         else:
             size[n] = v
@@ -145,3 +147,95 @@ def test_shared_expert_beside_small_kernels_keeps_off_the_tiles_that_hold_them_u
         if "<160,256," in launches[0]:
             assert -(-T // 160) * -(-Is // 128) <= 512, T
     assert any("<256,256," in l[0] for _, l in beside)
+
+
+# T, K, E of a layer of H 64, I 64, and whether its pairs are sorted beside gate/up: up to 128 of them, also where the
+# streaming kernel takes two token tiles per pass (a mean above 10).  test_gpu_kernel_edges.py computes them.
+SORT_BESIDE = [(63, 1, 12, True), (64, 1, 256, True), (65, 1, 256, True), (127, 1, 200, True), (64, 2, 33, True), (128, 1, 64, True),
+               (48, 2, 8, True), (64, 2, 8, True), (62, 2, 4, True), (129, 1, 64, False), (65, 2, 8, False)]
+
+
+def sorted_beside(launches):
+    """Whether the pairs were sorted in the narrow streaming kernel's gate/up launch (its last argument), or by the sort's own"""
+    beside = [l for l in launches if l.startswith("expert_stream_lds_kernel") and l.endswith(",1>")]
+    assert len(beside) + min(1, len(named(launches, "permute"))) == 1
+    return beside
+
+
+@pytest.mark.parametrize("T,K,E,beside", SORT_BESIDE)
+@pytest.mark.parametrize("gather", [False, True])
+def test_pairs_are_sorted_beside_gate_up(record, T, K, E, beside, gather):
+    (rc, launches), = record([layer(T, 64, E, K, 64, 0, gather)])
+    assert rc == 0
+    assert len(sorted_beside(launches)) == beside
+    if beside:
+        tiles = 2 if T * K / E > 10 else 1
+        assert sorted_beside(launches)[0].startswith(f"expert_stream_lds_kernel<{tiles},1,4,0,"), launches
+
+
+def test_pairs_are_sorted_beside_gate_up_and_a_riding_shared_expert(record):
+    for T, K, E, gather in [(1, 2, 8, False), (24, 2, 8, True), (32, 4, 60, False), (32, 4, 22, True)]:
+        (rc, launches), = record([layer(T, 64, E, K, 128, 512, gather)])
+        assert rc == 0
+        assert [l.split("<")[1] for l in sorted_beside(launches)] == ["1,1,4,1,0,1>"], (T, launches)
+    # a wide contraction of more than 6 rows per expert is the wide kernel's
+    (rc, launches), = record([layer(60, 320, 8, 1, 320, 0)])
+    assert rc == 0 and not sorted_beside(launches) and named(launches, "expert_stream_wide")
+
+
+H_, I_, P_ = 64, 64, 16        # T 8, K 2, E 8: bytes of the operands
+SORT_IN_USE = [dict(topk_ids=("workspace", 0)), dict(topk_ids=("workspace", P_ * I_ * 2 - 4)), dict(expert_offsets=("workspace", 8)),
+               dict(src_of_row=("workspace", 64)), dict(row_of_pair=("workspace", 128)), dict(x=("workspace", P_ * I_ * 2 - 16)),
+               dict(Xp=("workspace", 0)), dict(Xp=("x", 16)), dict(topk_ids=("row_of_pair", 0)), dict(topk_ids=("src_of_row", 4)),
+               dict(topk_ids=("expert_offsets", 32))]
+SORT_FREE = [dict(topk_ids=("workspace", P_ * I_ * 2)), dict(x=("workspace", P_ * I_ * 2)), dict(Xp=("x", 8 * H_ * 2)),
+             dict(topk_ids=("row_of_pair", P_ * 4)), dict(topk_ids=("expert_offsets", 36)), dict(permute_workspace=("workspace", 0))]
+
+
+@pytest.mark.parametrize("beside,memory", [(False, m) for m in SORT_IN_USE] + [(True, m) for m in SORT_FREE])
+def test_memory_that_gate_up_writes_keeps_the_sort_in_its_own_launch(record, beside, memory):
+    (rc, launches), = record([layer(8, H_, 8, 2, I_, 0, **memory)])
+    assert rc == 0 and len(sorted_beside(launches)) == beside
+
+
+# T 640, H 128, E 60, K 4, I 1152, Is 2304: the shared hidden rows are written while the routed experts' launches run
+HOST_ROWS, HOST_H = 640 * 4, 640 * 2304 * 2
+HOST_IN_USE = [(False, dict(shared_workspace=("workspace", 0))), (False, dict(shared_workspace=("workspace", HOST_ROWS * 1152 * 2 - 256))),
+               (False, dict(workspace=("shared_workspace", HOST_H - 256))), (False, dict(shared_workspace=("Xp", 0))),
+               (False, dict(shared_workspace=("Yp", 256))), (True, dict(src_of_row=("shared_workspace", 512))),
+               (False, dict(expert_offsets=("shared_workspace", 0))), (False, dict(x=("shared_workspace", HOST_H - 256))),
+               (False, dict(x=("workspace", 0))), (False, dict(Yp=("x", 256)))]
+HOST_FREE = [(False, dict(shared_workspace=("workspace", HOST_ROWS * 1152 * 2))), (False, dict(workspace=("shared_workspace", HOST_H))),
+             (False, dict(out=("shared_workspace", 0))), (False, dict(permute_workspace=("shared_workspace", 0)))]
+
+
+@pytest.mark.parametrize("hosted,gather,memory", [(False, *m) for m in HOST_IN_USE] + [(True, *m) for m in HOST_FREE])
+def test_memory_that_the_routed_experts_use_keeps_the_shared_gate_up_in_its_own_launch(record, hosted, gather, memory):
+    (rc, launches), = record([layer(640, 128, 60, 4, 1152, 2304, gather, **memory)])
+    assert rc == 0 and len(gate_up(launches)) == (1 if hosted else 2)
+
+
+@pytest.mark.parametrize("change,status", [(dict(shared_workspace=640 * 2304 * 2 - 1), -3), (dict(S=None), -1), (dict(sg=None), -1),
+                                           (dict(Wsd=None), -1), (dict(shared_policy=10), 0), (dict(policy=5), 0), (dict(wgate=False), 0)])
+def test_what_the_shared_call_refuses_is_left_to_it(record, change, status):
+    call = lambda gather: layer(640, 128, 60, 4, 1152, 2304, gather, **change)
+    for rc, launches in record([call(False), call(True)]):
+        assert rc == status
+        assert len(gate_up(launches)) == (1 if status or "wgate" in change else 2)
+        if status:     # the routed experts have been enqueued, the shared one has not
+            assert len(named(launches, "expert_tile_kernel")) == 2 and not named(launches, "combine")
+
+
+# mean rows of 60 experts and the height of the layer's tiles; H, I of which one projection is full width in the uncut call.
+# test_gpu_kernel_edges.py compares the bits at these sizes.
+@pytest.mark.parametrize("mean,bm", [(60, 128), (140, 160), (232, 256)])
+@pytest.mark.parametrize("H,I,down", [(256, 1152, False), (448, 1152, False), (2304, 64, True), (2304, 448, True)])
+def test_calls_on_a_few_experts_take_narrower_tiles(record, mean, bm, H, I, down):
+    p, P = lambda n: [["p", (i + 1) << 40] for i in range(n)], 60 * mean
+    call = lambda lo, hi: ["moe_expert_group_forward", [["i", lo], ["i", hi]] + p(5) + [["i", v] for v in (P, H, 60, I)] + p(2) +
+                           [["z", 1 << 38], ["p", None]]]
+    shapes = []
+    for rc, launches in record([call(0, 60), call(3, 10)]):
+        assert rc == 0 and len(launches) == 2
+        shapes.append(tuple(launches[down].split("<")[1].split(",")[:2]))
+    assert shapes[0] == (str(bm), "256") and shapes[1] in [(str(bm), "128"), (str(bm), "64")], shapes
