@@ -190,7 +190,7 @@ int moe_combine(const void* Yp, const int32_t* row_of_pair, const float* topk_w,
  * launches when shared_workspace has room for its parts (moe_shared_workspace_bytes includes it); S keeps the bits of
  * moe_shared_forward, so that out depends neither on the block cut nor on how the steps are called.
  * Larger ones may form its hidden rows in the launch of the routed experts' first kernel, and up to 128 pairs of a batch
- * whose experts stream their weights are sorted there; either way every output has the bits of its own call.
+ * whose experts stream their weights may be sorted there; either way every output has the bits of its own call.
  * next (NULL: off; may be x): also moe_residual_norm(x, out, next_eps), from the aggregation itself, with the bits of that
  * call.  A step that refuses its arguments ends the call with that step's status; the steps before it have been enqueued.
  * Memory may be shared as between the separate calls: one buffer of moe_workspace_bytes may be every workspace, and an

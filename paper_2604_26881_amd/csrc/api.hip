@@ -120,9 +120,20 @@ struct Hosted { const void *x, *Wsg, *Wsu; void* h; int T, Is; };
 
 // The micro-batch of a layer with few pairs, constructed inside the first launch of its experts (see expert_stream_lds.hip)
 struct Sort { const int32_t* ids; int32_t *offsets, *src, *rows; void* Xp; };
-bool sort_in_gateup(int P, int H, int E) {
+// What it costs is the look at the ids of every wave of that launch (`experts` of them by 16 columns each): of those without
+// rows, which otherwise leave after two scalar loads, while few others run (the first line), and of those with rows, whose
+// number grows with the pairs too (the second).  A layer in us, sorted apart -> here, on both sides of the first: 256 experts
+// of H 2048 at 8 pairs, I 768 47.0 -> 45.3, I 1024 50.9 -> 49.7 and 49.9 -> 49.8, I 1408 57.3 -> 57.8, I 2048 67.1 -> 69.7, at 16 92.4 ->
+// 93.1, at 32 146 -> 143; 60 of I 1408 at 4 47 -> 43; 160 of H 1024, I 2560 at 6 43.3 -> 44.2, 64 of I 4096 at 4 42.0 -> 43.5, 256 of
+// I 4096 at 16 94 -> 104.  Of the second: 256 experts of H 2048, I 768 at 64 pairs 112 -> 110, at 96 148 -> 149, at 128 178 ->
+// 183; of H 1024, I 512 at 72 54.3 -> 52.3, at 128 75.1 -> 77.3; I 256 at 128 56.9 -> 52.7; 160 of I 1536 at 60 92.9 -> 91.3, at 96
+// 122.0 -> 123.8; 64 of I 1536 at 72 81.6 -> 79.1, at 128 100.9 -> 101.8; 128 of I 1408 at 72 95.4 -> 93.7, of I 512 at 128 59.1 ->
+// 57.8.
+bool sort_in_gateup(int P, int H, int E, int I, int experts) {
   const int mean_rows = (P + E - 1) / E;
-  return P <= SORT_HERE_MAX && E > 1 && make_plan(mean_rows, E, 0).stream && stream_narrow(mean_rows, H);
+  const long long waves = (long long)experts * ((I + 15) / 16);
+  return P <= SORT_HERE_MAX && waves < 2048ll * std::max(P, 6) && waves * P * P <= 90000000ll && E > 1 &&
+         make_plan(mean_rows, E, 0).stream && stream_narrow(mean_rows, H);
 }
 
 int expert_group_forward_impl(int group_lo, int group_hi, const int32_t* ids, const void* A, const int32_t* gather,
@@ -573,7 +584,7 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
   const auto beside_hidden = [&](const void* p, size_t n) {
     return apart(p, n, workspace, h_routed) && (!ride || apart(p, n, riding, riding_bytes));
   };
-  const bool sort_here = T > 0 && policy == 0 && sort_in_gateup(P, H, E) && beside_hidden(topk_ids, pairs) && beside_hidden(x, x_bytes) &&
+  const bool sort_here = T > 0 && policy == 0 && sort_in_gateup(P, H, E, I, group_hi - group_lo) && beside_hidden(topk_ids, pairs) && beside_hidden(x, x_bytes) &&
                          beside_hidden(expert_offsets, offsets_bytes) && beside_hidden(src_of_row, pairs) &&
                          beside_hidden(row_of_pair, pairs) && apart(topk_ids, pairs, expert_offsets, offsets_bytes) &&
                          apart(topk_ids, pairs, src_of_row, pairs) && apart(topk_ids, pairs, row_of_pair, pairs) &&

@@ -47,10 +47,10 @@ struct StreamLdsShape {
 // blockIdx.y == 0 write the arrays, and the row copies where asked for, for the launches that follow: the same stable
 // counting sort as in permute.hip, by one wave.
 // It saves a launch of 3-4 us and the gap before it, and costs every wave its look at the ids, also those of experts without
-// rows.  A layer, us, sorted in a launch of its own -> here: H 64, 16 tokens, top 2 25.8 -> 22.7; 60 experts of H 2048, I 1408,
-// top 4 at 1 token 46.4 -> 42.6, at 13 125.4 -> 122.9, at 30 (120 pairs) 182.2 -> 180.1; 256 of H 1024, I 256, top 8 at 8
-// tokens 39.6 -> 36.1, at 16 (128 pairs) 54.5 -> 52.9.  Beyond 128 pairs it turns: 160 pairs of the 60 experts 194 -> 198, 180
-// of 64 experts of H 1536 114 -> 118, 1024 of the 256 96 -> 148.
+// rows: the rule beside sort_in_gateup draws the line.  A layer, us, sorted in a launch of its own -> here: H 64, 16 tokens,
+// top 2 25.8 -> 22.7; 60 experts of H 2048, I 1408, top 4 at 1 token 46.4 -> 42.6, at 13 125.4 -> 122.9, at 30 (120 pairs) 182.2 ->
+// 180.1; 256 of H 1024, I 256, top 8 at 8 tokens 39.6 -> 36.1, at 16 (128 pairs) 54.5 -> 52.9.  Beyond 128 pairs it turns everywhere: 160
+// pairs of the 60 experts 194 -> 198, 180 of 64 experts of H 1536 114 -> 118, 1024 of the 256 96 -> 148.
 constexpr int SORT_SPLIT = 16;   // waves that share the row copies of 64 pairs
 __device__ __forceinline__ int pair_expert(const GemmArgs& a, int p) {   // -1 past the last pair
   return p < a.n_pairs ? min(max(a.sort_ids[p], 0), a.experts_layer - 1) : -1;   // (an id outside [0,E) stays in the tables)

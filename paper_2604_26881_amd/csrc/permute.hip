@@ -3,7 +3,7 @@
 // (token, slot) pairs by expert id, followed by a coalesced gather of the token rows.
 // No atomics anywhere, so the result is deterministic; every step runs on many CUs.
 //
-// (A layer of up to 128 pairs whose experts stream their weights is sorted inside their first launch: expert_stream_lds.hip.)
+// (A layer of up to 128 pairs whose experts stream their weights may be sorted inside their first launch: expert_stream_lds.hip.)
 // The pairs are cut into chunks of 64 (one wave).
 // permute_hist_kernel: one wave per chunk.  Lanes with the same expert find each other with
 //   bit-sliced ballots (log2 E ballots); the first lane of each group writes the group size:

@@ -183,6 +183,17 @@ def test_pairs_are_sorted_beside_gate_up_and_a_riding_shared_expert(record):
     assert rc == 0 and not sorted_beside(launches) and named(launches, "expert_stream_wide")
 
 
+# T, K, E, H, I on either side of the two lines in the number of the launch's waves
+@pytest.mark.parametrize("T,K,E,H,I,beside", [
+    (1, 4, 60, 2048, 1408, True), (1, 1, 60, 2048, 3264, True), (1, 1, 60, 2048, 3328, False), (1, 8, 256, 2048, 960, True),
+    (1, 8, 256, 2048, 1024, False), (2, 8, 256, 1024, 4096, False), (4, 8, 256, 2048, 2048, True), (1, 4, 64, 1024, 4096, False),
+    (32, 4, 60, 2048, 1408, True), (16, 8, 256, 1024, 256, True), (16, 8, 256, 1024, 512, False), (9, 8, 256, 1024, 512, True),
+    (16, 8, 256, 2048, 768, False), (12, 8, 256, 2048, 768, False), (8, 8, 256, 2048, 768, True), (8, 8, 256, 1024, 4096, False)])
+def test_pairs_are_sorted_apart_beside_many_waves(record, T, K, E, H, I, beside):
+    (rc, launches), = record([layer(T, H, E, K, I, 0)])
+    assert rc == 0 and len(sorted_beside(launches)) == beside
+
+
 H_, I_, P_ = 64, 64, 16        # T 8, K 2, E 8: bytes of the operands
 SORT_IN_USE = [dict(topk_ids=("workspace", 0)), dict(topk_ids=("workspace", P_ * I_ * 2 - 4)), dict(expert_offsets=("workspace", 8)),
                dict(src_of_row=("workspace", 64)), dict(row_of_pair=("workspace", 128)), dict(x=("workspace", P_ * I_ * 2 - 16)),
