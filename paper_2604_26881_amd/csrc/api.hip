@@ -599,9 +599,9 @@ int moe_layer_forward(const void* x, const void* Wr, const float* bias, const in
   // The shared expert's hidden rows formed beside the routed ones: nothing that the routed experts still read or write may
   // lie there, and everything its own call would refuse is left to that call.
   const size_t shared_h = (size_t)T * (size_t)Is * 2;
-  const bool host = !ride && T > 0 && Is > 0 && dims_ok(H) && dims_ok(I) && dims_ok(Is) && policy == 0 && shared_policy == 0 && Wsg && Wsu && Wsd && S &&
-                    shared_workspace && shared_workspace_bytes >= shared_h && (!wgate || sg) && (Is + I - 1) / I <= MOE_SHARED_SETS_MAX &&
-                    (long long)T * (H > Is ? H : Is) < (1ll << 31) &&
+  const bool host = !ride && T > 0 && Is > 0 && dims_ok(H) && dims_ok(I) && dims_ok(Is) && policy == 0 && shared_policy == 0 &&
+                    Wsg && Wsu && Wsd && S && shared_workspace && shared_workspace_bytes >= shared_h && (!wgate || sg) &&
+                    (Is + I - 1) / I <= MOE_SHARED_SETS_MAX && (long long)T * (H > Is ? H : Is) < (1ll << 31) &&
                     apart(shared_workspace, shared_h, workspace, h_routed) && apart(shared_workspace, shared_h, x, x_bytes) &&
                     apart(shared_workspace, shared_h, Yp, (size_t)P * (size_t)H * 2) && apart(workspace, h_routed, x, x_bytes) &&
                     apart(Yp, (size_t)P * (size_t)H * 2, x, x_bytes) &&

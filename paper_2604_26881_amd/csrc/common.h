@@ -191,7 +191,7 @@ constexpr int STREAM_FEW_ROWS = 6;   // mean rows per expert up to which the nar
 // It also serves contractions of up to four K steps, where what counts is how soon a wave starts: 16 experts of H 256, I 256
 // at 7 to 26 rows, gate/up + down: 7.4-8.7 us narrow, 9.1-11 wide.
 inline bool stream_narrow(int mean_rows, int Kdim) { return mean_rows <= STREAM_FEW_ROWS || Kdim <= 256; }
-constexpr int SORT_HERE_MAX = 128;   // pairs up to which that kernel's gate/up launch constructs the micro-batch as well
+constexpr int SORT_HERE_MAX = 128;   // most pairs whose micro-batch that kernel's gate/up launch constructs as well (sort_in_gateup draws the line)
 // Streaming kernels that stage the weights through wave-private LDS rings (whole-line requests): a few rows per
 // expert, and up to a few dozen.
 int launch_stream_lds_gateup(const GemmArgs& a, hipStream_t st);
